@@ -18,8 +18,8 @@ namespace fg {
 // built per head -- all workgroups drain one head before the next, so concurrently running
 // items share that head's K/V in cache -- and longest-first inside a head.
 // blockIdx.x = (batch, head) slice; blockIdx.y splits the slice's query blocks when they are ranked exactly.
-// workspace layout: int32 ctrl[64] (ctrl[1] finished-workgroup count, ctrl[8 + q] head of the
-// queue of XCD q, which covers the q-th eighth of the slices), then int32 order[n_items].
+// workspace layout: int32 ctrl[64] (ctrl[queue_word(q)] = items popped from the queue of XCD q, which covers the
+// q-th eighth of the slices), then int32 order[n_items].
 // ------------------------------------------------------------------------------------------
 constexpr int kPlanThreads = 256;
 constexpr int kRankMax = 4096;     // slices with at most this many query blocks are ranked exactly
@@ -32,7 +32,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(const int64_t* indpt
   __shared__ int s_max;
   const int tid = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * QB;
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 16) ctrl[tid] = 0;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid < 64) ctrl[tid] = 0;
   if (!sorted || indptr == nullptr) {
     if (blockIdx.y == 0)
       for (int j = tid; j < QB; j += kPlanThreads) order[base + j] = (int32_t)(base + j);
@@ -88,6 +88,9 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(const int64_t* indpt
     order[base + pos] = (int32_t)(base + j);
   }
 }
+
+// Rewinds the queues for a launch that reuses the order an earlier pre-pass left in the workspace.
+__global__ void __launch_bounds__(64) rewind_kernel(int32_t* ctrl) { ctrl[threadIdx.x] = 0; }
 
 // ------------------------------------------------------------------------------------------
 // Mask validator (test helper): one workgroup per work item.
@@ -225,10 +228,6 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   const int R = grouped ? 128 / p->M : 1;                                   // member tiles per group
   const int QB_tiles = (p->L + p->M - 1) / p->M;
   const int QB_items = grouped ? (QB_tiles + R - 1) / R : QB_tiles;         // work items per (batch, head) slice
-  if (!(p->flags & FGATTN_FLAG_REUSE_PLAN)) {
-    rc = run_plan(indptr, p, workspace, stream, QB_items);
-    if (rc) return rc;
-  }
   FwdArgs a;
   a.q = static_cast<const uint16_t*>(q);
   a.k = static_cast<const uint16_t*>(k);
@@ -257,7 +256,6 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   a.n_recip16 = (65536u + (uint32_t)a.N - 1) / (uint32_t)a.N;
   a.QB = QB_items;
   a.n_items = (int32_t)((int64_t)p->B * p->H * QB_items);
-  a.static_assign = (p->flags & FGATTN_FLAG_STATIC_ASSIGN) ? 1 : 0;
   const float sabs = fabsf(p->scale);
   // scale = 0 is run with a tiny positive exponent factor: valid keys still get p = exp2(tiny * s) = 1 exactly,
   // while masked keys (score -inf) get exactly 0 instead of exp2(-inf * 0) = NaN
@@ -265,9 +263,33 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   if (!(a.c_log2 > 1e-30f)) a.c_log2 = 1e-30f;
   a.scale_abs = sabs;
   a.q_sign = p->scale < 0.0f ? 0x80008000u : 0u;
-  if (part != 0) return launch_part(a, part, dev.cus, stream);
-  if (grouped) return launch_grouped(a, p->d, dev.cus, stream);
-  return launch_forward(a, p->d, dev.cus, stream, nullptr);
+  auto launch = [&](int* grid_only) {
+    if (part != 0) return launch_part(a, part, dev.cus, stream, grid_only);
+    if (grouped) return launch_grouped(a, p->d, dev.cus, stream, grid_only);
+    return launch_forward(a, p->d, dev.cus, stream, grid_only);
+  };
+  // Every item has a workgroup of its own: all start at once, so an order would change nothing and the pre-pass (4 us at
+  // 128 items, where the forward kernel itself takes about 10) is left out.  Otherwise the pre-pass also zeroes the
+  // queue counters; a launch that reuses its order has them rewound.
+  a.schedule = SCHED_QUEUE;
+  int grid = 0;
+  rc = launch(&grid);
+  if (rc) return rc;
+  if (grid >= a.n_items) {
+    a.schedule = SCHED_DIRECT;
+  } else {
+    if (p->flags & FGATTN_FLAG_STATIC_ASSIGN) a.schedule = SCHED_STATIC;
+    // (the one-workgroup-per-unit part has a smaller grid than the launch whose order it would reuse, which may have
+    // needed none and written none: it always makes its own)
+    if (!(p->flags & FGATTN_FLAG_REUSE_PLAN) || part == FGATTN_PART_GATHER_ONE_WG) {
+      rc = run_plan(indptr, p, workspace, stream, QB_items);
+      if (rc) return rc;
+    } else if (a.schedule == SCHED_QUEUE) {
+      hipLaunchKernelGGL(rewind_kernel, dim3(1), dim3(64), 0, stream, a.counter);
+      if (hipGetLastError() != hipSuccess) return FGATTN_E_DEVICE;
+    }
+  }
+  return launch(nullptr);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -5,6 +5,13 @@
 
 namespace fg {
 
+// How work items reach the workgroups: popped from the per-XCD queues; item j to workgroup j mod grid; or, when every
+// item has a workgroup of its own, straight from the workgroup index (no order, no counters, no pre-pass).
+enum { SCHED_QUEUE = 0, SCHED_STATIC = 1, SCHED_DIRECT = 2 };
+
+// Word of ctrl[64] that counts the items popped from the queue of XCD q: two 128-byte lines, four queues on each.
+__host__ __device__ constexpr int queue_word(int q) { return 16 + 4 * (q & 3) + 16 * (q >> 2); }
+
 struct FwdArgs {
   const uint16_t* q;
   const uint16_t* k;
@@ -14,9 +21,9 @@ struct FwdArgs {
   const int64_t* indptr;   // null => dense: every key of [0, L) in order
   const int32_t* indices;
   const int32_t* order;    // work-item ids in processing order
-  int32_t* counter;        // int32 ctrl[64]: [1] finished-workgroup count, [8 + q] head of the queue of XCD q (zeroed by the pre-pass)
+  int32_t* counter;        // int32 ctrl[64]: [queue_word(q)] items popped from the queue of XCD q (zeroed before every launch)
   int64_t q_sb, q_sh, q_sl, k_sb, k_sh, k_sl, v_sb, v_sh, v_sl, o_sb, o_sh, o_sl;  // elements
-  int32_t H, L, M, N, QB, n_items, static_assign;
+  int32_t H, L, M, N, QB, n_items, schedule;
   // group -> key expansion without divisions: NT = keys per LDS tile of the launched variant
   int32_t nt_div_n, nt_mod_n;
   uint32_t n_recip16;   // ceil(65536 / N), used only when N < NT
@@ -36,14 +43,14 @@ struct FwdArgs {
 int launch_forward(const FwdArgs& a, int d, int cus, hipStream_t stream, int* grid_only);
 
 // Gather-only (part = 1) or compute-only (part = 2) instantiation of the M = 64, d = 128, N = 1 variant.
-int launch_part(const FwdArgs& a, int part, int cus, hipStream_t stream);
+int launch_part(const FwdArgs& a, int part, int cus, hipStream_t stream, int* grid_only);
 
 // Measurement aid: 16 MFMAs + 16 exponentials + `other` ordinary vector instructions per loop trip on 2 * cus workgroups
 // of four waves; `out` takes 2 * cus * 256 floats.
 int launch_issue_probe(int other, int iters, float* out, int cus, hipStream_t stream);
 
 // Grouped query tiles: the 128-row variant with membership masks (d = 64 / 128; N = 1 or N > 1).
-int launch_grouped(const FwdArgs& a, int d, int cus, hipStream_t stream);
+int launch_grouped(const FwdArgs& a, int d, int cus, hipStream_t stream, int* grid_only);
 
 // One translation unit per query-tile size keeps compile times parallel.
 int launch_mt32(const FwdArgs& a, int d, int cus, hipStream_t stream, int* grid_only);

@@ -318,35 +318,53 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
   int iter = 0;
   // the XCD this workgroup runs on (hardware register XCC_ID, bits 3:0) picks its home queue
   const int my_xcd = __builtin_amdgcn_s_getreg((4 - 1) << 11 | 0 << 6 | 20) & 7;
-  int queues_left = 8;
+  // Queue q holds the work of a contiguous eighth of the (batch, head) slices, in the order the pre-pass wrote, so that a
+  // head's K/V streams through one L2 instead of eight.  Its first blocks_of(q) items belong to the workgroups with
+  // blockIdx % 8 == q (where the hardware places them), one each, without asking; only the items after those are
+  // popped from the counter.  Atomics on one 128-byte line are served one per 12 ns whichever word they name (2048
+  // workgroups with eight each on a line: 183 us; a plain load each: 0), so a workgroup whose queue has run dry reads
+  // all counters with loads and pops only where something is left; a queue once dry stays dry.
+  auto queue_begin = [&](int q) { return ((q * (a.n_items / a.QB)) >> 3) * a.QB; };
+  auto blocks_of = [&](int q) { return ((int)gridDim.x - q + 7) >> 3; };
+  auto pop = [&](int q) -> int {   // one item of queue q, or -1
+    const int j = queue_begin(q) + blocks_of(q) + atomicAdd(a.counter + queue_word(q), 1);
+    return j < queue_begin(q + 1) ? a.order[j] : -1;
+  };
+  bool home_dry = false;
+  // (without a pre-pass the control words are cleared here, so that they hold the same after every kind of launch)
+  if (a.schedule == SCHED_DIRECT && blockIdx.x == 0 && tid < 64) a.counter[tid] = 0;
   for (;;) {
     // ---------------- fetch the next work item ----------------
-    if (a.static_assign) {
-      int j = blockIdx.x + iter * gridDim.x;
-      if (tid == 0) *s_item = j < a.n_items ? a.order[j] : -1;
-    } else {
-      // One queue per XCD (each XCD has its own L2): queue q holds the work of a contiguous eighth of the (batch, head)
-      // slices, in the order the pre-pass wrote, so that a head's K/V streams through one L2 instead of eight.  A
-      // workgroup drains the queue of the XCD it runs on, then moves on to the next ones and helps there; a queue once
-      // found empty stays empty, so `queues_left` only counts down.
-      if (tid == 0) {
-        int item = -1;
-        const int slices = a.n_items / a.QB;
-        while (queues_left > 0) {
-          const int q = (my_xcd + 8 - queues_left) & 7;
-          const int s0 = (q * slices) >> 3, s1 = ((q + 1) * slices) >> 3;
-          const int len = (s1 - s0) * a.QB;
-          if (len > 0) {
-            const int j = atomicAdd(a.counter + 8 + q, 1);
-            if (j < len) {
-              item = a.order[s0 * a.QB + j];
-              break;
-            }
-          }
-          queues_left--;
+    if (tid == 0) {
+      int item = -1;
+      if (a.schedule == SCHED_DIRECT) {   // at most one item per workgroup; a contiguous eighth of the items per XCD
+        const int r = blockIdx.x & 7, per = a.n_items >> 3, rem = a.n_items & 7;
+        if (iter == 0) item = r * per + min(r, rem) + (blockIdx.x >> 3);
+      } else if (a.schedule == SCHED_STATIC) {
+        const int j = blockIdx.x + iter * gridDim.x;
+        item = j < a.n_items ? a.order[j] : -1;
+      } else {
+        const int mine = queue_begin(blockIdx.x & 7) + (blockIdx.x >> 3);
+        if (iter == 0 && mine < queue_begin((blockIdx.x & 7) + 1)) item = a.order[mine];
+        if (item < 0 && !home_dry) {
+          item = pop(my_xcd);
+          home_dry = item < 0;
         }
-        *s_item = item;
+        while (item < 0) {
+          int popped[8];
+#pragma unroll
+          for (int q = 0; q < 8; q++) popped[q] = __hip_atomic_load(a.counter + queue_word(q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          int from = -1;   // the next queue after the home queue with something left
+#pragma unroll
+          for (int q = 0; q < 8; q++) {
+            const bool left = queue_begin(q) + blocks_of(q) + popped[q] < queue_begin(q + 1);
+            if (left && (from < 0 || ((q - my_xcd) & 7) < ((from - my_xcd) & 7))) from = q;
+          }
+          if (from < 0) break;
+          item = pop(from);
+        }
       }
+      *s_item = item;
     }
     iter++;
     __syncthreads();
@@ -959,16 +977,6 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     }
     // this item's LDS use (tile rings, merge scratch) ends here; the next item's begins with the work-item word
     __syncthreads();
-  }
-  // The last workgroup to leave rewinds the queue, so a later launch can reuse the stored order
-  // without a pre-pass.  Every workgroup reaches this point exactly once.
-  if (!a.static_assign && tid == 0) {
-    __threadfence();
-    const int done = atomicAdd(a.counter + 1, 1);
-    if (done == (int)gridDim.x - 1) {
-      atomicExch(a.counter + 1, 0);
-      for (int q = 0; q < 8; q++) atomicExch(a.counter + 8 + q, 0);
-    }
   }
 }
 

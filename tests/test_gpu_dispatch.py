@@ -1,0 +1,36 @@
+"""Which variant and schedule a call takes depends on its sizes: the sizes on both sides of every line."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_16518_amd import fgattn as F
+from paper_2509_16518_amd import workloads as W
+from gpu_util import Problem, check_against_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def sparse_rows(items, M, N=1, d=64, H=1, keys=70, seed=50):
+    """`items` query blocks over H heads, each with about `keys` active keys."""
+    L = items // H * M
+    return dataclasses.replace(W.TINY, name="dispatch", H=H, L=L, d=d, M=M, N=N, kind=W.MASK_RANDOM, density=min(1.0, keys / L),
+                               grid=(1, 1, 1), seed=seed + items)
+
+
+# 512 workgroups of the 64-row tile run at once (two per compute unit of 256): up to 512 items need no queue; the next
+# ones are popped; fewer heads than queues, and heads that do not divide among them, leave queues empty or uneven
+@pytest.mark.parametrize("items,H", [(1, 1), (7, 1), (9, 1), (511, 1), (512, 1), (513, 1), (520, 1), (1100, 11), (1536, 3)])
+def test_direct_and_queued_assignment(oracle_mod, items, H):
+    prob = Problem(sparse_rows(items, 64, d=128, H=H))
+    first = prob.run()
+    check_against_oracle(oracle_mod, prob, first, what="%d items" % items)
+    # the stored order is replayed with the queues rewound (or not needed), with other work in between
+    p, pr = prob.params(), prob.params(flags=F.FLAG_REUSE_PLAN)
+    ws = prob.workspace(p)
+    for params in (p, pr, pr):
+        prob.out.zero_()
+        F.fgattn_forward(prob.q, prob.k, prob.v, prob.d_indptr, prob.d_indices, params, prob.out, prob.lse, ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(W.bf16_bits_to_f64(prob.out.view(torch.int16).cpu().numpy().view(np.uint16)), first[0])
