@@ -253,7 +253,6 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   const int NT = a.M <= 32 ? 32 : a.M == 64 ? 64 : 32;   // keys per LDS tile of the variant launched for M
   a.nt_div_n = NT / a.N;
   a.nt_mod_n = NT % a.N;
-  a.n_recip16 = (65536u + (uint32_t)a.N - 1) / (uint32_t)a.N;
   a.QB = QB_items;
   a.n_items = (int32_t)((int64_t)p->B * p->H * QB_items);
   const float sabs = fabsf(p->scale);

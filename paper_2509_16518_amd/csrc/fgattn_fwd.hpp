@@ -130,12 +130,13 @@ struct FwdCfg {
   static constexpr int K_OFF = 0;
   static constexpr int V_OFF = KS * TENSOR_BYTES;
   static constexpr int RING_BYTES = (KS + VS) * TENSOR_BYTES;
-  static constexpr int BIAS_OFF = RING_BYTES;   // (variants with a per-key bias row only)
+  static constexpr int EXTRA_OFF = RING_BYTES;  // membership words or dropped-key words (variants that have them)
   static constexpr int MERGE_REGS = DBLK * 16 + 2;
   static constexpr int MERGE_BYTES = (KW - 1) * RW * MERGE_REGS * 256;
   static constexpr int ITEM_OFF = RING_BYTES - 16;   // the work-item id is handed to the waves through the ring's last bytes
-  static constexpr int LDS_BYTES_BIAS = BIAS_OFF + 2 * NT * 4 + 16;
-  static constexpr int NKEYSETS = KS - VS + 3;  // key-row sets alive at once: tiles t+VS-2 (V gather) .. t+KS (K gather)
+  static constexpr int MEMBER_BYTES = 2 * NT * 4;           // grouped query tiles: a membership word per key and K slot
+  static constexpr int DROP_BYTES = 2 * (2 * WV + 2) * 4;   // short last group: per K slot a tag, and a tag and a word of each wave
+  static constexpr int NKEYS = KS - VS + 3;     // tiles whose keys a wave keeps: t+VS-2 (V gather) .. t+KS (K gather)
   static_assert(MT == 32 || MT == 64 || MT == 128, "query tile");
   static_assert(WV >= RW && WV % RW == 0 && (WV == 1 || WV == 2 || WV == 4), "waves of a workgroup");
   static_assert(D == 64 || D == 128, "head dim");
@@ -146,35 +147,26 @@ struct FwdCfg {
 
 // Online softmax of one 32-key x 32-query score block held as an MFMA accumulator: one query per
 // lane (registers 8c..8c+7 of the accumulator are the keys 16c + 8*(e/4) + 4*(lane/32) + e%4).
-// First half: mask padded keys, new running max of this lane's query.
-// MASK_ROW: a row in LDS says which keys to mask out -- bias 0 for a real key and -inf for a padded / out-of-range
-//   one, or, with member >= 0 (grouped query tiles), per key the bit mask of the group members that selected it (a
-//   query of member MEMBER keeps only the keys whose bit is set).
-// MASK_TAIL: only the tile's trailing positions are masked: accumulator row r of this lane is valid iff r < limit.
-enum { MASK_NONE = 0, MASK_ROW = 1, MASK_TAIL = 2 };
+// First half: mask keys that do not count, new running max of this lane's query.
+// MASK_MEMBERS (grouped query tiles): a row in LDS holds, per key, the bit mask of the group members that selected it; a
+//   query of member `member` keeps only the keys whose bit is set.
+// MASK_DROP: bit 8*r4 + e of `drop` says that the key in accumulator register 4*r4 + e of this lane does not count.
+enum { MASK_NONE = 0, MASK_MEMBERS = 1, MASK_DROP = 2 };
 template <int MASK>
-__device__ __forceinline__ void softmax_max(f32x16& S, const float* bias_keys, int g, float m_run, float& m_new,
-                                            int member = -1, int limit = 0) {
-  if (MASK == MASK_ROW && member >= 0) {
+__device__ __forceinline__ void softmax_max(f32x16& S, const int* members, int g, float m_run, float& m_new,
+                                            int member, unsigned drop) {
+  if (MASK == MASK_MEMBERS) {
 #pragma unroll
     for (int r4 = 0; r4 < 4; r4++) {
-      i32x4 bv = *reinterpret_cast<const i32x4*>(bias_keys + 8 * r4 + 4 * g);
+      i32x4 bv = *reinterpret_cast<const i32x4*>(members + 8 * r4 + 4 * g);
 #pragma unroll
       for (int e = 0; e < 4; e++) S[4 * r4 + e] = ((bv[e] >> member) & 1) ? S[4 * r4 + e] : -INFINITY;
     }
-  } else if (MASK == MASK_ROW) {
-#pragma unroll
-    for (int r4 = 0; r4 < 4; r4++) {
-      f32x4 bv = *reinterpret_cast<const f32x4*>(bias_keys + 8 * r4 + 4 * g);
-#pragma unroll
-      for (int e = 0; e < 4; e++) S[4 * r4 + e] = bv[e] < 0.0f ? -INFINITY : S[4 * r4 + e];
-    }
-  } else if (MASK == MASK_TAIL) {
-    // register 4*r4 + e holds key row 8*r4 + 4*g + e of the wave's 32 keys; `limit` already has the 4*g taken off
+  } else if (MASK == MASK_DROP) {
 #pragma unroll
     for (int r4 = 0; r4 < 4; r4++)
 #pragma unroll
-      for (int e = 0; e < 4; e++) S[4 * r4 + e] = (8 * r4 + e) < limit ? S[4 * r4 + e] : -INFINITY;
+      for (int e = 0; e < 4; e++) S[4 * r4 + e] = (drop >> (8 * r4 + e)) & 1 ? -INFINITY : S[4 * r4 + e];
   }
   // 16 scores -> 1 in eight three-input maxima, three levels deep (this phase is a serial dependency of the key loop)
   const float t0 = max3(S[0], S[1], S[2]), t1 = max3(S[3], S[4], S[5]), t2 = max3(S[6], S[7], S[8]);
@@ -198,27 +190,31 @@ enum { NMODE_DENSE = 0, NMODE_N1 = 1, NMODE_GROUPS = 2, NMODE_GROUPS_SHORT = 3 }
 // the two halves of the kernel can be timed apart on the same launch shape).
 enum { PART_ALL = 0, PART_GATHER = 1, PART_COMPUTE = 2 };
 
-// Which variants keep a per-key row in LDS (bias / membership): a short last key group and grouped query tiles.
-// The others mask the ragged end of a list by position.
-constexpr bool variant_has_mask_row(int nmode, bool grouped) {
-  return grouped || nmode == NMODE_GROUPS_SHORT;
-}
+// LDS beyond the tile rings: grouped query tiles keep membership words there; with a short last key group the waves of a
+// workgroup tell each other which keys of a tile lie past the end of the sequence (a single wave knows by itself).
+// The ragged end of a list is masked by position and needs none.
 template <int MT, int D, int NMODE, bool GROUPED = false, int KS = 2, int VS = 2, int WV = 4>
 constexpr int fwd_lds_bytes() {
   using C = FwdCfg<MT, D, KS, VS, WV>;
-  return variant_has_mask_row(NMODE, GROUPED) ? C::LDS_BYTES_BIAS : C::RING_BYTES;
+  return C::RING_BYTES + (GROUPED ? C::MEMBER_BYTES : NMODE == NMODE_GROUPS_SHORT && WV > 1 ? C::DROP_BYTES : 0);
 }
 
-// id loads of the variants without a mask row: plain per-lane loads written as inline assembly so that the compiler
-// does not track them.  (A tracked load makes the compiler wait with vmcnt(0) before the first use, which would also
-// wait for every gather in flight: the counter is shared and the compiler cannot see the gathers.)  The kernel waits
-// with the s_waitcnt that precedes each tile's barrier (wait_vmem_le(loaded) ties the register to that wait for the compiler);
-// consumers clamp what they read to [0, L), so even a register read too early could never address out of bounds.
+// id loads: plain per-lane loads written as inline assembly so that the compiler does not track them.  (A tracked load
+// makes the compiler wait with vmcnt(0) before the first use, which would also wait for every gather in flight: the
+// counter is shared and the compiler cannot see the gathers.)  The kernel waits with the s_waitcnt that precedes each
+// tile's barrier (wait_vmem_le(loaded) ties the register to that wait for the compiler); consumers clamp what they read
+// to [0, L), so even a register read too early could never address out of bounds.
 __device__ __forceinline__ void load_id_untracked(int& dst, const int32_t* base, unsigned byte_off) {
   // (scalar base + 32-bit per-lane offset: no 64-bit address arithmetic on the vector ALU)
   base = static_cast<const int32_t*>(pin_scalar(base));
   asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
 }
+__device__ __forceinline__ void load_byte_untracked(int& dst, const uint8_t* base, unsigned byte_off) {
+  base = static_cast<const uint8_t*>(pin_scalar(base));
+  asm volatile("global_load_ubyte %0, %1, %2" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
+}
+// `loaded` (an untracked load's target) is valid from here on, by a wait just made
+__device__ __forceinline__ void arrived(int& loaded) { asm volatile("" : "+v"(loaded)); }
 template <int N>
 __device__ __forceinline__ void wait_vmem_le() {   // s_waitcnt vmcnt(N): at most N vector-memory loads still in flight
   static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
@@ -239,29 +235,27 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
   using C = FwdCfg<MT, D, KS, VS, WV>;
   constexpr bool DENSE = NMODE == NMODE_DENSE;
   constexpr bool WAVE_PRIO = NMODE == NMODE_DENSE || NMODE == NMODE_N1;
-  constexpr bool MASK_ROWS = variant_has_mask_row(NMODE, GROUPED);   // per-key bias / membership row in LDS
-  constexpr bool ASM_IDS = NMODE == NMODE_N1 && !GROUPED;            // ids through untracked loads
-  // ... whose cross-lane permute is issued before the barrier that precedes its use (measured on one box: 2.4% faster
-  // at 128 query rows, 2.5% slower at 64 -- also when the ids are requested an iteration earlier, so that the wait
-  // for them at the end of an iteration is free)
-  constexpr bool EARLY_PERMUTE = ASM_IDS && MT == 128;
+  constexpr bool SHORT_GROUP = NMODE == NMODE_GROUPS_SHORT;   // (the host picks the variant from L % N)
+  // the cross-lane permute of the ids is issued before the barrier that precedes its use (measured with one key per group:
+  // 2.4% faster at 128 query rows, 2.5% slower at 64)
+  constexpr bool EARLY_PERMUTE = NMODE == NMODE_N1 && !GROUPED && MT == 128;
   static_assert(!GROUPED || (MT == 128 && (NMODE == NMODE_N1 || NMODE == NMODE_GROUPS_SHORT)),
                 "groups are 128 query rows with a sparse list (any L: the variant that masks positions past the end)");
-  static_assert(!MASK_ROWS || (KS == 2 && VS == 2), "the mask row is a two-slot ring and its id loads are tracked");
-  // vector-memory operations per iteration and wave, in program order: [ids (ASM_IDS)] [V gathers] [K gathers]
-  constexpr int PER = 2 * C::IPW + (ASM_IDS ? 1 : 0);
+  // vector-memory operations per iteration and wave, in program order: V gathers, K gathers, ids of a later tile (and their
+  // membership bytes)
+  constexpr int NIDS = DENSE ? 0 : GROUPED ? 2 : 1;
+  constexpr int PER = 2 * C::IPW + NIDS;
   // What may still be in flight at the barrier that opens iteration t+1: everything issued after V(t) (gathered in
-  // iteration t+2-VS, first in its iteration) and after K(t+2) (gathered in iteration t+2-KS, last in its iteration)
-  constexpr int WAITN = cmin(C::IPW + (VS - 2) * PER, (KS - 2) * PER);
-  // ids are requested IDL iterations before they are turned into key rows; by then at least WAITN operations must
-  // have followed them (the smallest such lead, rounded up to a power of two to keep the unrolled loop short)
-  constexpr int IDL_MIN = ASM_IDS ? (WAITN <= 2 * C::IPW ? 1 : 1 + (WAITN - 2 * C::IPW + PER - 1) / PER) : 1;
-  constexpr int IDL = IDL_MIN <= 1 ? 1 : IDL_MIN <= 2 ? 2 : 4;
-  static_assert(IDL_MIN <= 4, "id lead");
-  constexpr int AFTER_IDS = 2 * C::IPW + (IDL - 1) * PER;   // operations issued after an id load by the end of the iteration before its use
-  static_assert(!ASM_IDS || (AFTER_IDS >= WAITN && AFTER_IDS <= 63), "id wait");
-  constexpr int U = clcm(clcm(KS, VS), clcm(2, IDL));   // iterations per unrolled loop body: every slot is an immediate
-  static_assert(U <= 12, "unroll");
+  // iteration t+2-VS, first in its iteration) and after K(t+2) (gathered in iteration t+2-KS).  With two slots each
+  // that is the id load at the end of iteration t alone: the list streams from device memory, and its latency passes
+  // under the whole of iteration t+1 instead of holding the barrier.
+  constexpr int WAITN = cmin(C::IPW + NIDS + (VS - 2) * PER, NIDS + (KS - 2) * PER);
+  // ids of tile t+KS+IDL are requested at the end of iteration t and turned into key rows at the start of iteration t+IDL
+  constexpr int IDL = 2;
+  constexpr int AFTER_IDS = (IDL - 1) * PER;   // operations issued after an id load by the end of the iteration before its use
+  static_assert(AFTER_IDS >= WAITN && AFTER_IDS <= 63, "id wait");
+  constexpr int U = clcm(clcm(KS, VS), 2);   // iterations per unrolled loop body: every slot is an immediate
+  static_assert(U <= 12 && U % IDL == 0, "unroll");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int tid = threadIdx.x;
@@ -274,9 +268,11 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
   // transposed-read role for V: 16-lane group (g,u); lane n = 4*kq + q addresses key kq, d offset 4q
   const int u = (lane >> 4) & 1, kq = (lane & 15) >> 2, qq = lane & 3;
 
-  float* bias = reinterpret_cast<float*>(smem + C::BIAS_OFF);
-  // per bias-ring slot: tile number + 1 of the last tile that put a key to be masked out into the slot
-  int* masked_tile = reinterpret_cast<int*>(smem + C::BIAS_OFF + 2 * C::NT * 4);
+  int* const members = reinterpret_cast<int*>(smem + C::EXTRA_OFF);   // GROUPED: [tile % 2][key of the tile]
+  // SHORT_GROUP: per tile % 2, the tag of the last tile with keys past the end of the sequence, then for each wave the
+  // tag of the last tile in which its rows had some, and which
+  int* const drops = reinterpret_cast<int*>(smem + C::EXTRA_OFF);
+  constexpr int DROP_SLOT = 2 * WV + 2;
   volatile int* s_item = reinterpret_cast<volatile int*>(smem + C::ITEM_OFF);
   const unsigned lds0 = lds_address(smem);
 
@@ -306,15 +302,13 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
 
   const unsigned k_rowb = (unsigned)(a.k_sl * 2), v_rowb = (unsigned)(a.v_sl * 2);
   const int N = DENSE ? 1 : a.N;
-  constexpr bool short_group = NMODE == NMODE_GROUPS_SHORT;   // (the host picks the variant from L % N)
-
-  // Per bias-ring slot: the tile that was last consumed from it had masked keys, so its row holds entries other
-  // than zero and the next tile's loaders must rewrite it whole (true at the start: LDS holds anything).
-  bool slot_dirty[2] = {true, true};
-  // (this bookkeeping is used only where a short last group can put masked keys into any tile: N keys per group
-  // with L not a multiple of N; elsewhere only a ragged last tile has them, and every checked tile writes its
-  // whole row)
-  constexpr bool LAZY_BIAS = NMODE == NMODE_GROUPS_SHORT && !GROUPED;
+  // tags of tiles, unique over the items of this workgroup: a word left by an earlier tile never looks current
+  constexpr bool TELL_DROPS = SHORT_GROUP && !GROUPED && WV > 1;
+  int tag0 = 1;
+  if (TELL_DROPS && tid < 2 * DROP_SLOT) drops[tid] = 0;   // (published by the barriers around the work-item word)
+  // place of this lane's row of tile 0 inside the list: group and key of the group (the same for every item)
+  const int lrow_id = wv * C::RPW + (lane & (C::RPW - 1));
+  const int gq0 = NMODE >= NMODE_GROUPS ? lrow_id / N : lrow_id, gr0 = NMODE >= NMODE_GROUPS ? lrow_id % N : 0;
   int iter = 0;
   // the XCD this workgroup runs on (hardware register XCC_ID, bits 3:0) picks its home queue
   const int my_xcd = __builtin_amdgcn_s_getreg((4 - 1) << 11 | 0 << 6 | 20) & 7;
@@ -399,10 +393,6 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     const int ntiles = (total + C::NT - 1) / C::NT;
     // (wave-uniform; pinned to scalar registers here, an item's set-up ahead of the first id load that uses it as its base)
     const int32_t* idx = DENSE ? nullptr : static_cast<const int32_t*>(pin_scalar(a.indices + beg));
-    // Row that padded / out-of-range positions of a tile fetch (their scores are masked out): the item's first
-    // active key, so that only rows of the active set are ever multiplied, even by zero (0 x Inf would be NaN).
-    int pad_key = 0;
-    if (!DENSE && cnt > 0) pad_key = __builtin_amdgcn_readfirstlane(idx[0]) * N;
     const uint16_t* kbase = a.k + b * a.k_sb + h * a.k_sh;
     const uint16_t* vbase = a.v + b * a.v_sb + h * a.v_sh;
 
@@ -422,155 +412,119 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // ---------------- loader ----------------
     // Position p = T*NT + wv*RPW + i*RPI + lrow of the compacted list is fetched by this lane with load
     // instruction i of tile T.  Pipeline per tile T (one iteration per tile, one barrier each):
-    //   iteration T-KS-IDL: group ids requested     iteration T-KS : ids -> key rows, K(T) gathered
+    //   iteration T-KS-2  : group ids requested     iteration T-KS : ids -> key rows, K(T) gathered
     //   iteration T-1     : S(T) = K(T) Q^T, row max iteration T-VS+2: V(T) gathered
     //   iteration T       : P(T) = exp(S(T) - m)     iteration T+1  : O += V(T)^T P(T)^T
-    // Past the end of the list the pipeline keeps running on the last tile again (clamped tile index): a few
-    // redundant, in-bounds gathers per work item instead of existence checks in every iteration.
-    int gi[C::IPW];       // group ids being fetched (next tile to convert)
-    int gm[C::IPW];       // GROUPED: their membership masks
-    int wi[C::IPW];       // offset of the key inside its group (NMODE_GROUPS)
-    int widx[IDL];        // coalesced id fetch: lane j holds the id of row j % RPW of this wave's rows; tile T in widx[T % IDL]
-    // key rows of tiles t+VS-2 .. t+KS in iteration t (set 0 feeds the V gathers, the last set the K gathers)
-    int keys[C::NKEYSETS][C::IPW];
-    constexpr int KNEW = C::NKEYSETS - 1;
-    int tq = 0, tr = 0;   // (T*NT) / N and (T*NT) % N for the next tile to fetch ids for, advanced without divisions
+    // Past the end of the list the pipeline keeps running on clamped positions: a few redundant, in-bounds gathers of
+    // active rows per work item instead of existence checks in every iteration.
+    //
+    // ids -> key rows: lane j of a wave turns the id of row j % RPW of the wave's part of the tile into a key row (one
+    // load and a handful of vector instructions per tile, whatever N is); a cross-lane permute then hands every lane
+    // the key of the row it fetches with each load instruction.  (With N keys per group every load instruction used to
+    // fetch and convert its own ids, in tracked loads that drained the gathers: 12 heads x 32760 tokens at 32x32 4.62 ms,
+    // now 3.81; 40 uneven heads at 64x8 7.14 ms, now 6.54.)
     const int lpos = wv * C::RPW + lrow;
-    const unsigned id_lane4 = (unsigned)(wv * C::RPW + (lane & (C::RPW - 1))) * 4u;   // byte offset of this lane's id inside a tile's ids
-    const int last = ntiles - 1;
-    const uint8_t* memb = GROUPED ? a.memb + beg : nullptr;
-    // a tile whose positions need checking: short last group, ragged last tile, or (GROUPED) always, since the mask
-    // row then carries the membership masks
-    auto tile_needs_check = [&](int T) { return GROUPED || short_group || (T + 1) * C::NT > total; };
-    // ... and whether the scores of tile T need the bias row at all: with a short last group only the tiles that
-    // contain it do, and the lanes that loaded its missing keys have said so in masked_tile (a stale entry of an
-    // earlier work item can only make a tile take the bias row needlessly: the row is written for every tile)
-    // (`entry` is masked_tile[T & 1], read by the caller early enough that its latency is hidden)
-    auto tile_has_masked_keys = [&](int T, int entry) {
-      if (GROUPED || (T + 1) * C::NT > total) return true;
-      if (!short_group) return false;
-      return __builtin_amdgcn_readfirstlane(entry) == T + 1;
-    };
-    // full tiles with one key per group: one coalesced load per wave brings the RPW ids of its rows;
-    // a cross-lane permute then hands each lane the id of its own row
-    auto coalesced_ids = [&](int T) { return NMODE == NMODE_N1 && (ASM_IDS || !tile_needs_check(T)); };
-    auto fetch_ids = [&](int T, int& wdst) {
-      if (NMODE == NMODE_DENSE) return;
-      if constexpr (ASM_IDS) {
-        // (the position is clamped into the list: a ragged last tile masks what lies past the end by position)
-        load_id_untracked(wdst, idx, min((unsigned)(T * C::NT * 4) + id_lane4, (unsigned)(cnt - 1) * 4u));
-        return;
-      }
-      if (__builtin_expect(coalesced_ids(T), 1)) {
-        wdst = idx[T * C::NT + wv * C::RPW + (lane & (C::RPW - 1))];
-        return;
-      }
-#pragma unroll
-      for (int i = 0; i < C::IPW; i++) {
-        int grp;
-        if (NMODE == NMODE_N1) {
-          grp = T * C::NT + lpos + i * C::RPI;
-        } else {
-          const int x = tr + lpos + i * C::RPI;          // < N + NT
-          // (24-bit multiplies, which run at full rate: x < 2 NT and the reciprocal has 17 bits; below, q N <= x)
-          const int q = N >= C::NT ? (x >= N ? 1 : 0) : (int)(__umul24((unsigned)x, a.n_recip16) >> 16);
-          grp = tq + q;
-          wi[i] = x - (int)__umul24((unsigned)q, (unsigned)N);
-        }
-        gi[i] = idx[min(grp, cnt - 1)];
-        if constexpr (GROUPED) gm[i] = memb[min(grp, cnt - 1)];
-      }
-      if ((NMODE == NMODE_GROUPS || NMODE == NMODE_GROUPS_SHORT) && T < last) {   // a repeated (clamped) last tile must see the same tq, tr again
-        tq += a.nt_div_n;
-        tr += a.nt_mod_n;
-        if (tr >= N) {
-          tr -= N;
-          tq += 1;
-        }
+    int gi[IDL];                   // the id of this lane's row: tile T in gi[T % IDL]
+    int gm[IDL];                   // GROUPED: its membership byte
+    int gr[IDL];                   // NMODE_GROUPS: the key's place inside its group
+    // Key rows of tiles t+VS-2 .. t+KS in iteration t (set 0 feeds the V gathers, the last set the K gathers): with up to
+    // four load instructions per tile as the permute handed them out; with eight (32 query rows) one key per lane,
+    // permuted once for K and again for V, which saves 14 registers and the moves between the sets (the other way
+    // round, a second permute at 64 query rows costs 3.5%).
+    constexpr bool KEEP_SPREAD = C::IPW <= 4;
+    constexpr int KNEW = C::NKEYS - 1;
+    int keys[C::NKEYS][KEEP_SPREAD ? C::IPW : 1];
+    int kk[C::IPW], vk[C::IPW];    // key rows of the next K and V gathers
+    int nq = gq0, nr = gr0;        // NMODE_GROUPS: place of the next tile to request, advanced without divisions
+    const uint8_t* memb = GROUPED ? static_cast<const uint8_t*>(pin_scalar(a.memb + beg)) : nullptr;
+    unsigned lone_drop[2] = {0u, 0u};   // SHORT_GROUP, one wave: keys past the end of the sequence, by tile % 2
+    auto fetch_ids = [&](int T, int& id, int& mb, int& off) {
+      if constexpr (DENSE) return;
+      if constexpr (NMODE == NMODE_N1) {
+        const unsigned at = min((unsigned)(T * C::NT + lrow_id), (unsigned)(cnt - 1));
+        load_id_untracked(id, idx, at * 4u);
+        if constexpr (GROUPED) load_byte_untracked(mb, memb, at);
+      } else {
+        const unsigned at = (unsigned)min(nq, cnt - 1);
+        off = nr;
+        load_id_untracked(id, idx, at * 4u);
+        if constexpr (GROUPED) load_byte_untracked(mb, memb, at);
+        nq += a.nt_div_n;
+        nr += a.nt_mod_n;
+        const bool wrap = nr >= N;
+        nr -= wrap ? N : 0;
+        nq += wrap ? 1 : 0;
       }
     };
-    // Variants without a mask row turn ids into key rows in two steps, so that the cross-lane permute of the first has
-    // the gather phase's first slots to complete before the second consumes it:
-    //   keys_begin: ids of tile T (in wsrc) -> this lane's raw ids (one key per group: a permute is issued, nothing waits);
-    //   keys_finish: raw ids -> key rows, clamped into the K/V slice; positions past the end of the list read the
-    //   item's first active row (their scores are masked out by position).
-    auto keys_begin = [&](int T, int wsrc, int (&kdst)[C::IPW]) {
-#pragma unroll
-      for (int i = 0; i < C::IPW; i++) {
-        if constexpr (DENSE) kdst[i] = T * C::NT + lpos + i * C::RPI;
-        else if constexpr (NMODE == NMODE_N1) kdst[i] = __builtin_amdgcn_ds_bpermute((i * C::RPI + lrow) << 2, wsrc);
-        else kdst[i] = (int)__umul24((unsigned)gi[i], (unsigned)N) + wi[i];   // (group id and N are below 2^24, and so is their product)
-      }
-    };
-    auto keys_finish = [&](int T, int (&kdst)[C::IPW]) {
-      if constexpr (!DENSE) {   // clamped: whatever the register held, the gather stays inside the K/V slice
-#pragma unroll
-        for (int i = 0; i < C::IPW; i++) kdst[i] = (int)min((unsigned)kdst[i], (unsigned)(a.L - 1));
-      }
-      if (__builtin_expect(tile_needs_check(T), 0)) {
-#pragma unroll
-        for (int i = 0; i < C::IPW; i++) kdst[i] = T * C::NT + lpos + i * C::RPI < total ? kdst[i] : pad_key;
-      }
-    };
-    // ids of tile T (fetched earlier, in wsrc) -> key rows in kdst; padded / out-of-range positions of a checked tile
-    // read the item's first active row and have their scores masked out
-    auto make_keys = [&](int T, int wsrc, int (&kdst)[C::IPW]) {
-      if constexpr (!MASK_ROWS) {
-        keys_begin(T, wsrc, kdst);
-        keys_finish(T, kdst);
-        return;
-      }
-      if (NMODE == NMODE_N1 && __builtin_expect(coalesced_ids(T), 1)) {
-#pragma unroll
-        for (int i = 0; i < C::IPW; i++) kdst[i] = __builtin_amdgcn_ds_bpermute((i * C::RPI + lrow) << 2, wsrc);
-        return;
-      }
-      const bool checked = tile_needs_check(T);
-      if constexpr (!LAZY_BIAS) {
-        // a checked tile writes its whole row (GROUPED: the membership masks, every tile)
-#pragma unroll
-        for (int i = 0; i < C::IPW; i++) {
-          const int p = T * C::NT + lpos + i * C::RPI;
-          // (group id and N are below 2^24 and so is their product, a key row)
-          int key = NMODE == NMODE_N1 ? gi[i] : (int)__umul24((unsigned)gi[i], (unsigned)N) + wi[i];
-          if (__builtin_expect(checked, 0)) {
-            const bool ok = p < total && key < a.L;
-            key = ok ? key : pad_key;
-            if (pc == 0) {
-              if constexpr (GROUPED)
-                reinterpret_cast<int*>(bias)[(T & 1) * C::NT + lpos + i * C::RPI] = ok ? gm[i] : 0;
-              else
-                bias[(T & 1) * C::NT + lpos + i * C::RPI] = ok ? 0.0f : -INFINITY;
-            }
+    // id -> this lane's key row (T = the tile, par = T % 2), clamped to [0, L): whatever the register held, the gather
+    // stays inside the K/V slice; a position past the end of the list or of the sequence reads an active row, so that
+    // only active rows are ever multiplied, even by zero (0 x Inf would be NaN), and its score is masked out
+    auto to_key = [&](int T, int par, int id, int mb, int off) {
+      const unsigned raw = NMODE >= NMODE_GROUPS ? __umul24((unsigned)id, (unsigned)N) + (unsigned)off : (unsigned)id;
+      if constexpr (GROUPED) {
+        // the membership word of this key; no member where there is no key
+        if (lane < C::RPW) members[par * C::NT + lrow_id] = T * C::NT + lrow_id < total && raw < (unsigned)a.L ? mb : 0;
+      } else if constexpr (SHORT_GROUP) {
+        const uint64_t past = __builtin_amdgcn_ballot_w64(raw >= (unsigned)a.L);
+        if constexpr (WV == 1) {
+          lone_drop[par] = (unsigned)past;
+        } else if (__builtin_expect(past != 0, 0)) {
+          if (lane == 0) {
+            drops[par * DROP_SLOT] = tag0 + T;
+            drops[par * DROP_SLOT + 2 + wv] = tag0 + T;
+            drops[par * DROP_SLOT + 2 + WV + wv] = (int)((unsigned)past & (0xFFFFFFFFu >> (32 - C::RPW)));
           }
-          kdst[i] = key;
         }
-        return;
       }
-      // Bias row of the slot: 0 for a real key, -inf for a padded / out-of-range one.  A row is all zeros unless its
-      // tile had such keys; then the tile's consumers mark the slot dirty and the loaders of the next tile in it
-      // write every entry.  Otherwise only the (rare) -inf entries are written, and the tile is announced in
-      // masked_tile so that the consumers look at the row at all.
-      const bool rewrite = slot_dirty[T & 1];
-      bool ok[C::IPW];
-      bool any_bad = false;
+      return (int)min(raw, (unsigned)(a.L - 1));
+    };
+    // key rows of tile T for this lane's load instructions
+    auto spread = [&](int T, int key, int (&dst)[C::IPW]) {
 #pragma unroll
       for (int i = 0; i < C::IPW; i++) {
-        const int p = T * C::NT + lpos + i * C::RPI;
-        int key = (int)__umul24((unsigned)gi[i], (unsigned)N) + wi[i];
-        ok[i] = !checked || (p < total && key < a.L);
-        any_bad |= !ok[i];
-        kdst[i] = ok[i] ? key : pad_key;
+        if constexpr (DENSE) dst[i] = min(T * C::NT + lpos + i * C::RPI, a.L - 1);
+        else dst[i] = __builtin_amdgcn_ds_bpermute((i * C::RPI + lrow) << 2, key);
       }
-      if (__builtin_expect(rewrite || __builtin_amdgcn_ballot_w64(any_bad) != 0, 0)) {
-        if (pc == 0) {
+    };
+    // tile T enters the pipeline as its newest key set / the V gathers' set leaves it
+    auto take_keys = [&](int T, int par, int id, int mb, int off) {
+      const int key = DENSE ? 0 : to_key(T, par, id, mb, off);
+      spread(T, key, kk);
+      if constexpr (KEEP_SPREAD) {
 #pragma unroll
-          for (int i = 0; i < C::IPW; i++)
-            if (rewrite || !ok[i]) bias[(T & 1) * C::NT + lpos + i * C::RPI] = ok[i] ? 0.0f : -INFINITY;
-        }
-        if (any_bad) masked_tile[T & 1] = T + 1;
-        slot_dirty[T & 1] = false;   // (a row left alone by unchecked tiles stays dirty until a tile rewrites it)
+        for (int i = 0; i < C::IPW; i++) keys[KNEW][i] = kk[i];
+      } else {
+        keys[KNEW][0] = key;
       }
+    };
+    auto v_keys = [&](int T) {
+      if constexpr (KEEP_SPREAD) {
+#pragma unroll
+        for (int i = 0; i < C::IPW; i++) vk[i] = keys[0][i];
+      } else {
+        spread(T, keys[0][0], vk);
+      }
+    };
+    auto rotate_keys = [&]() {
+#pragma unroll
+      for (int s = 0; s + 1 < C::NKEYS; s++)
+#pragma unroll
+        for (int i = 0; i < (KEEP_SPREAD ? C::IPW : 1); i++) keys[s][i] = keys[s + 1][i];
+    };
+    // keys of tile Tm that do not count, as bits of this lane's accumulator registers (see MASK_DROP)
+    auto dropped = [&](int Tm, int par) -> unsigned {
+      const int limit = total - Tm * C::NT - kw * 32;   // keys of this wave's part that lie inside the list
+      unsigned d = limit >= 32 ? 0u : limit <= 0 ? ~0u : ~0u << limit;
+      if constexpr (SHORT_GROUP && WV == 1) d |= lone_drop[par];
+      if constexpr (TELL_DROPS) {
+        const int* slot = drops + par * DROP_SLOT;
+#pragma unroll
+        for (int w2 = 0; w2 < WV; w2++) {   // (rows w2 * RPW .. of the tile are wave w2's)
+          const int at = w2 * C::RPW - kw * 32;
+          if (at >= 0 && at < 32 && slot[2 + w2] == tag0 + Tm) d |= (unsigned)slot[2 + WV + w2] << at;
+        }
+      }
+      return d >> (4 * g);
     };
     // LDS: K ring slots 0..KS-1 then V ring slots 0..VS-1, TENSOR_BYTES each.  A run of up to four gathers of one
     // wave lands back to back, so only the first writes M0 and the others use the instruction offset (which also
@@ -665,7 +619,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // ring: one MFMA of each per slot.  With EXP, every slot also takes its share of the exponentials of the previous
     // tile's scores So: P = exp2(c*(So - m)) packed to bf16 into Pout, and the row sum; they issue while the two matrix
     // instructions just issued execute.  With GATHER, every slot then issues one of this iteration's gathers: V rows
-    // (keys in key set 0) -> V slot `vwr`, then K rows (keys in the newest key set) -> K slot `kwr`, both released by
+    // (keys in vk) -> V slot `vwr`, then K rows (keys in kk) -> K slot `kwr`, both released by
     // the previous iteration.  The gather holds the wave; the matrix instructions execute underneath it.
     auto x_phase = [&](auto vrd_c, auto krd_c, auto vwr_c, auto kwr_c, const i32x4 (&Pin)[2], auto with_gather,
                        auto with_qk, f32x16& Sn, auto with_exp, const f32x16& So, i32x4 (&Pout)[2]) {
@@ -720,12 +674,12 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         if constexpr (GATHER) {
           if constexpr (e % DMA_EVERY == 0) {
             constexpr int j0 = (e / DMA_EVERY) * DMA_PER;
-            if constexpr (j0 < C::IPW) gather_v(std::integral_constant<int, j0>(), vwr, keys[0]);
-            else if constexpr (j0 < NDMA) gather_k(std::integral_constant<int, j0 - C::IPW>(), kwr, keys[KNEW]);
+            if constexpr (j0 < C::IPW) gather_v(std::integral_constant<int, j0>(), vwr, vk);
+            else if constexpr (j0 < NDMA) gather_k(std::integral_constant<int, j0 - C::IPW>(), kwr, kk);
             if constexpr (DMA_PER > 1) {
               constexpr int j1 = j0 + 1;
-              if constexpr (j1 < C::IPW) gather_v(std::integral_constant<int, j1>(), vwr, keys[0]);
-              else if constexpr (j1 < NDMA) gather_k(std::integral_constant<int, j1 - C::IPW>(), kwr, keys[KNEW]);
+              if constexpr (j1 < C::IPW) gather_v(std::integral_constant<int, j1>(), vwr, vk);
+              else if constexpr (j1 < NDMA) gather_k(std::integral_constant<int, j1 - C::IPW>(), kwr, kk);
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -742,13 +696,13 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         slot(std::integral_constant<int, 7>());
       }
     };
-    // Phase Y, vector ALU only in the key loop: the row max of the new scores Sn (tile Tm) and the rare decision to
+    // Phase Y, vector ALU only in the key loop: the row max of the new scores Sn (tile Tm, par = Tm % 2) and the rare decision to
     // move the exponent base (see kLazyLog2).  With MFMA (prologue only) it first computes Sn = K Q^T with K in slot
     // `kslot` of the K ring.
-    auto y_phase = [&](auto kslot, int Tm, f32x16& Sn, auto with_mfma) {
+    auto y_phase = [&](auto kslot, int Tm, int par, f32x16& Sn, auto with_mfma) {
       constexpr bool MFMA = decltype(with_mfma)::value;
       // written before the barrier that precedes this phase; consumed at its end
-      const int masked_entry = LAZY_BIAS ? masked_tile[Tm & 1] : 0;
+      const int drop_tag = TELL_DROPS ? drops[par * DROP_SLOT] : 0;
       if constexpr (PART == PART_GATHER) return;
       if constexpr (MFMA) {
         const unsigned char* kst = smem + C::K_OFF + kslot * C::TENSOR_BYTES;
@@ -767,26 +721,27 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         }
       }
       float m_new;
-      // (the same in every wave of the workgroup)
-      const bool masked = LAZY_BIAS ? tile_has_masked_keys(Tm, masked_entry) : tile_needs_check(Tm);
-      if (__builtin_expect(masked, 0)) {
-        if constexpr (MASK_ROWS)
-          softmax_max<MASK_ROW>(Sn, bias + (Tm & 1) * C::NT + kw * 32, g, m_pend, m_new, GROUPED ? my_member : -1);
-        else   // positions of the tile at and past `total` are padding
-          softmax_max<MASK_TAIL>(Sn, nullptr, g, m_pend, m_new, -1, total - Tm * C::NT - kw * 32 - 4 * g);
-      } else {
-        softmax_max<MASK_NONE>(Sn, nullptr, g, m_pend, m_new);
-      }
-      if constexpr (LAZY_BIAS) slot_dirty[Tm & 1] |= masked;
+      bool masked = (Tm + 1) * C::NT > total;   // (the same in every wave of the workgroup)
+      if constexpr (SHORT_GROUP && !GROUPED && WV == 1) masked |= lone_drop[par] != 0;
+      if constexpr (TELL_DROPS) masked |= __builtin_amdgcn_readfirstlane(drop_tag) == tag0 + Tm;
+      if constexpr (GROUPED)
+        softmax_max<MASK_MEMBERS>(Sn, members + par * C::NT + kw * 32, g, m_pend, m_new, my_member, 0u);
+      else if (__builtin_expect(masked, 0))
+        softmax_max<MASK_DROP>(Sn, nullptr, g, m_pend, m_new, 0, dropped(Tm, par));
+      else
+        softmax_max<MASK_NONE>(Sn, nullptr, g, m_pend, m_new, 0, 0u);
       m_pend = m_new;
       const bool lane_moves = m_new > m_move;   // (the first valid key of a lane also moves it: m_move = -inf until then)
       resc = __builtin_amdgcn_ballot_w64(lane_moves) != 0;
     };
-    auto rotate_keys = [&]() {
-#pragma unroll
-      for (int s = 0; s + 1 < C::NKEYSETS; s++)
-#pragma unroll
-        for (int i = 0; i < C::IPW; i++) keys[s][i] = keys[s + 1][i];
+    // at most N operations in flight, and the ids in register set e have arrived
+    auto wait_ids = [&](auto n, int e) {
+      if constexpr (DENSE) {
+        wait_vmem_le<decltype(n)::value>();
+      } else {
+        wait_vmem_le<decltype(n)::value>(gi[e]);
+        if constexpr (GROUPED) arrived(gm[e]);
+      }
     };
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
@@ -806,8 +761,8 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       // K(t+1) and V(t-1) become visible to every wave: all but the WAITN most recent vector-memory operations of this
       // wave have completed (they complete in order), which covers its share of both tiles and the ids converted
       // below; every wave is done reading K(t) and V(t-2), whose slots this iteration refills
-      if constexpr (ASM_IDS) wait_vmem_le<WAITN>(widx[(J + KS) % IDL]);
-      else wait_vmem_le<WAITN>();
+      constexpr int E = (J + KS) % IDL;
+      wait_ids(std::integral_constant<int, WAITN>(), E);
       __syncthreads();
       float alpha = 1.0f;
       if (__builtin_expect(resc, 0)) {   // the exponent base moves: l now, O after the MFMAs of the old base
@@ -816,11 +771,10 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         l_run2 *= alpha;
         set_base(m_pend);
       }
-      // ids requested IDL iterations ago -> key rows (with untracked id loads the cross-lane permute was already
-      // issued before the barrier, at the end of the previous iteration, and only its result is consumed here)
-      if constexpr (EARLY_PERMUTE) keys_finish(min(t + KS, last), keys[KNEW]);
-      else make_keys(min(t + KS, last), widx[(J + KS) % IDL], keys[KNEW]);
-      fetch_ids(min(t + KS + IDL, last), widx[(J + KS) % IDL]);
+      if constexpr (!EARLY_PERMUTE) {   // ids requested IDL iterations ago -> key rows
+        take_keys(t + KS, (J + KS) & 1, gi[E], gm[E], gr[E]);
+        v_keys(t + VS - 2);
+      }
       // wave priority: the gather phase above the vector-ALU phase above everything outside the key loop, so that
       // the waves that feed the memory pipe are issued first and a neighbour's prologue or epilogue never delays them
       // (measured: 1-3% faster with one key per group, 6% for the dense kernel at 128 rows; slower with N keys per
@@ -836,13 +790,16 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
 #pragma unroll
           for (int r = 0; r < 16; r++) O[db][r] *= alpha;
       }
-      y_phase(std::integral_constant<int, 0>(), min(t + 1, last), Sn, no());
+      fetch_ids(t + KS + IDL, gi[E], gm[E], gr[E]);
+      y_phase(std::integral_constant<int, 0>(), t + 1, (J + 1) & 1, Sn, no());
       rotate_keys();
       if constexpr (EARLY_PERMUTE) {
         // the ids of the tile whose K rows the next iteration gathers have arrived (their load was followed by
         // AFTER_IDS operations): hand them to the lanes now, so that the permute's latency passes in the barrier
-        wait_vmem_le<AFTER_IDS>(widx[(J + 1 + KS) % IDL]);
-        keys_begin(min(t + 1 + KS, last), widx[(J + 1 + KS) % IDL], keys[KNEW]);
+        constexpr int E1 = (J + 1 + KS) % IDL;
+        wait_ids(std::integral_constant<int, AFTER_IDS>(), E1);
+        take_keys(t + 1 + KS, (J + 1 + KS) & 1, gi[E1], gm[E1], gr[E1]);
+        v_keys(t + 1 + VS - 2);
       }
     };
 
@@ -854,43 +811,37 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       for (int c = 0; c < 2; c++)
 #pragma unroll
         for (int e = 0; e < 4; e++) PB[c][e] = 0;
-      int wpro[KS];   // ids of tiles 0 .. KS-1 (ASM_IDS: requested together)
-      if constexpr (ASM_IDS) {
+      int pid[KS], pmb[KS], poff[KS];   // ids of tiles 0 .. KS-1, requested together with those of the first iterations
 #pragma unroll
-        for (int T = 0; T < KS; T++) fetch_ids(min(T, last), wpro[T]);
+      for (int T = 0; T < KS; T++) fetch_ids(T, pid[T], pmb[T], poff[T]);
 #pragma unroll
-        for (int T = 0; T < IDL; T++) fetch_ids(min(KS + T, last), widx[(KS + T) % IDL]);
+      for (int T = KS; T < KS + IDL; T++) fetch_ids(T, gi[T % IDL], gm[T % IDL], gr[T % IDL]);
+      if constexpr (!DENSE) {
 #pragma unroll
-        for (int T = 0; T < KS; T++) wait_vmem_le<0>(wpro[T]);
+        for (int T = 0; T < KS; T++) {
+          wait_vmem_le<0>(pid[T]);
+          if constexpr (GROUPED) arrived(pmb[T]);
+        }
+#pragma unroll
+        for (int e = 0; e < IDL; e++) wait_ids(std::integral_constant<int, 0>(), e);
       }
-      int ktmp[C::IPW];
 #pragma unroll
       for (int T = 0; T < KS; T++) {
-        if constexpr (!ASM_IDS) fetch_ids(min(T, last), wpro[T]);
-        make_keys(min(T, last), wpro[T], ktmp);
-        burst_k(T, ktmp);
-        if (T == 0) {
-          burst_v(VS - 1, ktmp);
-#pragma unroll
-          for (int s = 0; s < C::NKEYSETS; s++)
-#pragma unroll
-            for (int i = 0; i < C::IPW; i++) keys[s][i] = ktmp[i];
-        }
-        if (T <= VS - 3) burst_v(T, ktmp);
-        if (T >= VS - 2) {
-#pragma unroll
-          for (int i = 0; i < C::IPW; i++) keys[T - (VS - 2)][i] = ktmp[i];
-        }
+        if (T > 0) rotate_keys();
+        take_keys(T, T & 1, pid[T], pmb[T], poff[T]);
+        burst_k(T, kk);
+        if (T == 0) burst_v(VS - 1, kk);
+        if (T <= VS - 3) burst_v(T, kk);
       }
-      if constexpr (!ASM_IDS) fetch_ids(min(KS, last), widx[KS % IDL]);
-      else if constexpr (EARLY_PERMUTE) {
-        wait_vmem_le<0>(widx[KS % IDL]);   // (arrived with the wait above; this ties the register to a wait for the compiler)
-        keys_begin(min(KS, last), widx[KS % IDL], keys[KNEW]);
+      rotate_keys();   // (tiles VS-2 .. KS-1 are in sets 0 ..)
+      if constexpr (EARLY_PERMUTE) {
+        take_keys(KS, KS & 1, gi[KS % IDL], gm[KS % IDL], gr[KS % IDL]);
+        v_keys(VS - 2);
       }
       wait_vmem_all();
       __syncthreads();
       // S(0) from K slot 0
-      y_phase(std::integral_constant<int, 0>(), 0, SA, yes());
+      y_phase(std::integral_constant<int, 0>(), 0, 0, SA, yes());
       set_base(m_pend);   // O = 0 and l = 0 so far: the first exponent base needs no rescale
       resc = false;
       int t = 0;
@@ -975,6 +926,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         }
       }
     }
+    tag0 += ntiles + KS + IDL + 1;
     // this item's LDS use (tile rings, merge scratch) ends here; the next item's begins with the work-item word
     __syncthreads();
   }

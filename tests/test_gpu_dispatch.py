@@ -34,3 +34,22 @@ def test_direct_and_queued_assignment(oracle_mod, items, H):
         F.fgattn_forward(prob.q, prob.k, prob.v, prob.d_indptr, prob.d_indices, params, prob.out, prob.lse, ws)
         torch.cuda.synchronize()
         assert np.array_equal(W.bf16_bits_to_f64(prob.out.view(torch.int16).cpu().numpy().view(np.uint16)), first[0])
+
+
+# keys per group on both sides of the tile sizes (32 and 64 keys), odd ones, more than a tile; the short last group stands
+# first, in the middle or last in its list (shuffled), and lists end inside, at and just past a tile
+@pytest.mark.parametrize("M", [16, 32, 64, 128])
+@pytest.mark.parametrize("N,L", [(3, 1027), (31, 1000), (32, 1000), (33, 1024), (63, 2060), (64, 2050), (65, 2015), (200, 1999)])
+def test_short_last_group_anywhere_in_the_list(oracle_mod, M, N, L):
+    w = dataclasses.replace(W.TINY, name="short", H=2, L=L, d=64 if N % 2 else 128, M=M, N=N, kind=W.MASK_RANDOM, density=0.4,
+                            grid=(1, 1, 1), seed=900 + M + N)
+    rng = np.random.default_rng(M * 1000 + N)
+    lists = []
+    for i in range(w.items):
+        ids = np.flatnonzero(rng.random(w.G) < 0.4)
+        ids = np.union1d(ids, [w.G - 1]) if i % 3 else ids   # two items of three hold the last group
+        lists.append(rng.permutation(ids if ids.size else np.array([0])).astype(np.int32))
+    indptr = np.zeros(w.items + 1, dtype=np.int64)
+    indptr[1:] = np.cumsum([x.size for x in lists])
+    prob = Problem(w, mask=(indptr, np.concatenate(lists)))
+    check_against_oracle(oracle_mod, prob, prob.run(), what="M=%d N=%d L=%d" % (M, N, L))
