@@ -9,9 +9,8 @@
 // S^T = K_rel Q^T and O^T = V_rel^T P^T with fp32 online-softmax state in registers (Sec. 2
 // "Efficient dense attention").  A gather instruction holds the wave that issues it until the
 // vector-memory path has taken it (~170 clocks under load); MFMAs issued before it keep
-// executing meanwhile, so each tile's key loop interleaves one gather with one MFMA of each
-// contraction and a share of the previous tile's exponentials; the row max and the base decision
-// follow in a short vector-ALU phase.  Work items are fetched from per-XCD device-side queues in the
+// executing meanwhile, so each tile's key loop interleaves them with the MFMAs of both contractions and the previous
+// tile's exponentials.  Work items are fetched from per-XCD device-side queues in the
 // order a pre-pass wrote (Sec. 4.2 "Load balancing", Appendix B).
 //
 // Transposed formulation: scores are produced as S^T (keys x queries) so that, in the MFMA
@@ -30,6 +29,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "fgattn_args.hpp"
 
@@ -103,7 +103,12 @@ __device__ __forceinline__ float lane_pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-constexpr float kLazyLog2 = 8.0f;   // how far (log2 units) the exponent base may lag behind the running max
+// A lane's sum of exponentials may grow to 2^32 before its exponent base moves.  P and O are floating point, so a base far
+// below the running max costs no accuracy, and sums below 2^32 keep O as far from overflow as a list of 2^24 keys with
+// the base at the max does.  The key loop therefore needs no row max: the sum it forms anyway tells when to look for one.
+// (11 of 83 vector instructions per tile and wave, and the only part that had to wait for all of S(t+1): 1-2% at 64 and
+// 128 query rows, where at these sizes the power limit sets the clock; the rest of the time is in the gathers' places.)
+constexpr float kSumLimit = 4294967296.0f;
 
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
@@ -147,34 +152,31 @@ struct FwdCfg {
 
 // Online softmax of one 32-key x 32-query score block held as an MFMA accumulator: one query per
 // lane (registers 8c..8c+7 of the accumulator are the keys 16c + 8*(e/4) + 4*(lane/32) + e%4).
-// First half: mask keys that do not count, new running max of this lane's query.
-// MASK_MEMBERS (grouped query tiles): a row in LDS holds, per key, the bit mask of the group members that selected it; a
+// Masks (a key that does not count gets the score -inf):
+// mask_members (grouped query tiles): a row in LDS holds, per key, the bit mask of the group members that selected it; a
 //   query of member `member` keeps only the keys whose bit is set.
-// MASK_DROP: bit 8*r4 + e of `drop` says that the key in accumulator register 4*r4 + e of this lane does not count.
-enum { MASK_NONE = 0, MASK_MEMBERS = 1, MASK_DROP = 2 };
-template <int MASK>
-__device__ __forceinline__ void softmax_max(f32x16& S, const int* members, int g, float m_run, float& m_new,
-                                            int member, unsigned drop) {
-  if (MASK == MASK_MEMBERS) {
+// mask_drop: bit 8*r4 + e of `drop` says that the key in accumulator register 4*r4 + e of this lane does not count.
+__device__ __forceinline__ void mask_members(f32x16& S, const int* members, int g, int member) {
 #pragma unroll
-    for (int r4 = 0; r4 < 4; r4++) {
-      i32x4 bv = *reinterpret_cast<const i32x4*>(members + 8 * r4 + 4 * g);
+  for (int r4 = 0; r4 < 4; r4++) {
+    i32x4 bv = *reinterpret_cast<const i32x4*>(members + 8 * r4 + 4 * g);
 #pragma unroll
-      for (int e = 0; e < 4; e++) S[4 * r4 + e] = ((bv[e] >> member) & 1) ? S[4 * r4 + e] : -INFINITY;
-    }
-  } else if (MASK == MASK_DROP) {
-#pragma unroll
-    for (int r4 = 0; r4 < 4; r4++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) S[4 * r4 + e] = (drop >> (8 * r4 + e)) & 1 ? -INFINITY : S[4 * r4 + e];
+    for (int e = 0; e < 4; e++) S[4 * r4 + e] = ((bv[e] >> member) & 1) ? S[4 * r4 + e] : -INFINITY;
   }
-  // 16 scores -> 1 in eight three-input maxima, three levels deep (this phase is a serial dependency of the key loop)
+}
+__device__ __forceinline__ void mask_drop(f32x16& S, unsigned drop) {
+#pragma unroll
+  for (int r4 = 0; r4 < 4; r4++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) S[4 * r4 + e] = (drop >> (8 * r4 + e)) & 1 ? -INFINITY : S[4 * r4 + e];
+}
+// largest score of this lane's query (lanes l and l^32 hold the two halves of one query's key set) and `m_run`
+__device__ __forceinline__ float row_max(const f32x16& S, float m_run) {
   const float t0 = max3(S[0], S[1], S[2]), t1 = max3(S[3], S[4], S[5]), t2 = max3(S[6], S[7], S[8]);
   const float t3 = max3(S[9], S[10], S[11]), t4 = max3(S[12], S[13], S[14]);
   const float mx = fmaxf(max3(t0, t1, t2), max3(t3, t4, S[15]));
-  // lanes l and l^32 hold the two halves of one query's key set
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-  m_new = max3(__uint_as_float(r[0]), __uint_as_float(r[1]), m_run);
+  return max3(__uint_as_float(r[0]), __uint_as_float(r[1]), m_run);
 }
 
 // NMODE selects how a compacted key position maps to a key row:
@@ -234,7 +236,7 @@ template <int MT, int D, int NMODE, int OCC, int PART = PART_ALL, bool GROUPED =
 __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs a) {
   using C = FwdCfg<MT, D, KS, VS, WV>;
   constexpr bool DENSE = NMODE == NMODE_DENSE;
-  constexpr bool WAVE_PRIO = NMODE == NMODE_DENSE || NMODE == NMODE_N1;
+  constexpr bool WAVE_PRIO = NMODE == NMODE_N1 || (NMODE != NMODE_DENSE && MT > 32);
   constexpr bool SHORT_GROUP = NMODE == NMODE_GROUPS_SHORT;   // (the host picks the variant from L % N)
   // the cross-lane permute of the ids is issued before the barrier that precedes its use (measured with one key per group:
   // 2.4% faster at 128 query rows, 2.5% slower at 64)
@@ -413,7 +415,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // Position p = T*NT + wv*RPW + i*RPI + lrow of the compacted list is fetched by this lane with load
     // instruction i of tile T.  Pipeline per tile T (one iteration per tile, one barrier each):
     //   iteration T-KS-2  : group ids requested     iteration T-KS : ids -> key rows, K(T) gathered
-    //   iteration T-1     : S(T) = K(T) Q^T, row max iteration T-VS+2: V(T) gathered
+    //   iteration T-1     : S(T) = K(T) Q^T          iteration T-VS+2: V(T) gathered
     //   iteration T       : P(T) = exp(S(T) - m)     iteration T+1  : O += V(T)^T P(T)^T
     // Past the end of the list the pipeline keeps running on clamped positions: a few redundant, in-bounds gathers of
     // active rows per work item instead of existence checks in every iteration.
@@ -586,28 +588,28 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       for (int r = 0; r < 16; r++) O[db][r] = 0.0f;
     f32x16 SA, SB;             // S^T of even / odd tiles (one is turned into P while the other accumulates)
     i32x4 PA[2], PB[2];        // P^T (packed bf16 pairs) of even / odd tiles: B operands of the second MFMA
-    float m_run = -INFINITY;   // exponent base (raw score units) of this lane's query; lags the true max lazily
+    float m_run = -INFINITY;   // exponent base (raw score units) of this lane's query: a score maximum it has seen
     float l_run = 0.0f, l_run2 = 0.0f;   // this lane's partial sum of exponentials, in two chains (even / odd scores)
-    // derived from the exponent base whenever it moves (set_base), so that the key loop computes neither per tile:
-    float neg_mc = 0.0f;           // -m_run * c_log2, 0 while m_run is -inf: the additive term of the exponent
-    float m_move = -INFINITY;      // a running max above this moves the base: m_run + kLazyLog2 / c_log2 (-inf while m_run is)
-    const float lazy_raw = kLazyLog2 / a.c_log2;
+    float neg_mc = 0.0f;       // -m_run * c_log2, 0 while m_run is -inf: the additive term of the exponent
+    bool no_base = false;      // wave-uniform: some lane that counts has met no valid key yet, hence has no base
     auto set_base = [&](float m) {
-      const bool none = m == -INFINITY;   // no valid key seen yet
       m_run = m;
-      neg_mc = none ? 0.0f : -m * a.c_log2;
-      m_move = none ? -INFINITY : m + lazy_raw;
+      neg_mc = m == -INFINITY ? 0.0f : -m * a.c_log2;
+      no_base = __builtin_amdgcn_ballot_w64(m == -INFINITY && my_row_valid) != 0;
     };
-    float m_pend = -INFINITY;  // running max including the tile in S
-    bool resc = false;         // wave-uniform: the tile in S moves the exponent base (O, l must be rescaled)
 
     constexpr int NE = C::SSTEPS;          // MFMA slots per phase: PV slot e = (d block e/2, key half e%2); QK slot e = d chunk e
     constexpr int AHEAD = 3;               // LDS fragment reads run this many slots ahead of their MFMA
     constexpr int VPS = 16 / NE;           // score values handled per slot
-    // gathers per iteration and wave: IPW of V then IPW of K, spread over the NE slots of phase X
+    // Gathers per iteration and wave: IPW of V then IPW of K, DMA_PER in each of the first slots of phase X.  The later
+    // they go, the less of the iteration is left for them to land; the more at once, the longer they wait for each other
+    // and keep this wave from issuing.  In the first four slots of eight: 12 heads x 32760 tokens at 64x1 2.06 ms (one
+    // per slot 2.12, in two slots 2.13, all at the start 2.19), 24 heads x 118800 tokens at 128x1 31.1 (every other
+    // slot 32.1).  A 32-row tile has one wave per workgroup and nobody to wait for at the barrier but its own gathers:
+    // all 16 at the start, at 32x32 3.53 ms (in four slots 3.59, in eight 3.96).
     constexpr int NDMA = 2 * C::IPW;
-    constexpr int DMA_PER = (NDMA + NE - 1) / NE;
-    constexpr int DMA_EVERY = NDMA >= NE ? 1 : NE / NDMA;
+    constexpr int DMA_PER = MT == 32 ? NDMA : (NDMA + 3) / 4;
+    static_assert(DMA_PER * NE >= NDMA, "every gather has a slot");
     auto read_vf = [&](const unsigned char* vst, int e) {
       const int db = e >> 1, c = e & 1;
       const unsigned char* p0 = vst + voff[db] + (16 * c) * C::ROWB;
@@ -618,11 +620,12 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // Phase X.  O^T += V^T P^T with V in slot `vrd` of the V ring and, with QK, Sn = K Q^T with K in slot `krd` of the K
     // ring: one MFMA of each per slot.  With EXP, every slot also takes its share of the exponentials of the previous
     // tile's scores So: P = exp2(c*(So - m)) packed to bf16 into Pout, and the row sum; they issue while the two matrix
-    // instructions just issued execute.  With GATHER, every slot then issues one of this iteration's gathers: V rows
+    // instructions just issued execute.  With GATHER, the first slots then issue this iteration's gathers: V rows
     // (keys in vk) -> V slot `vwr`, then K rows (keys in kk) -> K slot `kwr`, both released by
     // the previous iteration.  The gather holds the wave; the matrix instructions execute underneath it.
     auto x_phase = [&](auto vrd_c, auto krd_c, auto vwr_c, auto kwr_c, const i32x4 (&Pin)[2], auto with_gather,
-                       auto with_qk, f32x16& Sn, auto with_exp, const f32x16& So, i32x4 (&Pout)[2]) {
+                       auto with_qk, f32x16& Sn, auto with_exp, const f32x16& So, i32x4 (&Pout)[2], float& l_new,
+                       float& l_new2) {
       constexpr int vrd = decltype(vrd_c)::value, krd = decltype(krd_c)::value;
       constexpr int vwr = decltype(vwr_c)::value, kwr = decltype(kwr_c)::value;
       constexpr bool GATHER = decltype(with_gather)::value;
@@ -663,8 +666,8 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
             // scale = 0), so their p is exactly 0 without a select
             const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(So[r], a.c_log2, neg_mc));
             const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(So[r + 1], a.c_log2, neg_mc));
-            l_run += p0;
-            l_run2 += p1;
+            l_new = (r == 0 ? l_run : l_new) + p0;   // (l_run stays, for the case that the base has to move: new_base)
+            l_new2 = (r == 0 ? l_run2 : l_new2) + p1;
             f32x2 pp = {p0, p1};
             int pk = __builtin_bit_cast(int, __builtin_convertvector(pp, bf16x2));
             asm volatile("" : "+v"(pk));   // keeps the compiler from sinking the conversion out of the slot
@@ -672,16 +675,14 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
           }
         }
         if constexpr (GATHER) {
-          if constexpr (e % DMA_EVERY == 0) {
-            constexpr int j0 = (e / DMA_EVERY) * DMA_PER;
-            if constexpr (j0 < C::IPW) gather_v(std::integral_constant<int, j0>(), vwr, vk);
-            else if constexpr (j0 < NDMA) gather_k(std::integral_constant<int, j0 - C::IPW>(), kwr, kk);
-            if constexpr (DMA_PER > 1) {
-              constexpr int j1 = j0 + 1;
-              if constexpr (j1 < C::IPW) gather_v(std::integral_constant<int, j1>(), vwr, vk);
-              else if constexpr (j1 < NDMA) gather_k(std::integral_constant<int, j1 - C::IPW>(), kwr, kk);
-            }
-          }
+          [&]<int... I>(std::integer_sequence<int, I...>) {
+            auto one = [&](auto jc) {
+              constexpr int j = decltype(jc)::value;
+              if constexpr (j < C::IPW) gather_v(std::integral_constant<int, j>(), vwr, vk);
+              else if constexpr (j < NDMA) gather_k(std::integral_constant<int, j - C::IPW>(), kwr, kk);
+            };
+            (one(std::integral_constant<int, e * DMA_PER + I>()), ...);
+          }(std::make_integer_sequence<int, DMA_PER>());
           __builtin_amdgcn_sched_barrier(0);
         }
       };
@@ -696,9 +697,8 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
         slot(std::integral_constant<int, 7>());
       }
     };
-    // Phase Y, vector ALU only in the key loop: the row max of the new scores Sn (tile Tm, par = Tm % 2) and the rare decision to
-    // move the exponent base (see kLazyLog2).  With MFMA (prologue only) it first computes Sn = K Q^T with K in slot
-    // `kslot` of the K ring.
+    // Masks the new scores Sn (tile Tm, par = Tm % 2) where keys of the tile do not count.  With MFMA (prologue only) it
+    // first computes Sn = K Q^T with K in slot `kslot` of the K ring.
     auto y_phase = [&](auto kslot, int Tm, int par, f32x16& Sn, auto with_mfma) {
       constexpr bool MFMA = decltype(with_mfma)::value;
       // written before the barrier that precedes this phase; consumed at its end
@@ -720,19 +720,35 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
           Sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[e], qf[e], Sn, 0, 0, 0);
         }
       }
-      float m_new;
       bool masked = (Tm + 1) * C::NT > total;   // (the same in every wave of the workgroup)
       if constexpr (SHORT_GROUP && !GROUPED && WV == 1) masked |= lone_drop[par] != 0;
       if constexpr (TELL_DROPS) masked |= __builtin_amdgcn_readfirstlane(drop_tag) == tag0 + Tm;
       if constexpr (GROUPED)
-        softmax_max<MASK_MEMBERS>(Sn, members + par * C::NT + kw * 32, g, m_pend, m_new, my_member, 0u);
+        mask_members(Sn, members + par * C::NT + kw * 32, g, my_member);
       else if (__builtin_expect(masked, 0))
-        softmax_max<MASK_DROP>(Sn, nullptr, g, m_pend, m_new, 0, dropped(Tm, par));
-      else
-        softmax_max<MASK_NONE>(Sn, nullptr, g, m_pend, m_new, 0, 0u);
-      m_pend = m_new;
-      const bool lane_moves = m_new > m_move;   // (the first valid key of a lane also moves it: m_move = -inf until then)
-      resc = __builtin_amdgcn_ballot_w64(lane_moves) != 0;
+        mask_drop(Sn, dropped(Tm, par));
+    };
+    // The exponent base of every lane moves to the running max including the scores So, whose exponentials Pout and sums
+    // were formed with the old base and are formed again; O does not hold that tile yet.
+    auto new_base = [&](const f32x16& So, i32x4 (&Pout)[2], float& l_new, float& l_new2) {
+      const float m_new = row_max(So, m_run);
+      const float alpha = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_new) * a.c_log2);
+      set_base(m_new);
+      l_new = l_run * alpha;
+      l_new2 = l_run2 * alpha;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(So[r], a.c_log2, neg_mc));
+        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(So[r + 1], a.c_log2, neg_mc));
+        l_new += p0;
+        l_new2 += p1;
+        f32x2 pp = {p0, p1};
+        Pout[r >> 3][(r & 7) >> 1] = __builtin_bit_cast(int, __builtin_convertvector(pp, bf16x2));
+      }
+#pragma unroll
+      for (int db = 0; db < C::DBLK; db++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) O[db][r] *= alpha;
     };
     // at most N operations in flight, and the ids in register set e have arrived
     auto wait_ids = [&](auto n, int e) {
@@ -748,8 +764,8 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // Iteration t, J = t mod U (a constant, so every LDS slot and register set is an immediate):
     //   X: O += V(t-1)^T P(t-1)^T  ||  S(t+1) = K(t+1) Q^T  ||  P(t) = exp(S(t) - m)  ||  gathers V(t+VS-2) and K(t+KS)
     //      into the slots that iteration t-1 read last
-    //   Y: the row max of S(t+1), on the vector ALU
-    // A gathered tile has at least phase Y and the barrier's wait to arrive before it is published, and whole
+    // then, rarely: the exponent base moves, S(t+1) is masked
+    // A gathered tile has at least the barrier's wait to arrive before it is published, and whole
     // iterations more where the rings are deeper than two tiles.
     auto iteration = [&](auto jc, int t) {
       constexpr int J = decltype(jc)::value;
@@ -764,32 +780,27 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       constexpr int E = (J + KS) % IDL;
       wait_ids(std::integral_constant<int, WAITN>(), E);
       __syncthreads();
-      float alpha = 1.0f;
-      if (__builtin_expect(resc, 0)) {   // the exponent base moves: l now, O after the MFMAs of the old base
-        alpha = (m_run == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_pend) * a.c_log2);
-        l_run *= alpha;
-        l_run2 *= alpha;
-        set_base(m_pend);
-      }
       if constexpr (!EARLY_PERMUTE) {   // ids requested IDL iterations ago -> key rows
         take_keys(t + KS, (J + KS) & 1, gi[E], gm[E], gr[E]);
         v_keys(t + VS - 2);
       }
       // wave priority: the gather phase above the vector-ALU phase above everything outside the key loop, so that
       // the waves that feed the memory pipe are issued first and a neighbour's prologue or epilogue never delays them
-      // (measured: 1-3% faster with one key per group, 6% for the dense kernel at 128 rows; slower with N keys per
-      // group, whose loaders do more vector-ALU work, so not used there)
+      // (measured: 1% faster at 64 and 128 rows, 3% with grouped tiles, 6% at 16x1; 4% slower at 32x32 in single-wave
+      // workgroups, 3% for the dense kernel at 128 rows, 12% at d = 64: not used there)
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(3);
+      float l_new = l_run, l_new2 = l_run2;
       x_phase(std::integral_constant<int, (J + U - 1) % VS>(), std::integral_constant<int, (J + 1) % KS>(),
               std::integral_constant<int, (J + U - 2) % VS>(), std::integral_constant<int, J % KS>(), Pin, yes(), yes(), Sn,
-              yes(), So, Pout);
+              yes(), So, Pout, l_new, l_new2);
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(1);
-      if (__builtin_expect(resc, 0)) {
-#pragma unroll
-        for (int db = 0; db < C::DBLK; db++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) O[db][r] *= alpha;
+      if constexpr (PART != PART_GATHER) {
+        // (the same in all lanes; a sum past float overflows to +inf and is caught here too)
+        const bool over = __builtin_amdgcn_ballot_w64(fmaxf(l_new, l_new2) >= kSumLimit) != 0;
+        if (__builtin_expect(over || no_base, 0)) new_base(So, Pout, l_new, l_new2);
       }
+      l_run = l_new;
+      l_run2 = l_new2;
       fetch_ids(t + KS + IDL, gi[E], gm[E], gr[E]);
       y_phase(std::integral_constant<int, 0>(), t + 1, (J + 1) & 1, Sn, no());
       rotate_keys();
@@ -842,8 +853,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       __syncthreads();
       // S(0) from K slot 0
       y_phase(std::integral_constant<int, 0>(), 0, 0, SA, yes());
-      set_base(m_pend);   // O = 0 and l = 0 so far: the first exponent base needs no rescale
-      resc = false;
+      set_base(row_max(SA, -INFINITY));   // O = 0 and l = 0 so far: the first exponent base needs no rescale
       int t = 0;
       for (;;) {
 #define FG_STEP(J)                                             \
@@ -866,7 +876,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       if constexpr (UD > J) {                                                                                          \
         if (jd == J)                                                                                                   \
           x_phase(std::integral_constant<int, J % VS>(), std::integral_constant<int, 0>(), std::integral_constant<int, 0>(), \
-                  std::integral_constant<int, 0>(), (J & 1) ? PB : PA, no(), no(), SA, no(), SA, PA);                 \
+                  std::integral_constant<int, 0>(), (J & 1) ? PB : PA, no(), no(), SA, no(), SA, PA, l_run, l_run2);                 \
       }
       FG_DRAIN(0) FG_DRAIN(1) FG_DRAIN(2) FG_DRAIN(3) FG_DRAIN(4) FG_DRAIN(5) FG_DRAIN(6) FG_DRAIN(7)
 #undef FG_DRAIN

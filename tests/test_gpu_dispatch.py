@@ -53,3 +53,23 @@ def test_short_last_group_anywhere_in_the_list(oracle_mod, M, N, L):
     indptr[1:] = np.cumsum([x.size for x in lists])
     prob = Problem(w, mask=(indptr, np.concatenate(lists)))
     check_against_oracle(oracle_mod, prob, prob.run(), what="M=%d N=%d L=%d" % (M, N, L))
+
+
+# The exponent base of a query stays at its first tile's maximum until a lane's sum passes 2^32: scores that grow along the
+# list by less than that per tile (several moves), by far more than a float's exponent holds at one key (sums of +inf are
+# formed and formed again), that fall, and that stay level
+@pytest.mark.parametrize("M,d", [(16, 64), (32, 128), (64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("shape", ["ramp", "jump", "fall"])
+@pytest.mark.parametrize("N,L", [(1, 700), (8, 700)])
+def test_exponent_base_moves(oracle_mod, M, d, shape, N, L):
+    w = dataclasses.replace(W.TINY, name="base", H=2, L=L, d=d, M=M, N=N, kind=W.MASK_RANDOM, density=0.7, grid=(1, 1, 1),
+                            seed=77 + M + d)
+    q, k, v = W.make_qkv(w)
+    gain = {"ramp": np.linspace(0.1, 40.0, L), "jump": np.where(np.arange(L) == L - 90, 400.0, 0.2),
+            "fall": np.linspace(40.0, 0.1, L)}[shape]
+    k = W.f32_to_bf16_bits((W.bf16_bits_to_f64(k) * gain[None, None, :, None]).astype(np.float32))
+    prob = Problem(w, q, k, v)
+    check_against_oracle(oracle_mod, prob, prob.run(), what="%s M=%d d=%d N=%d" % (shape, M, d, N))
+    if N == 1:
+        dense = Problem(dataclasses.replace(w, kind=W.MASK_ALL), q, k, v)
+        check_against_oracle(oracle_mod, dense, dense.run(dense=True), what="dense " + shape)
