@@ -6,7 +6,7 @@
 //                     R - 1 ungrouped tiles closest to it (equal distances: lower tile index first)
 //   consecutive_kernel  "merge-consecutive": R consecutive tiles per group
 //   union_kernel      per group: OR of the members' rows, its popcount
-//   scan_kernel       counts -> union_indptr
+//   row_pointers_kernel  counts -> union_indptr (fgscan.hpp)
 //   emit_kernel       per group: the union's key-block ids in ascending order and, per id, the bit mask of the
 //                     members that selected it
 #include <hip/hip_runtime.h>
@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "fgattn.h"
+#include "fgscan.hpp"
 
 namespace fgg {
 
@@ -274,32 +275,6 @@ __global__ void __launch_bounds__(kThreads) union_kernel(const uint32_t* bits, c
   if (tid == 0) count[grp] = red[0];
 }
 
-__global__ void __launch_bounds__(1024) scan_kernel(const unsigned* count, int64_t rows, int64_t* indptr) {
-  __shared__ long long part[1024];
-  __shared__ long long carry;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    carry = 0;
-    indptr[0] = 0;
-  }
-  __syncthreads();
-  for (int64_t base = 0; base < rows; base += 1024) {
-    const int64_t r = base + tid;
-    part[tid] = r < rows ? (long long)count[r] : 0;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      const long long add = tid >= off ? part[tid - off] : 0;
-      __syncthreads();
-      part[tid] += add;
-      __syncthreads();
-    }
-    if (r < rows) indptr[r + 1] = carry + part[tid];
-    __syncthreads();
-    if (tid == 0) carry += part[1023];
-    __syncthreads();
-  }
-}
-
 // one workgroup per group: ids of the union in ascending order with their member masks
 __global__ void __launch_bounds__(kThreads) emit_kernel(const uint32_t* bits, const uint32_t* ubits,
                                                         const int32_t* group_tiles, const int64_t* uindptr, int QB,
@@ -462,7 +437,7 @@ int fgattn_group_select(const int64_t* mask_indptr, const int32_t* mask_indices,
   hipLaunchKernelGGL(union_kernel, dim3((unsigned)lo.groups), dim3(kThreads), 0, stream, bits, group_tiles, QB, Gw, R, NG,
                      ubits, count);
   if (!launched()) return FGATTN_E_DEVICE;
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, stream, count, lo.groups, union_indptr);
+  fgscan::launch_row_pointers(count, lo.groups, union_indptr, stream);
   return launched() ? FGATTN_OK : FGATTN_E_DEVICE;
 }
 

@@ -1,0 +1,50 @@
+"""The mask kernels on both sides of the lines that choose how a row is split."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_16518_amd import fgattn as F
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(H, L, d, M, N, seed, flags=0, scale=1.0):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    q, k = (torch.randn((1, H, L, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    p = F.make_params(q, k, k, q, M, N, scale * d ** -0.5, flags)
+    ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    return q, k, p, ws, torch.empty(H * ((L + M - 1) // M) + 1, dtype=torch.int64, device="cuda")
+
+
+def bit_rows(p, ws, rows, G):
+    """The kept set as the selection leaves it: the last rows * ceil(G / 32) words of the workspace's used part."""
+    Gw = (G + 31) // 32
+    used = F.fgattn_mask_workspace_bytes(p)
+    start = used - (rows * Gw * 4 + 255) // 256 * 256
+    words = ws[start:start + rows * Gw * 4].view(torch.int32).view(rows, Gw)
+    return ((words[:, :, None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1).view(rows, Gw * 32)[:, :G].bool()
+
+
+# one wave per row and several (few long rows), rows that end inside a pair of words, inside a batch of 32 words and at its
+# edges, outputs that start at every place of a 16-byte group, and buffers that end early
+@pytest.mark.parametrize("H,L,M,N", [(1, 40000, 128, 1), (1, 8192, 128, 1), (2, 4128, 16, 1), (1, 1024, 16, 1), (1, 1056, 16, 1),
+                                     (3, 2080, 64, 1), (1, 100, 16, 1), (2, 31, 16, 1)])
+def test_emitted_ids_are_the_bits_in_order(H, L, M, N):
+    q, k, p, ws, indptr = problem(H, L, 64, M, N, seed=L)
+    F.fgattn_mask_select(q, k, p, 0.8, indptr, ws)
+    rows, G = indptr.numel() - 1, (L + N - 1) // N
+    bits = bit_rows(p, ws, rows, G)
+    want = bits.nonzero()[:, 1].int()
+    assert torch.equal(indptr[1:] - indptr[:-1], bits.sum(1))
+    assert torch.equal(indptr[1:], bits.sum(1).cumsum(0)) and int(indptr[0]) == 0
+    nnz = want.numel()
+    say("    %d rows of %d, %d ids" % (rows, G, nnz))
+    for offset in range(4):
+        for cap in (nnz, nnz - 1, nnz - 3, nnz // 2 + 1):
+            cap = max(cap, 0)
+            buf = torch.full((nnz + 16,), -7, dtype=torch.int32, device="cuda")
+            F.fgattn_mask_emit(p, indptr, buf[offset:offset + cap], ws)
+            assert torch.equal(buf[offset:offset + cap], want[:cap]), (offset, cap)
+            assert (buf[:offset] == -7).all() and (buf[offset + cap:] == -7).all(), (offset, cap)
