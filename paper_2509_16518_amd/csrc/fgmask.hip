@@ -122,14 +122,22 @@ __global__ void __launch_bounds__(64) pool_kernel(const uint16_t* x, int64_t sb,
 // passed through LDS, from where every wave takes it as its B operand; the 16-byte chunks of a row
 // are XOR-swizzled so that both the row-wise writes and the column-wise operand reads are free of
 // bank conflicts.  In the accumulator a register holds one query block and 32 consecutive key
-// blocks across lanes, so every store covers whole 128-byte lines.
+// blocks across lanes, so every store covers whole 128-byte lines.  Bound: the writes of the scores (a kernel that
+// only stores this pattern takes 173-188 us per GiB).  With a lane test and its branches around every store, and 160 lane
+// exchanges per workgroup and wave for the ranges, it took 239 us for 805 MB (rows of 32760), now 206; 301 us per GiB (rows of
+// 118800, K shared as below), now 242.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTilesPerGroup = 16;
+// Workgroups go to the eight XCDs in turn.  With at least eight stretches of key blocks, every XCD keeps to its own eighth of
+// them and takes a stretch for up to kShareUnits consecutive score tiles (of one slice, mostly) before the next one, so
+// that the tiles read K through one L2 at about the same time.  (In the order of their indices they read it from device
+// memory again, half as many bytes as they write: rows of 118800 scores 337 us per GiB of scores, shared 301.)
+constexpr int kShareUnits = 8;
 
 template <int D>
-__global__ void __launch_bounds__(256) scores_kernel(const uint16_t* qp, const uint16_t* kp, int64_t k_slice_stride,
+__global__ void __launch_bounds__(256, 4) scores_kernel(const uint16_t* qp, const uint16_t* kp, int64_t k_slice_stride,
                                                       int64_t k_row_stride, int QB, int G, int Gs, float scale,
-                                                      int unit0, int YT, float* scores, unsigned* range) {
+                                                      int unit0, int nunits, int YT, int segs, float* scores, unsigned* range) {
   constexpr int STEPS = D / 16;
   constexpr int ROWB = D * 2;                 // bytes of a row of K
   constexpr int CHUNKS = ROWB / 16;           // 16-byte chunks per row
@@ -137,14 +145,27 @@ __global__ void __launch_bounds__(256) scores_kernel(const uint16_t* qp, const u
   constexpr int LPT = TILEB / 16 / 256;       // chunks per thread and tile
   static_assert(LPT >= 1, "a tile is at least one chunk per thread");
   __shared__ __attribute__((aligned(16))) unsigned char ktile[2][TILEB];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5;
-  // blockIdx.y names a score tile of this chunk: unit = slice * YT + (tile of 128 query blocks inside the slice)
-  const int unit = unit0 + blockIdx.y;
+  // which score tile of this chunk, and which stretch of its key blocks (see kShareUnits)
+  int local_unit, seg;
+  if (segs < 8) {
+    local_unit = blockIdx.x / segs;
+    seg = blockIdx.x - local_unit * segs;
+  } else {
+    const int xcd_segs = (segs + 7) >> 3, j = blockIdx.x >> 3;   // stretches of one XCD; its j-th workgroup
+    const int first = j / (xcd_segs * kShareUnits) * kShareUnits, r = j - first * xcd_segs;
+    const int share = min(kShareUnits, nunits - first);
+    local_unit = first + r % share;
+    seg = r / share * 8 + (blockIdx.x & 7);
+    if (seg >= segs) return;
+  }
+  // unit = slice * YT + (tile of 128 query blocks inside the slice)
+  const int unit = unit0 + local_unit;
   const int slice = unit / YT;
   const int qtile0 = (unit - slice * YT) * 128;
   const int q0 = qtile0 + wv * 32;   // (a wave past the last query block still helps with the tiles)
-  const int tile0 = blockIdx.x * kTilesPerGroup;
+  const int tile0 = seg * kTilesPerGroup;
   auto swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
   bf16x8 qf[STEPS];
   {
@@ -170,13 +191,19 @@ __global__ void __launch_bounds__(256) scores_kernel(const uint16_t* qp, const u
       *reinterpret_cast<i32x4*>(&ktile[buf][row * ROWB + ((c ^ swz(row)) * 16)]) = stage[i];
     }
   };
-  // running range of the scores this lane produced, per accumulator register (= per query block)
-  float vmax[16], vmin[16];
+  // running range of the scores this lane produced, per accumulator register (= per query block); the minimum negated
+  float vmax[16], vneg[16];
 #pragma unroll
   for (int r = 0; r < 16; r++) {
     vmax[r] = -INFINITY;
-    vmin[r] = INFINITY;
+    vneg[r] = -INFINITY;
   }
+  // Key blocks past the end repeat the last one and query blocks past the end the last query block: neither changes a
+  // range, and their scores land in the padding of a row and in rows of the tile that nobody reads.  So nothing in the loop
+  // depends on a lane but its 32-bit offset; the row of register r is a scalar base.
+  const bool busy = q0 < QB;   // (the same in all lanes of a wave)
+  float* const rows = scores + ((int64_t)local_unit * 128 + wv * 32) * Gs + (int64_t)tile0 * 32;
+  const unsigned lane_off = (unsigned)(4 * g) * (unsigned)Gs + (unsigned)ln;
   const int ntiles = min(kTilesPerGroup, (G - tile0 * 32 + 31) / 32);   // >= 1 by the grid
   fetch_tile(tile0);
   stash_tile(0);
@@ -184,43 +211,51 @@ __global__ void __launch_bounds__(256) scores_kernel(const uint16_t* qp, const u
   for (int t = 0; t < ntiles; t++) {
     if (t + 1 < ntiles) fetch_tile(tile0 + t + 1);
     const unsigned char* kt = ktile[t & 1];
-    f32x16 acc;
+    if (busy) {
+      f32x16 acc;
 #pragma unroll
-    for (int r = 0; r < 16; r++) acc[r] = 0.0f;
+      for (int r = 0; r < 16; r++) acc[r] = 0.0f;
 #pragma unroll
-    for (int s = 0; s < STEPS; s++) {
-      const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(kt + ln * ROWB + (((2 * s + g) ^ swz(ln)) * 16)));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[s], kf, acc, 0, 0, 0);
-    }
-    const int col = (tile0 + t) * 32 + ln;
-    if (col < G) {
+      for (int s = 0; s < STEPS; s++) {
+        const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(kt + ln * ROWB + (((2 * s + g) ^ swz(ln)) * 16)));
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[s], kf, acc, 0, 0, 0);
+      }
+      const unsigned off = lane_off + (unsigned)t * 32u;
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        const int qrow = q0 + 8 * (r / 4) + 4 * g + (r % 4);
         const float v = acc[r] * scale;
         vmax[r] = fmaxf(vmax[r], v);
-        vmin[r] = fminf(vmin[r], v);
-        if (qrow < QB) scores[((int64_t)blockIdx.y * 128 + (qrow - qtile0)) * Gs + col] = v;
+        vneg[r] = fmaxf(vneg[r], -v);
+        (rows + (int64_t)(8 * (r / 4) + r % 4) * Gs)[off] = v;
       }
     }
     if (t + 1 < ntiles) stash_tile((t + 1) & 1);   // (the buffer that was read in step t - 1, before the last barrier)
     __syncthreads();
   }
-  // one (max, min) update per query block and wave: reduce over the 32 lanes that share the block
+  if (!busy) return;
+  // One (max, min) update per query block and wave.  The 16 registers meet over the 32 lanes that share their query
+  // blocks by halves: a lane hands the half of its registers that its partner keeps to it and keeps the other, so after four
+  // steps it holds one register's maximum of 16 lanes (15 exchanges instead of 80), and after the fifth of all 32.
+  auto meet = [&](float (&x)[16]) {
 #pragma unroll
-  for (int r = 0; r < 16; r++) {
-    float a = vmax[r], b = vmin[r];
+    for (int b = 0; b < 4; b++) {
+      const int half = 8 >> b;
+      const bool upper = (ln >> b) & 1;
 #pragma unroll
-    for (int off = 16; off > 0; off >>= 1) {
-      a = fmaxf(a, __shfl_xor(a, off));
-      b = fminf(b, __shfl_xor(b, off));
+      for (int i = 0; i < half; i++) {
+        const float give = upper ? x[i] : x[i + half], keep = upper ? x[i + half] : x[i];
+        x[i] = fmaxf(keep, __shfl_xor(give, 1 << b));
+      }
     }
-    const int qrow = q0 + 8 * (r / 4) + 4 * g + (r % 4);
-    if (ln == 0 && qrow < QB && a >= b) {
-      unsigned* rr = range + 2 * ((int64_t)slice * QB + qrow);
-      atomicMax(rr, ordered_bits(a));
-      atomicMin(rr + 1, ordered_bits(b));
-    }
+    return fmaxf(x[0], __shfl_xor(x[0], 16));
+  };
+  const float hi = meet(vmax), lo = -meet(vneg);
+  const int r = ((ln & 1) << 3) | ((ln & 2) << 1) | ((ln & 4) >> 1) | ((ln & 8) >> 3);   // the register this lane ended up with
+  const int qrow = q0 + 8 * (r / 4) + 4 * g + (r % 4);
+  if (ln < 16 && qrow < QB) {
+    unsigned* rr = range + 2 * ((int64_t)slice * QB + qrow);
+    atomicMax(rr, ordered_bits(hi));
+    atomicMin(rr + 1, ordered_bits(lo));
   }
 }
 
@@ -1137,13 +1172,13 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
   for (int64_t unit0 = 0; unit0 < lo.units; unit0 += lo.chunk_units) {
     const int64_t nunits = lo.units - unit0 < lo.chunk_units ? lo.units - unit0 : lo.chunk_units;
     const int64_t chunk_rows = nunits * 128;
-    const dim3 sgrid(gx, (unsigned)nunits);
+    const dim3 sgrid((unsigned)((gx < 8 ? gx : (gx + 7) & ~7u) * nunits));
     if (p->d == 128)
       hipLaunchKernelGGL(scores_kernel<128>, sgrid, dim3(256), 0, stream, qp, kmat, k_slice_stride, k_row_stride, (int)lo.QB,
-                         (int)lo.G, (int)lo.Gs, p->scale, (int)unit0, (int)lo.YT, scores, range);
+                         (int)lo.G, (int)lo.Gs, p->scale, (int)unit0, (int)nunits, (int)lo.YT, (int)gx, scores, range);
     else
       hipLaunchKernelGGL(scores_kernel<64>, sgrid, dim3(256), 0, stream, qp, kmat, k_slice_stride, k_row_stride, (int)lo.QB,
-                         (int)lo.G, (int)lo.Gs, p->scale, (int)unit0, (int)lo.YT, scores, range);
+                         (int)lo.G, (int)lo.Gs, p->scale, (int)unit0, (int)nunits, (int)lo.YT, (int)gx, scores, range);
     if (!launched()) return FGATTN_E_DEVICE;
     if (lo.row_in_lds) {
       const unsigned wgs = (unsigned)(chunk_rows < 2 * cus ? chunk_rows : 2 * cus);   // two fit a compute unit

@@ -48,3 +48,35 @@ def test_emitted_ids_are_the_bits_in_order(H, L, M, N):
             F.fgattn_mask_emit(p, indptr, buf[offset:offset + cap], ws)
             assert torch.equal(buf[offset:offset + cap], want[:cap]), (offset, cap)
             assert (buf[:offset] == -7).all() and (buf[offset + cap:] == -7).all(), (offset, cap)
+
+
+# fewer than eight stretches of key blocks, eight, and counts off a multiple of eight; one score tile, more than share a
+# stretch, tiles whose last rows or whole waves are past the end, chunks that begin inside a slice; key blocks past the end
+# of a tile of 32; means that are all negative or far apart, so that a padded position would show in a row's range
+@pytest.mark.parametrize("H,L,d,M,N,one_tile", [(1, 3500, 64, 16, 1, False), (3, 4099, 128, 128, 1, False), (2, 4609, 64, 16, 1, True),
+                                                (11, 4100, 128, 32, 1, False), (1, 20000, 64, 16, 1, False), (5, 2050, 128, 64, 8, False)])
+def test_scores_of_every_tile_and_stretch(H, L, d, M, N, one_tile):
+    q, k, p, ws, indptr = problem(H, L, d, M, N, seed=L + 1, flags=F.FLAG_MASK_ONE_TILE_CHUNKS if one_tile else 0, scale=3.0)
+    q -= 2.0   # (means of one sign)
+    k += 2.0
+    F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
+    rows, G = indptr.numel() - 1, (L + N - 1) // N
+    QB = rows // H
+    got = bit_rows(p, ws, rows, G).view(H, QB, G)
+
+    def means(x, n):
+        pad = torch.nn.functional.pad(x.double(), (0, 0, 0, (-L) % n)).view(H, -1, n, d).sum(2)
+        count = torch.full((pad.shape[1], 1), float(n), device="cuda", dtype=torch.float64)
+        count[-1] = L - (pad.shape[1] - 1) * n
+        return (pad / count).float().bfloat16().double()
+    s = (means(q[0], M) @ means(k[0], N).transpose(1, 2)) * p.scale
+    prob = torch.softmax(s, -1)
+    mass = (prob * got).sum(-1)
+    # the kept set reaches p, and not without its least probable member; and it is a top set: no key block left out is more
+    # probable than one kept (both up to the rounding of fp32 scores and of the means to bf16, whose fp32 sums may differ in the
+    # last bit from the exact ones here)
+    tol = 1e-5 if M * N == 16 else 2e-2
+    least = torch.where(got, prob, 2.0).amin(-1)
+    most_out = torch.where(got, -1.0, prob).amax(-1)
+    assert (mass >= 0.9 - tol).all() and (mass - least < 0.9 + tol).all(), (mass.min(), (mass - least).max())
+    assert (most_out <= least * (1 + (1e-4 if tol < 1e-4 else 0.3)) + 1e-9).all(), float((most_out / least).max())
