@@ -53,7 +53,7 @@ enum {
   FGATTN_FLAG_REUSE_PLAN = 4,     /* skip the ordering pre-pass: `workspace` already holds the order built by an
                                      earlier fgattn_forward/fgattn_plan call for the same mask and params */
   /* Read by the fgattn_mask_* calls only (the others ignore it): use the general selection kernel, which reads a
-   * row of scores from device memory in every pass, also for rows of at most 32768 key blocks (which otherwise
+   * row of scores from device memory in every pass, also for rows of at most 131072 key blocks (which otherwise
    * take the kernel that reads the row once).  Same results; pass the same flags to all three mask calls. */
   FGATTN_FLAG_MASK_ROWS_IN_HBM = 8,
   /* Read by the fgattn_mask_* calls only: a score buffer of the smallest size (one tile of 128 query blocks)

@@ -6,10 +6,9 @@
 // Kernels (all on the caller's stream):
 //   pool_kernel        block means (fp32 running sum in row order, fp32 divide, one bf16 rounding)
 //   scores_kernel      S = scale * Q_avg K_avg^T with bf16 MFMA, fp32 scores to the workspace
-//   select_bins_kernel rows of up to 32768 scores: persistent 512-thread workgroups, two per compute unit; the
-//                      row is read once, the bin of every score stays in LDS as 16 bits; finds the CUT, the 64-bit
-//                      key (score, then lower id first) of the last kept key block, without sorting the row, and
-//                      leaves the kept set as one bit per key block
+//   select_codes_kernel  rows of up to 131072 scores: persistent workgroups; the row is read once, a byte per score (its
+//                      bin) stays in LDS; finds the CUT, the 64-bit key (score, then lower id first) of the last kept
+//                      key block, without sorting the row, and leaves the kept set as one bit per key block
 //   select_kernel      longer rows (or on request): the same selection, one workgroup per query block,
 //                      every pass reading the row from device memory; leaves the same outputs
 //   row_pointers_kernel  counts -> indptr (fgscan.hpp)
@@ -38,30 +37,20 @@ namespace fgm {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 constexpr int kSelThreads = 256;
 constexpr int kBins = 2048;
 constexpr int kCap = 2048;          // members of the crossing bin that are sorted in LDS
-// Rows of up to kRowBinsMax scores are selected by 512-thread workgroups that read the row once and keep the bin
-// of every score in LDS.
-constexpr int kRowThreads = 512;
+// Rows of up to kRowCodesMax scores are selected by workgroups that read the row once and keep a byte per score in LDS.
 constexpr int kRowBins = 1024;
-constexpr int kRowCap = 512;
-constexpr int kRowBinsMax = 32768;
+constexpr int kRowCodesMax = 131072;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 __device__ __forceinline__ unsigned ordered_bits(float s) {   // monotone: larger score, larger unsigned
   const unsigned u = __float_as_uint(s);
   return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-}
-// lane-wise arithmetic on the two 16-bit halves of a word
-typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
-__device__ __forceinline__ unsigned pk_sub_u16(unsigned a, unsigned b) {
-  return __builtin_bit_cast(unsigned, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ unsigned pk_min_u16(unsigned a, unsigned b) {
-  return __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 __device__ __forceinline__ float from_ordered(unsigned o) {
   const unsigned u = o ^ ((o >> 31) ? 0x80000000u : 0xFFFFFFFFu);
@@ -268,13 +257,13 @@ __device__ __forceinline__ unsigned long long rank_key(float s, int j) {
 }
 // Weight of a score relative to the row maximum: trunc(2^40 * 2^((s - rmax) * log2 e)), 2^-40 fixed point.
 // The bare exponential instruction differs from exp2f only below 2^-126, where the weight is zero either way.
-// The product with 2^40 is exact, and so is its split into a multiple of 2^16 and a remainder (the hardware
+// The products with powers of two are exact, and so is the split into a whole and a fractional part (the hardware
 // has no float -> 64-bit integer conversion).
 __device__ __forceinline__ unsigned long long weight_of(float s, float rmax) {
-  const float x = __builtin_amdgcn_exp2f((s - rmax) * kLog2e) * 1099511627776.0f;   // in [0, 2^40]
-  const unsigned hi = (unsigned)(x * (1.0f / 65536.0f));
-  const unsigned lo = (unsigned)__builtin_fmaf(-(float)hi, 65536.0f, x);
-  return ((unsigned long long)hi << 16) + lo;
+  const float x = __builtin_amdgcn_exp2f((s - rmax) * kLog2e) * 256.0f;   // in [0, 2^8]; the weight is trunc(2^32 x)
+  const unsigned hi = (unsigned)x;
+  const unsigned lo = (unsigned)(__builtin_amdgcn_fractf(x) * 4294967296.0f);
+  return ((unsigned long long)hi << 32) | lo;
 }
 
 // Visits every score of a row: four consecutive scores per thread and step (16-byte loads; rows start 16-byte
@@ -508,18 +497,15 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
     __syncthreads();
     unsigned na = 0;
     constexpr int STEP = THREADS * 4;
-    const float4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    const int last4 = (G - 1) & ~3;
     for (int base = 0; base < Gw * 32; base += 4 * STEP) {   // (the same trip count for all threads: they vote below)
-      float4 v[4];
+      f32x4 v[4];   // (unconditional loads, of the last scores again past the end: under a test they become 4-byte loads)
+#pragma unroll
+      for (int e = 0; e < 4; e++) v[e] = *reinterpret_cast<const f32x4*>(s + min(base + e * STEP + tid * 4, last4));
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         const int j4 = base + e * STEP + tid * 4;
-        v[e] = j4 < G ? *reinterpret_cast<const float4*>(s + j4) : zero4;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const int j4 = base + e * STEP + tid * 4;
-        const float x[4] = {v[e].x, v[e].y, v[e].z, v[e].w};
+        const float x[4] = {v[e][0], v[e][1], v[e][2], v[e][3]};
         unsigned nib = 0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -765,181 +751,209 @@ __global__ void __launch_bounds__(THREADS) select_kernel(const float* scores, co
                                         from_ordered(range[2 * row + 1]), G, top_p, cut, count, keep_bits, Gw);
 }
 
-// Rows of at most kRowBinsMax scores: the row is read from device memory ONCE.  That pass builds the mass histogram
-// and leaves, in LDS, the bin of every score as 16 bits; the second pass then works on those alone (eight per lane
-// and step: bin < crossing bin -> the key block is kept, eight such bits are a byte of the bit row; bin == crossing
-// bin -> a member, whose score is fetched again by id).  64 KB of bins + the histogram + the members let two 512-thread
-// workgroups share a compute unit, so the short barrier-separated phases of one row hide under the passes of
-// another; the workgroups are persistent and take rows in turn.  A crossing bin with more members than fit is
-// rare and handed to select_row, which starts that row over from device memory.
-template <int THREADS, int BINS, int CAP>
-struct alignas(16) BinsShared {
-  SelShared<THREADS, BINS, CAP> sel;
-  // the same memory serves the general path when a row is handed over (it needs no 16-bit bins)
-  union {
-    uint16_t bins[kRowBinsMax];
-    SelShared<THREADS, kBins, kCap> general;
-  };
+// Rows of at most MAXROW scores: the row is read from device memory ONCE.  That pass builds the mass histogram and leaves, in
+// LDS, a byte per score: its bin divided by four.  The second pass works on the bytes alone, sixteen per lane and step: a
+// smaller byte than the crossing bin's keeps the key block, an equal one makes it a member.  The members fetch their scores
+// again by id; those above the crossing bin are kept, those in it are ranked.  The row's bits replace the bytes in LDS as
+// they are read, so members add theirs with LDS atomics and the row of bits is written once.
+// Bound: the first pass's vector instructions and LDS atomics (one 64-bit addition per score) and the latencies of the short
+// phases between barriers, so what matters is how many waves a compute unit holds; bytes (16-bit bins before) let three
+// workgroups of 512 threads share one for rows of up to 32768 scores instead of two, and let rows of up to 131072 in at all
+// (before, they were read from memory in every pass).  6144 rows of 32760: 359 -> 256 us; 22296 rows of 118800:
+// 5.6 -> 4.5 ms.  (The histogram's atomics are not what binds: without seven eighths of them it is no faster.)  Too many members
+// for LDS are rare; such a row is left, with a count of zero, to select_left_kernel, which starts over from device memory
+// (in this kernel that path would cost the usual one its registers).
+template <int THREADS, int MAXROW, int IDCAP, typename ID>
+struct alignas(16) CodesShared {
+  SelShared<THREADS, kRowBins, 2> sel;   // (the ranked keys reuse the histogram's memory)
+  alignas(16) ID ids[IDCAP];
+  alignas(16) uint32_t codes[MAXROW / 4];
 };
 
-template <int THREADS, int BINS, int CAP>
-__global__ void __launch_bounds__(THREADS) select_bins_kernel(const float* scores, const unsigned* range, int64_t chunk_rows,
-                                                              int unit0, int YT, int QB, int G, int Gs, float top_p,
-                                                              unsigned long long* cut, unsigned* count, uint32_t* keep_bits,
-                                                              int Gw) {
-  static_assert(CAP == THREADS, "one member per thread in the ranking");
-  static_assert(BINS >= 128 && BINS % THREADS == 0 && BINS < 0x7FFF, "bins (16 bits each in LDS, one value set aside)");
-  __shared__ BinsShared<THREADS, BINS, CAP> shm;
+template <int THREADS, int MAXROW, int IDCAP, typename ID, int WAVES_PER_SIMD>
+__global__ void __launch_bounds__(THREADS, WAVES_PER_SIMD)
+select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_rows, int unit0, int YT, int QB, int G, int Gs,
+                    float top_p, unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
+  constexpr int BINS = kRowBins, CAP = THREADS;   // one ranked member per thread
+  static_assert(CAP <= BINS && BINS == 4 * 256 && MAXROW % 1024 == 0 && (sizeof(ID) > 2 || MAXROW <= 65536), "layout");
+  __shared__ CodesShared<THREADS, MAXROW, IDCAP, ID> shm;
   auto& sh = shm.sel;
-  const int tid = threadIdx.x, lane = tid & 63;
+  unsigned long long* const keys = sh.mass;
   for (int64_t local = blockIdx.x; local < chunk_rows; local += gridDim.x) {
     const int64_t row = chunk_row(local, unit0, YT, QB);
     if (row < 0) continue;   // (the same for all threads)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (what follows from the thread's number is formed anew for every row: kept, it spills)
     const float* s = scores + local * Gs;
     const float rmax = from_ordered(range[2 * row]), rmin = from_ordered(range[2 * row + 1]);
     uint32_t* const bits_row = keep_bits + row * Gw;
     const float width = rmax - rmin;
     const float inv = width > 0.0f ? (float)BINS / width : 0.0f;
-    auto value_bin = [&](float v) -> int {   // bin 0 holds the largest scores
-      const int b = (int)((rmax - v) * inv);
-      return b < 0 ? 0 : (b > BINS - 1 ? BINS - 1 : b);
-    };
+    // bin 0 holds the largest scores (rmax - v is not negative)
+    auto value_bin = [&](float v) -> unsigned { return min((unsigned)((rmax - v) * inv), (unsigned)(BINS - 1)); };
     __syncthreads();   // the row before this one is done with the shared state
     for (int i = tid; i < BINS; i += THREADS) sh.mass[i] = 0;
-    if (tid == 0) sh.ncand = 0;
+    if (tid == 0) {
+      sh.ncand = 0;
+      sh.bin_cnt = 0;
+    }
     __syncthreads();
 
-    // pass 1: four consecutive scores per thread and step, four steps in flight while four are processed; the bins go
-    // to LDS in the order of the key blocks; positions past the end get kPastEnd (no bin is as large)
-    constexpr unsigned kPastEnd = 0x7FFFu;
+    // pass 1: four consecutive scores per thread and step, DEPTH steps in flight while DEPTH are processed.  The loads are
+    // unconditional, 16 bytes of the row's padding or of its last scores again past the end (with a test around them the
+    // compiler makes four 4-byte loads and four branches of each: 311 us for 6144 rows of 32760).
     {
-      constexpr int STEP = THREADS * 4;
+      constexpr int STEP = THREADS * 4, DEPTH = WAVES_PER_SIMD > 4 ? 2 : 4;
       auto one = [&](float v) -> unsigned {
-        const int b = value_bin(v);
+        const unsigned b = value_bin(v);
         atomicAdd(&sh.mass[b], weight_of(v, rmax));
-        return (unsigned)b;
+        return b;
       };
-      auto four = [&](const float4& v, int j4) {
-        unsigned b0, b1, b2, b3;
-        if (j4 + 3 < G) {   // (all but the last four of a row whose length is not a multiple of four)
-          b0 = one(v.x);
-          b1 = one(v.y);
-          b2 = one(v.z);
-          b3 = one(v.w);
-        } else {
-          b0 = one(v.x);
-          b1 = j4 + 1 < G ? one(v.y) : kPastEnd;
-          b2 = j4 + 2 < G ? one(v.z) : kPastEnd;
-          b3 = kPastEnd;
+      auto store4 = [&](unsigned b0, unsigned b1, unsigned b2, unsigned b3, int j4) {
+        const unsigned b01 = (b0 | (b1 << 16)) >> 2, b23 = (b2 | (b3 << 16)) >> 2;   // bytes 0 and 2 are the codes
+        shm.codes[j4 >> 2] = __builtin_amdgcn_perm(b23, b01, 0x06040200u);
+      };
+      const int last4 = (G - 1) & ~3;   // the last four scores, or what is left of them
+      auto load4 = [&](f32x4 (&x)[DEPTH], int j0) {
+#pragma unroll
+        for (int e = 0; e < DEPTH; e++) x[e] = *reinterpret_cast<const f32x4*>(s + min(j0 + e * STEP, last4));
+      };
+      f32x4 cur[DEPTH], nxt[DEPTH];
+      load4(cur, tid * 4);
+#pragma unroll 1
+      for (int base = 0; base < G; base += DEPTH * STEP) {
+        load4(nxt, base + DEPTH * STEP + tid * 4);
+#pragma unroll
+        for (int e = 0; e < DEPTH; e++) {
+          const int j4 = base + e * STEP + tid * 4;
+          if (base + (e + 1) * STEP <= G) {   // (the same in all threads)
+            const unsigned b0 = one(cur[e][0]), b1 = one(cur[e][1]), b2 = one(cur[e][2]), b3 = one(cur[e][3]);
+            store4(b0, b1, b2, b3, j4);
+          } else if (j4 < G) {
+            unsigned b[4] = {0u, 0u, 0u, 0u};   // (codes of positions past the end are never looked at)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+              if (j4 + i < G) b[i] = one(cur[e][i]);
+            store4(b[0], b[1], b[2], b[3], j4);
+          }
         }
-        *reinterpret_cast<uint2*>(&shm.bins[j4]) = uint2{b0 | (b1 << 16), b2 | (b3 << 16)};
-      };
-      const float4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-      auto load4 = [&](float4 (&x)[4], int j0) {
 #pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = j0 + e * STEP < G ? *reinterpret_cast<const float4*>(s + j0 + e * STEP) : zero4;
-      };
-      float4 cur[4], nxt[4];
-      int j4 = tid * 4;
-      load4(cur, j4);
-      for (; j4 < G; j4 += 4 * STEP) {   // (no barrier inside: threads may leave at different trip counts)
-        load4(nxt, j4 + 4 * STEP);
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-          if (j4 + e * STEP < G) four(cur[e], j4 + e * STEP);
-#pragma unroll
-        for (int e = 0; e < 4; e++) cur[e] = nxt[e];
+        for (int e = 0; e < DEPTH; e++) cur[e] = nxt[e];
       }
     }
     __syncthreads();
     locate_bin<true>(sh, top_p);
 
-    // pass 2 on the bins, eight per lane and step with 16-bit arithmetic on pairs: bin - crossing bin is negative
-    // for a key block ranked above the crossing bin (it is kept) and zero for a member of it.  The eight sign bits of
-    // a lane make a byte of the row's bits, four lanes a word.  A wave owns a contiguous stretch of the row
-    // (a multiple of 512 key blocks).
+    // pass 2: sixteen codes per lane and step.  Per word of four, high bit of byte e: `less` says code e is below the crossing
+    // one (by the subtraction of the low seven bits, which cannot borrow, and the high bits), `same` that it is equal; a dot
+    // product with 1, 2, 4, 8 gathers the four bits.
+    const unsigned fine = sh.bin, code = fine >> 2;
+    unsigned n_codes;   // key blocks with a smaller code
     {
-      const unsigned b0 = sh.bin;
-      const unsigned b0b0 = b0 | (b0 << 16);
-      const int wv = tid >> 6;
-      const int per_wave = ((G + THREADS * 8 - 1) / (THREADS * 8)) * 512;   // key blocks per wave
-      const int k0 = wv * per_wave;                                            // first key block of this wave
-      const int steps = min(per_wave >> 9, max(0, (G - k0 + 511) >> 9));       // of this wave (the same in all lanes)
+      constexpr unsigned H = 0x80808080u;
+      const unsigned c4 = code * 0x01010101u, c4low = c4 & ~H, c_small = code < 128u ? ~0u : 0u;
       unsigned na = 0;
-      for (int i = 0; i < steps; i++) {
-        const int j8 = k0 + i * 512 + lane * 8;   // (below kRowBinsMax: at most G rounded up to 512)
-        const uint4 w = *reinterpret_cast<const uint4*>(&shm.bins[j8]);
-        const unsigned d0 = pk_sub_u16(w.x, b0b0), d1 = pk_sub_u16(w.y, b0b0), d2 = pk_sub_u16(w.z, b0b0), d3 = pk_sub_u16(w.w, b0b0);
-        // word r holds key blocks j8 + 2r (low half) and j8 + 2r + 1: their sign bits go to bits 2r and 16 + 2r
-        unsigned y = (d0 >> 15) & 0x00010001u;
-        y |= (d1 >> 13) & 0x00040004u;
-        y |= (d2 >> 11) & 0x00100010u;
-        y |= (d3 >> 9) & 0x00400040u;
-        unsigned byte = (y & 0x55u) | ((y >> 15) & 0xAAu);         // bit e: key block j8 + e is above the crossing bin
-        const int left = G - j8;                                   // key blocks of this lane inside the row
-        byte = left >= 8 ? byte : (left > 0 ? byte & ((1u << left) - 1u) : 0u);
-        na += (unsigned)__popc(byte);
-        unsigned word = byte << (8 * (lane & 3));
-        word |= __shfl_xor(word, 1);
-        word |= __shfl_xor(word, 2);
-        const int wi = ((k0 + i * 512) >> 5) + (lane >> 2);
-        if ((lane & 3) == 0 && wi < Gw) bits_row[wi] = word;
-        // members: some half of the differences is zero
-        const unsigned m01 = pk_min_u16(d0, d1), m23 = pk_min_u16(d2, d3);
-        const unsigned m = pk_min_u16(m01, m23);
-        if (min(m & 0xFFFFu, m >> 16) == 0u) {
-          const unsigned dd[4] = {d0, d1, d2, d3};
+#pragma unroll 1
+      for (int base = 0; base < G; base += THREADS * 16) {
+        const int j16 = base + tid * 16;
+        if (base + (tid & ~63) * 16 >= G) break;   // (the same in all lanes of a wave)
+        const int left = G - j16;   // codes of this lane inside the row
+        unsigned keep = 0, member = 0;
+        if (left > 0) {
+          const uint4 w4 = *reinterpret_cast<const uint4*>(&shm.codes[j16 >> 2]);
+          const unsigned w[4] = {w4.x, w4.y, w4.z, w4.w};
+          unsigned below[2] = {0u, 0u}, equal[2] = {0u, 0u};   // eight codes each, shifted left by seven
 #pragma unroll
-          for (int e = 0; e < 8; e++) {
-            const unsigned half = (e & 1 ? dd[e >> 1] >> 16 : dd[e >> 1]) & 0xFFFFu;
-            if (half == 0u && e < left) {
-              const unsigned pos = atomicAdd(&sh.ncand, 1u);
-              if (pos < (unsigned)CAP) sh.cand[pos] = (unsigned long long)(unsigned)(j8 + e);
-            }
+          for (int r = 0; r < 4; r++) {
+            const unsigned t = (w[r] | H) - c4low;
+            const unsigned less = ~((t & (w[r] | c_small)) | (w[r] & c_small)) & H;
+            const unsigned z = w[r] ^ c4;
+            const unsigned same = ~(((z & ~H) + ~H) | z) & H;
+            const unsigned weights = r & 1 ? 0x80402010u : 0x08040201u;
+            below[r >> 1] = __builtin_amdgcn_udot4(less, weights, below[r >> 1], false);
+            equal[r >> 1] = __builtin_amdgcn_udot4(same, weights, equal[r >> 1], false);
+          }
+          const unsigned inside = left >= 16 ? 0xFFFFu : (1u << left) - 1u;
+          keep = ((below[0] >> 7) | (below[1] << 1)) & inside;
+          member = ((equal[0] >> 7) | (equal[1] << 1)) & inside;
+        }
+        na += (unsigned)__popc(keep);
+        unsigned word = keep << (16 * (tid & 1));
+        word |= __shfl_xor(word, 1);
+        // the word takes the place of the codes it stands for: every lane has read its own, and no other lane reads these
+        if ((tid & 1) == 0 && left > 0) shm.codes[j16 >> 2] = word;
+        if (__builtin_amdgcn_ballot_w64(member != 0u) != 0) {
+          // places for the members of the whole wave with one atomic; a lane's own follow those of the lanes below it
+          const unsigned m = (unsigned)__popc(member);
+          unsigned pos = 0, all = 0;
+#pragma unroll
+          for (int b = 0; b < 5; b++) {   // (a count of at most 16, bit by bit)
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64((m >> b) & 1u);
+            pos += __builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u)) << b;
+            all += (unsigned)__popcll(lanes) << b;
+          }
+          unsigned first = 0;
+          if ((tid & 63) == 0) first = atomicAdd(&sh.ncand, all);
+          pos += (unsigned)__builtin_amdgcn_readfirstlane((int)first);
+#pragma unroll 1
+          while (member != 0u) {
+            if (pos < (unsigned)IDCAP) shm.ids[pos] = (ID)(j16 + __ffs(member) - 1);
+            pos++;
+            member &= member - 1;
           }
         }
       }
-      const unsigned long long na_all = block_sum_u64(sh, (unsigned long long)na);   // (its barriers also order the atomics before the read of ncand)
-      if (tid == 0) sh.n_above = (unsigned)na_all;
+      n_codes = (unsigned)block_sum_u64(sh, (unsigned long long)na);   // (its barriers also order the bits and the ids)
     }
-    const unsigned n = sh.ncand;   // (read by all threads after the barriers of the sum)
-    if (n > (unsigned)CAP) {
-      // too many members for one ranking: the general path takes the row from the start (it rewrites all outputs)
-      __syncthreads();
-      select_row<THREADS, kBins, kCap>(shm.general, s, row, rmax, rmin, G, top_p, cut, count, keep_bits, Gw);
+    const unsigned n_ids = sh.ncand;   // (read by all threads after the barriers of the sum)
+    auto keep_bit = [&](unsigned id) { atomicOr(&shm.codes[(id >> 5) * 8], 1u << (id & 31)); };
+    // members: above the crossing bin, in it (their rank keys are collected), or below it
+    unsigned more = 0;
+    if (n_ids <= (unsigned)IDCAP)
+#pragma unroll 1
+      for (unsigned i = tid; i < n_ids; i += THREADS) {
+        const unsigned id = (unsigned)shm.ids[i];
+        const float v = s[id];
+        const unsigned b = value_bin(v);
+        if (b < fine) {
+          keep_bit(id);
+          more++;
+        } else if (b == fine) {
+          const unsigned pos = atomicAdd(&sh.bin_cnt, 1u);
+          if (pos < (unsigned)CAP) keys[pos] = rank_key(v, (int)id);   // (the histogram is not needed any more)
+        }
+      }
+    const unsigned n_above = n_codes + (unsigned)block_sum_u64(sh, (unsigned long long)more);
+    const unsigned n = sh.bin_cnt;
+    if (n_ids > (unsigned)IDCAP || n > (unsigned)CAP) {
+      // too many members: left to select_left_kernel (a row that is done keeps at least one key block)
+      if (tid == 0) count[row] = 0u;
       continue;
     }
-    // the members: thread i holds member i -- rank key from the score, fetched again by id
-    unsigned long long key = 0ull;
-    if (tid < (int)n) {
-      const unsigned id = (unsigned)sh.cand[tid];
-      key = rank_key(s[id], (int)id);
-    }
-    __syncthreads();   // all ids read
-    if (tid < (((int)n + 7) & ~7)) sh.cand[tid] = key;   // (zeros up to a multiple of eight: they rank below every key)
+    // rank by counting (the keys are distinct), keys ordered by rank, crossing by a prefix of their masses over the threads
+    const unsigned long long key = tid < (int)n ? keys[tid] : 0ull;
+    if (tid >= (int)n && tid < (((int)n + 7) & ~7)) keys[tid] = 0ull;   // (zeros up to a multiple of eight: below every key)
     __syncthreads();
-    // rank by counting (the keys are distinct), masses ordered by rank through LDS, crossing by a prefix over the threads
     int rank = 0;
     if (tid < (int)n)
+#pragma unroll 1
       for (unsigned j = 0; j < n; j += 8) {   // eight keys per step: four 16-byte reads in flight
         unsigned long long o[8];
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
-          const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(&sh.cand[j + e]);
+          const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(&keys[j + e]);
           o[e] = two.x;
           o[e + 1] = two.y;
         }
 #pragma unroll
         for (int e = 0; e < 8; e++) rank += o[e] > key ? 1 : 0;
       }
-    __syncthreads();   // all of cand read: the ordered keys go back into it
-    if (tid < (int)n) {
-      sh.cand[rank] = key;
-      sh.mass[rank] = weight_of(from_ordered((unsigned)(key >> 32)), rmax);
-    }
+    __syncthreads();   // all keys read: the ordered ones go back
+    if (tid < (int)n) keys[rank] = key;
     __syncthreads();
     {
-      const unsigned long long w = tid < (int)n ? sh.mass[tid] : 0ull;
+      const unsigned long long mine = tid < (int)n ? keys[tid] : 0ull;
+      const unsigned long long w = tid < (int)n ? weight_of(from_ordered((unsigned)(mine >> 32)), rmax) : 0ull;
       unsigned long long before, all;
       block_exclusive_mass(sh, w, &before, &all);
       const unsigned long long target = sh.target, base = sh.mass_above;
@@ -948,25 +962,36 @@ __global__ void __launch_bounds__(THREADS) select_bins_kernel(const float* score
       const bool here = tid < (int)n && ((base + before < target && base + before + w >= target) ||
                                          (tid == (int)n - 1 && base + before + w < target) || (tid == 0 && base >= target));
       if (here) {
-        sh.cut = sh.cand[tid];
-        cut[row] = sh.cand[tid];
-        count[row] = sh.n_above + (unsigned)tid + 1u;
+        sh.cut = mine;
+        cut[row] = mine;
+        count[row] = n_above + (unsigned)tid + 1u;
       }
       if (n == 0 && tid == 0) {   // unreachable (the crossing bin has mass, hence members); no output is left unset
         sh.cut = ~0ull;
         cut[row] = ~0ull;
-        count[row] = sh.n_above;
+        count[row] = n_above;
       }
     }
-    // The bits of everything above the crossing bin are in memory (pass 2), stored by other waves of this workgroup:
-    // every wave waits until its own stores have completed before the barrier, so the atomics on the same words,
-    // which go to the same L2, come after them.  Members at or above the cut are kept too.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid < (int)n && key >= sh.cut) {
-      const unsigned id = 0xFFFFFFFFu - (unsigned)key;
-      atomicOr(&bits_row[id >> 5], 1u << (id & 31));
-    }
+    if (tid < (int)n && key >= sh.cut) keep_bit(0xFFFFFFFFu - (unsigned)key);
+    __syncthreads();
+#pragma unroll 1
+    for (int wi = tid; wi < Gw; wi += THREADS) bits_row[wi] = shm.codes[wi * 8];
+  }
+}
+
+// The rows that select_codes_kernel left: two per workgroup are looked at.
+template <int THREADS, int BINS, int CAP>
+__global__ void __launch_bounds__(THREADS) select_left_kernel(const float* scores, const unsigned* range, int64_t chunk_rows, int unit0,
+                                                              int YT, int QB, int G, int Gs, float top_p, unsigned long long* cut,
+                                                              unsigned* count, uint32_t* keep_bits, int Gw) {
+  __shared__ SelShared<THREADS, BINS, CAP> sh;
+  for (int64_t local = 2 * (int64_t)blockIdx.x; local < min(2 * (int64_t)blockIdx.x + 2, chunk_rows); local++) {
+    const int64_t row = chunk_row(local, unit0, YT, QB);
+    if (row < 0 || count[row] != 0u) continue;   // (the same for all threads)
+    select_row<THREADS, BINS, CAP>(sh, scores + local * Gs, row, from_ordered(range[2 * row]), from_ordered(range[2 * row + 1]),
+                                   G, top_p, cut, count, keep_bits, Gw);
+    __syncthreads();   // the next row uses the same shared state
   }
 }
 
@@ -1064,7 +1089,7 @@ static int layout_of(const fgattn_params* p, Layout* lo) {
   lo->G = ((int64_t)p->L + p->N - 1) / p->N;
   lo->Gs = (lo->G + 31) & ~(int64_t)31;   // rows start on 128-byte lines
   lo->Gw = (lo->G + 31) / 32;
-  lo->row_in_lds = lo->Gs <= kRowBinsMax && !(p->flags & FGATTN_FLAG_MASK_ROWS_IN_HBM);
+  lo->row_in_lds = lo->Gs <= kRowCodesMax && !(p->flags & FGATTN_FLAG_MASK_ROWS_IN_HBM);
   lo->rows = lo->slices * lo->QB;
   if (lo->rows > 0x7fffffffLL || lo->slices > 65535) return FGATTN_E_SHAPE;
   lo->YT = (lo->QB + 127) / 128;
@@ -1181,9 +1206,30 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
                          (int)lo.G, (int)lo.Gs, p->scale, (int)unit0, (int)nunits, (int)lo.YT, (int)gx, scores, range);
     if (!launched()) return FGATTN_E_DEVICE;
     if (lo.row_in_lds) {
-      const unsigned wgs = (unsigned)(chunk_rows < 2 * cus ? chunk_rows : 2 * cus);   // two fit a compute unit
-      hipLaunchKernelGGL((select_bins_kernel<kRowThreads, kRowBins, kRowCap>), dim3(wgs), dim3(kRowThreads), 0, stream, scores, range, chunk_rows,
-                         (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p, cut, count, keep_bits, (int)lo.Gw);
+      // As many persistent workgroups as LDS or registers let in: three per compute unit with the codes of 32768 scores, two
+      // with 65536, one, of 1024 threads, with 131072.  Short rows are all latency: workgroups of 256, seven of them (1764
+      // rows of 147 scores 38 us with two workgroups of 512 per unit -> 16).
+      int members = 512;   // that always fit
+      auto launch = [&](auto kernel, int threads, int per_cu) {
+        const int64_t fit = (int64_t)per_cu * cus;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(chunk_rows < fit ? chunk_rows : fit)), dim3(threads), 0, stream, scores, range,
+                           chunk_rows, (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p, cut, count, keep_bits,
+                           (int)lo.Gw);
+      };
+      if (lo.Gs <= 4096)
+        launch(select_codes_kernel<256, 4096, 2048, uint16_t, 7>, members = 256, 7);
+      else if (lo.Gs <= 32768)
+        launch(select_codes_kernel<512, 32768, 2048, uint16_t, 6>, 512, 3);
+      else if (lo.Gs <= 65536)
+        launch(select_codes_kernel<512, 65536, 2048, uint16_t, 4>, 512, 2);
+      else
+        launch(select_codes_kernel<1024, kRowCodesMax, 4096, uint32_t, 4>, 1024, 1);
+      if (lo.G > members) {
+        if (!launched()) return FGATTN_E_DEVICE;
+        hipLaunchKernelGGL((select_left_kernel<kSelThreads, kBins, kCap>), dim3((unsigned)((chunk_rows + 1) / 2)), dim3(kSelThreads),
+                           0, stream, scores, range, chunk_rows, (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p,
+                           cut, count, keep_bits, (int)lo.Gw);
+      }
     } else {
       hipLaunchKernelGGL((select_kernel<kSelThreads, kBins, kCap>), dim3((unsigned)chunk_rows), dim3(kSelThreads), 0, stream,
                          scores, range, (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p, cut, count, keep_bits,

@@ -80,3 +80,30 @@ def test_scores_of_every_tile_and_stretch(H, L, d, M, N, one_tile):
     most_out = torch.where(got, -1.0, prob).amax(-1)
     assert (mass >= 0.9 - tol).all() and (mass - least < 0.9 + tol).all(), (mass.min(), (mass - least).max())
     assert (most_out <= least * (1 + (1e-4 if tol < 1e-4 else 0.3)) + 1e-9).all(), float((most_out / least).max())
+
+
+# The selection that reads a row once, in each of its sizes, against the one that reads it in every pass.  Rows of scores that
+# are spread out, that leave most weights zero, that take a few values only, that sit close together beside one
+# dominant score, and that are all equal: from few members of the crossing bin to more than any kernel keeps.  Rows end
+# at, before and after a group of sixteen, a word, and the largest row of a kernel.
+@pytest.mark.parametrize("G", [1, 15, 147, 257, 1000, 4096, 4097, 8195, 32768, 32769, 65536, 65537, 118800, 131072, 131073])
+def test_selection_from_bytes_equals_selection_from_memory(G):
+    d, M = 64, 128
+    for kind in ("spread", "peaked", "few values", "close", "equal"):
+        for top_p in (0.3, 0.9, 1.0):
+            res = []
+            for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+                q, k, _, ws, indptr = problem(1, G, d, M, 1, seed=G, flags=flags)
+                if kind == "few values":
+                    k = (k[..., :1] > 0.5).to(k.dtype).expand_as(k).contiguous()
+                elif kind == "close":
+                    k = 1.0 + (k > 1.0).to(k.dtype) * 2.0 ** -7
+                    k[:, :, G // 2] = 40.0
+                    q = q.abs()
+                elif kind == "equal":
+                    k = torch.ones_like(k)
+                p = F.make_params(q, k, k, q, M, 1, (20.0 if kind == "peaked" else 1.0) * d ** -0.5, flags)
+                F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
+                res.append((indptr, bit_rows(p, ws, indptr.numel() - 1, G)))
+            assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
+            assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
