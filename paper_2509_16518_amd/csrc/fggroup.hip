@@ -21,6 +21,9 @@
 namespace fgg {
 
 constexpr int kThreads = 256;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+static bool launched() { return hipGetLastError() == hipSuccess; }
 
 // one workgroup per query tile: its bit row is built in LDS and written out whole
 __global__ void __launch_bounds__(kThreads) bitmap_kernel(const int64_t* indptr, const int32_t* indices, int Gw,
@@ -39,48 +42,84 @@ __global__ void __launch_bounds__(kThreads) bitmap_kernel(const int64_t* indptr,
   for (int i = tid; i < Gw; i += kThreads) bits[w * Gw + i] = row[i];
 }
 
-// 64 x 64 block of the distance matrix of one slice per workgroup; a thread owns a 4 x 4 patch
-__global__ void __launch_bounds__(kThreads) distance_kernel(const uint32_t* bits, int QB, int Gw, uint32_t* dist) {
-  __shared__ uint32_t A[64][33], B[64][33];
+// 64 x 64 block of the distance matrix of one slice per workgroup; a thread owns a 4 x 4 patch (rows ty*4 + a, columns
+// tx + 16*b).  The matrix is symmetric: only blocks on and above the diagonal are computed, the others are written from
+// them.  Words are read from LDS four at a time; rows of 36 words put the 16 columns a wave reads at once into
+// different banks.  Bound: latency and the counting adds.  12 slices of 2048 tiles x 2048 key blocks: 265 us with all blocks
+// computed, 270 with half of them but every word fetched by a load of its own that was waited for; 244 us with the
+// words of a step fetched together and one step ahead.
+template <typename T>
+__global__ void __launch_bounds__(kThreads) distance_kernel(const uint32_t* bits, int QB, int Gw, int ld, T* dist) {
+  __shared__ alignas(16) uint32_t words[2][64][36];
+  uint32_t (&A)[64][36] = words[0], (&B)[64][36] = words[1];
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const int slice = blockIdx.z;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+  if (j0 < i0) return;
   const uint32_t* base = bits + (int64_t)slice * QB * Gw;
   uint32_t acc[4][4];
 #pragma unroll
   for (int a = 0; a < 4; a++)
 #pragma unroll
     for (int b = 0; b < 4; b++) acc[a][b] = 0;
+  // 32 words of the 64 + 64 rows at a time, eight of each per thread, fetched one step ahead of their use; rows past the
+  // end repeat the last one (their distances are not written)
+  typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+  const int lr = tid >> 2, lc = (tid & 3) * 8;
+  const uint32_t* const rows[2] = {base + (int64_t)min(i0 + lr, QB - 1) * Gw + lc, base + (int64_t)min(j0 + lr, QB - 1) * Gw + lc};
+  u32x4 next[2][2];
+  auto fetch = [&](int w0) {
+    if (w0 + 32 <= Gw) {
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int h = 0; h < 2; h++) next[m][h] = *reinterpret_cast<const u32x4_any*>(rows[m] + w0 + 4 * h);
+    } else {
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) next[m][e >> 2][e & 3] = w0 + lc + e < Gw ? rows[m][w0 + e] : 0u;
+    }
+  };
+  fetch(0);
   for (int w0 = 0; w0 < Gw; w0 += 32) {
-    for (int t = tid; t < 64 * 32; t += kThreads) {
-      const int r = t >> 5, c = t & 31;
-      const bool inw = w0 + c < Gw;
-      A[r][c] = (inw && i0 + r < QB) ? base[(int64_t)(i0 + r) * Gw + w0 + c] : 0u;
-      B[r][c] = (inw && j0 + r < QB) ? base[(int64_t)(j0 + r) * Gw + w0 + c] : 0u;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      *reinterpret_cast<u32x4*>(&A[lr][lc + 4 * h]) = next[0][h];
+      *reinterpret_cast<u32x4*>(&B[lr][lc + 4 * h]) = next[1][h];
     }
     __syncthreads();
-#pragma unroll 8
-    for (int c = 0; c < 32; c++) {
-      uint32_t av[4], bv[4];
+    if (w0 + 32 < Gw) fetch(w0 + 32);
+#pragma unroll 2
+    for (int c = 0; c < 32; c += 4) {
+      u32x4 av[4], bv[4];
 #pragma unroll
-      for (int a = 0; a < 4; a++) av[a] = A[ty * 4 + a][c];
+      for (int a = 0; a < 4; a++) av[a] = *reinterpret_cast<const u32x4*>(&A[ty * 4 + a][c]);
 #pragma unroll
-      for (int b = 0; b < 4; b++) bv[b] = B[tx * 4 + b][c];
+      for (int b = 0; b < 4; b++) bv[b] = *reinterpret_cast<const u32x4*>(&B[tx + 16 * b][c]);
 #pragma unroll
       for (int a = 0; a < 4; a++)
 #pragma unroll
-        for (int b = 0; b < 4; b++) acc[a][b] += (uint32_t)__popc(av[a] ^ bv[b]);
+        for (int b = 0; b < 4; b++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) acc[a][b] += (uint32_t)__popc(av[a][e] ^ bv[b][e]);
     }
     __syncthreads();
   }
-  uint32_t* out = dist + (int64_t)slice * QB * QB;
+  // through LDS, so that the block and its mirror image are both written in whole rows
+  T* out = dist + (int64_t)slice * QB * ld;
+  uint32_t (&block)[64][65] = *reinterpret_cast<uint32_t (*)[64][65]>(words);
+  static_assert(sizeof(block) <= sizeof(words), "the block takes the place of the words");
 #pragma unroll
   for (int a = 0; a < 4; a++)
 #pragma unroll
-    for (int b = 0; b < 4; b++) {
-      const int i = i0 + ty * 4 + a, j = j0 + tx * 4 + b;
-      if (i < QB && j < QB) out[(int64_t)i * QB + j] = acc[a][b];
-    }
+    for (int b = 0; b < 4; b++) block[ty * 4 + a][tx + 16 * b] = acc[a][b];
+  __syncthreads();
+  const int c = tid & 63;
+  for (int r = tid >> 6; r < 64; r += kThreads / 64) {
+    if (i0 + r < QB && j0 + c < QB) out[(int64_t)(i0 + r) * ld + j0 + c] = (T)block[r][c];
+    if (j0 > i0 && j0 + r < QB && i0 + c < QB) out[(int64_t)(j0 + r) * ld + i0 + c] = (T)block[c][r];
+  }
 }
 
 __global__ void __launch_bounds__(kThreads) consecutive_kernel(int QB, int R, int NG, int32_t* group_tiles) {
@@ -141,7 +180,6 @@ __global__ void __launch_bounds__(kThreads) greedy_kernel(const uint32_t* dist, 
       }
       __syncthreads();
     }
-    if (R == 1) __syncthreads();   // no pick, hence no barrier since seed_s was read
   }
 }
 
@@ -164,88 +202,166 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
   return (unsigned)__builtin_amdgcn_readlane((int)y, 63);
 }
 
-// The same heuristic for slices of at most KPT * kThreads tiles whose (distance, index) pairs fit 32 bits
-// (`jbits` for the index): the representative's row of distances is read once per group into registers, KPT
-// keys per thread, and every pick is a register minimum, a wave minimum and one barrier.
-template <int KPT>
-__global__ void __launch_bounds__(kThreads) greedy_small_kernel(const uint32_t* dist, int QB, int R, int NG, int jbits,
+// The same heuristic for slices of at most KPT * kThreads tiles whose (distance, index) pairs fit 32 bits (`jbits` for
+// the index).  One workgroup per slice and one group after the other, so what counts is the chain of instructions per group
+// (with 1024 threads, whose 16 waves repeat the parts that every wave needs, 975 us at the size below) and that no load is
+// part of it:
+//   - the next representative is one of the first R unused tiles after this one (at most R - 1 of them are picked), so the
+//     distances of those R rows are fetched while this group picks.  One compute unit draws 10-20 bytes per ns from beyond
+//     its L2, so the bytes count too: 16-bit distances where they fit, and only the tiles from the row's own on (those
+//     before it are used by the time it represents a group); with whole rows of 32 bits 832 us;
+//   - a wave takes its own R - 1 smallest keys with register and cross-lane minima, the waves' lists meet in LDS after the
+//     group's one barrier, and every wave takes the R - 1 smallest of those: all waves know the picks, and each keeps the whole
+//     bitmap of used tiles in registers (64 per lane), so nothing is published.
+// 12 slices of 2048 tiles, R = 8: 975 -> 750 us (a barrier per pick, one row fetched ahead before).
+// T = uint16_t: rows start 16-byte aligned and hold at least 15 elements past QB (of any value); T = uint32_t: no such assumption.
+template <typename T, int KPT, int R>
+__global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, int QB, int ld, int NG, int jbits,
                                                                 int32_t* group_tiles) {
-  extern __shared__ unsigned char used[];
-  __shared__ unsigned best[2][kThreads / 64];
-  __shared__ int seed_s, spec_s;
-  const int tid = threadIdx.x, wv = tid >> 6;
+  constexpr int WAVES = kThreads / 64, PICKS = R - 1;
+  static_assert(R >= 2 && R <= 8 && WAVES * PICKS <= 64, "a list entry per lane");
+  static_assert(KPT * kThreads <= 64 * 64 && KPT <= 32, "a lane keeps 64 tiles of the bitmap, and a bit per key");
+  __shared__ unsigned lists[2][64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.x;
-  const uint32_t* D = dist + (int64_t)slice * QB * QB;
+  const T* D = dist + (int64_t)slice * QB * ld;
   int32_t* out = group_tiles + (int64_t)slice * NG * R;
   const unsigned jmask = (1u << jbits) - 1u;
-  for (int i = tid; i < QB; i += kThreads) used[i] = 0;
+  if (tid < 128) lists[tid >> 6][lane] = 0xFFFFFFFFu;   // (entries past WAVES * PICKS stay)
+  // tiles 64 * lane .. + 63; those past the end count as used
+  const int mine = QB - lane * 64;
+  unsigned used_lo = mine >= 32 ? 0u : mine <= 0 ? ~0u : ~0u << mine;
+  unsigned used_hi = mine >= 64 ? 0u : mine <= 32 ? ~0u : ~0u << (mine - 32);
+  auto unused_word = [&](int l) {   // of lane l, in scalar registers
+    return ~(((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)used_hi, l) << 32) |
+             (unsigned)__builtin_amdgcn_readlane((int)used_lo, l));
+  };
+  auto mark = [&](int tile) {
+    const unsigned bit = lane == tile >> 6 ? 1u << (tile & 31) : 0u;
+    if (tile & 32) used_hi |= bit;
+    else used_lo |= bit;
+  };
+  const int j0 = tid * KPT;   // this thread's tiles: j0 .. j0 + KPT - 1
+  unsigned alive = QB - j0 >= KPT ? (1u << KPT) - 1u : QB > j0 ? (1u << (QB - j0)) - 1u : 0u;   // bit i: tile j0 + i is unused
+  constexpr int WORDS = KPT * sizeof(T) / 4;
+  struct Part { uint32_t w[WORDS]; };   // a thread's part of a row of distances
+  auto fetch = [&](Part& p, int tile) {
+    if (j0 + KPT <= tile || j0 >= QB) return;
+    const T* src = D + (int64_t)tile * ld + j0;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+      for (int i = 0; i < WORDS; i += 4) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src + 2 * i);
+#pragma unroll
+        for (int e = 0; e < 4; e++) p.w[i + e] = v[e];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < WORDS; i++) p.w[i] = src[min(i, QB - 1 - j0)];
+    }
+  };
+  Part row = {};         // of the representative
+  fetch(row, 0);
+  auto take = [&](int tile) { alive &= ~(tile / KPT == tid ? 1u << (tile & (KPT - 1)) : 0u); };
   __syncthreads();
-  int next = 0;        // every tile below `next` is used (the same value in all threads)
-  unsigned round = 0;  // picks so far: selects the half of best[] in use
-  // distances of row `ahead_row`, read one group early: the first unused tile after the representative becomes
-  // the next representative unless this group picks it
-  unsigned ahead[KPT] = {};
-  int ahead_row = -1;
-  for (int g = 0; g < NG; g++) {
-    if (tid == 0) {
-      int s = next;
-      while (s < QB && used[s]) s++;
-      seed_s = s;
-      if (s < QB) used[s] = 1;
-      int c = s + 1;
-      while (c < QB && used[c]) c++;
-      spec_s = c;
-    }
-    __syncthreads();
-    const int seed = seed_s, spec = spec_s;
-    next = seed + 1;
-    if (tid == 0) out[g * R] = seed < QB ? seed : -1;
-    unsigned key[KPT];   // (distance, index) of the unused tiles this thread owns, all ones otherwise
-    const uint32_t* drow = D + (int64_t)(seed < QB ? seed : 0) * QB;
-    // (all loads unconditional, with clamped indices: they are issued back to back, and the rows read ahead stay
-    // in flight while this group picks)
-    unsigned now[KPT];
-#pragma unroll
-    for (int i = 0; i < KPT; i++) now[i] = drow[min(i * kThreads + tid, QB - 1)];
-    const bool have = seed == ahead_row;
-#pragma unroll
-    for (int i = 0; i < KPT; i++) {
-      const int j = i * kThreads + tid;
-      const bool cand = seed < QB && j < QB && !used[j];
-      const unsigned dv = have ? ahead[i] : now[i];
-      key[i] = cand ? ((dv << jbits) | (unsigned)j) : 0xFFFFFFFFu;
-    }
-    ahead_row = spec < QB ? spec : -1;
+  int seed = 0;
+  for (int g = 0; g < NG; g++) {   // (every group but the last takes R tiles, so the representative exists)
+    mark(seed);
+    take(seed);
+    int cand[R];
+    Part ahead[R] = {};
     {
-      const uint32_t* srow = D + (int64_t)(spec < QB ? spec : 0) * QB;
+      int l = seed >> 6;
+      uint64_t free = unused_word(l);
 #pragma unroll
-      for (int i = 0; i < KPT; i++) ahead[i] = srow[min(i * kThreads + tid, QB - 1)];
-    }
-    for (int r = 1; r < R; r++, round++) {
-      unsigned mine = key[0];
-#pragma unroll
-      for (int i = 1; i < KPT; i++) mine = min(mine, key[i]);
-      const unsigned w = wave_min_u32(mine);
-      if ((tid & 63) == 0) best[round & 1][wv] = w;
-      __syncthreads();
-      unsigned win = best[round & 1][0];
-#pragma unroll
-      for (int k = 1; k < kThreads / 64; k++) win = min(win, best[round & 1][k]);
-      if (win != 0xFFFFFFFFu) {
-        const int j = (int)(win & jmask);
-#pragma unroll
-        for (int i = 0; i < KPT; i++)
-          if (j == i * kThreads + tid) key[i] = 0xFFFFFFFFu;
-        if (tid == 0) {
-          used[j] = 1;
-          out[g * R + r] = j;
-        }
-      } else if (tid == 0) {
-        out[g * R + r] = -1;
+      for (int c = 0; c < R; c++) {
+        while (free == 0 && l < 63) free = unused_word(++l);
+        cand[c] = free != 0 ? l * 64 + __builtin_ctzll(free) : QB;
+        free &= free - 1;   // (zero stays zero)
+        if (cand[c] < QB) fetch(ahead[c], cand[c]);
       }
     }
-    __syncthreads();   // seed_s is rewritten for the next group (also orders groups without picks, R = 1)
+    unsigned key[KPT];   // (distance, index) of the unused tiles this thread owns, all ones otherwise
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+      const unsigned dv = sizeof(T) == 2 ? (row.w[i / 2] >> (16 * (i & 1))) & 0xFFFFu : row.w[i];
+      key[i] = (alive >> i) & 1u ? (dv << jbits) | (unsigned)(j0 + i) : 0xFFFFFFFFu;
+    }
+    unsigned top = 0xFFFFFFFFu;   // lane r: the wave's r-th smallest
+#pragma unroll
+    for (int r = 0; r < PICKS; r++) {
+      unsigned m = key[0];
+#pragma unroll
+      for (int i = 1; i < KPT; i++) m = min(m, key[i]);
+      const unsigned w = wave_min_u32(m);
+      top = lane == r ? w : top;
+      if (r + 1 < PICKS && m == w) {   // (keys are distinct: one lane)
+#pragma unroll
+        for (int i = 0; i < KPT; i++) key[i] = key[i] == w ? 0xFFFFFFFFu : key[i];
+      }
+    }
+    unsigned* const list = lists[g & 1];   // (read by every wave before it comes to the next group's barrier)
+    if (lane < PICKS) list[wv * PICKS + lane] = top;
+    __syncthreads();
+    unsigned a = list[lane];
+    int picked = lane == 0 ? seed : -1;   // lane r: the group's r-th member
+#pragma unroll
+    for (int r = 0; r < PICKS; r++) {
+      const unsigned w = wave_min_u32(a);
+      a = a == w ? 0xFFFFFFFFu : a;
+      if (w != 0xFFFFFFFFu) {
+        const int j = (int)(w & jmask);
+        picked = lane == r + 1 ? j : picked;
+        mark(j);
+        take(j);
+      }
+    }
+    if (tid < R) out[g * R + tid] = picked;
+    int next = QB;
+    {
+      int l = seed >> 6;
+      uint64_t free = unused_word(l);
+      while (free == 0 && l < 63) free = unused_word(++l);
+      if (free != 0) next = l * 64 + __builtin_ctzll(free);
+    }
+    seed = next;
+    if (seed >= QB) {   // all taken: what is left of the list (nothing, by its length) holds no tile
+      for (int t = (g + 1) * R + tid; t < NG * R; t += kThreads) out[t] = -1;
+      break;
+    }
+#pragma unroll
+    for (int c = 0; c < R; c++)
+      if (cand[c] == seed) row = ahead[c];
   }
+}
+
+template <typename T, int R>
+static void launch_greedy_small(const T* dist, int slices, int QB, int ld, int NG, int jbits, int32_t* group_tiles,
+                                hipStream_t stream) {
+  const dim3 grid((unsigned)slices), block(kThreads);
+  if (QB <= 4 * kThreads && sizeof(T) == 4)
+    hipLaunchKernelGGL((greedy_small_kernel<T, 4 * (4 / sizeof(T)), R>), grid, block, 0, stream, dist, QB, ld, NG, jbits, group_tiles);
+  else if (QB <= 8 * kThreads)
+    hipLaunchKernelGGL((greedy_small_kernel<T, 8, R>), grid, block, 0, stream, dist, QB, ld, NG, jbits, group_tiles);
+  else
+    hipLaunchKernelGGL((greedy_small_kernel<T, 16, R>), grid, block, 0, stream, dist, QB, ld, NG, jbits, group_tiles);
+}
+
+// Distances in 16 bits where no distance is larger and the workspace (4 bytes per pair of tiles) has room for the stride:
+// rows start 16-byte aligned and, by the odd multiple of 16 bytes added, on different memory channels.
+static bool distances_fit_16(int64_t QB, int64_t G) { return G <= 0xFFFF && QB >= 128; }
+static int distance_stride(int QB) { return ((QB + 7) & ~7) + 72; }   // 2 (QB + 79) <= 4 QB for QB >= 79
+
+template <typename T>
+static bool greedy_small(const uint32_t* bits, T* dist, int slices, int QB, int Gw, int ld, int R, int NG, int jbits,
+                         int32_t* group_tiles, hipStream_t stream) {
+  hipLaunchKernelGGL(distance_kernel<T>, dim3((unsigned)((QB + 63) / 64), (unsigned)((QB + 63) / 64), (unsigned)slices),
+                     dim3(kThreads), 0, stream, bits, QB, Gw, ld, dist);
+  if (!launched()) return false;
+  if (R == 2) launch_greedy_small<T, 2>(dist, slices, QB, ld, NG, jbits, group_tiles, stream);
+  else if (R == 4) launch_greedy_small<T, 4>(dist, slices, QB, ld, NG, jbits, group_tiles, stream);
+  else launch_greedy_small<T, 8>(dist, slices, QB, ld, NG, jbits, group_tiles, stream);
+  return launched();
 }
 
 // one workgroup per group: OR of the members' rows into `ubits`, number of set bits into `count`
@@ -372,8 +488,6 @@ static int device_ok() {
   return known[dev] == 1 ? FGATTN_OK : FGATTN_E_DEVICE;
 }
 
-static bool launched() { return hipGetLastError() == hipSuccess; }
-
 }  // namespace fgg
 
 extern "C" {
@@ -409,29 +523,28 @@ int fgattn_group_select(const int64_t* mask_indptr, const int32_t* mask_indices,
   hipLaunchKernelGGL(bitmap_kernel, dim3((unsigned)(lo.slices * lo.QB)), dim3(kThreads), (size_t)Gw * 4, stream, mask_indptr,
                      mask_indices, Gw, bits);
   if (!launched()) return FGATTN_E_DEVICE;
-  if (mode == FGATTN_GROUP_CONSECUTIVE) {
+  // (128 rows are a group by themselves: the greedy order of groups of one is the order of the tiles)
+  if (mode == FGATTN_GROUP_CONSECUTIVE || R == 1) {
     hipLaunchKernelGGL(consecutive_kernel, dim3((unsigned)((NG * R + kThreads - 1) / kThreads), (unsigned)lo.slices),
                        dim3(kThreads), 0, stream, QB, R, NG, group_tiles);
   } else {
-    hipLaunchKernelGGL(distance_kernel, dim3((unsigned)((QB + 63) / 64), (unsigned)((QB + 63) / 64), (unsigned)lo.slices),
-                       dim3(kThreads), 0, stream, bits, QB, Gw, dist);
-    if (!launched()) return FGATTN_E_DEVICE;
     // a distance is at most twice the number of key blocks; with the tile index below it in 32 bits where it fits
     int jbits = 1;
     while ((1 << jbits) < QB) jbits++;
     const bool small = QB <= 16 * kThreads && (2 * lo.G + 1) < ((int64_t)1 << (32 - jbits));
-    if (small && QB <= 4 * kThreads)
-      hipLaunchKernelGGL(greedy_small_kernel<4>, dim3((unsigned)lo.slices), dim3(kThreads), (size_t)QB, stream, dist, QB, R,
-                         NG, jbits, group_tiles);
-    else if (small && QB <= 8 * kThreads)
-      hipLaunchKernelGGL(greedy_small_kernel<8>, dim3((unsigned)lo.slices), dim3(kThreads), (size_t)QB, stream, dist, QB, R,
-                         NG, jbits, group_tiles);
-    else if (small)
-      hipLaunchKernelGGL(greedy_small_kernel<16>, dim3((unsigned)lo.slices), dim3(kThreads), (size_t)QB, stream, dist, QB, R,
-                         NG, jbits, group_tiles);
-    else
+    if (small && distances_fit_16(QB, lo.G)) {
+      if (!greedy_small(bits, reinterpret_cast<uint16_t*>(dist), (int)lo.slices, QB, Gw, distance_stride(QB), R, NG, jbits,
+                        group_tiles, stream))
+        return FGATTN_E_DEVICE;
+    } else if (small) {
+      if (!greedy_small(bits, dist, (int)lo.slices, QB, Gw, QB, R, NG, jbits, group_tiles, stream)) return FGATTN_E_DEVICE;
+    } else {
+      hipLaunchKernelGGL(distance_kernel<uint32_t>, dim3((unsigned)((QB + 63) / 64), (unsigned)((QB + 63) / 64), (unsigned)lo.slices),
+                         dim3(kThreads), 0, stream, bits, QB, Gw, QB, dist);
+      if (!launched()) return FGATTN_E_DEVICE;
       hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)lo.slices), dim3(kThreads), (size_t)QB, stream, dist, QB, R, NG,
                          group_tiles);
+    }
   }
   if (!launched()) return FGATTN_E_DEVICE;
   hipLaunchKernelGGL(union_kernel, dim3((unsigned)lo.groups), dim3(kThreads), 0, stream, bits, group_tiles, QB, Gw, R, NG,

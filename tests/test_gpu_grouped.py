@@ -202,3 +202,31 @@ def test_grouping_seeded_random_shapes(oracle_mod, M, N, d, L, H, B, kind, densi
         assert np.array_equal(a, b), name
     out = run_grouped(prob, *got)
     check_against_oracle(oracle_mod, prob, out, what=w.name + " " + mode)
+
+
+# tiles per slice on both sides of what a thread keeps in registers (one, two and four keys of 1024 threads, then none), for
+# every group size; few key blocks, so that most distances are equal to others and the order of the tiles decides; a last
+# group that is full, short and of one tile; blocks of the distance matrix on, off and past the diagonal
+@pytest.mark.parametrize("M,QB,G", [(16, 1023, 40), (16, 1024, 6), (16, 1025, 40), (16, 2048, 33), (16, 2049, 6), (16, 4096, 20),
+                                    (16, 4097, 20), (32, 1021, 6), (32, 1500, 70), (32, 2100, 6), (64, 130, 6), (64, 1030, 70),
+                                    (64, 2051, 6), (128, 65, 6), (128, 1100, 40)])
+def test_greedy_grouping_at_the_edges_of_its_variants(M, QB, G):
+    L = QB * M - 3
+    w = W.Workload("grouping-edges", H=2, L=L, d=64, M=M, N=(L + G - 1) // G, kind=W.MASK_RANDOM, density=0.4, seed=6800 + QB)
+    prob = Problem(w)
+    say("device grouping %d-row tiles: %d tiles, %d key blocks" % (M, w.QB, w.G))
+    got = gpu_grouping(prob, "xor")
+    ref = GR.grouped_mask(prob.indptr, prob.indices, w.H, w.QB, w.G, 128 // M, "xor")
+    for a, b, name in zip(got, ref, ("group_tiles", "union_indptr", "union_indices", "union_members")):
+        assert np.array_equal(a, b), name
+
+
+def test_greedy_grouping_with_distances_past_16_bits():
+    # 66048 key blocks: distances stay in 32 bits, with eight tiles per thread
+    w = W.Workload("grouping-wide", H=1, L=66048, d=64, M=64, N=1, kind=W.MASK_RANDOM, density=0.01, seed=6900)
+    prob = Problem(w)
+    say("device grouping: %d tiles, %d key blocks" % (w.QB, w.G))
+    got = gpu_grouping(prob, "xor")
+    ref = GR.grouped_mask(prob.indptr, prob.indices, w.H, w.QB, w.G, 2, "xor")
+    for a, b, name in zip(got, ref, ("group_tiles", "union_indptr", "union_indices", "union_members")):
+        assert np.array_equal(a, b), name
