@@ -775,7 +775,7 @@ __global__ void __launch_bounds__(THREADS, WAVES_PER_SIMD)
 select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_rows, int unit0, int YT, int QB, int G, int Gs,
                     float top_p, unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
   constexpr int BINS = kRowBins, CAP = THREADS;   // one ranked member per thread
-  static_assert(CAP <= BINS && BINS == 4 * 256 && MAXROW % 1024 == 0 && (sizeof(ID) > 2 || MAXROW <= 65536), "layout");
+  static_assert(IDCAP % THREADS == 0 && CAP <= BINS && BINS == 4 * 256 && MAXROW % 1024 == 0 && (sizeof(ID) > 2 || MAXROW <= 65536), "layout");
   __shared__ CodesShared<THREADS, MAXROW, IDCAP, ID> shm;
   auto& sh = shm.sel;
   unsigned long long* const keys = sh.mass;
@@ -909,20 +909,34 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
     auto keep_bit = [&](unsigned id) { atomicOr(&shm.codes[(id >> 5) * 8], 1u << (id & 31)); };
     // members: above the crossing bin, in it (their rank keys are collected), or below it
     unsigned more = 0;
-    if (n_ids <= (unsigned)IDCAP)
+    if (n_ids <= (unsigned)IDCAP) {
+      // (four scores of a thread in flight at once: one after the other, a row of 118800 with its 2000 members waits for
+      // device memory three times)
+      constexpr int PER = 4;
+      static_assert(IDCAP % (PER * THREADS) == 0, "whole steps");
 #pragma unroll 1
-      for (unsigned i = tid; i < n_ids; i += THREADS) {
-        const unsigned id = (unsigned)shm.ids[i];
-        const float v = s[id];
-        const unsigned b = value_bin(v);
-        if (b < fine) {
-          keep_bit(id);
-          more++;
-        } else if (b == fine) {
-          const unsigned pos = atomicAdd(&sh.bin_cnt, 1u);
-          if (pos < (unsigned)CAP) keys[pos] = rank_key(v, (int)id);   // (the histogram is not needed any more)
+      for (unsigned base = 0; base < n_ids; base += PER * THREADS) {
+        unsigned id[PER];
+        float v[PER];
+#pragma unroll
+        for (int e = 0; e < PER; e++) id[e] = min((unsigned)shm.ids[base + e * THREADS + tid], (unsigned)(G - 1));
+#pragma unroll
+        for (int e = 0; e < PER; e++)
+          if (base + e * THREADS < n_ids) v[e] = s[id[e]];   // (the same in all threads)
+#pragma unroll
+        for (int e = 0; e < PER; e++) {
+          if (base + e * THREADS + tid >= n_ids) continue;
+          const unsigned b = value_bin(v[e]);
+          if (b < fine) {
+            keep_bit(id[e]);
+            more++;
+          } else if (b == fine) {
+            const unsigned pos = atomicAdd(&sh.bin_cnt, 1u);
+            if (pos < (unsigned)CAP) keys[pos] = rank_key(v[e], (int)id[e]);   // (the histogram is not needed any more)
+          }
         }
       }
+    }
     const unsigned n_above = n_codes + (unsigned)block_sum_u64(sh, (unsigned long long)more);
     const unsigned n = sh.bin_cnt;
     if (n_ids > (unsigned)IDCAP || n > (unsigned)CAP) {
@@ -930,26 +944,39 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
       if (tid == 0) count[row] = 0u;
       continue;
     }
-    // rank by counting (the keys are distinct), keys ordered by rank, crossing by a prefix of their masses over the threads
+    // rank by counting (the keys are distinct), keys ordered by rank, crossing by a prefix of their masses over the threads.
+    // As many threads as there are share the counting for a key, each over its part of the keys (with that and the members'
+    // scores fetched together, rows of 118800 take 371 us per GiB of scores, 378 before).
     const unsigned long long key = tid < (int)n ? keys[tid] : 0ull;
+    unsigned* const ranks = reinterpret_cast<unsigned*>(shm.ids);   // (the ids are not needed any more)
+    static_assert(sizeof(shm.ids) >= THREADS * sizeof(unsigned), "a rank per thread");
     if (tid >= (int)n && tid < (((int)n + 7) & ~7)) keys[tid] = 0ull;   // (zeros up to a multiple of eight: below every key)
+    ranks[tid] = 0u;
     __syncthreads();
-    int rank = 0;
-    if (tid < (int)n)
+    {
+      const unsigned slots = max((n + 63u) & ~63u, 64u), parts = (unsigned)THREADS / slots;
+      const unsigned part = (unsigned)tid / slots, slot = (unsigned)tid - part * slots;
+      const unsigned per = (((n + 7u) >> 3) + parts - 1u) / parts * 8u;
+      if (part < parts && slot < n) {
+        const unsigned long long ranked = keys[slot];
+        unsigned rank = 0;
 #pragma unroll 1
-      for (unsigned j = 0; j < n; j += 8) {   // eight keys per step: four 16-byte reads in flight
-        unsigned long long o[8];
+        for (unsigned j = part * per; j < min(part * per + per, n); j += 8) {   // eight keys per step: four 16-byte reads in flight
+          unsigned long long o[8];
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(&keys[j + e]);
-          o[e] = two.x;
-          o[e + 1] = two.y;
+          for (int e = 0; e < 8; e += 2) {
+            const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(&keys[j + e]);
+            o[e] = two.x;
+            o[e + 1] = two.y;
+          }
+#pragma unroll
+          for (int e = 0; e < 8; e++) rank += o[e] > ranked ? 1u : 0u;
         }
-#pragma unroll
-        for (int e = 0; e < 8; e++) rank += o[e] > key ? 1 : 0;
+        if (rank != 0u) atomicAdd(&ranks[slot], rank);
       }
+    }
     __syncthreads();   // all keys read: the ordered ones go back
-    if (tid < (int)n) keys[rank] = key;
+    if (tid < (int)n) keys[ranks[tid]] = key;
     __syncthreads();
     {
       const unsigned long long mine = tid < (int)n ? keys[tid] : 0ull;
@@ -1002,7 +1029,7 @@ __global__ void __launch_bounds__(THREADS) select_left_kernel(const float* score
 // over waits for the next ids.  No barrier and no loop over bits.  (Stores straight from the lanes whose bit is set are no
 // faster than a workgroup per row that ran over the set bits of a word per thread, 87 us against 83 below: an instruction
 // with every third lane active makes as many requests as a full one.)  12 heads x 512 rows of 32760 83 -> 74 us,
-// 24 x 929 rows of 118800 1690 -> 1470 us (5.6 GB of ids).
+// 24 x 929 rows of 118800 1690 -> 1470-1560 us (5.6 GB of ids).
 constexpr int kEmitBatch = 32;   // words of a row staged between two flushes
 __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bits, int Gw, int seg_words, int segs, int64_t units,
                                                         const int64_t* indptr, int32_t* indices, int64_t capacity) {
