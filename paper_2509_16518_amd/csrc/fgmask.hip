@@ -67,41 +67,53 @@ __device__ __forceinline__ uint16_t mean_bf16(float acc, int n) {
   return (uint16_t)(u >> 16);
 }
 
-__global__ void __launch_bounds__(64) pool_kernel(const uint16_t* x, int64_t sb, int64_t sh, int64_t sl, int H, int L,
-                                                   int d, int rows_per_block, int nblocks, uint16_t* pooled,
-                                                   unsigned* range_init) {
+struct PoolTensor {
+  const uint16_t* x;
+  int64_t sb, sh, sl;   // strides in elements
+  int rows_per_block, nblocks;
+  uint16_t* pooled;
+};
+
+// One wave per block, of Q first (blockIdx.x < q.nblocks), then of K.  Bound: latency for short inputs, where Q and K share a
+// launch (12 heads x 9360 rows in blocks of 64: 2 x 6.2 us and the gap between -> 9.9), bytes for long ones (24 heads x
+// 118800 rows of Q in blocks of 128: 182 us, 4 TB/s).  Sixteen rows are in flight.
+__global__ void __launch_bounds__(64) pool_kernel(PoolTensor q, PoolTensor k, int H, int L, int d, unsigned* range_init) {
   const int c = threadIdx.x * 2;
-  const int blk = blockIdx.x;
+  const bool of_k = (int)blockIdx.x >= q.nblocks;
+  const PoolTensor& t = of_k ? k : q;
+  const int blk = (int)blockIdx.x - (of_k ? q.nblocks : 0);
   const int slice = blockIdx.y;
   if (c >= d) return;
-  // the Q pass also resets the (max, min) pair of the score row this query block will own
-  if (range_init != nullptr && c == 0) {
-    range_init[2 * ((int64_t)slice * nblocks + blk)] = 0u;
-    range_init[2 * ((int64_t)slice * nblocks + blk) + 1] = 0xFFFFFFFFu;
+  // the Q part also resets the (max, min) pair of the score row this query block will own
+  if (!of_k && c == 0) {
+    range_init[2 * ((int64_t)slice * q.nblocks + blk)] = 0u;
+    range_init[2 * ((int64_t)slice * q.nblocks + blk) + 1] = 0xFFFFFFFFu;
   }
   const int b = slice / H, h = slice - b * H;
-  const int r0 = blk * rows_per_block;
-  const int r1 = min(r0 + rows_per_block, L);
-  const uint16_t* p = x + b * sb + h * sh + (int64_t)r0 * sl + c;   // 4-byte aligned: strides are multiples of 8 elements
+  const int r0 = blk * t.rows_per_block;
+  const int r1 = min(r0 + t.rows_per_block, L);
+  const int64_t sl = t.sl;
+  const uint16_t* p = t.x + b * t.sb + h * t.sh + (int64_t)r0 * sl + c;   // 4-byte aligned: strides are multiples of 8 elements
   float acc0 = 0.0f, acc1 = 0.0f;
   int r = r0;
-  for (; r + 8 <= r1; r += 8, p += 8 * sl) {
-    unsigned w[8];
+  auto batch = [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    for (; r + N <= r1; r += N, p += N * sl) {
+      unsigned w[N];
 #pragma unroll
-    for (int i = 0; i < 8; i++) w[i] = *reinterpret_cast<const unsigned*>(p + i * sl);
+      for (int i = 0; i < N; i++) w[i] = *reinterpret_cast<const unsigned*>(p + i * sl);
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-      acc0 = acc0 + __uint_as_float(w[i] << 16);
-      acc1 = acc1 + __uint_as_float(w[i] & 0xFFFF0000u);
+      for (int i = 0; i < N; i++) {
+        acc0 = acc0 + __uint_as_float(w[i] << 16);
+        acc1 = acc1 + __uint_as_float(w[i] & 0xFFFF0000u);
+      }
     }
-  }
-  for (; r < r1; r++, p += sl) {
-    const unsigned w = *reinterpret_cast<const unsigned*>(p);
-    acc0 = acc0 + __uint_as_float(w << 16);
-    acc1 = acc1 + __uint_as_float(w & 0xFFFF0000u);
-  }
+  };
+  batch(std::integral_constant<int, 16>());
+  batch(std::integral_constant<int, 8>());
+  batch(std::integral_constant<int, 1>());
   const unsigned out = (unsigned)mean_bf16(acc0, r1 - r0) | ((unsigned)mean_bf16(acc1, r1 - r0) << 16);
-  *reinterpret_cast<unsigned*>(pooled + ((int64_t)slice * nblocks + blk) * d + c) = out;
+  *reinterpret_cast<unsigned*>(t.pooled + ((int64_t)slice * t.nblocks + blk) * d + c) = out;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1203,22 +1215,19 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
   const uint16_t* qx = static_cast<const uint16_t*>(q);
   const uint16_t* kx = static_cast<const uint16_t*>(k);
 
-  hipLaunchKernelGGL(pool_kernel, dim3((unsigned)lo.QB, (unsigned)lo.slices), dim3(64), 0, stream, qx, p->q_stride_b,
-                     p->q_stride_h, p->q_stride_l, p->H, p->L, p->d, p->M, (int)lo.QB, qp, range);
-  if (!launched()) return FGATTN_E_DEVICE;
-  const uint16_t* kmat = kx;
-  int64_t k_slice_stride = 0, k_row_stride = p->k_stride_l;
-  bool k_in_place = p->N == 1 && p->B == 1;   // a block of one row is the row itself; slices are then heads
+  const PoolTensor pool_q = {qx, p->q_stride_b, p->q_stride_h, p->q_stride_l, p->M, (int)lo.QB, qp};
+  const PoolTensor pool_k = {kx, p->k_stride_b, p->k_stride_h, p->k_stride_l, p->N, (int)lo.G, kp};
+  const uint16_t* kmat = kp;
+  int64_t k_slice_stride = lo.G * p->d, k_row_stride = p->d;
+  const bool k_in_place = p->N == 1 && p->B == 1;   // a block of one row is the row itself; slices are then heads
   if (k_in_place) {
+    kmat = kx;
     k_slice_stride = p->k_stride_h;
-  } else {
-    hipLaunchKernelGGL(pool_kernel, dim3((unsigned)lo.G, (unsigned)lo.slices), dim3(64), 0, stream, kx, p->k_stride_b,
-                       p->k_stride_h, p->k_stride_l, p->H, p->L, p->d, p->N, (int)lo.G, kp, static_cast<unsigned*>(nullptr));
-    if (!launched()) return FGATTN_E_DEVICE;
-    kmat = kp;
-    k_slice_stride = lo.G * p->d;
-    k_row_stride = p->d;
+    k_row_stride = p->k_stride_l;
   }
+  hipLaunchKernelGGL(pool_kernel, dim3((unsigned)(lo.QB + (k_in_place ? 0 : lo.G)), (unsigned)lo.slices), dim3(64), 0, stream,
+                     pool_q, pool_k, p->H, p->L, p->d, range);
+  if (!launched()) return FGATTN_E_DEVICE;
   uint32_t* keep_bits = reinterpret_cast<uint32_t*>(ws + lo.bits_off);
   const unsigned gx = (unsigned)((lo.G + kTilesPerGroup * 32 - 1) / (kTilesPerGroup * 32));
   for (int64_t unit0 = 0; unit0 < lo.units; unit0 += lo.chunk_units) {
