@@ -260,6 +260,7 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   // while masked keys (score -inf) get exactly 0 instead of exp2(-inf * 0) = NaN
   a.c_log2 = sabs * 1.44269504088896340736f;
   if (!(a.c_log2 > 1e-30f)) a.c_log2 = 1e-30f;
+  a.lazy_raw = kLazyLog2 / a.c_log2;
   a.scale_abs = sabs;
   a.q_sign = p->scale < 0.0f ? 0x80008000u : 0u;
   auto launch = [&](int* grid_only) {

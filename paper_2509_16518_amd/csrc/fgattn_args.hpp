@@ -12,6 +12,10 @@ enum { SCHED_QUEUE = 0, SCHED_STATIC = 1, SCHED_DIRECT = 2 };
 // Word of ctrl[64] that counts the items popped from the queue of XCD q: two 128-byte lines, four queues on each.
 __host__ __device__ constexpr int queue_word(int q) { return 16 + 4 * (q & 3) + 16 * (q >> 2); }
 
+// How far (log2 units) the exponent base may lag behind the running max: no exponential exceeds 2^8, so O stays below
+// 2^8 * (keys of the list) * max|V|, and a result does not depend on anything but the list's own running maxima.
+constexpr float kLazyLog2 = 8.0f;
+
 struct FwdArgs {
   const uint16_t* q;
   const uint16_t* k;
@@ -27,6 +31,7 @@ struct FwdArgs {
   // position in the list -> (group, key of the group) without divisions: NT = keys per LDS tile of the launched variant
   int32_t nt_div_n, nt_mod_n;
   float c_log2;      // |scale| * log2(e): exp(scale*s) == exp2(c_log2 * s')
+  float lazy_raw;    // how far a running max may pass the exponent base (raw score units) before the base moves
   float scale_abs;   // |scale|
   uint32_t q_sign;   // 0x80008000 if scale < 0 (the sign is moved onto Q, exactly), else 0
   // grouped query tiles (Sec. 4.2): M is then the group's rows (128), QB the groups per slice, indptr / indices the

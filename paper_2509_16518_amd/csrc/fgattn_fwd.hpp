@@ -102,13 +102,11 @@ __device__ __forceinline__ float lane_pair_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-// A lane's sum of exponentials may grow to 2^32 before its exponent base moves.  P and O are floating point, so a base far
-// below the running max costs no accuracy, and sums below 2^32 keep O as far from overflow as a list of 2^24 keys with
-// the base at the max does.  The key loop therefore needs no row max: the sum it forms anyway tells when to look for one.
-// (11 of 83 vector instructions per tile and wave, and the only part that had to wait for all of S(t+1): 1-2% at 64 and
-// 128 query rows, where at these sizes the power limit sets the clock; the rest of the time is in the gathers' places.)
-constexpr float kSumLimit = 4294967296.0f;
+// maximum over the same two lanes
+__device__ __forceinline__ float lane_pair_max(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
@@ -170,13 +168,11 @@ __device__ __forceinline__ void mask_drop(f32x16& S, unsigned drop) {
 #pragma unroll
     for (int e = 0; e < 4; e++) S[4 * r4 + e] = (drop >> (8 * r4 + e)) & 1 ? -INFINITY : S[4 * r4 + e];
 }
-// largest score of this lane's query (lanes l and l^32 hold the two halves of one query's key set) and `m_run`
-__device__ __forceinline__ float row_max(const f32x16& S, float m_run) {
+// largest score of this lane's query
+__device__ __forceinline__ float row_max(const f32x16& S) {
   const float t0 = max3(S[0], S[1], S[2]), t1 = max3(S[3], S[4], S[5]), t2 = max3(S[6], S[7], S[8]);
   const float t3 = max3(S[9], S[10], S[11]), t4 = max3(S[12], S[13], S[14]);
-  const float mx = fmaxf(max3(t0, t1, t2), max3(t3, t4, S[15]));
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-  return max3(__uint_as_float(r[0]), __uint_as_float(r[1]), m_run);
+  return lane_pair_max(fmaxf(max3(t0, t1, t2), max3(t3, t4, S[15])));
 }
 
 // NMODE selects how a compacted key position maps to a key row:
@@ -590,12 +586,11 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     i32x4 PA[2], PB[2];        // P^T (packed bf16 pairs) of even / odd tiles: B operands of the second MFMA
     float m_run = -INFINITY;   // exponent base (raw score units) of this lane's query: a score maximum it has seen
     float l_run = 0.0f, l_run2 = 0.0f;   // this lane's partial sum of exponentials, in two chains (even / odd scores)
+    float m_pend = -INFINITY;  // running max of this lane's query, over the tiles whose exponentials have been formed
     float neg_mc = 0.0f;       // -m_run * c_log2, 0 while m_run is -inf: the additive term of the exponent
-    bool no_base = false;      // wave-uniform: some lane that counts has met no valid key yet, hence has no base
     auto set_base = [&](float m) {
       m_run = m;
       neg_mc = m == -INFINITY ? 0.0f : -m * a.c_log2;
-      no_base = __builtin_amdgcn_ballot_w64(m == -INFINITY && my_row_valid) != 0;
     };
 
     constexpr int NE = C::SSTEPS;          // MFMA slots per phase: PV slot e = (d block e/2, key half e%2); QK slot e = d chunk e
@@ -619,13 +614,13 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     };
     // Phase X.  O^T += V^T P^T with V in slot `vrd` of the V ring and, with QK, Sn = K Q^T with K in slot `krd` of the K
     // ring: one MFMA of each per slot.  With EXP, every slot also takes its share of the exponentials of the previous
-    // tile's scores So: P = exp2(c*(So - m)) packed to bf16 into Pout, and the row sum; they issue while the two matrix
-    // instructions just issued execute.  With GATHER, the first slots then issue this iteration's gathers: V rows
-    // (keys in vk) -> V slot `vwr`, then K rows (keys in kk) -> K slot `kwr`, both released by
+    // tile's scores So: P = exp2(c*(So - m)) packed to bf16 into Pout, the row sum, and this lane's part m_lane of the row
+    // max; they issue while the two matrix instructions just issued execute.  With GATHER, the first slots then issue this
+    // iteration's gathers: V rows (keys in vk) -> V slot `vwr`, then K rows (keys in kk) -> K slot `kwr`, both released by
     // the previous iteration.  The gather holds the wave; the matrix instructions execute underneath it.
     auto x_phase = [&](auto vrd_c, auto krd_c, auto vwr_c, auto kwr_c, const i32x4 (&Pin)[2], auto with_gather,
                        auto with_qk, f32x16& Sn, auto with_exp, const f32x16& So, i32x4 (&Pout)[2], float& l_new,
-                       float& l_new2) {
+                       float& l_new2, float& m_lane) {
       constexpr int vrd = decltype(vrd_c)::value, krd = decltype(krd_c)::value;
       constexpr int vwr = decltype(vwr_c)::value, kwr = decltype(kwr_c)::value;
       constexpr bool GATHER = decltype(with_gather)::value;
@@ -668,6 +663,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
             const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(So[r + 1], a.c_log2, neg_mc));
             l_new = (r == 0 ? l_run : l_new) + p0;   // (l_run stays, for the case that the base has to move: new_base)
             l_new2 = (r == 0 ? l_run2 : l_new2) + p1;
+            m_lane = max3(r == 0 ? m_pend : m_lane, So[r], So[r + 1]);
             f32x2 pp = {p0, p1};
             int pk = __builtin_bit_cast(int, __builtin_convertvector(pp, bf16x2));
             asm volatile("" : "+v"(pk));   // keeps the compiler from sinking the conversion out of the slot
@@ -728,12 +724,12 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       else if (__builtin_expect(masked, 0))
         mask_drop(Sn, dropped(Tm, par));
     };
-    // The exponent base of every lane moves to the running max including the scores So, whose exponentials Pout and sums
-    // were formed with the old base and are formed again; O does not hold that tile yet.
+    // The exponent base of every lane moves to the running max, which includes the scores So: their exponentials Pout and
+    // sums were formed with the old base (some may be +inf) and are formed again; O does not hold that tile yet.
     auto new_base = [&](const f32x16& So, i32x4 (&Pout)[2], float& l_new, float& l_new2) {
-      const float m_new = row_max(So, m_run);
-      const float alpha = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_new) * a.c_log2);
-      set_base(m_new);
+#pragma clang fp contract(off)   // (l * alpha is rounded before the tile's sums are added to it)
+      const float alpha = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_pend) * a.c_log2);
+      set_base(m_pend);
       l_new = l_run * alpha;
       l_new2 = l_run2 * alpha;
 #pragma unroll
@@ -764,7 +760,10 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     // Iteration t, J = t mod U (a constant, so every LDS slot and register set is an immediate):
     //   X: O += V(t-1)^T P(t-1)^T  ||  S(t+1) = K(t+1) Q^T  ||  P(t) = exp(S(t) - m)  ||  gathers V(t+VS-2) and K(t+KS)
     //      into the slots that iteration t-1 read last
-    // then, rarely: the exponent base moves, S(t+1) is masked
+    // then, rarely: the exponent base moves, S(t+1) is masked.  The row max of S(t) belongs in X too: all of S(t) is there, so
+    // its maxima issue under the matrix instructions.  After X, over S(t+1), they wait for the last of its products: 12
+    // heads x 32760 tokens at 32x32 3.66 ms in X, 3.82 after it, at 64x1 2.11 and 2.13, 16 x 2635 at 32x8 24.4 and 25.1 us.
+    // (Formed with the base that held until then, a tile's exponentials are formed again when it moves.)
     // A gathered tile has at least the barrier's wait to arrive before it is published, and whole
     // iterations more where the rings are deeper than two tiles.
     auto iteration = [&](auto jc, int t) {
@@ -789,15 +788,16 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       // (measured: 1% faster at 64 and 128 rows, 3% with grouped tiles, 6% at 16x1; 4% slower at 32x32 in single-wave
       // workgroups, 3% for the dense kernel at 128 rows, 12% at d = 64: not used there)
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(3);
-      float l_new = l_run, l_new2 = l_run2;
+      float l_new = l_run, l_new2 = l_run2, m_lane = m_pend;
       x_phase(std::integral_constant<int, (J + U - 1) % VS>(), std::integral_constant<int, (J + 1) % KS>(),
               std::integral_constant<int, (J + U - 2) % VS>(), std::integral_constant<int, J % KS>(), Pin, yes(), yes(), Sn,
-              yes(), So, Pout, l_new, l_new2);
+              yes(), So, Pout, l_new, l_new2, m_lane);
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(1);
       if constexpr (PART != PART_GATHER) {
-        // (the same in all lanes; a sum past float overflows to +inf and is caught here too)
-        const bool over = __builtin_amdgcn_ballot_w64(fmaxf(l_new, l_new2) >= kSumLimit) != 0;
-        if (__builtin_expect(over || no_base, 0)) new_base(So, Pout, l_new, l_new2);
+        m_pend = lane_pair_max(m_lane);
+        // (the same in all lanes; the first valid key of a lane also moves it: m_run = -inf until then)
+        const bool moves = __builtin_amdgcn_ballot_w64(m_pend > m_run + a.lazy_raw) != 0;
+        if (__builtin_expect(moves, 0)) new_base(So, Pout, l_new, l_new2);
       }
       l_run = l_new;
       l_run2 = l_new2;
@@ -853,7 +853,8 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       __syncthreads();
       // S(0) from K slot 0
       y_phase(std::integral_constant<int, 0>(), 0, 0, SA, yes());
-      set_base(row_max(SA, -INFINITY));   // O = 0 and l = 0 so far: the first exponent base needs no rescale
+      m_pend = row_max(SA);
+      set_base(m_pend);   // O = 0 and l = 0 so far: the first exponent base needs no rescale
       int t = 0;
       for (;;) {
 #define FG_STEP(J)                                             \
@@ -876,7 +877,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       if constexpr (UD > J) {                                                                                          \
         if (jd == J)                                                                                                   \
           x_phase(std::integral_constant<int, J % VS>(), std::integral_constant<int, 0>(), std::integral_constant<int, 0>(), \
-                  std::integral_constant<int, 0>(), (J & 1) ? PB : PA, no(), no(), SA, no(), SA, PA, l_run, l_run2);                 \
+                  std::integral_constant<int, 0>(), (J & 1) ? PB : PA, no(), no(), SA, no(), SA, PA, l_run, l_run2, m_pend);         \
       }
       FG_DRAIN(0) FG_DRAIN(1) FG_DRAIN(2) FG_DRAIN(3) FG_DRAIN(4) FG_DRAIN(5) FG_DRAIN(6) FG_DRAIN(7)
 #undef FG_DRAIN
