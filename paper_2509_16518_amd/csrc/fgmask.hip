@@ -279,8 +279,8 @@ __device__ __forceinline__ unsigned long long weight_of(float s, float rmax) {
 }
 
 // Visits every score of a row: four consecutive scores per thread and step (16-byte loads; rows start 16-byte
-// aligned and their stride is a multiple of four floats), four steps in flight.
-template <int THREADS, typename Fn>
+// aligned and their stride is a multiple of four floats), DEPTH steps in flight.
+template <int THREADS, int DEPTH, typename Fn>
 __device__ __forceinline__ void for_each_score(const float* s, int G, Fn&& fn) {
   constexpr int STEP = THREADS * 4;
   auto whole = [&](const float4& v, int j4) {
@@ -296,15 +296,14 @@ __device__ __forceinline__ void for_each_score(const float* s, int G, Fn&& fn) {
     if (j4 + 3 < G) fn(v.w, j4 + 3);
   };
   int j4 = threadIdx.x * 4;
-  for (; j4 + 3 * STEP + 3 < G; j4 += 4 * STEP) {
-    const float4 a = *reinterpret_cast<const float4*>(s + j4);
-    const float4 b = *reinterpret_cast<const float4*>(s + j4 + STEP);
-    const float4 c = *reinterpret_cast<const float4*>(s + j4 + 2 * STEP);
-    const float4 d = *reinterpret_cast<const float4*>(s + j4 + 3 * STEP);
-    whole(a, j4);
-    whole(b, j4 + STEP);
-    whole(c, j4 + 2 * STEP);
-    whole(d, j4 + 3 * STEP);
+  if constexpr (DEPTH > 1) {
+    for (; j4 + (DEPTH - 1) * STEP + 3 < G; j4 += DEPTH * STEP) {
+      float4 v[DEPTH];
+#pragma unroll
+      for (int e = 0; e < DEPTH; e++) v[e] = *reinterpret_cast<const float4*>(s + j4 + e * STEP);
+#pragma unroll
+      for (int e = 0; e < DEPTH; e++) whole(v[e], j4 + e * STEP);
+    }
   }
   for (; j4 < G; j4 += STEP) ragged(*reinterpret_cast<const float4*>(s + j4), j4);
 }
@@ -436,17 +435,30 @@ __device__ __forceinline__ void sort_candidates(SH& sh, int n2) {
     }
 }
 
-// Selection for one query block (row of scores `s`, in device memory or in LDS); called by all threads of the
-// workgroup.  Writes the cut, the count and the kept set as one bit per key block (`keep_bits`, Gw words per row).
+// Bin of a score in a histogram over a row's range [rmin, rmax] (collected by the scores kernel); bin 0 holds the largest
+// scores, and inv = BINS / (rmax - rmin), 0 for a row of equal scores.
+template <int BINS>
+__device__ __forceinline__ float bins_per_score(float rmax, float rmin) {
+  const float width = rmax - rmin;
+  return width > 0.0f ? (float)BINS / width : 0.0f;
+}
+template <int BINS>
+__device__ __forceinline__ unsigned value_bin_of(float v, float rmax, float inv) {
+  return min((unsigned)((rmax - v) * inv), (unsigned)(BINS - 1));   // (rmax - v is not negative)
+}
+
+// The part of the selection after the row's histogram (locate_bin<true> has named the crossing bin, the mass above it and the
+// target in sh); called by all threads of the workgroup.  Writes the cut, the count and the kept set as one bit per key block
+// (`keep_bits`, Gw words per row), from a row of scores `s` in device memory.
 //
-// Passes over the row: (1) histogram of mass over the score range; (2) the scores ranked above the crossing bin
-// are counted and written as bits straight away, the bin's members are collected; then the members are ranked,
-// and the bits of those at or above the cut are added.  Only a crossing bin
-// with more members than the sort holds takes further passes, and a last one that writes all bits from the cut.
-template <int THREADS, int BINS, int CAP, typename SH>
-__device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, float rmax, float rmin, int G, float top_p,
-                                           unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
-  const int tid = threadIdx.x, lane = tid & 63;
+// Passes over the row: the scores ranked above the crossing bin are counted and written as bits straight away, the bin's
+// members are collected; then the members are ranked, and the bits of those at or above the cut are added.  Only a crossing
+// bin with more members than the sort holds takes further passes, and a last one that writes all bits from the cut.
+template <int THREADS, int BINS, int CAP, int DEPTH, typename SH>
+__device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, float rmax, float inv, int G, float top_p,
+                                         unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));   // (see select_codes_kernel: nothing here is worth keeping from row to row)
   uint32_t* const bits_row = keep_bits + row * Gw;
   // All bits of the row from the cut (in sh.cut): set where the rank key is not below it.  A thread ranks four
   // consecutive key blocks, eight lanes make a word.
@@ -485,37 +497,24 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
     }
   };
 
-  // [rmin, rmax]: range of the scores (collected by the scores kernel)
-  const float width = rmax - rmin;
-  const float inv = width > 0.0f ? (float)BINS / width : 0.0f;
-  auto value_bin = [&](float v) -> int {   // bin 0 holds the largest scores
-    const int b = (int)((rmax - v) * inv);
-    return b < 0 ? 0 : (b > BINS - 1 ? BINS - 1 : b);
-  };
-
-  // pass 1: mass of the row and its histogram over the score range
-  for (int i = tid; i < BINS; i += THREADS) sh.mass[i] = 0;
-  __syncthreads();
-  for_each_score<THREADS>(s, G, [&](float v, int) { atomicAdd(&sh.mass[value_bin(v)], weight_of(v, rmax)); });
-  __syncthreads();
-  locate_bin<true>(sh, top_p);
+  auto value_bin = [&](float v) -> int { return (int)value_bin_of<BINS>(v, rmax, inv); };
 
   // One pass: counts the scores ranked above the crossing bin and collects the rank keys of its members, as many
   // as fit the sort.  cls(v): -1 above the bin, 0 inside, +1 below or outside what was the bin before.  WITH_BITS:
   // "above" of a thread's four consecutive key blocks is a nibble of the row's bits, eight lanes make a word (every
-  // word of the row is written once).  Four 16-byte loads are in flight.
+  // word of the row is written once).  DEPTH 16-byte loads are in flight.
   auto count_and_collect = [&](auto&& cls, auto with_bits) {
     if (tid == 0) sh.ncand = 0;
     __syncthreads();
     unsigned na = 0;
     constexpr int STEP = THREADS * 4;
     const int last4 = (G - 1) & ~3;
-    for (int base = 0; base < Gw * 32; base += 4 * STEP) {   // (the same trip count for all threads: they vote below)
-      f32x4 v[4];   // (unconditional loads, of the last scores again past the end: under a test they become 4-byte loads)
+    for (int base = 0; base < Gw * 32; base += DEPTH * STEP) {   // (the same trip count for all threads: they vote below)
+      f32x4 v[DEPTH];   // (unconditional loads, of the last scores again past the end: under a test they become 4-byte loads)
 #pragma unroll
-      for (int e = 0; e < 4; e++) v[e] = *reinterpret_cast<const f32x4*>(s + min(base + e * STEP + tid * 4, last4));
+      for (int e = 0; e < DEPTH; e++) v[e] = *reinterpret_cast<const f32x4*>(s + min(base + e * STEP + tid * 4, last4));
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
+      for (int e = 0; e < DEPTH; e++) {
         const int j4 = base + e * STEP + tid * 4;
         const float x[4] = {v[e][0], v[e][1], v[e][2], v[e][3]};
         unsigned nib = 0;
@@ -572,7 +571,7 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
     }
     __syncthreads();
     unsigned lo = 0xFFFFFFFFu, hi = 0u;
-    for_each_score<THREADS>(s, G, [&, bin, by_value, klo, khi](float v, int) {
+    for_each_score<THREADS, DEPTH>(s, G, [&, bin, by_value, klo, khi](float v, int) {
       const unsigned o = ordered_bits(v);
       const bool in = by_value ? (value_bin(v) == (int)bin) : (o >= klo && o <= khi);
       if (in) {
@@ -590,7 +589,7 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
     const unsigned long long R = (unsigned long long)(khi - klo) + 1ull;
     for (int i = tid; i < BINS; i += THREADS) sh.mass[i] = 0;
     __syncthreads();
-    for_each_score<THREADS>(s, G, [&](float v, int) {
+    for_each_score<THREADS, DEPTH>(s, G, [&](float v, int) {
       const unsigned o = ordered_bits(v);
       if (o >= klo && o <= khi) {
         const int b = (int)(((unsigned long long)(khi - o) * BINS) / R);
@@ -741,6 +740,20 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
   write_all_bits();   // (this path is only reached through the narrowing rounds)
 }
 
+// Selection for one query block; called by all threads of the workgroup.  One pass for the mass of the row and its histogram
+// over the score range, then rank_row.
+template <int THREADS, int BINS, int CAP, int DEPTH, typename SH>
+__device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, float rmax, float rmin, int G, float top_p,
+                                           unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
+  const float inv = bins_per_score<BINS>(rmax, rmin);
+  for (int i = threadIdx.x; i < BINS; i += THREADS) sh.mass[i] = 0;
+  __syncthreads();
+  for_each_score<THREADS, DEPTH>(s, G, [&](float v, int) { atomicAdd(&sh.mass[value_bin_of<BINS>(v, rmax, inv)], weight_of(v, rmax)); });
+  __syncthreads();
+  locate_bin<true>(sh, top_p);
+  rank_row<THREADS, BINS, CAP, DEPTH>(sh, s, row, rmax, inv, G, top_p, cut, count, keep_bits, Gw);
+}
+
 // Row `local` of a chunk's score buffer that starts at score tile unit0: the (slice, query block) row it holds, or
 // -1 for the unused rows of a slice's last tile.
 __device__ __forceinline__ int64_t chunk_row(int64_t local, int unit0, int YT, int QB) {
@@ -759,7 +772,7 @@ __global__ void __launch_bounds__(THREADS) select_kernel(const float* scores, co
   const int64_t local = blockIdx.x;
   const int64_t row = chunk_row(local, unit0, YT, QB);
   if (row < 0) return;
-  select_row<THREADS, BINS, CAP>(sh, scores + local * Gs, row, from_ordered(range[2 * row]),
+  select_row<THREADS, BINS, CAP, 4>(sh, scores + local * Gs, row, from_ordered(range[2 * row]),
                                         from_ordered(range[2 * row + 1]), G, top_p, cut, count, keep_bits, Gw);
 }
 
@@ -773,12 +786,13 @@ __global__ void __launch_bounds__(THREADS) select_kernel(const float* scores, co
 // workgroups of 512 threads share one for rows of up to 32768 scores instead of two, and let rows of up to 131072 in at all
 // (before, they were read from memory in every pass).  6144 rows of 32760: 359 -> 256 us; 22296 rows of 118800:
 // 5.6 -> 4.5 ms.  (The histogram's atomics are not what binds: without seven eighths of them it is no faster.)  Too many members
-// for LDS are rare; such a row is left, with a count of zero, to select_left_kernel, which starts over from device memory
-// (in this kernel that path would cost the usual one its registers).
+// for LDS are rare (many equal scores): such a row goes on from its histogram as in select_kernel, after the other rows.  (A
+// launch of its own, which started those rows over, cost every call 2 us, 33.8 -> 31.6 us for 16 rows of 1000; 1858 rows of
+// 118800 equal scores 3.02 -> 2.42 ms, 3072 rows of 32760 1.29 -> 0.91.)
 template <int THREADS, int MAXROW, int IDCAP, typename ID>
 struct alignas(16) CodesShared {
-  SelShared<THREADS, kRowBins, 2> sel;   // (the ranked keys reuse the histogram's memory)
-  alignas(16) ID ids[IDCAP];
+  static constexpr int CAND = IDCAP * sizeof(ID) / 8;
+  SelShared<THREADS, kRowBins, CAND> sel;   // (the ranked keys reuse the histogram's memory, the members' ids lie in sel.cand)
   alignas(16) uint32_t codes[MAXROW / 4];
 };
 
@@ -791,6 +805,8 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
   __shared__ CodesShared<THREADS, MAXROW, IDCAP, ID> shm;
   auto& sh = shm.sel;
   unsigned long long* const keys = sh.mass;
+  ID* const ids = reinterpret_cast<ID*>(sh.cand);
+  bool left = false;   // some row had too many members
   for (int64_t local = blockIdx.x; local < chunk_rows; local += gridDim.x) {
     const int64_t row = chunk_row(local, unit0, YT, QB);
     if (row < 0) continue;   // (the same for all threads)
@@ -799,10 +815,8 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
     const float* s = scores + local * Gs;
     const float rmax = from_ordered(range[2 * row]), rmin = from_ordered(range[2 * row + 1]);
     uint32_t* const bits_row = keep_bits + row * Gw;
-    const float width = rmax - rmin;
-    const float inv = width > 0.0f ? (float)BINS / width : 0.0f;
-    // bin 0 holds the largest scores (rmax - v is not negative)
-    auto value_bin = [&](float v) -> unsigned { return min((unsigned)((rmax - v) * inv), (unsigned)(BINS - 1)); };
+    const float inv = bins_per_score<BINS>(rmax, rmin);
+    auto value_bin = [&](float v) -> unsigned { return value_bin_of<BINS>(v, rmax, inv); };
     __syncthreads();   // the row before this one is done with the shared state
     for (int i = tid; i < BINS; i += THREADS) sh.mass[i] = 0;
     if (tid == 0) {
@@ -909,7 +923,7 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
           pos += (unsigned)__builtin_amdgcn_readfirstlane((int)first);
 #pragma unroll 1
           while (member != 0u) {
-            if (pos < (unsigned)IDCAP) shm.ids[pos] = (ID)(j16 + __ffs(member) - 1);
+            if (pos < (unsigned)IDCAP) ids[pos] = (ID)(j16 + __ffs(member) - 1);
             pos++;
             member &= member - 1;
           }
@@ -931,7 +945,7 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
         unsigned id[PER];
         float v[PER];
 #pragma unroll
-        for (int e = 0; e < PER; e++) id[e] = min((unsigned)shm.ids[base + e * THREADS + tid], (unsigned)(G - 1));
+        for (int e = 0; e < PER; e++) id[e] = min((unsigned)ids[base + e * THREADS + tid], (unsigned)(G - 1));
 #pragma unroll
         for (int e = 0; e < PER; e++)
           if (base + e * THREADS < n_ids) v[e] = s[id[e]];   // (the same in all threads)
@@ -952,16 +966,25 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
     const unsigned n_above = n_codes + (unsigned)block_sum_u64(sh, (unsigned long long)more);
     const unsigned n = sh.bin_cnt;
     if (n_ids > (unsigned)IDCAP || n > (unsigned)CAP) {
-      // too many members: left to select_left_kernel (a row that is done keeps at least one key block)
-      if (tid == 0) count[row] = 0u;
+      // too many members: the row goes on from its histogram below.  (A row that is done keeps at least one key block; the
+      // state waits in the row's own bits, eight words at least here: a row that short has no more members than fit.)
+      left = true;
+      if (tid == 0) {
+        count[row] = 0u;
+        bits_row[0] = sh.bin;
+        bits_row[1] = (uint32_t)sh.mass_above;
+        bits_row[2] = (uint32_t)(sh.mass_above >> 32);
+        bits_row[3] = (uint32_t)sh.target;
+        bits_row[4] = (uint32_t)(sh.target >> 32);
+      }
       continue;
     }
     // rank by counting (the keys are distinct), keys ordered by rank, crossing by a prefix of their masses over the threads.
     // As many threads as there are share the counting for a key, each over its part of the keys (with that and the members'
     // scores fetched together, rows of 118800 take 371 us per GiB of scores, 378 before).
     const unsigned long long key = tid < (int)n ? keys[tid] : 0ull;
-    unsigned* const ranks = reinterpret_cast<unsigned*>(shm.ids);   // (the ids are not needed any more)
-    static_assert(sizeof(shm.ids) >= THREADS * sizeof(unsigned), "a rank per thread");
+    unsigned* const ranks = reinterpret_cast<unsigned*>(sh.cand);   // (the ids are not needed any more)
+    static_assert(sizeof(sh.cand) >= THREADS * sizeof(unsigned), "a rank per thread");
     if (tid >= (int)n && tid < (((int)n + 7) & ~7)) keys[tid] = 0ull;   // (zeros up to a multiple of eight: below every key)
     ranks[tid] = 0u;
     __syncthreads();
@@ -1017,20 +1040,24 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
 #pragma unroll 1
     for (int wi = tid; wi < Gw; wi += THREADS) bits_row[wi] = shm.codes[wi * 8];
   }
-}
-
-// The rows that select_codes_kernel left: two per workgroup are looked at.
-template <int THREADS, int BINS, int CAP>
-__global__ void __launch_bounds__(THREADS) select_left_kernel(const float* scores, const unsigned* range, int64_t chunk_rows, int unit0,
-                                                              int YT, int QB, int G, int Gs, float top_p, unsigned long long* cut,
-                                                              unsigned* count, uint32_t* keep_bits, int Gw) {
-  __shared__ SelShared<THREADS, BINS, CAP> sh;
-  for (int64_t local = 2 * (int64_t)blockIdx.x; local < min(2 * (int64_t)blockIdx.x + 2, chunk_rows); local++) {
+  if (!left) return;   // (the same in all threads)
+  // (a loop of its own: inside the one above, this path costs the usual one its registers)
+  for (int64_t local = blockIdx.x; local < chunk_rows; local += gridDim.x) {
     const int64_t row = chunk_row(local, unit0, YT, QB);
-    if (row < 0 || count[row] != 0u) continue;   // (the same for all threads)
-    select_row<THREADS, BINS, CAP>(sh, scores + local * Gs, row, from_ordered(range[2 * row]), from_ordered(range[2 * row + 1]),
-                                   G, top_p, cut, count, keep_bits, Gw);
-    __syncthreads();   // the next row uses the same shared state
+    if (row < 0) continue;
+    __syncthreads();   // the row before this one is done with the shared state; this one's words have been written
+    if (count[row] != 0u) continue;
+    const uint32_t* const state = keep_bits + row * Gw;
+    if (threadIdx.x == 0) {
+      sh.bin = state[0];
+      sh.mass_above = state[1] | ((unsigned long long)state[2] << 32);
+      sh.target = state[3] | ((unsigned long long)state[4] << 32);
+      sh.n_above = 0;
+    }
+    __syncthreads();
+    const float rmax = from_ordered(range[2 * row]), rmin = from_ordered(range[2 * row + 1]);
+    rank_row<THREADS, BINS, CodesShared<THREADS, MAXROW, IDCAP, ID>::CAND, 2>(
+        sh, scores + local * Gs, row, rmax, bins_per_score<BINS>(rmax, rmin), G, top_p, cut, count, keep_bits, Gw);
   }
 }
 
@@ -1245,7 +1272,6 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
       // As many persistent workgroups as LDS or registers let in: three per compute unit with the codes of 32768 scores, two
       // with 65536, one, of 1024 threads, with 131072.  Short rows are all latency: workgroups of 256, seven of them (1764
       // rows of 147 scores 38 us with two workgroups of 512 per unit -> 16).
-      int members = 512;   // that always fit
       auto launch = [&](auto kernel, int threads, int per_cu) {
         const int64_t fit = (int64_t)per_cu * cus;
         hipLaunchKernelGGL(kernel, dim3((unsigned)(chunk_rows < fit ? chunk_rows : fit)), dim3(threads), 0, stream, scores, range,
@@ -1253,19 +1279,13 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
                            (int)lo.Gw);
       };
       if (lo.Gs <= 4096)
-        launch(select_codes_kernel<256, 4096, 2048, uint16_t, 7>, members = 256, 7);
+        launch(select_codes_kernel<256, 4096, 2048, uint16_t, 7>, 256, 7);
       else if (lo.Gs <= 32768)
         launch(select_codes_kernel<512, 32768, 2048, uint16_t, 6>, 512, 3);
       else if (lo.Gs <= 65536)
         launch(select_codes_kernel<512, 65536, 2048, uint16_t, 4>, 512, 2);
       else
         launch(select_codes_kernel<1024, kRowCodesMax, 4096, uint32_t, 4>, 1024, 1);
-      if (lo.G > members) {
-        if (!launched()) return FGATTN_E_DEVICE;
-        hipLaunchKernelGGL((select_left_kernel<kSelThreads, kBins, kCap>), dim3((unsigned)((chunk_rows + 1) / 2)), dim3(kSelThreads),
-                           0, stream, scores, range, chunk_rows, (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p,
-                           cut, count, keep_bits, (int)lo.Gw);
-      }
     } else {
       hipLaunchKernelGGL((select_kernel<kSelThreads, kBins, kCap>), dim3((unsigned)chunk_rows), dim3(kSelThreads), 0, stream,
                          scores, range, (int)unit0, (int)lo.YT, (int)lo.QB, (int)lo.G, (int)lo.Gs, top_p, cut, count, keep_bits,

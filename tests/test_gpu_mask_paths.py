@@ -107,3 +107,19 @@ def test_selection_from_bytes_equals_selection_from_memory(G):
                 res.append((indptr, bit_rows(p, ws, indptr.numel() - 1, G)))
             assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
             assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
+
+
+# Rows with more members than a workgroup keeps come after its other rows: several rows per workgroup of each kernel size, of
+# which none, some or all are such rows (heads of equal keys between heads of ordinary ones)
+@pytest.mark.parametrize("H,L,M", [(20, 2000, 16), (3, 8195, 16), (2, 40000, 64), (2, 70000, 128)])
+def test_overfull_rows_among_others(H, L, M):
+    for full in ([], list(range(0, H, 2)), list(range(H))):
+        res = []
+        for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+            q, k, p, ws, indptr = problem(H, L, 64, M, 1, seed=L + len(full), flags=flags)
+            k[:, full] = 1.0
+            F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
+            indices = torch.zeros(int(indptr[-1]), dtype=torch.int32, device="cuda")
+            F.fgattn_mask_emit(p, indptr, indices, ws)
+            res.append((indptr, indices))
+        assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1]), full
