@@ -50,8 +50,9 @@ enum {
    * contiguous share of the heads; a workgroup whose queue is empty takes from the others). */
   FGATTN_FLAG_STATIC_ASSIGN = 1,  /* ablation "no scheduler": item j goes to workgroup j mod grid, natural order */
   FGATTN_FLAG_FIFO_QUEUE = 2,     /* device-side queue, but natural order (no longest-first ordering) */
-  FGATTN_FLAG_REUSE_PLAN = 4,     /* skip the ordering pre-pass: `workspace` already holds the order built by an
-                                     earlier fgattn_forward/fgattn_plan call for the same mask and params */
+  FGATTN_FLAG_REUSE_PLAN = 4,     /* skip the ordering pre-pass: `workspace` already holds the order left by an
+                                     earlier fgattn_plan or forward call for the same mask and params (any forward call
+                                     without this flag leaves one; where all items start at once, the natural order) */
   /* Read by the fgattn_mask_* calls only (the others ignore it): use the general selection kernel, which reads a
    * row of scores from device memory in every pass, also for rows of at most 131072 key blocks (which otherwise
    * take the kernel that reads the row once).  Same results; pass the same flags to all three mask calls. */

@@ -271,17 +271,20 @@ static int run_forward(const void* q, const void* k, const void* v, const int64_
   // Every item has a workgroup of its own: all start at once, so an order would change nothing and the pre-pass (4 us at
   // 128 items, where the forward kernel itself takes about 10) is left out.  Otherwise the pre-pass also zeroes the
   // queue counters; a launch that reuses its order has them rewound.
+  // Whether items outnumber the workgroups depends on the variant (d = 64, M = 128: more workgroups for lists than for the
+  // dense kernel), so a later call on the same workspace with FGATTN_FLAG_REUSE_PLAN may need the order that this one does
+  // without: a direct launch leaves the natural one, unless the workspace holds one already.
   a.schedule = SCHED_QUEUE;
+  a.leave_order = 0;
   int grid = 0;
   rc = launch(&grid);
   if (rc) return rc;
   if (grid >= a.n_items) {
     a.schedule = SCHED_DIRECT;
+    a.leave_order = (p->flags & FGATTN_FLAG_REUSE_PLAN) ? 0 : 1;
   } else {
     if (p->flags & FGATTN_FLAG_STATIC_ASSIGN) a.schedule = SCHED_STATIC;
-    // (the one-workgroup-per-unit part has a smaller grid than the launch whose order it would reuse, which may have
-    // needed none and written none: it always makes its own)
-    if (!(p->flags & FGATTN_FLAG_REUSE_PLAN) || part == FGATTN_PART_GATHER_ONE_WG) {
+    if (!(p->flags & FGATTN_FLAG_REUSE_PLAN)) {
       rc = run_plan(indptr, p, workspace, stream, QB_items);
       if (rc) return rc;
     } else if (a.schedule == SCHED_QUEUE) {

@@ -24,10 +24,11 @@ struct FwdArgs {
   float* lse;
   const int64_t* indptr;   // null => dense: every key of [0, L) in order
   const int32_t* indices;
-  const int32_t* order;    // work-item ids in processing order
+  int32_t* order;          // work-item ids in processing order
   int32_t* counter;        // int32 ctrl[64]: [queue_word(q)] items popped from the queue of XCD q (zeroed before every launch)
   int64_t q_sb, q_sh, q_sl, k_sb, k_sh, k_sl, v_sb, v_sh, v_sl, o_sb, o_sh, o_sl;  // elements
   int32_t H, L, M, N, QB, n_items, schedule;
+  int32_t leave_order;     // SCHED_DIRECT: leave the natural order in `order` (see run_forward)
   // position in the list -> (group, key of the group) without divisions: NT = keys per LDS tile of the launched variant
   int32_t nt_div_n, nt_mod_n;
   float c_log2;      // |scale| * log2(e): exp(scale*s) == exp2(c_log2 * s')

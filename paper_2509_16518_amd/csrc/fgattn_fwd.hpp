@@ -257,6 +257,11 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int tid = threadIdx.x;
+  // without a pre-pass, what it leaves in the workspace is written here: cleared control words and an order
+  if (a.schedule == SCHED_DIRECT) {
+    if (blockIdx.x == 0 && tid < 64) a.counter[tid] = 0;
+    if (a.leave_order && tid == 0) a.order[blockIdx.x] = blockIdx.x;
+  }
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int rw = wv / C::KW, kw = wv % C::KW;
@@ -323,8 +328,6 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
     return j < queue_begin(q + 1) ? a.order[j] : -1;
   };
   bool home_dry = false;
-  // (without a pre-pass the control words are cleared here, so that they hold the same after every kind of launch)
-  if (a.schedule == SCHED_DIRECT && blockIdx.x == 0 && tid < 64) a.counter[tid] = 0;
   for (;;) {
     // ---------------- fetch the next work item ----------------
     if (tid == 0) {

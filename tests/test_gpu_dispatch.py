@@ -36,6 +36,29 @@ def test_direct_and_queued_assignment(oracle_mod, items, H):
         assert np.array_equal(W.bf16_bits_to_f64(prob.out.view(torch.int16).cpu().numpy().view(np.uint16)), first[0])
 
 
+# A call whose items all have a workgroup of their own needs no order, but one on the same workspace may: at d = 64 the
+# variants for lists run more workgroups than the dense ones.  (The workspace holds zeros at first: an order that nobody
+# wrote would be item 0 over and over, in range.)
+@pytest.mark.parametrize("M,items", [(128, 600), (128, 513), (32, 2100), (16, 2560), (64, 400), (128, 300)])
+def test_direct_call_leaves_an_order(M, items):
+    prob = Problem(sparse_rows(items, M))
+    want = prob.run(dense=True)
+    p, pr = prob.params(), prob.params(flags=F.FLAG_REUSE_PLAN)
+    ws = prob.workspace(p)
+    ws.zero_()
+    order = ws[256:256 + 4 * items].view(torch.int32)
+    F.fgattn_forward(prob.q, prob.k, prob.v, prob.d_indptr, prob.d_indices, p, prob.out, prob.lse, ws)
+    assert torch.equal(order.sort()[0], torch.arange(items, device="cuda", dtype=torch.int32))
+    prob.out.view(torch.int16).fill_(0x7FC0)
+    F.fgattn_dense_forward(prob.q, prob.k, prob.v, pr, prob.out, prob.lse, ws)
+    assert np.array_equal(W.bf16_bits_to_f64(prob.out.view(torch.int16).cpu().numpy().view(np.uint16)), want[0])
+    # an order that is there already stays
+    F.fgattn_plan(prob.d_indptr, p, ws)
+    planned = order.clone()
+    F.fgattn_forward(prob.q, prob.k, prob.v, prob.d_indptr, prob.d_indices, pr, prob.out, prob.lse, ws)
+    assert torch.equal(order, planned)
+
+
 # keys per group on both sides of the tile sizes (32 and 64 keys), odd ones, more than a tile; the short last group stands
 # first, in the middle or last in its list (shuffled), and lists end inside, at and just past a tile
 @pytest.mark.parametrize("M", [16, 32, 64, 128])
