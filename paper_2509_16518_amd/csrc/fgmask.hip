@@ -1311,10 +1311,14 @@ int fgattn_mask_emit(const fgattn_params* p, const int64_t* mask_indptr, int32_t
   rc = device_ok(&cus);
   if (rc) return rc;
   const char* ws = static_cast<const char*>(workspace);
-  // a wave per row, or several per row (each counts the bits ahead of its stretch) until two rounds of waves fill the chip,
-  // with at least 4096 key blocks each
-  int64_t segs = (2 * 32 * (int64_t)cus + lo.rows - 1) / lo.rows;
-  if (segs > (lo.Gw + 127) / 128) segs = (lo.Gw + 127) / 128;
+  // a wave per row, or several per row (each counts the bits ahead of its stretch): until two rounds of waves fill the chip,
+  // with at least 4096 key blocks each, and until every SIMD has four, with at least 1024 each (250 rows of 4000 one wave per
+  // row 7.8 us, four 5.3; 1000 rows 9.1 and 7.5; 3000 rows of 8000 with stretches that short 20, with two per row 17.6)
+  auto stretches = [&](int64_t waves, int64_t words) {
+    const int64_t by_waves = (waves + lo.rows - 1) / lo.rows, by_words = (lo.Gw + words - 1) / words;
+    return by_waves < by_words ? by_waves : by_words;
+  };
+  const int64_t few = stretches(2 * 32 * (int64_t)cus, 128), more = stretches(4 * 4 * (int64_t)cus, 32), segs = few > more ? few : more;
   const int64_t seg_words = ((lo.Gw + segs - 1) / segs + 1) & ~(int64_t)1;
   const int64_t units = lo.rows * segs;
   hipLaunchKernelGGL(emit_bits_kernel, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, static_cast<hipStream_t>(stream_v),

@@ -30,7 +30,7 @@ def bit_rows(p, ws, rows, G):
 # one wave per row and several (few long rows), rows that end inside a pair of words, inside a batch of 32 words and at its
 # edges, outputs that start at every place of a 16-byte group, and buffers that end early
 @pytest.mark.parametrize("H,L,M,N", [(1, 40000, 128, 1), (1, 8192, 128, 1), (2, 4128, 16, 1), (1, 1024, 16, 1), (1, 1056, 16, 1),
-                                     (3, 2080, 64, 1), (1, 100, 16, 1), (2, 31, 16, 1)])
+                                     (3, 2080, 64, 1), (1, 100, 16, 1), (2, 31, 16, 1), (1, 4000, 16, 1), (1, 1100, 64, 1)])
 def test_emitted_ids_are_the_bits_in_order(H, L, M, N):
     q, k, p, ws, indptr = problem(H, L, 64, M, N, seed=L)
     F.fgattn_mask_select(q, k, p, 0.8, indptr, ws)
