@@ -59,6 +59,17 @@ def test_direct_call_leaves_an_order(M, items):
     assert torch.equal(order, planned)
 
 
+# A workgroup that is not resident keeps the item it begins with from the others, so a launch has no more of them than compute
+# units hold: LDS is given out in pieces of 1280 bytes of 160 KiB (the 32-row tile takes 32768 bytes at d = 128, 16384 at 64)
+@pytest.mark.parametrize("M", [16, 32])
+@pytest.mark.parametrize("d,per_unit", [(128, 4), (64, 9)])
+@pytest.mark.parametrize("N", [1, 8, 7])
+def test_no_more_workgroups_than_are_resident(M, d, per_unit, N):
+    q = torch.empty((1, 40, 4096, d), dtype=torch.bfloat16, device="cuda")
+    grid = F.fgattn_grid_size(F.make_params(q, q, q, q, M, N, 0.1))
+    assert 0 < grid <= per_unit * torch.cuda.get_device_properties(0).multi_processor_count
+
+
 # keys per group on both sides of the tile sizes (32 and 64 keys), odd ones, more than a tile; the short last group stands
 # first, in the middle or last in its list (shuffled), and lists end inside, at and just past a tile
 @pytest.mark.parametrize("M", [16, 32, 64, 128])
