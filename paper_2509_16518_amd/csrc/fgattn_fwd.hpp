@@ -228,11 +228,13 @@ __device__ __forceinline__ void wait_vmem_le(int& loaded) {   // the same, and `
 // them, listed in a.group_tiles) that shares one gathered key list -- the union of the members' lists -- while
 // every member attends only to its own key blocks: a.memb holds, per entry of the union list, the bit mask of the
 // members that selected it, and scores of the others are set to -inf before the softmax.
-template <int MT, int D, int NMODE, int OCC, int PART = PART_ALL, bool GROUPED = false, int KS = 2, int VS = 2, int WV = 4>
+// DENSE_PRIO: the dense kernel raises the wave priority in its gather phase (the others always or never do).
+template <int MT, int D, int NMODE, int OCC, int PART = PART_ALL, bool GROUPED = false, int KS = 2, int VS = 2, int WV = 4,
+          bool DENSE_PRIO = false>
 __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs a) {
   using C = FwdCfg<MT, D, KS, VS, WV>;
   constexpr bool DENSE = NMODE == NMODE_DENSE;
-  constexpr bool WAVE_PRIO = NMODE == NMODE_N1 || (NMODE != NMODE_DENSE && MT > 32);
+  constexpr bool WAVE_PRIO = DENSE ? DENSE_PRIO : NMODE == NMODE_N1 || MT > 32;
   constexpr bool SHORT_GROUP = NMODE == NMODE_GROUPS_SHORT;   // (the host picks the variant from L % N)
   // the cross-lane permute of the ids is issued before the barrier that precedes its use (measured with one key per group:
   // 2.4% faster at 128 query rows, 2.5% slower at 64)
@@ -789,7 +791,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       // wave priority: the gather phase above the vector-ALU phase above everything outside the key loop, so that
       // the waves that feed the memory pipe are issued first and a neighbour's prologue or epilogue never delays them
       // (measured: 1% faster at 64 and 128 rows, 3% with grouped tiles, 6% at 16x1; 4% slower at 32x32 in single-wave
-      // workgroups, 3% for the dense kernel at 128 rows, 12% at d = 64: not used there)
+      // workgroups: not used there.  For the dense kernels see where they are launched)
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(3);
       float l_new = l_run, l_new2 = l_run2, m_lane = m_pend;
       x_phase(std::integral_constant<int, (J + U - 1) % VS>(), std::integral_constant<int, (J + 1) % KS>(),

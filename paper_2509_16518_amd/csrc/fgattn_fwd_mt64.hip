@@ -11,7 +11,8 @@ template <int D, int OCC>
 static int launch_d(const FwdArgs& a, int cus, hipStream_t stream, int* grid_only) {
   static int occ[4][64];
   if (a.indptr == nullptr)
-    return launch_variant(fgattn_fwd_kernel<64, D, NMODE_DENSE, OCC>, fwd_lds_bytes<64, D, NMODE_DENSE>(), a, cus, stream, grid_only, occ[0]);
+    // (with a raised priority in the gather phase: 2-6% faster in 12 of 14 sizes from 157 to 6144 items, 1% slower in two)
+    return launch_variant(fgattn_fwd_kernel<64, D, NMODE_DENSE, OCC, PART_ALL, false, 2, 2, 4, true>, fwd_lds_bytes<64, D, NMODE_DENSE>(), a, cus, stream, grid_only, occ[0]);
   if (a.N == 1)
     return launch_variant(fgattn_fwd_kernel<64, D, NMODE_N1, OCC>, fwd_lds_bytes<64, D, NMODE_N1>(), a, cus, stream, grid_only, occ[1]);
   if (a.N > 0 && a.L % a.N == 0)

@@ -107,3 +107,13 @@ def test_exponent_base_moves(oracle_mod, M, d, shape, N, L):
     if N == 1:
         dense = Problem(dataclasses.replace(w, kind=W.MASK_ALL), q, k, v)
         check_against_oracle(oracle_mod, dense, dense.run(dense=True), what="dense " + shape)
+
+
+# Dense calls on both sides of the line between items that all start at once (their own variant at 128 rows) and a queue
+@pytest.mark.parametrize("M,d,items", [(128, 128, 511), (128, 128, 513), (128, 64, 512), (128, 64, 769), (64, 128, 512), (64, 64, 770)])
+def test_dense_direct_and_queued(oracle_mod, M, d, items):
+    heads = 16
+    w = dataclasses.replace(W.TINY, name="dense", H=heads, L=(items // heads) * M + (M // 2 if items % heads else 0), d=d, M=M, N=1,
+                            kind=W.MASK_ALL, grid=(1, 1, 1), seed=items)
+    prob = Problem(w)
+    check_against_oracle(oracle_mod, prob, prob.run(dense=True), what="%d items" % w.items, items=np.arange(0, w.items, 37))
