@@ -527,7 +527,11 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
           if (at >= 0 && at < 32 && slot[2 + w2] == tag0 + Tm) d |= (unsigned)slot[2 + WV + w2] << at;
         }
       }
-      return d >> (4 * g);
+      // (the lane's number formed anew: kept through the key loop for this rare path, it is spilled, and a reload waits for
+      // the gathers in flight as well)
+      int zero = 0;
+      asm volatile("" : "+v"(zero));
+      return d >> (4 * (__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero)) >> 5));
     };
     // LDS: K ring slots 0..KS-1 then V ring slots 0..VS-1, TENSOR_BYTES each.  A run of up to four gathers of one
     // wave lands back to back, so only the first writes M0 and the others use the instruction offset (which also

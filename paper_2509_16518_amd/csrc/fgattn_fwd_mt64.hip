@@ -21,8 +21,9 @@ static int launch_d(const FwdArgs& a, int cus, hipStream_t stream, int* grid_onl
 }
 
 int launch_mt64(const FwdArgs& a, int d, int cus, hipStream_t stream, int* grid_only) {
-  // d = 64 needs at most 168 registers: three workgroups per compute unit instead of two (dense, 12 heads x 32760 tokens
-  // 3.89 -> 3.53 ms; dense, 16 heads x 2635 tokens, 672 items 54 -> 43 us)
+  // d = 64 fits the 168 registers of three workgroups per compute unit instead of two (dense, 12 heads x 32760 tokens 3.89 ->
+  // 3.53 ms, 16 heads x 2635 tokens 54 -> 43 us; lists of 8 keys per group with a short last one, 12 heads x 32764 tokens,
+  // 1.71 -> 1.23 ms); that last variant spills one register, which it reloads once per item
   if (d == 64) return launch_d<64, 3>(a, cus, stream, grid_only);
   return launch_d<128, 2>(a, cus, stream, grid_only);
 }
