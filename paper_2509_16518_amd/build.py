@@ -86,6 +86,122 @@ def check_inline_asm_hazards(asm_path):
                 window.pop(0)
 
 
+def check_untracked_loads(asm_path):
+    """The compiler takes the target register of a load written as inline assembly (marked fg_id) as written at once, and
+    as free when it is not read again; the load writes it later.  Every path from such a load must therefore come to an
+    `s_waitcnt vmcnt(n)` that covers it (at most n vector-memory operations were issued after it; they complete in order)
+    before anything reads or writes the register.  Follows all paths of every function: per instruction, the registers
+    that may still be waiting and the fewest operations issued since.  Branches on a condition that was just set to a
+    constant (the compiler joins loop exits that way) are followed in their one direction.  Returns how many marked loads
+    it followed."""
+    import re
+    pair = re.compile(r"s\[(\d+):(\d+)\]")
+    sregs = re.compile(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b")
+    vreg = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
+    vmcnt = re.compile(r"vmcnt\((\d+)\)")
+    vmem = ("global_", "buffer_", "flat_", "scratch_")
+
+    def regs(text):
+        found = set()
+        for lo, hi, one in vreg.findall(text):
+            found.update(range(int(lo), int(hi) + 1) if lo else (int(one),))
+        return found
+
+    def constants(known, op, args):
+        """What is known of scalar pairs and vcc after an instruction: all ones / nothing set (kept: True / False)."""
+        ops = [x.strip() for x in args.split(",")]
+        if op == "s_mov_b64" and pair.fullmatch(ops[0]) and ops[1] in ("-1", "0"):
+            known = {k: v for k, v in known.items() if not clash(k, ops[0])}
+            known[ops[0]] = ops[1] == "-1"
+        elif op in ("s_and_b64", "s_andn2_b64") and ops[:2] == ["vcc", "exec"]:
+            known = {k: v for k, v in known.items() if k != "vcc"}
+            if ops[2] in known:
+                known["vcc"] = known[ops[2]] == (op == "s_and_b64")
+        elif not op.startswith("s_cbranch") and not op.startswith("v_cndmask"):
+            known = {k: v for k, v in known.items() if not clash(k, args)}
+        return known
+
+    def clash(key, args):
+        if key == "vcc":
+            return "vcc" in args
+        lo, hi = map(int, pair.fullmatch(key).groups())
+        return any(int(a or c) <= hi and int(b or c) >= lo for a, b, c in sregs.findall(args))
+
+    def follow(code, labels):
+        """code: (line number, opcode, operands, marked)"""
+        # (instruction, what is known of scalar conditions) -> {register: fewest vector-memory operations since its load}
+        waiting = {(0, frozenset()): {}}
+        todo = list(waiting)
+        while todo:
+            at, known = place = todo.pop()
+            n, op, args, marked = code[at]
+            state, known = dict(waiting[place]), constants(dict(known), op, args)
+            touched = regs(args) & state.keys()
+            if touched:
+                raise RuntimeError("%s:%d: v%s is touched while a load into it may be in flight: %s %s" %
+                                   (asm_path, n, sorted(touched), op, args))
+            if op == "s_waitcnt":
+                m = vmcnt.search(args)
+                limit = int(m.group(1)) if m else (0 if args.strip() == "0" else 64)
+                state = {r: c for r, c in state.items() if c < limit}
+            elif op.startswith(vmem):
+                state = {r: min(c + 1, 63) for r, c in state.items()}
+                if marked:
+                    (target,) = regs(args.split(",")[0])
+                    state[target] = 0
+            after = []
+            if op.startswith(("s_branch", "s_cbranch")):
+                after.append(labels[args.strip()])
+            elif op.startswith(("s_setpc", "s_swappc", "s_call")):
+                raise RuntimeError("%s:%d: %s is not followed" % (asm_path, n, op))
+            # (a forward s_cbranch_execnz ends a block that some lanes run, or it would have been skipped: always taken)
+            always = op in ("s_branch", "s_endpgm") or (op == "s_cbranch_execnz" and after[0] > at)
+            if op in ("s_cbranch_vccnz", "s_cbranch_vccz") and "vcc" in known:
+                always = known["vcc"] == (op == "s_cbranch_vccnz")
+                if not always:
+                    after = []
+            if not always and at + 1 < len(code):
+                after.append(at + 1)
+            for b in [(b, frozenset(known.items())) for b in after]:
+                old = waiting.get(b)
+                new = state if old is None else {r: min(old.get(r, 64), state.get(r, 64)) for r in old.keys() | state.keys()}
+                if new != old:
+                    waiting[b] = new
+                    todo.append(b)
+
+    loads, code, labels = 0, [], {}
+    with open(asm_path) as f:
+        for n, line in enumerate(f, 1):
+            text, _, comment = line.partition(";")
+            text = text.strip()
+            if text.startswith(".Lfunc_end"):
+                if any(marked for _, _, _, marked in code):
+                    follow(code, labels)
+                code, labels = [], {}
+            elif text.endswith(":"):
+                labels[text[:-1]] = len(code)
+            elif text and not text.startswith("."):
+                op, _, args = text.partition(" ") if " " in text else text.partition("\t")
+                marked = "fg_id" in comment and op.startswith("global_load")
+                loads += marked
+                code.append((n, op, args, marked))
+    return loads
+
+
+def check_spills(asm_path):
+    """A forward kernel that spills vector registers reloads them through the counter its gathers are waited for with.
+    One register is tolerated (it is reloaded once per item where the key loop has no room)."""
+    import re
+    name = None
+    with open(asm_path) as f:
+        for line in f:
+            m = re.match(r"\s+\.(name|vgpr_spill_count):\s+(\S+)", line)
+            if m and m.group(1) == "name":
+                name = m.group(2)
+            elif m and "fgattn_fwd_kernel" in (name or "") and int(m.group(2)) > 1:
+                raise RuntimeError("%s: %s spills %s vector registers" % (asm_path, name, m.group(2)))
+
+
 def build_hip(force=True, extra_flags=()):
     """Compile every .hip translation unit for gfx950 (in parallel) and link libfgattn.so in-tree."""
     from concurrent.futures import ThreadPoolExecutor
@@ -103,6 +219,8 @@ def build_hip(force=True, extra_flags=()):
         if f.endswith("-gfx950.s"):
             check_m0_writes(os.path.join(objdir, f))
             check_inline_asm_hazards(os.path.join(objdir, f))
+            check_untracked_loads(os.path.join(objdir, f))
+            check_spills(os.path.join(objdir, f))
         elif not f.endswith(".o"):
             os.remove(os.path.join(objdir, f))   # other intermediates of -save-temps
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIBFGATTN])

@@ -200,16 +200,18 @@ constexpr int fwd_lds_bytes() {
 // id loads: plain per-lane loads written as inline assembly so that the compiler does not track them.  (A tracked load
 // makes the compiler wait with vmcnt(0) before the first use, which would also wait for every gather in flight: the
 // counter is shared and the compiler cannot see the gathers.)  The kernel waits with the s_waitcnt that precedes each
-// tile's barrier (wait_vmem_le(loaded) ties the register to that wait for the compiler); consumers clamp what they read
-// to [0, L), so even a register read too early could never address out of bounds.
+// tile's barrier (wait_vmem_le(loaded) ties the register to that wait for the compiler), and with a wait that ties all of
+// them where the key loop ends.  In between, the compiler must neither copy nor reuse such a register: the build follows
+// every path of the generated code from each marked load (fg_id) to its wait and fails if one is touched.  Consumers clamp
+// what they read to [0, L), so even a register read too early could never address out of bounds.
 __device__ __forceinline__ void load_id_untracked(int& dst, const int32_t* base, unsigned byte_off) {
   // (scalar base + 32-bit per-lane offset: no 64-bit address arithmetic on the vector ALU)
   base = static_cast<const int32_t*>(pin_scalar(base));
-  asm volatile("global_load_dword %0, %1, %2" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
+  asm volatile("global_load_dword %0, %1, %2 ; fg_id" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
 }
 __device__ __forceinline__ void load_byte_untracked(int& dst, const uint8_t* base, unsigned byte_off) {
   base = static_cast<const uint8_t*>(pin_scalar(base));
-  asm volatile("global_load_ubyte %0, %1, %2" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
+  asm volatile("global_load_ubyte %0, %1, %2 ; fg_id" : "=v"(dst) : "v"(byte_off), "s"(base) : "memory");
 }
 // `loaded` (an untracked load's target) is valid from here on, by a wait just made
 __device__ __forceinline__ void arrived(int& loaded) { asm volatile("" : "+v"(loaded)); }
@@ -878,6 +880,13 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
       }
       if constexpr (WAVE_PRIO) __builtin_amdgcn_s_setprio(0);
       wait_vmem_all();
+      if constexpr (!DENSE) {   // (the ids of tiles past the end, which nobody reads)
+#pragma unroll
+        for (int e = 0; e < IDL; e++) {
+          arrived(gi[e]);
+          if constexpr (GROUPED) arrived(gm[e]);
+        }
+      }
       __syncthreads();
       // O += V(ntiles-1)^T P(ntiles-1)^T: the slot and the register set depend on ntiles - 1 modulo lcm(VS, 2)
       constexpr int UD = clcm(VS, 2);
