@@ -516,7 +516,7 @@ __global__ void __launch_bounds__(WV * 64, OCC) fgattn_fwd_kernel(const FwdArgs 
 #pragma unroll
         for (int i = 0; i < (KEEP_SPREAD ? C::IPW : 1); i++) keys[s][i] = keys[s + 1][i];
     };
-    // keys of tile Tm that do not count, as bits of this lane's accumulator registers (see MASK_DROP)
+    // keys of tile Tm that do not count, as bits of this lane's accumulator registers (see mask_drop)
     auto dropped = [&](int Tm, int par) -> unsigned {
       const int limit = total - Tm * C::NT - kw * 32;   // keys of this wave's part that lie inside the list
       unsigned d = limit >= 32 ? 0u : limit <= 0 ? ~0u : ~0u << limit;

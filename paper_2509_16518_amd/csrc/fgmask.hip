@@ -1163,7 +1163,7 @@ static int layout_of(const fgattn_params* p, Layout* lo) {
   const size_t tile_bytes = (size_t)128 * lo->Gs * 4;
   lo->chunk_units = (p->flags & FGATTN_FLAG_MASK_ONE_TILE_CHUNKS) ? 1 : (int64_t)(kScoreBudget / tile_bytes);
   if (lo->chunk_units < 1) lo->chunk_units = 1;
-  if (lo->chunk_units > 65535) lo->chunk_units = 65535;   // (a chunk's tiles are the y dimension of a grid)
+  if (lo->chunk_units > 65535) lo->chunk_units = 65535;   // (bounds the grids of a chunk whose rows are short)
   if (lo->chunk_units > lo->units) lo->chunk_units = lo->units;
   size_t off = 0;
   lo->qp_off = off;

@@ -65,9 +65,10 @@ def test_validate_mask_flags_bad_masks():
 @pytest.mark.parametrize("M", [64, 128])
 def test_forward_part_is_a_measurement_aid_only(M):
     # built for M = 64 / 128, d = 128, N = 1 only; runs, leaves the real entry point's results untouched afterwards
-    w = W.Workload("part", H=2, L=2048, d=128, M=M, N=1, kind=W.MASK_RANDOM, density=0.3, seed=5100)
+    w = W.Workload("part", H=40, L=2048, d=128, M=M, N=1, kind=W.MASK_RANDOM, density=0.3, seed=5100)
     prob = Problem(w)
     p = prob.params(flags=F.FLAG_REUSE_PLAN)
+    assert w.items > F.fgattn_grid_size(p)   # (otherwise no order is used)
     ws = prob.workspace(p)
     F.fgattn_plan(prob.d_indptr, p, ws)
     scratch_out, scratch_lse = torch.empty_like(prob.out), torch.empty_like(prob.lse)
@@ -85,7 +86,7 @@ def test_forward_part_is_a_measurement_aid_only(M):
     pt = tiny.params()
     expect(F.E_SHAPE, lambda: F.fgattn_forward_part(tiny.q, tiny.k, tiny.v, tiny.d_indptr, tiny.d_indices, pt, tiny.out,
                                                     tiny.lse, tiny.workspace(pt), F.PART_GATHER))
-    # the stored order is still usable: the partial kernels rewind the queue like the full one
+    # the stored order is still usable after the partial kernels
     F.fgattn_forward(prob.q, prob.k, prob.v, prob.d_indptr, prob.d_indices, p, prob.out, prob.lse, ws)
     torch.cuda.synchronize()
     a = prob.out.clone()
@@ -119,7 +120,7 @@ def test_grid_size_is_reported_for_every_variant(M, N, L):
 def test_forward_is_graph_capturable():
     # the library allocates nothing and clears no memory on the hot path: a call (ordering pre-pass + kernel) can be
     # captured into a graph; every replay must reproduce the eager result bit for bit
-    w = W.Workload("graph", H=3, L=2048, d=128, M=64, N=1, kind=W.MASK_SKEW_LEN, density=0.3, skew=0.7, seed=5200)
+    w = W.Workload("graph", H=24, L=2048, d=128, M=64, N=1, kind=W.MASK_SKEW_LEN, density=0.3, skew=0.7, seed=5200)
     prob = Problem(w)
     p = prob.params()
     ws = prob.workspace(p)

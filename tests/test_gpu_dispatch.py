@@ -89,9 +89,9 @@ def test_short_last_group_anywhere_in_the_list(oracle_mod, M, N, L):
     check_against_oracle(oracle_mod, prob, prob.run(), what="M=%d N=%d L=%d" % (M, N, L))
 
 
-# The exponent base of a query stays at its first tile's maximum until a lane's sum passes 2^32: scores that grow along the
-# list by less than that per tile (several moves), by far more than a float's exponent holds at one key (sums of +inf are
-# formed and formed again), that fall, and that stay level
+# The exponent base of a query follows the running maximum by steps of at least 2^8: scores that grow along the list by less
+# than that and by more per tile (several moves), by far more than a float's exponent holds at one key (sums of +inf are formed
+# and formed again), and that fall
 @pytest.mark.parametrize("M,d", [(16, 64), (32, 128), (64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("shape", ["ramp", "jump", "fall"])
 @pytest.mark.parametrize("N,L", [(1, 700), (8, 700)])

@@ -204,8 +204,8 @@ def test_grouping_seeded_random_shapes(oracle_mod, M, N, d, L, H, B, kind, densi
     check_against_oracle(oracle_mod, prob, out, what=w.name + " " + mode)
 
 
-# tiles per slice on both sides of what a thread keeps in registers (one, two and four keys of 1024 threads, then none), for
-# every group size; few key blocks, so that most distances are equal to others and the order of the tiles decides; a last
+# tiles per slice on both sides of what a thread keeps in registers (four, eight and sixteen keys of 256 threads, then none), for
+# every group size, with distances of 32 bits (fewer than 128 tiles) and of 16; few key blocks, so that most distances are equal to others and the order of the tiles decides; a last
 # group that is full, short and of one tile; blocks of the distance matrix on, off and past the diagonal
 @pytest.mark.parametrize("M,QB,G", [(16, 1023, 40), (16, 1024, 6), (16, 1025, 40), (16, 2048, 33), (16, 2049, 6), (16, 4096, 20),
                                     (16, 4097, 20), (32, 1021, 6), (32, 1500, 70), (32, 2100, 6), (64, 130, 6), (64, 1030, 70),

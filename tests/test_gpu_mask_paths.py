@@ -18,13 +18,19 @@ def problem(H, L, d, M, N, seed, flags=0, scale=1.0):
     return q, k, p, ws, torch.empty(H * ((L + M - 1) // M) + 1, dtype=torch.int64, device="cuda")
 
 
-def bit_rows(p, ws, rows, G):
-    """The kept set as the selection leaves it: the last rows * ceil(G / 32) words of the workspace's used part."""
-    Gw = (G + 31) // 32
-    used = F.fgattn_mask_workspace_bytes(p)
-    start = used - (rows * Gw * 4 + 255) // 256 * 256
-    words = ws[start:start + rows * Gw * 4].view(torch.int32).view(rows, Gw)
-    return ((words[:, :, None] >> torch.arange(32, device="cuda", dtype=torch.int32)) & 1).view(rows, Gw * 32)[:, :G].bool()
+def emitted(p, ws, indptr):
+    ids = torch.zeros(max(int(indptr[-1]), 1), dtype=torch.int32, device="cuda")
+    F.fgattn_mask_emit(p, indptr, ids, ws)
+    return ids[:int(indptr[-1])]
+
+
+def kept_rows(p, ws, indptr, G):
+    """The kept set as [rows, G] truth values, from the emitted ids."""
+    rows = indptr.numel() - 1
+    row = torch.repeat_interleave(torch.arange(rows, device="cuda"), indptr[1:] - indptr[:-1])
+    kept = torch.zeros((rows, G), dtype=torch.bool, device="cuda")
+    kept[row, emitted(p, ws, indptr).long()] = True
+    return kept
 
 
 # one wave per row and several (few long rows), rows that end inside a pair of words, inside a batch of 32 words and at its
@@ -32,11 +38,18 @@ def bit_rows(p, ws, rows, G):
 @pytest.mark.parametrize("H,L,M,N", [(1, 40000, 128, 1), (1, 8192, 128, 1), (2, 4128, 16, 1), (1, 1024, 16, 1), (1, 1056, 16, 1),
                                      (3, 2080, 64, 1), (1, 100, 16, 1), (2, 31, 16, 1), (1, 4000, 16, 1), (1, 1100, 64, 1)])
 def test_emitted_ids_are_the_bits_in_order(H, L, M, N):
-    q, k, p, ws, indptr = problem(H, L, 64, M, N, seed=L)
-    F.fgattn_mask_select(q, k, p, 0.8, indptr, ws)
-    rows, G = indptr.numel() - 1, (L + N - 1) // N
-    bits = bit_rows(p, ws, rows, G)
+    # Which ids a row keeps is known beforehand: query block r looks at column r % 64, where a key holds +1 or -1.  Scores are 64 or
+    # -64, so the +1 keys share the whole mass equally and top_p = 1 keeps every one of them and nothing else.
+    q, k, _, ws, indptr = problem(H, L, 64, M, N, seed=L)
+    QB = (L + M - 1) // M
+    q.zero_()
+    q[:, :, torch.arange(L), torch.arange(L) // M % 64] = 64.0
+    k.copy_(torch.where(k > -0.5, 1.0, -1.0))
+    p = F.make_params(q, k, k, q, M, N, 1.0)
+    F.fgattn_mask_select(q, k, p, 1.0, indptr, ws)
+    bits = (k[0][:, :, torch.arange(QB) % 64] > 0).transpose(1, 2).reshape(H * QB, L)
     want = bits.nonzero()[:, 1].int()
+    rows, G = H * QB, L
     assert torch.equal(indptr[1:] - indptr[:-1], bits.sum(1))
     assert torch.equal(indptr[1:], bits.sum(1).cumsum(0)) and int(indptr[0]) == 0
     nnz = want.numel()
@@ -62,7 +75,7 @@ def test_scores_of_every_tile_and_stretch(H, L, d, M, N, one_tile):
     F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
     rows, G = indptr.numel() - 1, (L + N - 1) // N
     QB = rows // H
-    got = bit_rows(p, ws, rows, G).view(H, QB, G)
+    got = kept_rows(p, ws, indptr, G).view(H, QB, G)
 
     def means(x, n):
         pad = torch.nn.functional.pad(x.double(), (0, 0, 0, (-L) % n)).view(H, -1, n, d).sum(2)
@@ -104,7 +117,7 @@ def test_selection_from_bytes_equals_selection_from_memory(G):
                     k = torch.ones_like(k)
                 p = F.make_params(q, k, k, q, M, 1, (20.0 if kind == "peaked" else 1.0) * d ** -0.5, flags)
                 F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
-                res.append((indptr, bit_rows(p, ws, indptr.numel() - 1, G)))
+                res.append((indptr, emitted(p, ws, indptr)))
             assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
             assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
 
@@ -119,7 +132,5 @@ def test_overfull_rows_among_others(H, L, M):
             q, k, p, ws, indptr = problem(H, L, 64, M, 1, seed=L + len(full), flags=flags)
             k[:, full] = 1.0
             F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
-            indices = torch.zeros(int(indptr[-1]), dtype=torch.int32, device="cuda")
-            F.fgattn_mask_emit(p, indptr, indices, ws)
-            res.append((indptr, indices))
+            res.append((indptr, emitted(p, ws, indptr)))
         assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1]), full
