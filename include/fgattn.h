@@ -12,7 +12,8 @@
  * caller-provided `workspace` of at least fgattn_workspace_bytes() bytes, 256-byte aligned.
  * Calls are asynchronous on `stream` (a hipStream_t passed as void*; NULL = default stream)
  * and never synchronise the host, except fgattn_validate_mask.  Two calls that share a
- * workspace must be ordered on one stream.
+ * workspace must be ordered on one stream.  A call's results are the same bits every time, whatever
+ * the schedule; across versions of the library the tolerance is the promise, not the bits.
  *
  * Return value: 0 (FGATTN_OK) or a negative FGATTN_E* code; fgattn_strerror() names it.
  * No C++ exceptions cross this boundary.
@@ -113,7 +114,7 @@ int fgattn_dense_forward(const void* q, const void* k, const void* v, const fgat
  *   union_indptr  : int64 [B*H*G_s + 1], union_indices: int32 key-block ids of each group's union (any order, no
  *                   duplicates), union_members: uint8, one per entry of union_indices: bit r set iff member r of
  *                   the group selected that key block.
- * Everything else as in fgattn_forward (same workspace size; FGATTN_FLAG_REUSE_PLAN refers to a plan made by
+ * Everything else as in fgattn_forward (same workspace size; FGATTN_FLAG_REUSE_PLAN refers to an order left by
  * this call).  Contents of the four arrays are not checked.
  */
 int fgattn_forward_grouped(const void* q, const void* k, const void* v, const int32_t* group_tiles,
@@ -233,9 +234,9 @@ int fgattn_forward_part(const void* q, const void* k, const void* v, const int64
  * the forward kernel's occupancy (two four-wave workgroups per compute unit), a loop of 16 MFMAs (32x32x16 bf16), 16
  * exponentials and `other_valu_per_16_mfma` ordinary vector instructions per trip, `iters` trips, no memory traffic:
  * what a SIMD sustains on the mix of one wave-tile of the key loop (Sec. 2's softmax between the two matrix products).
- * Built for other_valu_per_16_mfma = 67 (64-row sparse tile), 61 (128-row sparse tile), 59 (128-row dense tile), and 0 =
- * the MFMAs alone, without the exponentials; anything else gives FGATTN_E_FLAGS.  `scratch`: device memory, at least 2048 B per compute unit (results nobody
- * reads); *flop (host) receives the MFMA FLOP count of the launch, so that FLOP / measured time is the ceiling.
+ * Built for other_valu_per_16_mfma = 71 (64-row sparse tile), 66 (128-row sparse tile), 64 (128-row dense tile), for 67, 61 and
+ * 59 (the same tiles in earlier builds), and 0 = the MFMAs alone, without the exponentials; anything else gives
+ * FGATTN_E_FLAGS.  `scratch`: device memory, at least 2048 B per compute unit (results nobody reads); *flop (host) receives the MFMA FLOP count of the launch, so that FLOP / measured time is the ceiling.
  * Asynchronous on `stream`. */
 int fgattn_issue_probe(int other_valu_per_16_mfma, int iters, void* scratch, size_t scratch_bytes, double* flop, void* stream);
 

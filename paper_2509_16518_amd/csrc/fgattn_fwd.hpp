@@ -22,8 +22,8 @@
 // 128 query rows with RW = MT/32 waves along the rows and KW = WV/RW waves along the keys of a
 // tile (NT = 32*KW keys); waves that split the keys keep private (max, sum, O) and merge once
 // per work item.  WV is 4 except for the 32-row tile, which runs as single-wave workgroups: a wave's K and V
-// slots take 32 KB at d = 128, so LDS admits five waves per compute unit, and five independent workgroups use
-// them all (a four-wave workgroup would leave it at four).
+// slots take 32 KB at d = 128, of which LDS holds four per compute unit, and independent waves need no merge of their key
+// halves at the end of an item and never wait for each other.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -7,9 +7,9 @@ namespace fg {
 
 static_assert(FwdCfg<32, 128, 2, 2, 1>::NT == (32 <= 32 ? 32 : 32 == 64 ? 64 : 32), "host-side NT table out of date");
 
-// WPS: waves per SIMD the register budget is set for.  d = 128: two (256 registers; LDS admits five waves per CU
-// anyway).  d = 64 (16 KB of LDS per wave): three for the one-key-per-group variant (ten waves per CU, a few spilled
-// registers) and two for the others, whose loaders need more registers -- as measured, 3-5% either way.
+// WPS: waves per SIMD the register budget is set for.  d = 128: two (256 registers; LDS holds four waves per CU
+// anyway).  d = 64 (16 KB of LDS per wave): three for the one-key-per-group variant (nine waves per CU by LDS) and two for the
+// others, whose loaders need more registers -- as measured, 3-5% either way.
 template <int D, int WPS_N1, int WPS>
 static int launch_d(const FwdArgs& a, int cus, hipStream_t stream, int* grid_only) {
   static int occ[4][64];

@@ -73,6 +73,9 @@ int launch_issue_probe(int other, int iters, float* out, int cus, hipStream_t st
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 65536, stream, out, iters);
     return hipGetLastError() == hipSuccess ? FGATTN_OK : FGATTN_E_DEVICE;
   };
+  if (other == 71) return go(issue_probe_kernel<71>);
+  if (other == 66) return go(issue_probe_kernel<66>);
+  if (other == 64) return go(issue_probe_kernel<64>);
   if (other == 59) return go(issue_probe_kernel<59>);
   if (other == 61) return go(issue_probe_kernel<61>);
   if (other == 67) return go(issue_probe_kernel<67>);

@@ -99,7 +99,7 @@ def test_issue_probe_is_a_measurement_aid_only():
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     scratch = torch.zeros(2048 * cus + 64, dtype=torch.uint8, device="cuda")
     scratch[2048 * cus:] = 0x5A
-    for other in (0, 59, 61, 67):
+    for other in (0, 59, 61, 64, 66, 67, 71):
         flop = F.fgattn_issue_probe(other, 8, scratch[:2048 * cus])
         assert flop == 2.0 * cus * 4 * 8 * 16 * 32768.0
     torch.cuda.synchronize()
