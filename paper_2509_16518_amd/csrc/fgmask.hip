@@ -1061,18 +1061,43 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
   }
 }
 
-// Kept ids in ascending order, from the bit rows that the selection leaves.  Bound: the writes of the ids (4 bytes each).  A
-// wave takes a stretch of one row, 64 key blocks per step: their bits go to two scalar registers, a lane's place among the
-// kept ones is the count of set bits below it, and the lanes whose bit is set put their id into the wave's own piece of
-// LDS, next to each other.  From there whole 16-byte groups go to memory, on 16-byte boundaries of the output; what is left
-// over waits for the next ids.  No barrier and no loop over bits.  (Stores straight from the lanes whose bit is set are no
-// faster than a workgroup per row that ran over the set bits of a word per thread, 87 us against 83 below: an instruction
-// with every third lane active makes as many requests as a full one.)  12 heads x 512 rows of 32760 83 -> 74 us,
-// 24 x 929 rows of 118800 1690 -> 1470-1560 us (5.6 GB of ids).
+// Kept ids in ascending order, from the bit rows that the selection leaves.  Bound: the writes of the ids (4 bytes each: for
+// 24 x 929 rows of 118800, 5.6 GB of ids, 1.27 ms; without the stores the kernel takes 0.64).  A wave takes a stretch of one
+// row, a byte of it (eight key blocks) per lane and step.  A table gives the places of a byte's set bits, a prefix over the
+// lanes where a lane's ids begin, and the ids go next to each other into the wave's own piece of LDS.  From there whole
+// 128-byte lines go to memory, past the caches (nothing reads them soon); what is left over waits for the next ids.  No
+// barrier and no loop over bits.  (A bit per lane, with the words handed out through scalar registers, takes twice the
+// instructions, and 16-byte groups leave lines in parts: 12 heads x 512 rows of 32760 73 -> 55 us, 24 x 929 rows of 118800
+// 1490-1640 -> 1210-1270 us.  A loop over each lane's bits runs as long as the fullest lane's: 91 and 1510 us.  Stores
+// straight from the lanes whose bit is set make as many requests as full ones.)
 constexpr int kEmitBatch = 32;   // words of a row staged between two flushes
+// inclusive prefix sum over the lanes of a wave, without LDS
+__device__ __forceinline__ unsigned lane_prefix(unsigned x) {
+  auto add = [&](auto ctrl, auto rows) {
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+  };
+  add(std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xf>());   // row_shr:1, 2, 4, 8
+  add(std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xf>());
+  add(std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xf>());
+  add(std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xf>());
+  add(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>());   // row_bcast:15 into rows 1 and 3
+  add(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>());   // row_bcast:31 into rows 2 and 3
+  return x;
+}
 __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bits, int Gw, int seg_words, int segs, int64_t units,
                                                         const int64_t* indptr, int32_t* indices, int64_t capacity) {
-  __shared__ alignas(16) int32_t stages[4][kEmitBatch * 32 + 4];
+  __shared__ alignas(16) int32_t stages[4][kEmitBatch * 32 + 40];
+  // of every byte, the places of its set bits, ascending, a byte each; the rest are zero
+  __shared__ uint2 places[256];
+  {
+    uint64_t p = 0;
+    int n = 0;
+#pragma unroll
+    for (int b = 0; b < 8; b++)
+      if ((threadIdx.x >> b) & 1u) p |= (uint64_t)b << (8 * n++);
+    places[threadIdx.x] = make_uint2((unsigned)p, (unsigned)(p >> 32));
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t unit = (int64_t)blockIdx.x * 4 + wv;
   if (unit >= units) return;
@@ -1087,38 +1112,54 @@ __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bit
   if (w0 > 0)
     for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
   const int64_t out = indptr[row] + (unsigned)__builtin_amdgcn_readfirstlane((int)before);
-  // stage[i] goes to indices[to + i]; indices + to lies on a 16-byte boundary, so up to three slots at the start are no ids
-  unsigned skip = (unsigned)((reinterpret_cast<uintptr_t>(indices + out) >> 2) & 3);
+  // stage[i] goes to indices[to + i]; indices + to lies on a 128-byte line, so up to 31 slots at the start are no ids
+  unsigned skip = (unsigned)((reinterpret_cast<uintptr_t>(indices + out) >> 2) & 31);
   int64_t to = out - skip;
   unsigned fill = skip;
   for (int w = w0; w < w1; w += 64) {
+    asm volatile("" : "+v"(words));   // (waits for these words here: after the next load is under way, it would wait for that too)
     const uint32_t next = w + 64 + lane < w1 ? bits[w + 64 + lane] : 0u;
     for (int half = 0; half < 64 && w + half < w1; half += kEmitBatch) {
 #pragma unroll
-      for (int i = 0; i < kEmitBatch; i += 2) {   // (words past the end are zero)
-        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)words, half + i);
-        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)words, half + i + 1);
-        const uint64_t mask = ((uint64_t)hi << 32) | lo;
-        const unsigned rank = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-        if (__builtin_amdgcn_inverse_ballot_w64(mask)) stage[fill + rank] = (w + half + i) * 32 + lane;
-        fill += (unsigned)__popcll(mask);
+      for (int i = 0; i < kEmitBatch; i += 16) {   // sixteen words at a step, a byte per lane (words past the end are zero)
+        const unsigned word = (unsigned)__builtin_amdgcn_ds_bpermute((half + i + (lane >> 2)) * 4, (int)words);
+        const unsigned byte = (word >> (8 * (lane & 3))) & 0xFFu, count = (unsigned)__popc(byte);
+        const uint2 p = places[byte];
+        const unsigned incl = lane_prefix(count);
+        auto* const at = (volatile __attribute__((address_space(3))) int32_t*)(stage + fill + (incl - count));   // (in the order written)
+        const int id = (w + half + i) * 32 + lane * 8;
+        // Eight ids a lane, the last one first: what a lane writes past its count lands on places of lanes above it, which write
+        // them again in a later one of these instructions (a lane without ids writes none, so "above" is by one instruction
+        // at least), or past the last id, where the next step begins.
+        if (count != 0u) {
+          at[7] = id | (int)(p.y >> 24);
+          at[6] = id | (int)((p.y >> 16) & 0xFFu);
+          at[5] = id | (int)((p.y >> 8) & 0xFFu);
+          at[4] = id | (int)(p.y & 0xFFu);
+          at[3] = id | (int)(p.x >> 24);
+          at[2] = id | (int)((p.x >> 16) & 0xFFu);
+          at[1] = id | (int)((p.x >> 8) & 0xFFu);
+          at[0] = id | (int)(p.x & 0xFFu);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        fill += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
       }
       // whole groups to memory (LDS operations of a wave complete in order)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const unsigned groups = fill >> 2;
-      if (skip == 0 && to + (int64_t)(groups * 4) <= capacity) {
-        for (unsigned i = lane; i < groups; i += 64)
-          *reinterpret_cast<i32x4*>(indices + to + 4 * i) = *reinterpret_cast<const i32x4*>(stage + 4 * i);
+      const unsigned whole = fill & ~31u;
+      if (skip == 0 && to + (int64_t)whole <= capacity) {
+        for (unsigned i = 4 * lane; i < whole; i += 256)
+          __builtin_nontemporal_store(*reinterpret_cast<const i32x4*>(stage + i), reinterpret_cast<i32x4*>(indices + to + i));
       } else {   // the stretch's first flush, or the end of the buffer
-        for (unsigned i = lane; i < groups * 4; i += 64)
+        for (unsigned i = lane; i < whole; i += 64)
           if (i >= skip && to + i < capacity) indices[to + i] = stage[i];
       }
-      if (groups > 0) {
-        const int rest = lane < 4 ? stage[groups * 4 + lane] : 0;   // (up to three ids; the array has four slots to spare)
+      if (whole > 0) {
+        const int rest = stage[whole + (lane & 31)];   // (up to 31 ids; the array has the slots to spare)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (lane < 4) stage[lane] = rest;
-        to += groups * 4;
-        fill &= 3;
+        if (lane < 32) stage[lane] = rest;
+        to += whole;
+        fill &= 31;
         skip = 0;
       }
     }

@@ -63,6 +63,30 @@ def test_emitted_ids_are_the_bits_in_order(H, L, M, N):
             assert (buf[:offset] == -7).all() and (buf[offset + cap:] == -7).all(), (offset, cap)
 
 
+# outputs that start at every place of a 128-byte line and end early; rows that keep everything (eight ids in every byte), long
+# runs of nothing between single ids, and every byte there is
+@pytest.mark.parametrize("L,M", [(3000, 128), (1024, 16), (1025, 16), (33, 16)])
+def test_emitted_ids_at_every_place_of_a_line(L, M):
+    q, k, p, ws, indptr = problem(1, L, 64, M, 1, seed=L)
+    j = torch.arange(L, device="cuda")
+    for on in (torch.ones_like(j, dtype=torch.bool), (j % 700 == 5) | (j == L - 1), (((j // 8) >> (j % 8)) & 1 != 0) | (j == 0)):
+        # query blocks hold e_0 and keys +1 or -1 in column 0: scores 64 and -64, so top_p = 1 keeps exactly the former
+        q.zero_()
+        q[..., 0] = 64.0
+        k.copy_(torch.where(on, 1.0, -1.0)[None, None, :, None].expand_as(k))
+        p = F.make_params(q, k, k, q, M, 1, 1.0)
+        F.fgattn_mask_select(q, k, p, 1.0, indptr, ws)
+        want = on.nonzero()[:, 0].int().repeat((L + M - 1) // M)
+        nnz = want.numel()
+        assert int(indptr[-1]) == nnz
+        for offset in range(32):
+            cap = nnz - offset % 3
+            buf = torch.full((nnz + 64,), -7, dtype=torch.int32, device="cuda")
+            F.fgattn_mask_emit(p, indptr, buf[offset:offset + cap], ws)
+            assert torch.equal(buf[offset:offset + cap], want[:cap]), offset
+            assert (buf[:offset] == -7).all() and (buf[offset + cap:] == -7).all(), offset
+
+
 # fewer than eight stretches of key blocks, eight, and counts off a multiple of eight; one score tile, more than share a
 # stretch, tiles whose last rows or whole waves are past the end, chunks that begin inside a slice; key blocks past the end
 # of a tile of 32; means that are all negative or far apart, so that a padded position would show in a row's range
