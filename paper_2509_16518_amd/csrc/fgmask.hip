@@ -11,10 +11,11 @@
 //                      key block, without sorting the row, and leaves the kept set as one bit per key block
 //   select_kernel      longer rows (or on request): the same selection, one workgroup per query block,
 //                      every pass reading the row from device memory; leaves the same outputs
+//   (fgmask_stream.hpp)  many long rows: the same selection from scores that are formed anew for each pass instead of kept
 //   row_pointers_kernel  counts -> indptr (fgscan.hpp)
 //   emit_bits_kernel   kept ids, ascending, into indices (from the bit rows)
 //
-// The scores are the only large intermediate (4 bytes per pair of query block and key block).  They are
+// Where scores are kept, they are the only large intermediate (4 bytes per pair of query block and key block).  They are
 // produced and consumed in chunks of whole score tiles (128 query blocks of one slice), scores_kernel and
 // the selection kernel alternating over one buffer of bounded size; what outlives a chunk is one bit per pair.
 //
@@ -271,12 +272,13 @@ __device__ __forceinline__ unsigned long long rank_key(float s, int j) {
 // The bare exponential instruction differs from exp2f only below 2^-126, where the weight is zero either way.
 // The products with powers of two are exact, and so is the split into a whole and a fractional part (the hardware
 // has no float -> 64-bit integer conversion).
-__device__ __forceinline__ unsigned long long weight_of(float s, float rmax) {
-  const float x = __builtin_amdgcn_exp2f((s - rmax) * kLog2e) * 256.0f;   // in [0, 2^8]; the weight is trunc(2^32 x)
+__device__ __forceinline__ unsigned long long weight_below(float below) {   // below = s - rmax
+  const float x = __builtin_amdgcn_exp2f(below * kLog2e) * 256.0f;   // in [0, 2^8]; the weight is trunc(2^32 x)
   const unsigned hi = (unsigned)x;
   const unsigned lo = (unsigned)(__builtin_amdgcn_fractf(x) * 4294967296.0f);
   return ((unsigned long long)hi << 32) | lo;
 }
+__device__ __forceinline__ unsigned long long weight_of(float s, float rmax) { return weight_below(s - rmax); }
 
 // Visits every score of a row: four consecutive scores per thread and step (16-byte loads; rows start 16-byte
 // aligned and their stride is a multiple of four floats), DEPTH steps in flight.
@@ -447,15 +449,25 @@ __device__ __forceinline__ unsigned value_bin_of(float v, float rmax, float inv)
   return min((unsigned)((rmax - v) * inv), (unsigned)(BINS - 1));   // (rmax - v is not negative)
 }
 
-// The part of the selection after the row's histogram (locate_bin<true> has named the crossing bin, the mass above it and the
-// target in sh); called by all threads of the workgroup.  Writes the cut, the count and the kept set as one bit per key block
-// (`keep_bits`, Gw words per row), from a row of scores `s` in device memory.
+// where a score lies relative to bin `bin` of that histogram: -1 above, 0 inside, 1 below
+template <int BINS>
+__device__ __forceinline__ auto place_by_bin(unsigned bin, float rmax, float inv) {
+  return [=](float v) -> int {
+    const unsigned b = value_bin_of<BINS>(v, rmax, inv);
+    return b < bin ? -1 : (b == bin ? 0 : 1);
+  };
+}
+
+// The part of the selection after the row's histogram: sh holds the mass above the crossing bin, the target and n_above = 0, and
+// place(score) says where a score lies, -1 above the bin, 0 in it, 1 below.  Called by all threads of the workgroup.  Writes
+// the cut, the count and the kept set as one bit per key block (`keep_bits`, Gw words per row), from a row of scores `s` in
+// device memory.
 //
 // Passes over the row: the scores ranked above the crossing bin are counted and written as bits straight away, the bin's
 // members are collected; then the members are ranked, and the bits of those at or above the cut are added.  Only a crossing
 // bin with more members than the sort holds takes further passes, and a last one that writes all bits from the cut.
-template <int THREADS, int BINS, int CAP, int DEPTH, typename SH>
-__device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, float rmax, float inv, int G, float top_p,
+template <int THREADS, int BINS, int CAP, int DEPTH, typename SH, typename Place>
+__device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, float rmax, Place place, int G, float top_p,
                                          unsigned long long* cut, unsigned* count, uint32_t* keep_bits, int Gw) {
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));   // (see select_codes_kernel: nothing here is worth keeping from row to row)
@@ -465,19 +477,23 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
   auto write_all_bits = [&]() {
     __syncthreads();
     const unsigned long long c = sh.cut;
-    for (int base = 0; base < Gw * 32; base += THREADS * 4) {
-      const int j4 = base + tid * 4;
-      unsigned nib = 0;
-      if (j4 < G) {
-        const float4 v = *reinterpret_cast<const float4*>(s + j4);
-        nib = (rank_key(v.x, j4) >= c ? 1u : 0u) | (j4 + 1 < G && rank_key(v.y, j4 + 1) >= c ? 2u : 0u) |
-              (j4 + 2 < G && rank_key(v.z, j4 + 2) >= c ? 4u : 0u) | (j4 + 3 < G && rank_key(v.w, j4 + 3) >= c ? 8u : 0u);
+    const int last4 = (G - 1) & ~3;
+    for (int base = 0; base < Gw * 32; base += DEPTH * THREADS * 4) {
+      f32x4 v[DEPTH];
+#pragma unroll
+      for (int e = 0; e < DEPTH; e++) v[e] = *reinterpret_cast<const f32x4*>(s + min(base + (e * THREADS + tid) * 4, last4));
+#pragma unroll
+      for (int e = 0; e < DEPTH; e++) {
+        const int j4 = base + (e * THREADS + tid) * 4;
+        unsigned nib = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) nib |= j4 + i < G && rank_key(v[e][i], j4 + i) >= c ? 1u << i : 0u;
+        unsigned word = nib << (4 * (tid & 7));
+        word |= __shfl_xor(word, 1);
+        word |= __shfl_xor(word, 2);
+        word |= __shfl_xor(word, 4);
+        if ((tid & 7) == 0 && (j4 >> 5) < Gw) bits_row[j4 >> 5] = word;
       }
-      unsigned word = nib << (4 * (tid & 7));
-      word |= __shfl_xor(word, 1);
-      word |= __shfl_xor(word, 2);
-      word |= __shfl_xor(word, 4);
-      if ((tid & 7) == 0 && (j4 >> 5) < Gw) bits_row[j4 >> 5] = word;
     }
   };
   // The bits of everything above the crossing bin are in memory already (pass 2): add those of the collected
@@ -497,8 +513,6 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
     }
   };
 
-  auto value_bin = [&](float v) -> int { return (int)value_bin_of<BINS>(v, rmax, inv); };
-
   // One pass: counts the scores ranked above the crossing bin and collects the rank keys of its members, as many
   // as fit the sort.  cls(v): -1 above the bin, 0 inside, +1 below or outside what was the bin before.  WITH_BITS:
   // "above" of a thread's four consecutive key blocks is a nibble of the row's bits, eight lanes make a word (every
@@ -517,14 +531,24 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
       for (int e = 0; e < DEPTH; e++) {
         const int j4 = base + e * STEP + tid * 4;
         const float x[4] = {v[e][0], v[e][1], v[e][2], v[e][3]};
-        unsigned nib = 0;
+        unsigned nib = 0, all = 0;
+        uint64_t in[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
           const int c = j4 + i < G ? cls(x[i]) : 1;
           nib |= c < 0 ? 1u << i : 0u;
-          if (c == 0) {
-            const unsigned pos = atomicAdd(&sh.ncand, 1u);
-            if (pos < (unsigned)CAP) sh.cand[pos] = rank_key(x[i], j4 + i);
+          in[i] = __builtin_amdgcn_ballot_w64(c == 0);
+          all += (unsigned)__popcll(in[i]);
+        }
+        if (all != 0u) {   // (one addition per wave for all its members: one each, to the same word, they are served one by one)
+          unsigned first = 0;
+          if ((tid & 63) == 0) first = atomicAdd(&sh.ncand, all);
+          first = (unsigned)__builtin_amdgcn_readfirstlane((int)first);
+#pragma unroll
+          for (int i = 0; i < 4; i++) {
+            const unsigned pos = first + __builtin_amdgcn_mbcnt_hi((unsigned)(in[i] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in[i], 0u));
+            if (((in[i] >> (tid & 63)) & 1u) && pos < (unsigned)CAP) sh.cand[pos] = rank_key(x[i], j4 + i);
+            first += (unsigned)__popcll(in[i]);
           }
         }
         na += (unsigned)__popc(nib);
@@ -544,24 +568,15 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
     }
     __syncthreads();
   };
-  {
-    const int b0 = (int)sh.bin;
-    count_and_collect(
-        [&](float v) {
-          const int b = value_bin(v);
-          return b < b0 ? -1 : (b == b0 ? 0 : 1);
-        },
-        std::true_type{});
-  }
+  count_and_collect(place, std::true_type{});
 
   // The members of the crossing bin form a contiguous stretch of the ranking.  While there are too many to
   // sort, narrow the stretch: take the range [klo, khi] of their ordered score bits and histogram it again,
   // now linearly in those bits (every round divides the range by BINS, so a few rounds reach a single value).
-  bool by_value = true;     // how the current bin is defined: value_bin() == bin, or key range [klo, khi]
+  bool by_place = true;     // how the current bin is defined: place() == 0, or key range [klo, khi]
   bool bits_partial = true; // the bits in memory are those of pass 2 (everything above the first crossing bin)
   unsigned klo = 0, khi = 0;
   for (int round = 0; round < 6; round++) {
-    const unsigned bin = sh.bin;
     if (sh.bin_cnt <= (unsigned)CAP) break;
     bits_partial = false;   // members of the first bin get ranked above the final one: all bits are rewritten at the end
     // range of ordered bits inside the current bin
@@ -571,9 +586,9 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
     }
     __syncthreads();
     unsigned lo = 0xFFFFFFFFu, hi = 0u;
-    for_each_score<THREADS, DEPTH>(s, G, [&, bin, by_value, klo, khi](float v, int) {
+    for_each_score<THREADS, DEPTH>(s, G, [&, by_place, klo, khi](float v, int) {
       const unsigned o = ordered_bits(v);
-      const bool in = by_value ? (value_bin(v) == (int)bin) : (o >= klo && o <= khi);
+      const bool in = by_place ? place(v) == 0 : (o >= klo && o <= khi);
       if (in) {
         lo = min(lo, o);
         hi = max(hi, o);
@@ -584,7 +599,7 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
     __syncthreads();
     klo = sh.klo;
     khi = sh.khi;
-    by_value = false;
+    by_place = false;
     if (klo == khi) break;   // one score value left: a run of equal scores, handled by id below
     const unsigned long long R = (unsigned long long)(khi - klo) + 1ull;
     for (int i = tid; i < BINS; i += THREADS) sh.mass[i] = 0;
@@ -716,16 +731,15 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
   if (t_keep < 1) t_keep = 1;
   if (t_keep > bin_cnt) t_keep = bin_cnt;
   unsigned run = 0;   // members seen in the chunks before this one (the same in every thread)
+  const int last4 = (G - 1) & ~3;
+  f32x4 next = *reinterpret_cast<const f32x4*>(s + min(tid * 4, last4));
   for (int base = 0; base < G && (unsigned long long)run < t_keep; base += THREADS * 4) {
     const int j4 = base + tid * 4;
-    bool in[4] = {false, false, false, false};
-    if (j4 < G) {
-      const float4 v = *reinterpret_cast<const float4*>(s + j4);
-      in[0] = ordered_bits(v.x) == klo;
-      in[1] = j4 + 1 < G && ordered_bits(v.y) == klo;
-      in[2] = j4 + 2 < G && ordered_bits(v.z) == klo;
-      in[3] = j4 + 3 < G && ordered_bits(v.w) == klo;
-    }
+    const f32x4 v = next;
+    next = *reinterpret_cast<const f32x4*>(s + min(j4 + THREADS * 4, last4));
+    bool in[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) in[e] = j4 + e < G && ordered_bits(v[e]) == klo;
     unsigned total;
     unsigned pos = run + block_exclusive<THREADS>((unsigned)in[0] + in[1] + in[2] + in[3], sh.wave_tot, &total);
 #pragma unroll
@@ -751,7 +765,7 @@ __device__ __forceinline__ void select_row(SH& sh, const float* s, int64_t row, 
   for_each_score<THREADS, DEPTH>(s, G, [&](float v, int) { atomicAdd(&sh.mass[value_bin_of<BINS>(v, rmax, inv)], weight_of(v, rmax)); });
   __syncthreads();
   locate_bin<true>(sh, top_p);
-  rank_row<THREADS, BINS, CAP, DEPTH>(sh, s, row, rmax, inv, G, top_p, cut, count, keep_bits, Gw);
+  rank_row<THREADS, BINS, CAP, DEPTH>(sh, s, row, rmax, place_by_bin<BINS>(sh.bin, rmax, inv), G, top_p, cut, count, keep_bits, Gw);
 }
 
 // Row `local` of a chunk's score buffer that starts at score tile unit0: the (slice, query block) row it holds, or
@@ -1057,7 +1071,7 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
     __syncthreads();
     const float rmax = from_ordered(range[2 * row]), rmin = from_ordered(range[2 * row + 1]);
     rank_row<THREADS, BINS, CodesShared<THREADS, MAXROW, IDCAP, ID>::CAND, 2>(
-        sh, scores + local * Gs, row, rmax, bins_per_score<BINS>(rmax, rmin), G, top_p, cut, count, keep_bits, Gw);
+        sh, scores + local * Gs, row, rmax, place_by_bin<BINS>(sh.bin, rmax, bins_per_score<BINS>(rmax, rmin)), G, top_p, cut, count, keep_bits, Gw);
   }
 }
 
@@ -1169,6 +1183,12 @@ __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bit
   if (lane < (int)fill && lane >= (int)skip && to + lane < capacity) indices[to + lane] = stage[lane];
 }
 
+}  // namespace fgm
+
+#include "fgmask_stream.hpp"
+
+namespace fgm {
+
 // ---------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------
@@ -1243,6 +1263,109 @@ static int device_ok(int* cus = nullptr) {
 
 static bool launched() { return hipGetLastError() == hipSuccess; }
 
+// Lays out the score buffer (`bytes` at `at`) for the selection without scores (fgmask_stream.hpp), in chunks of whole
+// slices.  False where it does not fit, or where the selection from scores is the better one: with few scores the six kernels
+// of a chunk are mostly set-up, the more so at head dim 128, where a score takes twice the matrix work (at 128, 2 heads x 512
+// rows of 32760 scores, 34 million, 118 us from scores and 161 without; 40 x 256 x 4096, 42 million, 147 and 158; 4 x 512 x
+// 32760, 67 million, 184 and 187; 929 x 118800, 110 million, 411 and 378; 40 x 585 x 9360, 219 million, 725 and 456; at 64,
+// 12 x 256 x 16384, 50 million, 157 and 132; 24 x 929 x 3713, 83 million, 458 and 366), and a histogram has to be worth its
+// setting up for 64 rows.
+static int64_t stream_min_scores(int d) { return (int64_t)(d == 128 ? 72 : 48) << 20; }
+constexpr int64_t kStreamMinRow = 2048;
+
+static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus, StreamArgs* a) {
+  if (lo.G < kStreamMinRow || lo.rows * lo.G < stream_min_scores(d)) return false;
+  const int64_t ktiles = (lo.G + 31) / 32, per_slice = (lo.QB + kSweepRows - 1) / kSweepRows, tiles = (lo.QB + kMassRows - 1) / kMassRows;
+  a->steps = (int)((ktiles + kMassWaves - 1) / kMassWaves);
+  for (int64_t chunks = 1; chunks <= lo.slices; chunks++) {
+    const int64_t slices = (lo.slices + chunks - 1) / chunks, units = slices * per_slice, rows = slices * lo.QB;
+    // sweep: one round of the three workgroups that a compute unit holds, if the rows allow; lists for an eighth of a stretch's
+    // key blocks (about one in a hundred is a member)
+    int64_t segs = (3 * (int64_t)cus + units - 1) / units;
+    if (segs > 64) segs = 64;
+    int64_t seg_tiles = ((ktiles + segs - 1) / segs + 3) & ~(int64_t)3;
+    if (seg_tiles < 16) seg_tiles = 16;
+    segs = (ktiles + seg_tiles - 1) / seg_tiles;
+    if (segs > 64 || seg_tiles > 2047) return false;   // (a wave settles 64 lists; a list's places have 16 bits)
+    const int64_t cap = seg_tiles * 32 / 8;
+    // mass: one workgroup fits a compute unit; setting up a row tile and leaving its histogram cost it about six steps
+    const int64_t most = cus & ~7;
+    int64_t pieces = 1, turn = 1, least = INT64_MAX;
+    for (int64_t n = 1; n <= 8 && n <= a->steps; n++) {
+      const int64_t m = (slices * tiles * n + most - 1) / most, cost = m * ((a->steps + n - 1) / n) + 6 * (1 + (m + n - 1) / n);
+      if (cost < least) {
+        least = cost;
+        pieces = n;
+        turn = m;
+      }
+    }
+    const int64_t groups = ((slices * tiles * pieces + turn - 1) / turn + 7) & ~(int64_t)7;
+    size_t off = 256;
+    const size_t cuts = off;
+    off = align256(off + (size_t)rows * sizeof(RowCut));
+    const size_t hist = off, scratch = off;   // (rows of scores for overfull_kernel, when all but the cuts is done with)
+    const int over_rows = slices * ((lo.QB + 7) / 8) >= 2 * cus ? 8 : 4;   // (two workgroups to a compute unit)
+    const size_t scratch_group = (size_t)over_rows * lo.Gs * sizeof(float);
+    off = align256(off + (size_t)(groups + slices * tiles) * kMassWords * 8);
+    const size_t counts = off;
+    off = align256(off + (size_t)(rows * segs) * sizeof(uint2));
+    const size_t lists = off;
+    off = align256(off + (size_t)(rows * segs * cap) * sizeof(Member));
+    if (off > bytes || scratch + scratch_group > bytes) continue;
+    a->slices = (int)slices;
+    a->units = (int)units;
+    a->segs = (int)segs;
+    a->seg_tiles = (int)seg_tiles;
+    a->tiles = (int)(slices * tiles);
+    a->pieces = (int)pieces;
+    a->turn = (int)turn;
+    a->groups = (int)groups;
+    a->cap = (int)cap;
+    a->overfull = reinterpret_cast<unsigned*>(at);
+    a->hist = reinterpret_cast<unsigned long long*>(at + hist);
+    a->cuts = reinterpret_cast<RowCut*>(at + cuts);
+    a->counts = reinterpret_cast<uint2*>(at + counts);
+    a->lists = reinterpret_cast<Member*>(at + lists);
+    a->scratch = reinterpret_cast<float*>(at + scratch);
+    a->scratch_fits = (int)((bytes - scratch) / scratch_group < 65535 ? (bytes - scratch) / scratch_group : 65535);
+    a->over_rows = over_rows;
+    return true;
+  }
+  return false;
+}
+
+template <int D>
+static bool launch_stream(StreamArgs a, const Layout& lo, int cus, hipStream_t stream) {
+  const int64_t per_slice = (lo.QB + kSweepRows - 1) / kSweepRows, tiles = (lo.QB + kMassRows - 1) / kMassRows;
+  const int64_t over_per_slice = (lo.QB + a.over_rows - 1) / a.over_rows;
+  const int step = a.slices;
+  for (int64_t slice0 = 0; slice0 < lo.slices; slice0 += step) {
+    a.slice0 = (int)slice0;
+    a.slices = (int)(lo.slices - slice0 < step ? lo.slices - slice0 : step);
+    a.units = (int)(a.slices * per_slice);
+    a.tiles = (int)(a.slices * tiles);
+    const dim3 sweep((unsigned)((a.segs < 8 ? a.segs : (a.segs + 7) & ~7) * a.units));
+    hipLaunchKernelGGL((sweep_kernel<D, false>), sweep, dim3(256), 0, stream, a);
+    if (!launched()) return false;
+    hipLaunchKernelGGL(mass_kernel<D>, dim3(a.groups), dim3(kMassWaves * 64), 0, stream, a);
+    if (!launched()) return false;
+    hipLaunchKernelGGL(locate_kernel, dim3(2 * a.tiles), dim3(kLocateParts * 32), 0, stream, a);
+    if (!launched()) return false;
+    hipLaunchKernelGGL((sweep_kernel<D, true>), sweep, dim3(256), 0, stream, a);
+    if (!launched()) return false;
+    const int64_t rows = (int64_t)a.slices * lo.QB, waves = (rows + 3) / 4;
+    hipLaunchKernelGGL(settle_kernel, dim3((unsigned)(waves < 8 * cus ? waves : 8 * cus)), dim3(256), 0, stream, a);
+    if (!launched()) return false;
+    int64_t over = a.slices * over_per_slice;
+    if (over > 2 * cus) over = 2 * cus;
+    over = (over + 7) & ~(int64_t)7;
+    if (over > a.scratch_fits) over = a.scratch_fits >= 8 ? a.scratch_fits & ~7 : a.scratch_fits;
+    hipLaunchKernelGGL(overfull_kernel<D>, dim3((unsigned)over), dim3(kOverfullThreads), 0, stream, a);
+    if (!launched()) return false;
+  }
+  return true;
+}
+
 }  // namespace fgm
 
 extern "C" {
@@ -1298,6 +1421,29 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
   if (!launched()) return FGATTN_E_DEVICE;
   uint32_t* keep_bits = reinterpret_cast<uint32_t*>(ws + lo.bits_off);
   const unsigned gx = (unsigned)((lo.G + kTilesPerGroup * 32 - 1) / (kTilesPerGroup * 32));
+  const size_t score_bytes = lo.cut_off - lo.scores_off;
+  StreamArgs sa;
+  if (!(p->flags & (FGATTN_FLAG_MASK_ROWS_IN_HBM | FGATTN_FLAG_MASK_ONE_TILE_CHUNKS)) &&
+      plan_stream(lo, p->d, ws + lo.scores_off, score_bytes, cus, &sa)) {
+    sa.qp = qp;
+    sa.kp = kmat;
+    sa.k_slice_stride = k_slice_stride;
+    sa.k_row_stride = k_row_stride;
+    sa.scale = p->scale;
+    sa.top_p = top_p;
+    sa.QB = (int)lo.QB;
+    sa.G = (int)lo.G;
+    sa.Gw = (int)lo.Gw;
+    sa.Gs = (int)lo.Gs;
+    sa.range = range;
+    sa.cut = cut;
+    sa.count = count;
+    sa.keep_bits = keep_bits;
+    if (!(p->d == 128 ? launch_stream<128>(sa, lo, cus, stream) : launch_stream<64>(sa, lo, cus, stream)))
+      return FGATTN_E_DEVICE;
+    fgscan::launch_row_pointers(count, lo.rows, mask_indptr, stream);
+    return launched() ? FGATTN_OK : FGATTN_E_DEVICE;
+  }
   for (int64_t unit0 = 0; unit0 < lo.units; unit0 += lo.chunk_units) {
     const int64_t nunits = lo.units - unit0 < lo.chunk_units ? lo.units - unit0 : lo.chunk_units;
     const int64_t chunk_rows = nunits * 128;

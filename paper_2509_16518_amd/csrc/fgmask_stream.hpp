@@ -1,0 +1,767 @@
+// Top-p selection for many long rows without a buffer of scores: included by fgmask.hip.
+//
+// The scores of a row are formed three times by the matrix cores instead of once, and never reach memory: a score takes
+// 2 d operations, less time than its four bytes take to memory and back, and the same products in the same order
+// give the same bits each time.
+//   sweep_kernel<D, false>  the largest and the smallest score of every row
+//   mass_kernel             a histogram of mass over the row's range (LDS), as fixed-point weights
+//   locate_kernel           the bin where the descending mass crosses the target, as two thresholds on a score's product
+//   sweep_kernel<D, true>   the bits of all key blocks above that bin; a list of its members and their scores
+//   settle_kernel           ranks the members, adds the bits of those at or above the cut
+//   overfull_kernel         rows whose lists were too short: scores formed into a row of memory, then select_row
+// The matrix product has the keys in its rows and the queries in its columns, so a lane owns one query: its range, its
+// thresholds and its place in the lists are plain registers, and the 32 lanes of a histogram update name 32 different
+// banks.  Against scores in memory, both mask calls, with the same emit kernel: 12 heads x 512 rows of 32760 532 -> 365 us,
+// 24 x 929 rows of 118800 8.57 -> 4.75 ms (per eight heads of it: sweep 0.20, mass 0.50, locate 0.012, sweep 0.41, settle 0.12 ms).
+#pragma once
+
+namespace fgm {
+
+constexpr int kSweepRows = 256;      // query blocks of a sweep workgroup: four waves of 64
+constexpr int kSweepStep = 2;        // key tiles between two barriers of a sweep
+constexpr int kMassRows = 64;        // query blocks of a mass workgroup, which all its waves share
+constexpr int kMassWaves = 8;        // waves of a mass workgroup, each with key tiles of its own
+constexpr int kMassBins = 312;       // 64 rows x 312 bins x 8 bytes fill 156 of 160 KB of LDS
+constexpr int kMassWords = 2 * kMassBins * 32;   // 64-bit words of a histogram: [row / 32][bin][row % 32]
+constexpr int kSettleBins = 512;
+constexpr int kOverfullThreads = 512;
+
+struct Member {
+  float score;
+  unsigned id;
+};
+// What locate_kernel leaves for a row.  With x = (product of the row and a key block) * sign of the scale: the key block lies above the
+// crossing bin if x >= above, in it or above it if x >= inside.
+struct alignas(16) RowCut {
+  float neg_above, neg_inside;       // (negated)
+  unsigned lo, hi;                   // ordered bits of the scores that the bin can hold
+  unsigned long long mass_above, target;
+};
+
+struct StreamArgs {
+  const uint16_t* qp;                // block means of Q: [slice][QB][D]
+  const uint16_t* kp;                // of K (or K itself)
+  int64_t k_slice_stride, k_row_stride;   // elements
+  float scale, top_p;
+  int QB, G, Gw, Gs;
+  int slice0, slices;                // of this chunk
+  int units, segs, seg_tiles;        // sweep: workgroup rows of kSweepRows, stretches of key tiles, tiles of a stretch
+  int tiles, steps;                  // mass: row tiles of kMassRows, steps (of kMassWaves key tiles) per row tile
+  int pieces, turn, groups;          // pieces of a row tile's steps, pieces per workgroup, workgroups (a multiple of eight)
+  int cap;                           // list entries per row and stretch
+  unsigned* range;                   // [row] (max, min) as ordered bits
+  unsigned long long* hist;          // [workgroup + row tile][kMassWords]
+  RowCut* cuts;                      // [row of the chunk]
+  uint2* counts;                     // [row of the chunk][stretch]: key blocks above the bin, members
+  Member* lists;                     // [row of the chunk][stretch][cap]
+  unsigned long long* cut;           // [row]
+  unsigned* count;                   // [row]; 0 marks a row left to overfull_kernel
+  uint32_t* keep_bits;               // [row][Gw]
+  unsigned* overfull;                // number of such rows
+  int over_rows;                     // overfull_kernel: rows formed at a time, 8 or 4
+  float* scratch;                    // over_rows x Gs floats per workgroup,
+  int scratch_fits;                  // for this many workgroups at most
+};
+
+// ---- arithmetic that several kernels have to agree on to the last bit (no contraction into fused operations) ----
+// first value of a histogram bin's float form: 2^23 + bin has the bin in its low bits
+constexpr float kBinBias = 8388608.0f;
+
+// bins per unit of score, negated; 0 for a row of equal scores
+__device__ __forceinline__ float neg_bins_per_score(float rmax, float rmin) {
+#pragma clang fp contract(off)
+  const float width = rmax - rmin;
+  return width > 0.0f ? -(float)(kMassBins - 1) / width : 0.0f;
+}
+// below = score - rmax (not positive).  The low 16 bits of the result are the bin, falling scores in rising bins (0 to
+// kMassBins - 1; 0 also for what infinite scores make of it).
+__device__ __forceinline__ float biased_bin(float below, float neg_bins) { return __builtin_fmaf(below, neg_bins, kBinBias); }
+// Rounds results of 64-bit floating point toward zero from here on (MODE register, bits 3:2), as mass_update needs.  (No other
+// 64-bit float instruction may be in the kernel: the compiler would set the mode back ahead of it.)
+__device__ __forceinline__ void round_f64_toward_zero() { __builtin_amdgcn_s_setreg(1 | (2 << 6) | (1 << 11), 3); }
+// Of four scores: weight = weight_below(below) and place = bin * 256 + base.  2^-1074 is the unit of a 64-bit float without
+// an exponent, so the product of e = exp2(..) with 2^(40 - 1074), rounded toward zero, holds trunc(2^40 e) as its bits: two
+// instructions for five.  In one statement because the compiler does not know the mode; the instructions between an exponential
+// and the use of its result are the wait states that the hardware asks for there, and four at a time keep results from
+// being waited for.
+__device__ __forceinline__ void mass_update(const float (&below)[4], float neg_bins, unsigned base, unsigned long long (&weight)[4], unsigned (&place)[4]) {
+  float e0, e1, e2, e3;
+  asm("v_exp_f32 %0, %12\n\t"
+      "v_exp_f32 %1, %13\n\t"
+      "v_exp_f32 %2, %14\n\t"
+      "v_exp_f32 %3, %15\n\t"
+      "v_mad_u32_u16 %4, %16, %20, %21\n\t"
+      "v_mad_u32_u16 %5, %17, %20, %21\n\t"
+      "v_mad_u32_u16 %6, %18, %20, %21\n\t"
+      "v_mad_u32_u16 %7, %19, %20, %21\n\t"
+      "v_cvt_f64_f32 %8, %0\n\t"
+      "v_cvt_f64_f32 %9, %1\n\t"
+      "v_cvt_f64_f32 %10, %2\n\t"
+      "v_cvt_f64_f32 %11, %3\n\t"
+      "v_mul_f64 %8, %8, %22\n\t"
+      "v_mul_f64 %9, %9, %22\n\t"
+      "v_mul_f64 %10, %10, %22\n\t"
+      "v_mul_f64 %11, %11, %22"
+      : "=&v"(e0), "=&v"(e1), "=&v"(e2), "=&v"(e3), "=&v"(place[0]), "=&v"(place[1]), "=&v"(place[2]), "=&v"(place[3]),
+        "=&v"(weight[0]), "=&v"(weight[1]), "=&v"(weight[2]), "=&v"(weight[3])
+      : "v"(below[0] * kLog2e), "v"(below[1] * kLog2e), "v"(below[2] * kLog2e), "v"(below[3] * kLog2e),
+        "v"(biased_bin(below[0], neg_bins)), "v"(biased_bin(below[1], neg_bins)), "v"(biased_bin(below[2], neg_bins)),
+        "v"(biased_bin(below[3], neg_bins)), "s"(256), "v"(base), "s"(1ull << 40));
+}
+__device__ __forceinline__ float score_of(float product, float scale) {
+#pragma clang fp contract(off)
+  return product * scale;
+}
+__device__ __forceinline__ float below_max(float score, float rmax) {
+#pragma clang fp contract(off)
+  return score - rmax;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Sweep: 256 query blocks (64 per wave, B operand, kept in registers: each operand read from LDS serves two matrix instructions)
+// against a stretch of key tiles of 32, read once per workgroup and passed through XOR-swizzled LDS (as in scores_kernel).
+// Bound: the first by the matrix cores at the clock that the power limit leaves them (226 GFLOP in 0.20 ms, the rate of a large
+// matrix product); the second, 0.41 ms, by vector instructions (61% of issue slots) and by waits around the members' stores.
+//   EMIT false: each row's largest and smallest score, two atomics per row and workgroup.
+//   EMIT true:  a bit per pair (above the crossing bin), and the members of the bin.  The sign of (threshold - product) is
+//               shifted into a word per lane, two instructions per score and threshold.  A row belongs to one wave, so places
+//               in its list are counted in registers.
+// ---------------------------------------------------------------------------------------------
+template <int D, bool EMIT>
+__global__ void __launch_bounds__(256, 3) sweep_kernel(const StreamArgs a) {
+  constexpr int STEPS = D / 16, ROWB = D * 2, CHUNKS = ROWB / 16, TILEB = 32 * ROWB, LPT = kSweepStep * TILEB / 16 / 256;
+  __shared__ __attribute__((aligned(16))) unsigned char ktile[2][kSweepStep * TILEB];
+  __shared__ f32x4 picks[EMIT ? 4 : 1][EMIT ? 4 : 1][64];   // a wave's products: [wave][register / 4][lane][register % 4]
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 31, g = lane >> 5;
+  // (see kShareUnits: every XCD keeps to its own eighth of the stretches)
+  int local_unit, seg;
+  if (a.segs < 8) {
+    local_unit = blockIdx.x / a.segs;
+    seg = blockIdx.x - local_unit * a.segs;
+  } else {
+    const int xcd_segs = (a.segs + 7) >> 3, j = blockIdx.x >> 3;
+    const int first = j / (xcd_segs * kShareUnits) * kShareUnits, r = j - first * xcd_segs;
+    const int share = min(kShareUnits, a.units - first);
+    local_unit = first + r % share;
+    seg = r / share * 8 + (blockIdx.x & 7);
+    if (seg >= a.segs) return;
+  }
+  const int per_slice = (a.QB + kSweepRows - 1) / kSweepRows;
+  const int local_slice = local_unit / per_slice, slice = a.slice0 + local_slice;
+  const int q0 = (local_unit - local_slice * per_slice) * kSweepRows + wv * 64;
+  const bool busy = q0 < a.QB;   // (a wave past the last query block still helps with the tiles)
+  auto swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  bf16x8 qf[2][STEPS];
+#pragma unroll
+  for (int grp = 0; grp < 2; grp++) {
+    const char* src = reinterpret_cast<const char*>(a.qp + ((int64_t)slice * a.QB + min(q0 + 32 * grp + ln, a.QB - 1)) * D);
+#pragma unroll
+    for (int s = 0; s < STEPS; s++) qf[grp][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(src + (2 * s + g) * 16));
+  }
+  const char* kbase = reinterpret_cast<const char*>(a.kp + slice * a.k_slice_stride);
+  i32x4 stage[LPT];
+  auto fetch_tile = [&](int tile) {   // key blocks past the end repeat the last one
+#pragma unroll
+    for (int i = 0; i < LPT; i++) {
+      const int ci = i * 256 + tid, row = ci / CHUNKS, c = ci % CHUNKS;
+      stage[i] = *reinterpret_cast<const i32x4*>(kbase + (int64_t)min(tile * 32 + row, a.G - 1) * a.k_row_stride * 2 + c * 16);
+    }
+  };
+  auto stash_tile = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < LPT; i++) {
+      const int ci = i * 256 + tid, row = ci / CHUNKS, c = ci % CHUNKS;
+      *reinterpret_cast<i32x4*>(&ktile[buf][row * ROWB + ((c ^ swz(row)) * 16)]) = stage[i];
+    }
+  };
+  const int tile0 = seg * a.seg_tiles;
+  const int ntiles = min(a.seg_tiles, (a.G - tile0 * 32 + 31) / 32);   // >= 1 by the grid
+  // range
+  float most[2] = {-INFINITY, -INFINITY}, least[2] = {INFINITY, INFINITY};
+  // bits and members: this lane's queries (of both groups, for the products), and row (group g, ln) (for the words)
+  const float sign = a.scale < 0.0f ? -1.0f : 1.0f;
+  float neg_above[2], neg_inside[2];
+  unsigned list[2];            // first list entry of the queries
+  unsigned listed = 0;         // members so far, of group 0 and (upper half) of group 1; the same in both lanes of a query
+  unsigned kept = 0;
+  unsigned words[4];
+  uint32_t* bits_row = nullptr;
+  bool row_ok = false;
+  if constexpr (EMIT) {
+#pragma unroll
+    for (int grp = 0; grp < 2; grp++) {
+      const int row = local_slice * a.QB + min(q0 + 32 * grp + ln, a.QB - 1);
+      neg_above[grp] = a.cuts[row].neg_above;
+      neg_inside[grp] = a.cuts[row].neg_inside;
+      if (q0 + 32 * grp + ln >= a.QB) neg_above[grp] = neg_inside[grp] = -INFINITY;   // no row: nothing is at or above
+      list[grp] = ((unsigned)row * (unsigned)a.segs + (unsigned)seg) * (unsigned)a.cap;
+    }
+    const int q = q0 + 32 * g + ln;
+    row_ok = q < a.QB;
+    bits_row = a.keep_bits + ((int64_t)slice * a.QB + min(q, a.QB - 1)) * a.Gw;
+  }
+  fetch_tile(tile0);
+  stash_tile(0);
+  __syncthreads();
+  for (int t0 = 0; t0 < ntiles; t0 += kSweepStep) {
+    if (t0 + kSweepStep < ntiles) fetch_tile(tile0 + t0 + kSweepStep);
+    bool stashed = false;
+#pragma unroll
+    for (int sub = 0; sub < kSweepStep; sub++) {
+      const int t = t0 + sub;
+      if (!busy || t >= ntiles) break;
+      const unsigned char* kt = ktile[(t0 / kSweepStep) & 1] + sub * TILEB;
+      f32x16 acc[2];
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[0][r] = acc[1][r] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) {
+        const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(kt + ln * ROWB + (((2 * s + g) ^ swz(ln)) * 16)));
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0][s], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[1][s], acc[1], 0, 0, 0);
+      }
+      if constexpr (!EMIT) {
+#pragma unroll
+        for (int grp = 0; grp < 2; grp++)
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            most[grp] = fmaxf(fmaxf(most[grp], acc[grp][r]), acc[grp][r + 1]);
+            least[grp] = fminf(fminf(least[grp], acc[grp][r]), acc[grp][r + 1]);
+          }
+      } else {
+        const int key0 = (tile0 + t) * 32;
+        const unsigned valid = key0 + 32 <= a.G ? ~0u : ~0u >> (32 - (a.G - key0));   // (the same in all lanes)
+        unsigned spread[2], member[2];
+#pragma unroll
+        for (int grp = 0; grp < 2; grp++) {
+          unsigned not_above = 0, not_inside = 0;   // bit r: accumulator register r, key 8 (r / 4) + 4 g + r % 4 of the tile
+#pragma unroll
+          for (int r = 15; r >= 0; r--) {
+            const float da = __builtin_fmaf(acc[grp][r], sign, neg_above[grp]), di = __builtin_fmaf(acc[grp][r], sign, neg_inside[grp]);
+            not_above = __builtin_amdgcn_alignbit(not_above, __float_as_uint(da), 31);
+            not_inside = __builtin_amdgcn_alignbit(not_inside, __float_as_uint(di), 31);
+          }
+          unsigned x = ~not_above & 0xFFFFu;
+          x = (x | (x << 8)) & 0x00FF00FFu;
+          spread[grp] = (x | (x << 4)) & 0x0F0F0F0Fu;
+          unsigned m = not_above & ~not_inside & 0xFFFFu;
+          if (valid != ~0u) {
+            unsigned v = (valid >> (4 * g)) & 0x0F0F0F0Fu;
+            v = (v | (v >> 4)) & 0x00FF00FFu;
+            m &= (v | (v >> 8)) & 0xFFFFu;
+          }
+          member[grp] = m;
+        }
+        // lanes of the first half collect the words of group 0, of the second half those of group 1
+        const auto halves = __builtin_amdgcn_permlane32_swap(spread[0], spread[1], false, false);
+        const unsigned word = (halves[0] | (halves[1] << 4)) & valid;
+        kept += (unsigned)__popc(word);
+        words[t & 3] = word;
+        if (row_ok) {
+          uint32_t* const to = bits_row + tile0 + (t & ~3);
+          if ((t & 3) == 3) {
+            struct __attribute__((packed, aligned(4))) Four { uint32_t w[4]; };   // (rows start on 4-byte boundaries)
+            *reinterpret_cast<Four*>(to) = Four{{words[0], words[1], words[2], words[3]}};
+          } else if (t + 1 == ntiles) {
+            to[0] = words[0];
+            if ((t & 3) > 0) to[1] = words[1];
+            if ((t & 3) > 1) to[2] = words[2];
+          }
+        }
+        // The next tiles go to LDS before the members' stores: after them, the wait for their loads (they complete in order) would
+        // be one for the stores too.
+        if (!stashed && (sub == kSweepStep - 1 || t + 1 == ntiles)) {
+          if (t0 + kSweepStep < ntiles) stash_tile((t0 / kSweepStep + 1) & 1);
+          stashed = true;
+        }
+        if (__builtin_amdgcn_ballot_w64((member[0] | member[1]) != 0u) != 0) {
+          const unsigned mine = (unsigned)__popc(member[0]) | ((unsigned)__popc(member[1]) << 16);
+          const auto both = __builtin_amdgcn_permlane32_swap(mine, mine, false, false);   // of the first half's lane, of the second's
+          const unsigned start = listed + (g ? both[0] : 0u);
+          listed += both[0] + both[1];
+#pragma unroll
+          for (int grp = 0; grp < 2; grp++) {
+            unsigned pos = grp ? start >> 16 : start & 0xFFFFu, m = member[grp];
+            // (which register it is differs from lane to lane: LDS can be indexed so; a selection tree takes 20 instructions)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; r4++)
+              picks[wv][r4][lane] = f32x4{acc[grp][4 * r4], acc[grp][4 * r4 + 1], acc[grp][4 * r4 + 2], acc[grp][4 * r4 + 3]};
+            const float* const mine_at = reinterpret_cast<const float*>(&picks[wv][0][lane]);
+            while (m != 0u && pos < (unsigned)a.cap) {
+              const int r = __ffs(m) - 1;
+              m &= m - 1;
+              const float product = mine_at[(r >> 2) * 256 + (r & 3)];
+              a.lists[list[grp] + pos] = Member{score_of(product, a.scale), (unsigned)(key0 + 8 * (r >> 2) + 4 * g + (r & 3))};
+              pos++;
+            }
+          }
+        }
+      }
+    }
+    if (!stashed && t0 + kSweepStep < ntiles) stash_tile((t0 / kSweepStep + 1) & 1);   // (the buffer that was read before the last barrier)
+    __syncthreads();
+  }
+  if (!busy) return;
+  if constexpr (!EMIT) {
+#pragma unroll
+    for (int grp = 0; grp < 2; grp++) {
+      const float hi = fmaxf(most[grp], __shfl_xor(most[grp], 32)), lo = fminf(least[grp], __shfl_xor(least[grp], 32));
+      const float s0 = score_of(hi, a.scale), s1 = score_of(lo, a.scale);   // (rounding keeps the order)
+      const int q = q0 + 32 * grp + ln;
+      if (g == 0 && q < a.QB) {
+        unsigned* rr = a.range + 2 * ((int64_t)slice * a.QB + q);
+        atomicMax(rr, ordered_bits(fmaxf(s0, s1)));
+        atomicMin(rr + 1, ordered_bits(fminf(s0, s1)));
+      }
+    }
+  } else {
+    if (row_ok) {
+      const int row = local_slice * a.QB + q0 + 32 * g + ln;
+      a.counts[(int64_t)row * a.segs + seg] = make_uint2(kept, g ? listed >> 16 : listed & 0xFFFFu);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Histogram of mass.  A workgroup of eight waves keeps 64 query blocks in registers (all waves the same) and their histograms
+// in LDS, and walks over key tiles, eight at a step, one per wave, whose operands each wave loads for itself (a tile is
+// used by no other wave; through LDS, whole rows at a time, the same loads take 532 us instead of 504 per eight heads of 118800
+// rows).  Bound: vector instructions, eleven per score of which the exponential takes two slots and the conversion to
+// 64 bits two (59% of issue slots; 25% more of them, with the weight formed by 32-bit operations, 7% more time), the
+// histogram's updates (one per score, 8 clocks of LDS per 64) and the matrix instructions, which issue between them.
+// ---------------------------------------------------------------------------------------------
+template <int D>
+__global__ void __launch_bounds__(kMassWaves * 64, 2) mass_kernel(const StreamArgs a) {
+  constexpr int STEPS = D / 16, THREADS = kMassWaves * 64;
+  __shared__ __attribute__((aligned(16))) struct {
+    unsigned long long hist[kMassWords];
+  } sh;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 31, g = lane >> 5;
+  const int per_slice = (a.QB + kMassRows - 1) / kMassRows;
+  round_f64_toward_zero();
+  for (int i = tid * 2; i < kMassWords; i += THREADS * 2) *reinterpret_cast<ulonglong2*>(&sh.hist[i]) = ulonglong2{0ull, 0ull};
+  // A row tile's keys are cut into `pieces`, and a workgroup takes `turn` consecutive pieces of the line of all of them (slice,
+  // row tile, piece).  The line is dealt to the XCDs in eighths, so that the workgroups of an XCD that begin at the same of
+  // the few places of K walk over it in step and it comes through L2 once for them.  (Any places: 7 TB/s of K from beyond L2.)
+  const int group = (blockIdx.x & 7) * (a.groups >> 3) + (int)(blockIdx.x >> 3);
+  const int last = min((group + 1) * a.turn, a.tiles * a.pieces);
+  for (int piece = group * a.turn; piece < last;) {
+    const int tile = piece / a.pieces, local_slice = tile / per_slice;
+    const int first_piece = piece - tile * a.pieces, end_piece = min(last - tile * a.pieces, a.pieces);
+    const int slice = a.slice0 + local_slice, q0 = (tile - local_slice * per_slice) * kMassRows;
+    const int s0 = (int)((int64_t)first_piece * a.steps / a.pieces), s1 = (int)((int64_t)end_piece * a.steps / a.pieces);
+    piece += end_piece - first_piece;
+    bf16x8 qf[2][STEPS];
+    float rmax[2], neg_bins[2];
+#pragma unroll
+    for (int grp = 0; grp < 2; grp++) {
+      const int64_t row = (int64_t)slice * a.QB + min(q0 + 32 * grp + ln, a.QB - 1);
+      const char* src = reinterpret_cast<const char*>(a.qp + row * D);
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) qf[grp][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(src + (2 * s + g) * 16));
+      rmax[grp] = from_ordered(a.range[2 * row]);
+      neg_bins[grp] = neg_bins_per_score(rmax[grp], from_ordered(a.range[2 * row + 1]));
+    }
+    const char* kbase = reinterpret_cast<const char*>(a.kp + slice * a.k_slice_stride);
+    i32x4 keys_a[STEPS], keys_b[STEPS];   // of even and odd steps from s0 on
+    auto fetch = [&](i32x4 (&kf)[STEPS], int step) {   // key blocks past the end repeat the last one
+      const char* src = kbase + (int64_t)min((step * kMassWaves + wv) * 32 + ln, a.G - 1) * a.k_row_stride * 2 + g * 16;
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) kf[s] = *reinterpret_cast<const i32x4*>(src + s * 32);
+    };
+    const unsigned base = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sh.hist + ln * 8;
+    // products of the wave's tile of a step (its keys are in kf), the next one's keys on their way; between(i) fills the
+    // slots after each pair of matrix instructions with the work of the tile before
+    auto products = [&](f32x16 (&acc)[2], const i32x4 (&kf)[STEPS], i32x4 (&kf_next)[STEPS], int next, auto&& between) {
+#pragma unroll
+      for (int r = 0; r < 16; r++) acc[0][r] = acc[1][r] = 0.0f;
+      fetch(kf_next, next);
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) {
+        const bf16x8 k8 = __builtin_bit_cast(bf16x8, kf[s]);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k8, qf[0][s], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k8, qf[1][s], acc[1], 0, 0, 0);
+        between(s);
+      }
+    };
+    // registers r .. r + 3 of a group's products into the histogram, or only the first n of them
+    auto add = [&](const f32x16 (&acc)[2], int grp, int r, int n) {
+      float below[4];
+      unsigned long long weight[4];
+      unsigned place[4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) below[i] = below_max(score_of(acc[grp][r + i], a.scale), rmax[grp]);
+      mass_update(below, neg_bins[grp], base + grp * (kMassBins * 256), weight, place);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        if (i < n)
+          __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long*)place[i], weight[i], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // the tile of `step` (products in cur) into the histogram, and the products of the next one's into nxt
+    auto one_step = [&](int step, const f32x16 (&cur)[2], f32x16 (&nxt)[2], const i32x4 (&kf)[STEPS], i32x4 (&kf_next)[STEPS]) {
+      const int key0 = (step * kMassWaves + wv) * 32;
+      constexpr int PER = 32 / STEPS;
+      if (key0 + 32 <= a.G && step + 1 < s1) {
+        products(nxt, kf, kf_next, min(step + 2, s1 - 1), [&](int slot_no) {
+#pragma unroll
+          for (int x = 0; x < PER; x += 4) add(cur, (slot_no * PER + x) >> 4, (slot_no * PER + x) & 15, 4);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        return;
+      }
+#pragma unroll
+      for (int grp = 0; grp < 2; grp++)
+#pragma unroll
+        for (int r = 0; r < 16; r += 4) add(cur, grp, r, a.G - (key0 + 2 * r + 4 * g));
+      if (step + 1 < s1) products(nxt, kf, kf_next, min(step + 2, s1 - 1), [](int) {});
+    };
+    f32x16 even[2], odd[2];
+    fetch(keys_a, s0);
+    products(even, keys_a, keys_b, min(s0 + 1, s1 - 1), [](int) {});
+    __syncthreads();   // the histogram is clear
+#pragma unroll 1
+    for (int step = s0; step < s1; step += 2) {
+      one_step(step, even, odd, keys_b, keys_a);
+      if (step + 1 < s1) one_step(step + 1, odd, even, keys_a, keys_b);
+    }
+    __syncthreads();
+    unsigned long long* const out = a.hist + (int64_t)(group + tile) * kMassWords;
+    for (int i = tid * 2; i < kMassWords; i += THREADS * 2) {
+      *reinterpret_cast<ulonglong2*>(out + i) = *reinterpret_cast<const ulonglong2*>(&sh.hist[i]);
+      *reinterpret_cast<ulonglong2*>(&sh.hist[i]) = ulonglong2{0ull, 0ull};
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The crossing bin of 32 rows: the parts of their histograms are added, a prefix over the bins meets the target, and the
+// bin's two edges become thresholds on the product (by bisection over all floats, with the arithmetic of the histogram).
+// ---------------------------------------------------------------------------------------------
+constexpr int kLocateParts = 24;   // threads per row
+__global__ void __launch_bounds__(kLocateParts * 32) locate_kernel(const StreamArgs a) {
+  constexpr int PARTS = kLocateParts, PER = kMassBins / PARTS;
+  static_assert(kMassBins % PARTS == 0, "whole parts");
+  __shared__ unsigned long long part_mass[PARTS][32];
+  __shared__ unsigned crossing[32];
+  __shared__ unsigned long long above[32], goal[32];
+  __shared__ float edge[2][32];
+  const int tid = threadIdx.x, ln = tid & 31, part = tid >> 5;
+  const int tile = blockIdx.x >> 1, grp = blockIdx.x & 1;
+  if (blockIdx.x == 0 && tid == 0) *a.overfull = 0;
+  const int per_slice = (a.QB + kMassRows - 1) / kMassRows;
+  const int local_slice = tile / per_slice, q = (tile - local_slice * per_slice) * kMassRows + 32 * grp + ln;
+  unsigned long long mass[PER] = {};
+  for (int group = tile * a.pieces / a.turn; group <= ((tile + 1) * a.pieces - 1) / a.turn; group++) {
+    const unsigned long long* h = a.hist + (int64_t)(group + tile) * kMassWords + (grp * kMassBins + part * PER) * 32 + ln;
+#pragma unroll
+    for (int i = 0; i < PER; i++) mass[i] += h[i * 32];
+  }
+  unsigned long long mine = 0;
+#pragma unroll
+  for (int i = 0; i < PER; i++) mine += mass[i];
+  part_mass[part][ln] = mine;
+  if (tid < 32) crossing[tid] = kMassBins - 1;
+  __syncthreads();
+  unsigned long long run = 0, Z = 0;
+  for (int p = 0; p < PARTS; p++) {
+    if (p == part) run = Z;
+    Z += part_mass[p][ln];
+  }
+  const double t = ceil((double)a.top_p * (double)Z);
+  unsigned long long target = t < 1.0 ? 1ull : (unsigned long long)t;
+  if (target > Z) target = Z;
+  if (part == 0) {
+    goal[ln] = target;
+    above[ln] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; i++) {
+    if (run < target && target <= run + mass[i]) {
+      crossing[ln] = (unsigned)(part * PER + i);
+      above[ln] = run;
+    }
+    run += mass[i];
+  }
+  __syncthreads();
+  const bool ok = q < a.QB;
+  const int64_t row = (int64_t)(a.slice0 + local_slice) * a.QB + min(q, a.QB - 1);
+  const float rmax = from_ordered(a.range[2 * row]);
+  const float mag = fabsf(a.scale);
+  if (part < 2) {
+    // the smallest x whose bin is below `limit` (part 0: above the crossing bin; part 1: in it or above)
+    const float limit = kBinBias + (float)(crossing[ln] + part);
+    const float neg_bins = neg_bins_per_score(rmax, from_ordered(a.range[2 * row + 1]));
+    auto higher = [&](unsigned o) {
+      return biased_bin(below_max(score_of(from_ordered(o), mag), rmax), neg_bins) < limit;
+    };
+    unsigned lo = ordered_bits(-3.402823466e38f), hi = ordered_bits(3.402823466e38f);
+    float x;
+    if (higher(lo)) {
+      x = -INFINITY;
+    } else if (!higher(hi)) {
+      x = INFINITY;
+    } else {   // not higher(lo), higher(hi)
+      while (hi - lo > 1u) {
+        const unsigned mid = lo + ((hi - lo) >> 1);
+        if (higher(mid)) hi = mid;
+        else lo = mid;
+      }
+      x = from_ordered(hi);
+    }
+    edge[part][ln] = x;
+  }
+  __syncthreads();
+  if (part == 0 && ok) {
+    RowCut c;
+    const float xa = edge[0][ln], xi = edge[1][ln];
+    c.neg_above = -xa;
+    c.neg_inside = -xi;
+    // ordered bits of the bin's scores: below that of the first one above it, not below that of its own first one
+    c.hi = xa == INFINITY ? ordered_bits(rmax) : ordered_bits(score_of(xa, mag)) - 1u;
+    c.lo = xi == -INFINITY ? 0u : ordered_bits(score_of(xi, mag));
+    c.mass_above = above[ln];
+    c.target = goal[ln];
+    a.cuts[(int64_t)local_slice * a.QB + q] = c;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The cut of a row among the members of its crossing bin: one wave per row, no barriers.  Rounds of 512 bins over the
+// range of rank keys (score, then lower id) that holds the cut, until 64 or fewer are left (one, by then, in a run of
+// equal scores), which are ranked by counting.
+// ---------------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
+  __shared__ unsigned long long all_mass[4][kSettleBins];
+  __shared__ unsigned long long all_cand[4][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  unsigned long long* const mass = all_mass[wv];
+  unsigned long long* const cand = all_cand[wv];
+  const int rows = a.slices * a.QB;
+  auto order = []() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };   // (LDS operations of a wave complete in order)
+  for (int local = blockIdx.x * 4 + wv; local < rows; local += gridDim.x * 4) {
+    const int64_t row = (int64_t)a.slice0 * a.QB + local;
+    const RowCut c = a.cuts[local];
+    const float rmax = from_ordered(a.range[2 * row]);
+    uint2 n = make_uint2(0u, 0u);   // of stretch `lane`
+    if (lane < a.segs) n = a.counts[(int64_t)local * a.segs + lane];
+    if (__builtin_amdgcn_ballot_w64(n.y > (unsigned)a.cap) != 0) {
+      if (lane == 0) {
+        a.count[row] = 0u;
+        atomicAdd(a.overfull, 1u);
+      }
+      continue;
+    }
+    unsigned kept = n.x;
+    for (int off = 32; off > 0; off >>= 1) kept += __shfl_xor(kept, off);
+    const Member* const lists = a.lists + (int64_t)local * a.segs * a.cap;
+    // fn(key, there is one), by all lanes together: half a wave per list (256 consecutive bytes), four pairs of lists and
+    // two steps of each in flight
+    auto for_each = [&](auto&& fn) {
+      for (int seg = 0; seg < a.segs; seg += 8) {
+        unsigned len[4], longest = 0;
+        const Member* list[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int s0 = min(seg + 2 * e, 62);   // (stretches past the last have empty lists; 64 at most, an even number before the last)
+          const unsigned n0 = seg + 2 * e < 64 ? (unsigned)__builtin_amdgcn_readlane((int)n.y, s0) : 0u;
+          const unsigned n1 = seg + 2 * e < 64 ? (unsigned)__builtin_amdgcn_readlane((int)n.y, s0 + 1) : 0u;
+          len[e] = lane < 32 ? n0 : n1;
+          longest = max(longest, max(n0, n1));
+          list[e] = lists + (int64_t)min(s0 + (lane >> 5), a.segs - 1) * a.cap;
+        }
+        for (unsigned base = 0; base < longest; base += 64) {
+          Member m[2][4];
+#pragma unroll
+          for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              if (base + 32 * h < longest) m[h][e] = list[e][min(base + 32 * h + (lane & 31), (unsigned)(a.cap - 1))];
+#pragma unroll
+          for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+              if (base + 32 * h < longest) fn(rank_key(m[h][e].score, (int)m[h][e].id), base + 32 * h + (lane & 31) < len[e]);
+        }
+      }
+    };
+    unsigned long long klo = (unsigned long long)c.lo << 32, khi = ((unsigned long long)c.hi << 32) | 0xFFFFFFFFull;
+    unsigned long long before = c.mass_above, cut_key = ~0ull;
+    uint32_t* const bits_row = a.keep_bits + row * a.Gw;
+    auto keep = [&](unsigned long long key) {
+      const unsigned id = 0xFFFFFFFFu - (unsigned)key;
+      atomicOr(&bits_row[id >> 5], 1u << (id & 31));
+    };
+    unsigned found = 0;
+    for (int round = 0; round < 9; round++) {
+      const unsigned long long span = khi - klo;
+      const int bits = span == 0 ? 0 : 64 - __clzll((long long)span);
+      const int shift = max(0, bits - 9);
+      for (int i = lane; i < kSettleBins; i += 64) mass[i] = 0;
+      order();
+      for_each([&](unsigned long long key, bool is) {
+        if (is && key >= klo && key <= khi)
+          atomicAdd(&mass[(khi - key) >> shift], weight_of(from_ordered((unsigned)(key >> 32)), rmax));
+      });
+      order();
+      // the crossing bin: eight consecutive bins per lane
+      constexpr int PER = kSettleBins / 64;
+      unsigned long long own[PER], sum = 0;
+#pragma unroll
+      for (int i = 0; i < PER; i++) sum += own[i] = mass[lane * PER + i];
+      unsigned long long incl = sum;
+      for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+      }
+      unsigned long long run = before + incl - sum;
+      const uint64_t reach = __builtin_amdgcn_ballot_w64(before + incl >= c.target);
+      const int owner = reach ? __ffsll((unsigned long long)reach) - 1 : 63;   // (the last one if the masses fell short)
+      int bin = PER - 1;
+#pragma unroll
+      for (int i = 0; i < PER - 1; i++)
+        if (bin == PER - 1) {
+          if (run + own[i] >= c.target) bin = i;
+          else run += own[i];
+        }
+      bin = __shfl(lane * PER + bin, owner);
+      before = __shfl(run, owner);
+      const unsigned long long top = khi;   // (what lies above the range has been dealt with)
+      khi -= (unsigned long long)bin << shift;
+      const unsigned long long deep = (1ull << shift) - 1ull;
+      if (khi - klo > deep) klo = khi - deep;
+      // those above the bin are kept; how many are in it, and the first 64 of them
+      found = 0;
+      for_each([&](unsigned long long key, bool is) {
+        if (is && key > khi && key <= top) keep(key);
+        kept += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(is && key > khi && key <= top));
+        const bool in = is && key >= klo && key <= khi;
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(in);
+        const unsigned pos = found + __builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
+        if (in && pos < 64u) cand[pos] = key;
+        found += (unsigned)__popcll(lanes);
+      });
+      order();
+      if (found <= 64u) break;
+    }
+    if (found > 0u) {
+      const int cn = (int)min(found, 64u);
+      const unsigned long long key = lane < cn ? cand[lane] : 0ull;
+      int rank = 0;
+      for (int j = 0; j < cn; j++) {
+        const unsigned long long other = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(key >> 32), j) << 32) |
+                                         (unsigned)__builtin_amdgcn_readlane((int)(unsigned)key, j);
+        rank += other > key ? 1 : 0;
+      }
+      order();
+      if (lane < cn) {
+        mass[rank] = weight_of(from_ordered((unsigned)(key >> 32)), rmax);
+        cand[rank] = key;
+      }
+      order();
+      unsigned long long incl = lane < cn ? mass[lane] : 0ull;
+      for (int off = 1; off < 64; off <<= 1) {
+        const unsigned long long up = __shfl_up(incl, off);
+        if (lane >= off) incl += up;
+      }
+      const uint64_t reach = __builtin_amdgcn_ballot_w64(lane < cn && before + incl >= c.target);
+      cut_key = cand[reach ? __ffsll((unsigned long long)reach) - 1 : cn - 1];
+      order();
+      if (lane < cn && key >= cut_key) keep(key);
+      kept += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(lane < cn && key >= cut_key));
+    }   // (none found is out of reach: the crossing bin has mass, hence members)
+    if (lane == 0) {
+      a.cut[row] = cut_key;
+      a.count[row] = kept;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Rows with more members in some stretch than its list takes (scores crowded beside a few that stand out, many equal
+// ones): eight or four rows at a time are formed into memory, and the selection goes on from the crossing bin as it does for
+// rows of kept scores.  Bound: reading K once per such group, then the latency of a row's passes.  6144 rows of 32760 equal
+// scores, eight at a time 2.07 ms for the select call (four 2.65, sixteen 3.09; from kept scores 1.56); 1858 of 118800, which
+// make too few groups of eight, four at a time 2.06 ms (eight 2.20; from kept scores 2.17); 6144 rows of 32760 scores crowded
+// beside one large one 0.27 ms (from kept scores 0.96).
+// ---------------------------------------------------------------------------------------------
+template <int D>
+__global__ void __launch_bounds__(kOverfullThreads, 4) overfull_kernel(const StreamArgs a) {
+  constexpr int STEPS = D / 16, WAVES = kOverfullThreads / 64;
+  if (*a.overfull == 0) return;
+  __shared__ SelShared<kOverfullThreads, kBins, kCap> sh;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 31, g = lane >> 5;
+  const int per_slice = (a.QB + a.over_rows - 1) / a.over_rows;
+  float* const scratch = a.scratch + (int64_t)blockIdx.x * a.over_rows * a.Gs;
+  // (an eighth of the rows per XCD, where there are workgroups enough: those of a slice read its keys at about the same time)
+  const int64_t all = (int64_t)a.slices * per_slice;
+  const int xcds = (gridDim.x & 7) == 0 ? 8 : 1, xcd = (int)blockIdx.x & (xcds - 1);
+  const int e_end = (int)(all * (xcd + 1) / xcds), e_step = (int)gridDim.x / xcds;
+  for (int e = (int)(all * xcd / xcds) + (int)blockIdx.x / xcds; e < e_end; e += e_step) {
+    const int local_slice = e / per_slice, slice = a.slice0 + local_slice, q0 = (e - local_slice * per_slice) * a.over_rows;
+    const int64_t row0 = (int64_t)slice * a.QB + q0;
+    const int n = min(a.over_rows, a.QB - q0);
+    unsigned todo = 0;
+    for (int i = 0; i < n; i++) todo |= a.count[row0 + i] == 0u ? 1u << i : 0u;   // (the same in all threads)
+    __syncthreads();   // (all have read them; the rows before these are done with the scratch)
+    if (todo == 0u) continue;
+    {
+      const char* src = reinterpret_cast<const char*>(a.qp + (row0 + min(ln & (a.over_rows - 1), n - 1)) * D);
+      bf16x8 qf[STEPS];
+#pragma unroll
+      for (int s = 0; s < STEPS; s++) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(src + (2 * s + g) * 16));
+      const char* kbase = reinterpret_cast<const char*>(a.kp + slice * a.k_slice_stride) + g * 16;
+      auto fetch = [&](i32x4 (&kf)[STEPS], int tile) {   // key blocks past the end repeat the last one
+        const char* key = kbase + (int64_t)min(tile * 32 + ln, a.G - 1) * a.k_row_stride * 2;
+#pragma unroll
+        for (int s = 0; s < STEPS; s++) kf[s] = *reinterpret_cast<const i32x4*>(key + s * 32);
+      };
+      auto form = [&](const i32x4 (&kf)[STEPS], int tile) {
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < STEPS; s++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[s], acc, 0, 0, 0);
+        if (ln < a.over_rows && tile * 32 < a.G) {   // (the rows hold Gs floats, whole tiles)
+#pragma unroll
+          for (int r = 0; r < 16; r += 4)
+            *reinterpret_cast<f32x4*>(scratch + (int64_t)ln * a.Gs + tile * 32 + 2 * r + 4 * g) =
+                f32x4{score_of(acc[r], a.scale), score_of(acc[r + 1], a.scale), score_of(acc[r + 2], a.scale), score_of(acc[r + 3], a.scale)};
+        }
+      };
+      i32x4 even[STEPS], odd[STEPS];
+      fetch(even, wv);
+      for (int tile = wv; tile * 32 < a.G; tile += 2 * WAVES) {
+        fetch(odd, tile + WAVES);
+        form(even, tile);
+        fetch(even, tile + 2 * WAVES);
+        form(odd, tile + WAVES);
+      }
+    }
+    for (int i = 0; i < n; i++) {
+      __syncthreads();   // the scores are written; the row before this one is done with the shared state
+      if (!((todo >> i) & 1u)) continue;
+      const int64_t row = row0 + i;
+      const RowCut c = a.cuts[(int64_t)local_slice * a.QB + q0 + i];
+      if (tid == 0) {
+        sh.mass_above = c.mass_above;
+        sh.target = c.target;
+        sh.n_above = 0;
+      }
+      const unsigned lo = c.lo, hi = c.hi;
+      rank_row<kOverfullThreads, kBins, kCap, 4>(
+          sh, scratch + (int64_t)i * a.Gs, row, from_ordered(a.range[2 * row]),
+          [=](float v) -> int {
+            const unsigned o = ordered_bits(v);
+            return o > hi ? -1 : (o >= lo ? 0 : 1);
+          },
+          a.G, a.top_p, a.cut, a.count, a.keep_bits, a.Gw);
+    }
+  }
+}
+
+}  // namespace fgm

@@ -158,3 +158,39 @@ def test_overfull_rows_among_others(H, L, M):
             F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
             res.append((indptr, emitted(p, ws, indptr)))
         assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1]), full
+
+
+# Many long rows go without a buffer of scores: against the kernel that reads kept scores in every pass.  Rows and key blocks
+# off every multiple of a tile, a wave and a workgroup; the shortest rows that go this way and rows longer than any kernel keeps in LDS;
+# key block means and K in place, in either storage order; one chunk of slices and two; scores that are spread out, mostly
+# without weight, of negative scale, and, in every other head, crowded beside a few large ones (lists that overflow).
+@pytest.mark.parametrize("B,H,L,d,M,N,tokens_first", [(1, 1, 33000, 64, 16, 1, False), (2, 3, 15001, 128, 16, 1, True), (1, 7, 40000, 128, 128, 1, True),
+                                                      (1, 2, 131073, 64, 128, 1, False), (1, 45, 30000, 128, 64, 8, False),
+                                                      (1, 13, 32768, 64, 16, 16, True), (1, 2, 118800, 64, 16, 1, False)])
+def test_selection_without_scores_equals_selection_from_memory(B, H, L, d, M, N, tokens_first):
+    rows, G = B * H * ((L + M - 1) // M), (L + N - 1) // N
+    assert rows * G >= (72 if d == 128 else 48) << 20 and G >= 2048
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L + d)
+
+    def tensor():
+        x = torch.randn((B, L, H, d) if tokens_first else (B, H, L, d), generator=gen, device="cuda").bfloat16()
+        return x.transpose(1, 2) if tokens_first else x
+    q, k = tensor(), tensor()
+    indptr = torch.empty(rows + 1, dtype=torch.int64, device="cuda")
+    for kind, top_p, gain in (("spread", 0.3, 1.0), ("peaked", 0.9, 30.0), ("negative", 0.5, -4.0), ("crowded", 0.9, 1.0), ("every", 1.0, 4.0)):
+        if kind == "crowded":
+            q, k = q.abs(), k.clone()
+            k[:, ::2] = 1.0 + (k[:, ::2] > 1.0).to(k.dtype) * 2.0 ** -7
+            k[:, ::2, L // 2:L // 2 + N] = 40.0
+        if kind == "every" and rows * G > 1 << 29:
+            continue   # (ids of nearly all pairs)
+        res = []
+        for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+            p = F.make_params(q, k, k, q, M, N, gain * d ** -0.5, flags)
+            ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+            F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
+            res.append((indptr.clone(), emitted(p, ws, indptr)))
+        say("    %s: %.3f kept" % (kind, int(indptr[-1]) / (rows * G)))
+        assert torch.equal(res[0][0], res[1][0]), kind
+        assert torch.equal(res[0][1], res[1][1]), kind
