@@ -242,11 +242,13 @@ __global__ void __launch_bounds__(256, 4) scores_kernel(const uint16_t* qp, cons
 #pragma unroll
     for (int b = 0; b < 4; b++) {
       const int half = 8 >> b;
-      const bool upper = (ln >> b) & 1;
+      // (by bits: as `upper ? x[i] : x[i + half]` the compiler indexes the array and selects among all sixteen, 889 conditional
+      // moves in all)
+      const unsigned upper = (unsigned)-((ln >> b) & 1);
 #pragma unroll
       for (int i = 0; i < half; i++) {
-        const float give = upper ? x[i] : x[i + half], keep = upper ? x[i + half] : x[i];
-        x[i] = fmaxf(keep, __shfl_xor(give, 1 << b));
+        const unsigned lower_half = __float_as_uint(x[i]), upper_half = __float_as_uint(x[i + half]), swap = (lower_half ^ upper_half) & upper;
+        x[i] = fmaxf(__uint_as_float(lower_half ^ swap), __shfl_xor(__uint_as_float(upper_half ^ swap), 1 << b));
       }
     }
     return fmaxf(x[0], __shfl_xor(x[0], 16));
