@@ -129,7 +129,10 @@ __global__ void __launch_bounds__(64) pool_kernel(PoolTensor q, PoolTensor k, in
 // exchanges per workgroup and wave for the ranges, it took 239 us for 805 MB (rows of 32760), now 206; 301 us per GiB (rows of
 // 118800, K shared as below), now 242.
 // ---------------------------------------------------------------------------------------------
-constexpr int kTilesPerGroup = 16;
+// Tiles of a workgroup: with sixteen, the calls that come this way leave compute units idle or a second round nearly empty (both
+// mask calls, 12 heads x 147 rows of 9360 scores 110 us, 98 with eight, 101 with four; 40 x 64 x 4096 85, 74, 75; 2 x 512 x 32760
+// 113, 105, 107; 40 x 256 x 4096 142, 141, 140).
+constexpr int kTilesPerGroup = 8;
 // Workgroups go to the eight XCDs in turn.  With at least eight stretches of key blocks, every XCD keeps to its own eighth of
 // them and takes a stretch for up to kShareUnits consecutive score tiles (of one slice, mostly) before the next one, so
 // that the tiles read K through one L2 at about the same time.  (In the order of their indices they read it from device
