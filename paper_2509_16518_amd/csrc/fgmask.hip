@@ -11,6 +11,7 @@
 //                      key block, without sorting the row, and leaves the kept set as one bit per key block
 //   select_kernel      longer rows (or on request): the same selection, one workgroup per query block,
 //                      every pass reading the row from device memory; leaves the same outputs
+//   (fgmask_short.hpp)  rows of at most 1024 scores: scores and selection in one kernel, a wave per row
 //   (fgmask_stream.hpp)  many long rows: the same selection from scores that are formed anew for each pass instead of kept
 //   row_pointers_kernel  counts -> indptr (fgscan.hpp)
 //   emit_bits_kernel   kept ids, ascending, into indices (from the bit rows)
@@ -759,6 +760,12 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
   write_all_bits();   // (this path is only reached through the narrowing rounds)
 }
 
+}  // namespace fgm
+
+#include "fgmask_wave.hpp"
+
+namespace fgm {
+
 // Selection for one query block; called by all threads of the workgroup.  One pass for the mass of the row and its histogram
 // over the score range, then rank_row.
 template <int THREADS, int BINS, int CAP, int DEPTH, typename SH>
@@ -1090,19 +1097,6 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
 // 1490-1640 -> 1210-1270 us.  A loop over each lane's bits runs as long as the fullest lane's: 91 and 1510 us.  Stores
 // straight from the lanes whose bit is set make as many requests as full ones.)
 constexpr int kEmitBatch = 32;   // words of a row staged between two flushes
-// inclusive prefix sum over the lanes of a wave, without LDS
-__device__ __forceinline__ unsigned lane_prefix(unsigned x) {
-  auto add = [&](auto ctrl, auto rows) {
-    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
-  };
-  add(std::integral_constant<int, 0x111>(), std::integral_constant<int, 0xf>());   // row_shr:1, 2, 4, 8
-  add(std::integral_constant<int, 0x112>(), std::integral_constant<int, 0xf>());
-  add(std::integral_constant<int, 0x114>(), std::integral_constant<int, 0xf>());
-  add(std::integral_constant<int, 0x118>(), std::integral_constant<int, 0xf>());
-  add(std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>());   // row_bcast:15 into rows 1 and 3
-  add(std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>());   // row_bcast:31 into rows 2 and 3
-  return x;
-}
 __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bits, int Gw, int seg_words, int segs, int64_t units,
                                                         const int64_t* indptr, int32_t* indices, int64_t capacity) {
   __shared__ alignas(16) int32_t stages[4][kEmitBatch * 32 + 40];
@@ -1190,6 +1184,7 @@ __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bit
 
 }  // namespace fgm
 
+#include "fgmask_short.hpp"
 #include "fgmask_stream.hpp"
 
 namespace fgm {
@@ -1425,6 +1420,25 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
                      pool_q, pool_k, p->H, p->L, p->d, range);
   if (!launched()) return FGATTN_E_DEVICE;
   uint32_t* keep_bits = reinterpret_cast<uint32_t*>(ws + lo.bits_off);
+  if (lo.G <= kShortMax && !(p->flags & (FGATTN_FLAG_MASK_ROWS_IN_HBM | FGATTN_FLAG_MASK_ONE_TILE_CHUNKS))) {
+    auto launch = [&](auto d, auto k) {
+      hipLaunchKernelGGL((short_rows_kernel<decltype(d)::value, decltype(k)::value>),
+                         dim3((unsigned)((lo.QB + kShortRows - 1) / kShortRows), (unsigned)lo.slices), dim3(kShortRows * 64), 0, stream, qp,
+                         kmat, k_slice_stride, k_row_stride, (int)lo.QB, (int)lo.G, (int)lo.Gw, p->scale, top_p, cut, count, keep_bits);
+    };
+    auto launch_k = [&](auto d) {
+      if (lo.G <= 64) launch(d, std::integral_constant<int, 1>());
+      else if (lo.G <= 128) launch(d, std::integral_constant<int, 2>());
+      else if (lo.G <= 256) launch(d, std::integral_constant<int, 4>());
+      else if (lo.G <= 512) launch(d, std::integral_constant<int, 8>());
+      else launch(d, std::integral_constant<int, 16>());
+    };
+    if (p->d == 128) launch_k(std::integral_constant<int, 128>());
+    else launch_k(std::integral_constant<int, 64>());
+    if (!launched()) return FGATTN_E_DEVICE;
+    fgscan::launch_row_pointers(count, lo.rows, mask_indptr, stream);
+    return launched() ? FGATTN_OK : FGATTN_E_DEVICE;
+  }
   const unsigned gx = (unsigned)((lo.G + kTilesPerGroup * 32 - 1) / (kTilesPerGroup * 32));
   const size_t score_bytes = lo.cut_off - lo.scores_off;
   StreamArgs sa;

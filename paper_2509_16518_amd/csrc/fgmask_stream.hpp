@@ -530,9 +530,7 @@ __global__ void __launch_bounds__(kLocateParts * 32) locate_kernel(const StreamA
 }
 
 // ---------------------------------------------------------------------------------------------
-// The cut of a row among the members of its crossing bin: one wave per row, no barriers.  Rounds of 512 bins over the
-// range of rank keys (score, then lower id) that holds the cut, until 64 or fewer are left (one, by then, in a run of
-// equal scores), which are ranked by counting.
+// The cut of a row among the members of its crossing bin: one wave per row (cut_of_many).
 // ---------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
   __shared__ unsigned long long all_mass[4][kSettleBins];
@@ -541,7 +539,6 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
   unsigned long long* const mass = all_mass[wv];
   unsigned long long* const cand = all_cand[wv];
   const int rows = a.slices * a.QB;
-  auto order = []() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };   // (LDS operations of a wave complete in order)
   for (int local = blockIdx.x * 4 + wv; local < rows; local += gridDim.x * 4) {
     const int64_t row = (int64_t)a.slice0 * a.QB + local;
     const RowCut c = a.cuts[local];
@@ -588,91 +585,15 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
         }
       }
     };
-    unsigned long long klo = (unsigned long long)c.lo << 32, khi = ((unsigned long long)c.hi << 32) | 0xFFFFFFFFull;
-    unsigned long long before = c.mass_above, cut_key = ~0ull;
     uint32_t* const bits_row = a.keep_bits + row * a.Gw;
-    auto keep = [&](unsigned long long key) {
-      const unsigned id = 0xFFFFFFFFu - (unsigned)key;
-      atomicOr(&bits_row[id >> 5], 1u << (id & 31));
-    };
-    unsigned found = 0;
-    for (int round = 0; round < 9; round++) {
-      const unsigned long long span = khi - klo;
-      const int bits = span == 0 ? 0 : 64 - __clzll((long long)span);
-      const int shift = max(0, bits - 9);
-      for (int i = lane; i < kSettleBins; i += 64) mass[i] = 0;
-      order();
-      for_each([&](unsigned long long key, bool is) {
-        if (is && key >= klo && key <= khi)
-          atomicAdd(&mass[(khi - key) >> shift], weight_of(from_ordered((unsigned)(key >> 32)), rmax));
-      });
-      order();
-      // the crossing bin: eight consecutive bins per lane
-      constexpr int PER = kSettleBins / 64;
-      unsigned long long own[PER], sum = 0;
-#pragma unroll
-      for (int i = 0; i < PER; i++) sum += own[i] = mass[lane * PER + i];
-      unsigned long long incl = sum;
-      for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
-      unsigned long long run = before + incl - sum;
-      const uint64_t reach = __builtin_amdgcn_ballot_w64(before + incl >= c.target);
-      const int owner = reach ? __ffsll((unsigned long long)reach) - 1 : 63;   // (the last one if the masses fell short)
-      int bin = PER - 1;
-#pragma unroll
-      for (int i = 0; i < PER - 1; i++)
-        if (bin == PER - 1) {
-          if (run + own[i] >= c.target) bin = i;
-          else run += own[i];
-        }
-      bin = __shfl(lane * PER + bin, owner);
-      before = __shfl(run, owner);
-      const unsigned long long top = khi;   // (what lies above the range has been dealt with)
-      khi -= (unsigned long long)bin << shift;
-      const unsigned long long deep = (1ull << shift) - 1ull;
-      if (khi - klo > deep) klo = khi - deep;
-      // those above the bin are kept; how many are in it, and the first 64 of them
-      found = 0;
-      for_each([&](unsigned long long key, bool is) {
-        if (is && key > khi && key <= top) keep(key);
-        kept += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(is && key > khi && key <= top));
-        const bool in = is && key >= klo && key <= khi;
-        const uint64_t lanes = __builtin_amdgcn_ballot_w64(in);
-        const unsigned pos = found + __builtin_amdgcn_mbcnt_hi((unsigned)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lanes, 0u));
-        if (in && pos < 64u) cand[pos] = key;
-        found += (unsigned)__popcll(lanes);
-      });
-      order();
-      if (found <= 64u) break;
-    }
-    if (found > 0u) {
-      const int cn = (int)min(found, 64u);
-      const unsigned long long key = lane < cn ? cand[lane] : 0ull;
-      int rank = 0;
-      for (int j = 0; j < cn; j++) {
-        const unsigned long long other = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(key >> 32), j) << 32) |
-                                         (unsigned)__builtin_amdgcn_readlane((int)(unsigned)key, j);
-        rank += other > key ? 1 : 0;
-      }
-      order();
-      if (lane < cn) {
-        mass[rank] = weight_of(from_ordered((unsigned)(key >> 32)), rmax);
-        cand[rank] = key;
-      }
-      order();
-      unsigned long long incl = lane < cn ? mass[lane] : 0ull;
-      for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-      }
-      const uint64_t reach = __builtin_amdgcn_ballot_w64(lane < cn && before + incl >= c.target);
-      cut_key = cand[reach ? __ffsll((unsigned long long)reach) - 1 : cn - 1];
-      order();
-      if (lane < cn && key >= cut_key) keep(key);
-      kept += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(lane < cn && key >= cut_key));
-    }   // (none found is out of reach: the crossing bin has mass, hence members)
+    const unsigned long long cut_key = cut_of_many<kSettleBins>(
+        for_each,
+        [&](unsigned long long key, bool is) {
+          const unsigned id = 0xFFFFFFFFu - (unsigned)key;
+          if (is) atomicOr(&bits_row[id >> 5], 1u << (id & 31));
+          kept += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(is));
+        },
+        (unsigned long long)c.lo << 32, ((unsigned long long)c.hi << 32) | 0xFFFFFFFFull, cand, mass, c.mass_above, c.target, rmax);
     if (lane == 0) {
       a.cut[row] = cut_key;
       a.count[row] = kept;

@@ -194,3 +194,35 @@ def test_selection_without_scores_equals_selection_from_memory(B, H, L, d, M, N,
         say("    %s: %.3f kept" % (kind, int(indptr[-1]) / (rows * G)))
         assert torch.equal(res[0][0], res[1][0]), kind
         assert torch.equal(res[0][1], res[1][1]), kind
+
+
+# Rows short enough for a wave each: a lane's count of scores on both sides of every step, query blocks off a multiple of the
+# workgroup's eight, key block means and K in place; scores spread out, without weight, equal, of few values (more than 64 members of
+# the crossing bin) and crowded
+@pytest.mark.parametrize("B,H,L,d,M,N", [(1, 3, 64, 64, 16, 1), (1, 2, 65, 128, 16, 1), (2, 2, 129, 64, 16, 1), (1, 2, 256, 128, 128, 1),
+                                         (1, 3, 2050, 64, 32, 8), (1, 1, 512, 128, 16, 1), (2, 3, 8208, 128, 64, 16), (1, 2, 1023, 64, 16, 1),
+                                         (1, 2, 1024, 128, 64, 1), (1, 2, 1025, 64, 64, 1)])
+def test_short_rows_equal_selection_from_memory(B, H, L, d, M, N):
+    rows, G = B * H * ((L + M - 1) // M), (L + N - 1) // N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L + d)
+    q, k0 = (torch.randn((B, H, L, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    indptr = torch.empty(rows + 1, dtype=torch.int64, device="cuda")
+    for kind, gain in (("spread", 1.0), ("peaked", 30.0), ("negative", -4.0), ("equal", 1.0), ("few values", 1.0), ("crowded", 1.0), ("zero scale", 0.0)):
+        k = k0
+        if kind == "equal":
+            k = torch.ones_like(k0)
+        elif kind == "few values":
+            k = (k0[..., :1] > 0.5).to(k0.dtype).expand_as(k0).contiguous()
+        elif kind == "crowded":
+            k = 1.0 + (k0 > 1.0).to(k0.dtype) * 2.0 ** -7
+            k[:, :, L // 2:L // 2 + N] = 40.0
+        for top_p in (0.3, 0.9, 1.0):
+            res = []
+            for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+                p = F.make_params(q, k, k, q, M, N, gain * d ** -0.5, flags)
+                ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+                F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
+                res.append((indptr.clone(), emitted(p, ws, indptr)))
+            assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
+            assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
