@@ -202,6 +202,42 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
   return (unsigned)__builtin_amdgcn_readlane((int)y, 63);
 }
 
+// Ascending order of a lane's keys (odd-even merge sort).
+template <int N>
+__device__ __forceinline__ void sort_keys(unsigned (&k)[N]) {
+  static_assert(N == 4 || N == 8 || N == 16, "written out for these");
+  auto order = [&](int i, int j) {
+    const unsigned a = min(k[i], k[j]), b = max(k[i], k[j]);
+    k[i] = a;
+    k[j] = b;
+  };
+  auto four = [&](int o) {
+    order(o, o + 1); order(o + 2, o + 3); order(o, o + 2); order(o + 1, o + 3); order(o + 1, o + 2);
+  };
+  auto eight = [&](int o) {
+    four(o);
+    four(o + 4);
+    order(o, o + 4); order(o + 1, o + 5); order(o + 2, o + 6); order(o + 3, o + 7);
+    order(o + 2, o + 4); order(o + 3, o + 5);
+    order(o + 1, o + 2); order(o + 3, o + 4); order(o + 5, o + 6);
+  };
+  if constexpr (N == 4) {
+    four(0);
+  } else if constexpr (N == 8) {
+    eight(0);
+  } else {
+    eight(0);
+    eight(8);
+#pragma unroll
+    for (int i = 0; i < 8; i++) order(i, i + 8);
+#pragma unroll
+    for (int i = 4; i < 8; i++) order(i, i + 4);
+    order(2, 4); order(3, 5); order(6, 8); order(7, 9); order(10, 12); order(11, 13);
+#pragma unroll
+    for (int i = 1; i < 15; i += 2) order(i, i + 1);
+  }
+}
+
 // The same heuristic for slices of at most KPT * kThreads tiles whose (distance, index) pairs fit 32 bits (`jbits` for
 // the index).  One workgroup per slice and one group after the other, so what counts is the chain of instructions per group
 // (with 1024 threads, whose 16 waves repeat the parts that every wave needs, 975 us at the size below) and that no load is
@@ -210,10 +246,12 @@ __device__ __forceinline__ unsigned wave_min_u32(unsigned x) {
 //     distances of those R rows are fetched while this group picks.  One compute unit draws 10-20 bytes per ns from beyond
 //     its L2, so the bytes count too: 16-bit distances where they fit, and only the tiles from the row's own on (those
 //     before it are used by the time it represents a group); with whole rows of 32 bits 832 us;
-//   - a wave takes its own R - 1 smallest keys with register and cross-lane minima, the waves' lists meet in LDS after the
-//     group's one barrier, and every wave takes the R - 1 smallest of those: all waves know the picks, and each keeps the whole
-//     bitmap of used tiles in registers (64 per lane), so nothing is published.
-// 12 slices of 2048 tiles, R = 8: 975 -> 750 us (a barrier per pick, one row fetched ahead before).
+//   - every lane sorts its own keys, and a wave takes its R - 1 smallest from the lanes' heads with a cross-lane minimum each;
+//   - the waves' lists meet in LDS after the group's one barrier, where every lane ranks one entry against all of them: all
+//     waves know the picks, and each keeps the whole bitmap of used tiles in registers (64 per lane), so nothing is published;
+//   - no conditional move: one that reads vcc takes four times an ordinary instruction's time.
+// 12 slices of 2048 tiles, R = 8: 975 us with a barrier per pick and one row fetched ahead, 750 with minima over all of a lane's
+// keys and over the lists for every pick, GREEDY_NOW now.
 // T = uint16_t: rows start 16-byte aligned and hold at least 15 elements past QB (of any value); T = uint32_t: no such assumption.
 template <typename T, int KPT, int R>
 __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, int QB, int ld, int NG, int jbits,
@@ -221,7 +259,9 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
   constexpr int WAVES = kThreads / 64, PICKS = R - 1;
   static_assert(R >= 2 && R <= 8 && WAVES * PICKS <= 64, "a list entry per lane");
   static_assert(KPT * kThreads <= 64 * 64 && KPT <= 32, "a lane keeps 64 tiles of the bitmap, and a bit per key");
-  __shared__ unsigned lists[2][64];
+  constexpr int ENTRIES = WAVES * PICKS, QUADS = (ENTRIES + 3) / 4;
+  __shared__ alignas(16) unsigned lists[2][64];
+  __shared__ int picks[WAVES][8];   // by rank, each wave's own copy
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.x;
   const T* D = dist + (int64_t)slice * QB * ld;
@@ -236,10 +276,13 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
     return ~(((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)used_hi, l) << 32) |
              (unsigned)__builtin_amdgcn_readlane((int)used_lo, l));
   };
-  auto mark = [&](int tile) {
-    const unsigned bit = lane == tile >> 6 ? 1u << (tile & 31) : 0u;
-    if (tile & 32) used_hi |= bit;
-    else used_lo |= bit;
+  // all ones where the two (small) numbers are equal
+  auto equal = [](int a, int b) { return (unsigned)(((a ^ b) - 1) >> 31); };
+  auto mark = [&](int tile) {   // (the tile is the same in all lanes)
+    const uint64_t bit = 1ull << (tile & 63);
+    const unsigned here = equal(lane, tile >> 6);
+    used_lo |= (unsigned)bit & here;
+    used_hi |= (unsigned)(bit >> 32) & here;
   };
   const int j0 = tid * KPT;   // this thread's tiles: j0 .. j0 + KPT - 1
   unsigned alive = QB - j0 >= KPT ? (1u << KPT) - 1u : QB > j0 ? (1u << (QB - j0)) - 1u : 0u;   // bit i: tile j0 + i is unused
@@ -262,7 +305,7 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
   };
   Part row = {};         // of the representative
   fetch(row, 0);
-  auto take = [&](int tile) { alive &= ~(tile / KPT == tid ? 1u << (tile & (KPT - 1)) : 0u); };
+  auto take = [&](int tile) { alive &= ~((1u << (tile & (KPT - 1))) & equal(tid, tile / KPT)); };
   __syncthreads();
   int seed = 0;
   for (int g = 0; g < NG; g++) {   // (every group but the last takes R tiles, so the representative exists)
@@ -285,38 +328,50 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
       const unsigned dv = sizeof(T) == 2 ? (row.w[i / 2] >> (16 * (i & 1))) & 0xFFFFu : row.w[i];
-      key[i] = (alive >> i) & 1u ? (dv << jbits) | (unsigned)(j0 + i) : 0xFFFFFFFFu;
+      key[i] = ((dv << jbits) | (unsigned)(j0 + i)) | ~(unsigned)__builtin_amdgcn_sbfe((int)alive, i, 1);
     }
-    unsigned top = 0xFFFFFFFFu;   // lane r: the wave's r-th smallest
+    sort_keys(key);
+    unsigned top = 0u;   // lane r: the wave's r-th smallest
 #pragma unroll
     for (int r = 0; r < PICKS; r++) {
-      unsigned m = key[0];
+      const unsigned w = wave_min_u32(key[0]);
+      top |= w & equal(lane, r);
+      if (r + 1 < PICKS && key[0] == w) {   // (keys are distinct: one lane, or all that have none left)
+        asm volatile("" : "+v"(key[0]));    // (stays a branch)
 #pragma unroll
-      for (int i = 1; i < KPT; i++) m = min(m, key[i]);
-      const unsigned w = wave_min_u32(m);
-      top = lane == r ? w : top;
-      if (r + 1 < PICKS && m == w) {   // (keys are distinct: one lane)
-#pragma unroll
-        for (int i = 0; i < KPT; i++) key[i] = key[i] == w ? 0xFFFFFFFFu : key[i];
+        for (int i = 0; i < KPT - 1 && i < PICKS - 1 - r; i++) key[i] = key[i + 1];
+        if (KPT - 1 < PICKS - 1 - r) key[KPT - 1] = 0xFFFFFFFFu;
       }
     }
     unsigned* const list = lists[g & 1];   // (read by every wave before it comes to the next group's barrier)
     if (lane < PICKS) list[wv * PICKS + lane] = top;
     __syncthreads();
-    unsigned a = list[lane];
-    int picked = lane == 0 ? seed : -1;   // lane r: the group's r-th member
+    const unsigned a = list[lane];   // (all ones past the entries)
+    const bool there = a != 0xFFFFFFFFu;
+    unsigned rank = 0;
+#pragma unroll
+    for (int i = 0; i < QUADS; i++) {
+      const u32x4 e = *reinterpret_cast<const u32x4*>(&list[4 * i]);
+#pragma unroll
+      for (int x = 0; x < 4; x++) rank += e[x] < a ? 1u : 0u;
+    }
+    const int got = min(PICKS, (int)__popcll(__builtin_amdgcn_ballot_w64(there)));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (there && rank < (unsigned)PICKS) picks[wv][rank] = (int)(a & jmask);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (LDS operations of a wave complete in order)
+    int tile[PICKS];
+#pragma unroll
+    for (int r = 0; r < PICKS; r++) tile[r] = picks[wv][r];
+    if (tid < R) out[g * R + tid] = tid == 0 ? seed : tid <= got ? picks[0][max(tid - 1, 0)] : -1;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int r = 0; r < PICKS; r++) {
-      const unsigned w = wave_min_u32(a);
-      a = a == w ? 0xFFFFFFFFu : a;
-      if (w != 0xFFFFFFFFu) {
-        const int j = (int)(w & jmask);
-        picked = lane == r + 1 ? j : picked;
+      const int j = __builtin_amdgcn_readfirstlane(tile[r]);
+      if (r < got) {
         mark(j);
         take(j);
       }
     }
-    if (tid < R) out[g * R + tid] = picked;
     int next = QB;
     {
       int l = seed >> 6;
