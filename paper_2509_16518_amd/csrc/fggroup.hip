@@ -306,8 +306,11 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
   Part row = {};         // of the representative
   fetch(row, 0);
   auto take = [&](int tile) { alive &= ~((1u << (tile & (KPT - 1))) & equal(tid, tile / KPT)); };
+#pragma unroll
+  for (int i = 0; i < WORDS; i++) asm volatile("" : "+v"(row.w[i]));   // (has arrived: inside the loop nothing waits for it)
   __syncthreads();
   int seed = 0;
+  int picked = -1;   // lane r of the first wave: the r-th member of the group before, stored one group late (see below)
   for (int g = 0; g < NG; g++) {   // (every group but the last takes R tiles, so the representative exists)
     mark(seed);
     take(seed);
@@ -324,6 +327,9 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
         if (cand[c] < QB) fetch(ahead[c], cand[c]);
       }
     }
+    // The wait for the next representative's row, at the end of a group, is for all operations before it too: a store of this
+    // group's members there would be waited for as well.
+    if (g > 0 && tid < R) out[(g - 1) * R + tid] = picked;
     unsigned key[KPT];   // (distance, index) of the unused tiles this thread owns, all ones otherwise
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
@@ -362,7 +368,7 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
     int tile[PICKS];
 #pragma unroll
     for (int r = 0; r < PICKS; r++) tile[r] = picks[wv][r];
-    if (tid < R) out[g * R + tid] = tid == 0 ? seed : tid <= got ? picks[0][max(tid - 1, 0)] : -1;
+    if (tid < R) picked = tid == 0 ? seed : tid <= got ? picks[0][max(tid - 1, 0)] : -1;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int r = 0; r < PICKS; r++) {
@@ -380,6 +386,9 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
       if (free != 0) next = l * 64 + __builtin_ctzll(free);
     }
     seed = next;
+    if (seed >= QB || g + 1 == NG) {
+      if (tid < R) out[g * R + tid] = picked;
+    }
     if (seed >= QB) {   // all taken: what is left of the list (nothing, by its length) holds no tile
       for (int t = (g + 1) * R + tid; t < NG * R; t += kThreads) out[t] = -1;
       break;
