@@ -248,49 +248,53 @@ __device__ __forceinline__ void sort_keys(unsigned (&k)[N]) {
 //     before it are used by the time it represents a group); with whole rows of 32 bits 832 us;
 //   - every lane sorts its own keys, and a wave takes its R - 1 smallest from the lanes' heads with a cross-lane minimum each;
 //   - the waves' lists meet in LDS after the group's one barrier, where every lane ranks one entry against all of them: all
-//     waves know the picks, and each keeps the whole bitmap of used tiles in registers (64 per lane), so nothing is published;
-//   - no conditional move: one that reads vcc takes four times an ordinary instruction's time.
-// 12 slices of 2048 tiles, R = 8: 975 us with a barrier per pick and one row fetched ahead, 750 with minima over all of a lane's
-// keys and over the lists for every pick, GREEDY_NOW now.
+//     waves know the picks, and each keeps its own bitmap of used tiles, so nothing is published;
+//   - nothing in a group waits for what the group itself has issued to memory (rows fetched ahead, members stored);
+//   - no conditional moves in the chain: one that reads vcc takes four times an ordinary instruction's time.
+// 12 slices of 2048 tiles, R = 8: 975 us with a barrier per pick and one row fetched ahead; 750 with minima over all of a lane's
+// keys and over the lists for every pick; 650 with sorted heads and ranks; 592 without a wait for the rows fetched ahead; 500 with
+// the bitmap in LDS, where a lane notes a pick with one addition (in registers a pick took two dozen instructions).
 // T = uint16_t: rows start 16-byte aligned and hold at least 15 elements past QB (of any value); T = uint32_t: no such assumption.
 template <typename T, int KPT, int R>
 __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, int QB, int ld, int NG, int jbits,
                                                                 int32_t* group_tiles) {
   constexpr int WAVES = kThreads / 64, PICKS = R - 1;
   static_assert(R >= 2 && R <= 8 && WAVES * PICKS <= 64, "a list entry per lane");
-  static_assert(KPT * kThreads <= 64 * 64 && KPT <= 32, "a lane keeps 64 tiles of the bitmap, and a bit per key");
+  static_assert(KPT * kThreads <= 64 * 64 && KPT <= 32, "64 words of the bitmap, and a bit per key");
   constexpr int ENTRIES = WAVES * PICKS, QUADS = (ENTRIES + 3) / 4;
   __shared__ alignas(16) unsigned lists[2][64];
-  __shared__ int picks[WAVES][8];   // by rank, each wave's own copy
+  __shared__ int picks[8];   // by rank + 1; the first wave's
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slice = blockIdx.x;
   const T* D = dist + (int64_t)slice * QB * ld;
   int32_t* out = group_tiles + (int64_t)slice * NG * R;
   const unsigned jmask = (1u << jbits) - 1u;
   if (tid < 128) lists[tid >> 6][lane] = 0xFFFFFFFFu;   // (entries past WAVES * PICKS stay)
-  // tiles 64 * lane .. + 63; those past the end count as used
+  // used tiles as bits, each wave's own copy; those past the end count as used
+  __shared__ uint64_t used[WAVES][64];
   const int mine = QB - lane * 64;
-  unsigned used_lo = mine >= 32 ? 0u : mine <= 0 ? ~0u : ~0u << mine;
-  unsigned used_hi = mine >= 64 ? 0u : mine <= 32 ? ~0u : ~0u << (mine - 32);
+  used[wv][lane] = mine >= 64 ? 0ull : mine <= 0 ? ~0ull : ~0ull << mine;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (LDS operations of a wave complete in order)
+  uint64_t free_tiles = 0;   // unused ones of tiles 64 * lane .. + 63, as of the last look
+  auto look = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    free_tiles = ~used[wv][lane];
+  };
   auto unused_word = [&](int l) {   // of lane l, in scalar registers
-    return ~(((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)used_hi, l) << 32) |
-             (unsigned)__builtin_amdgcn_readlane((int)used_lo, l));
+    return ((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)(free_tiles >> 32), l) << 32) |
+           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)free_tiles, l);
   };
-  // all ones where the two (small) numbers are equal
-  auto equal = [](int a, int b) { return (unsigned)(((a ^ b) - 1) >> 31); };
-  auto mark = [&](int tile) {   // (the tile is the same in all lanes)
-    const uint64_t bit = 1ull << (tile & 63);
-    const unsigned here = equal(lane, tile >> 6);
-    used_lo |= (unsigned)bit & here;
-    used_hi |= (unsigned)(bit >> 32) & here;
-  };
+  auto mark = [&](int tile) { atomicOr(reinterpret_cast<unsigned*>(used[wv]) + (tile >> 5), 1u << (tile & 31)); };
   const int j0 = tid * KPT;   // this thread's tiles: j0 .. j0 + KPT - 1
-  unsigned alive = QB - j0 >= KPT ? (1u << KPT) - 1u : QB > j0 ? (1u << (QB - j0)) - 1u : 0u;   // bit i: tile j0 + i is unused
+  static_assert(KPT <= 32 && 32 % KPT == 0, "a thread's tiles lie in one word");
+  const unsigned* const my_word = reinterpret_cast<const unsigned*>(used[wv]) + (j0 >> 5);   // (their bits, from bit j0 % 32 on)
   constexpr int WORDS = KPT * sizeof(T) / 4;
   struct Part { uint32_t w[WORDS]; };   // a thread's part of a row of distances
+  const int reach = j0 < QB ? j0 + KPT : 0;   // this thread has a part of the rows of tiles below
   auto fetch = [&](Part& p, int tile) {
-    if (j0 + KPT <= tile || j0 >= QB) return;
-    const T* src = D + (int64_t)tile * ld + j0;
+    if (reach <= tile) return;
+    const char* const row_of = reinterpret_cast<const char*>(D + (int64_t)tile * ld);   // (a scalar base and a lane's offset)
+    const T* src = reinterpret_cast<const T*>(row_of + (unsigned)j0 * (unsigned)sizeof(T));
     if constexpr (sizeof(T) == 2) {
 #pragma unroll
       for (int i = 0; i < WORDS; i += 4) {
@@ -305,15 +309,15 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
   };
   Part row = {};         // of the representative
   fetch(row, 0);
-  auto take = [&](int tile) { alive &= ~((1u << (tile & (KPT - 1))) & equal(tid, tile / KPT)); };
 #pragma unroll
   for (int i = 0; i < WORDS; i++) asm volatile("" : "+v"(row.w[i]));   // (has arrived: inside the loop nothing waits for it)
   __syncthreads();
   int seed = 0;
   int picked = -1;   // lane r of the first wave: the r-th member of the group before, stored one group late (see below)
   for (int g = 0; g < NG; g++) {   // (every group but the last takes R tiles, so the representative exists)
-    mark(seed);
-    take(seed);
+    if (lane == 0) mark(seed);
+    look();
+    const unsigned taken = *my_word >> (j0 & 31);   // bit i: tile j0 + i is used
     int cand[R];
     Part ahead[R] = {};
     {
@@ -334,14 +338,14 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
       const unsigned dv = sizeof(T) == 2 ? (row.w[i / 2] >> (16 * (i & 1))) & 0xFFFFu : row.w[i];
-      key[i] = ((dv << jbits) | (unsigned)(j0 + i)) | ~(unsigned)__builtin_amdgcn_sbfe((int)alive, i, 1);
+      key[i] = ((dv << jbits) | (unsigned)(j0 + i)) | (unsigned)__builtin_amdgcn_sbfe((int)taken, i, 1);
     }
     sort_keys(key);
     unsigned top = 0u;   // lane r: the wave's r-th smallest
 #pragma unroll
     for (int r = 0; r < PICKS; r++) {
       const unsigned w = wave_min_u32(key[0]);
-      top |= w & equal(lane, r);
+      top |= w & (unsigned)(((lane ^ r) - 1) >> 31);   // (all ones in lane r)
       if (r + 1 < PICKS && key[0] == w) {   // (keys are distinct: one lane, or all that have none left)
         asm volatile("" : "+v"(key[0]));    // (stays a branch)
 #pragma unroll
@@ -359,25 +363,20 @@ __global__ void __launch_bounds__(kThreads) greedy_small_kernel(const T* dist, i
     for (int i = 0; i < QUADS; i++) {
       const u32x4 e = *reinterpret_cast<const u32x4*>(&list[4 * i]);
 #pragma unroll
-      for (int x = 0; x < 4; x++) rank += e[x] < a ? 1u : 0u;
-    }
-    const int got = min(PICKS, (int)__popcll(__builtin_amdgcn_ballot_w64(there)));
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (there && rank < (unsigned)PICKS) picks[wv][rank] = (int)(a & jmask);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (LDS operations of a wave complete in order)
-    int tile[PICKS];
-#pragma unroll
-    for (int r = 0; r < PICKS; r++) tile[r] = picks[wv][r];
-    if (tid < R) picked = tid == 0 ? seed : tid <= got ? picks[0][max(tid - 1, 0)] : -1;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int r = 0; r < PICKS; r++) {
-      const int j = __builtin_amdgcn_readfirstlane(tile[r]);
-      if (r < got) {
-        mark(j);
-        take(j);
+      for (int x = 0; x < 4; x++) {
+        // (keys of 16-bit distances have a bit to spare: the sign of a difference, without a compare and its wait states)
+        if constexpr (sizeof(T) == 2) rank += ((e[x] & 0x7FFFFFFFu) - (a & 0x7FFFFFFFu)) >> 31;
+        else rank += e[x] < a ? 1u : 0u;
       }
     }
+    const int got = min(PICKS, (int)__popcll(__builtin_amdgcn_ballot_w64(there)));
+    if (there && rank < (unsigned)PICKS) {
+      mark((int)(a & jmask));
+      if (wv == 0) picks[1 + rank] = (int)(a & jmask);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (tid < R) picked = tid == 0 ? seed : tid <= got ? picks[tid] : -1;
+    look();
     int next = QB;
     {
       int l = seed >> 6;
