@@ -316,16 +316,21 @@ __device__ __forceinline__ void for_each_score(const float* s, int G, Fn&& fn) {
   for (; j4 < G; j4 += STEP) ragged(*reinterpret_cast<const float4*>(s + j4), j4);
 }
 
+}  // namespace fgm
+
+#include "fgmask_wave.hpp"
+
+namespace fgm {
+
+// (Sums over a wave go by its own data paths, lane_prefix.  By shuffles through LDS, two for every 64-bit step, the sums of
+// select_codes_kernel cost the whole of fgattn_mask_select and _emit 1-5%: 12 x 147 rows of 9360 scores 97.6 us, now 93.1; 40 x 64 rows
+// of 4096 74.3, now 70.8; 512 rows of 32760 72.4, now 71.6)
 // Exclusive prefix of `n` over the threads of the workgroup in thread order; *total gets the sum.
 // wave_tot: THREADS / 64 words of shared memory.  Contains two barriers.
 template <int THREADS>
 __device__ __forceinline__ unsigned block_exclusive(unsigned n, unsigned* wave_tot, unsigned* total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  unsigned incl = n;
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
+  const unsigned incl = lane_prefix(n);
   if (lane == 63) wave_tot[wv] = incl;
   __syncthreads();
   unsigned before = 0;
@@ -350,8 +355,8 @@ struct SelShared {
 
 template <int THREADS, int BINS, int CAP>
 __device__ __forceinline__ unsigned long long block_sum_u64(SelShared<THREADS, BINS, CAP>& sh, unsigned long long v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  if ((threadIdx.x & 63) == 0) sh.wave_m[threadIdx.x >> 6] = v;
+  v = lane_prefix(v);
+  if ((threadIdx.x & 63) == 63) sh.wave_m[threadIdx.x >> 6] = v;
   __syncthreads();
   unsigned long long r = 0;
   for (int w2 = 0; w2 < THREADS / 64; w2++) r += sh.wave_m[w2];
@@ -364,11 +369,7 @@ template <int THREADS, int BINS, int CAP>
 __device__ __forceinline__ void block_exclusive_mass(SelShared<THREADS, BINS, CAP>& sh, unsigned long long m,
                                                      unsigned long long* em, unsigned long long* tm) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  unsigned long long im = m;
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned long long um = __shfl_up(im, off);
-    if (lane >= off) im += um;
-  }
+  const unsigned long long im = lane_prefix(m);
   if (lane == 63) sh.wave_m[wv] = im;
   __syncthreads();
   unsigned long long bm = 0;
@@ -661,22 +662,13 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
       if (tid < 64) {
         const int n = (int)bin_cnt;
         const unsigned long long key = tid < n ? sh.cand[tid] : 0ull;
-        const unsigned key_lo = (unsigned)key, key_hi = (unsigned)(key >> 32);
         int rank = 0;
-        for (int j = 0; j < n; j++) {
-          const unsigned long long other = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)key_hi, j) << 32) |
-                                           (unsigned)__builtin_amdgcn_readlane((int)key_lo, j);
-          rank += other > key ? 1 : 0;
-        }
+        for (int j = 0; j < n; j++) rank += of_lane(key, j) > key ? 1 : 0;
         if (tid < n) {
-          sh.mass[rank] = weight_of(from_ordered(key_hi), rmax);
+          sh.mass[rank] = weight_of(from_ordered((unsigned)(key >> 32)), rmax);
           sh.mass[64 + rank] = key;
         }
-        unsigned long long inc = tid < n ? sh.mass[tid] : 0ull;   // (same wave: LDS accesses complete in order)
-        for (int off = 1; off < 64; off <<= 1) {
-          const unsigned long long up = __shfl_up(inc, off);
-          if (tid >= off) inc += up;
-        }
+        const unsigned long long inc = lane_prefix(tid < n ? sh.mass[tid] : 0ull);   // (same wave: LDS accesses complete in order)
         const unsigned long long reached = __ballot(tid < n && sh.mass_above + inc >= sh.target);
         const int idx = reached ? __ffsll((long long)reached) - 1 : n - 1;   // (the last one if the masses fell short)
         if (tid == idx) {
@@ -759,12 +751,6 @@ __device__ __forceinline__ void rank_row(SH& sh, const float* s, int64_t row, fl
   }
   write_all_bits();   // (this path is only reached through the narrowing rounds)
 }
-
-}  // namespace fgm
-
-#include "fgmask_wave.hpp"
-
-namespace fgm {
 
 // Selection for one query block; called by all threads of the workgroup.  One pass for the mass of the row and its histogram
 // over the score range, then rank_row.
