@@ -42,84 +42,129 @@ __global__ void __launch_bounds__(kThreads) bitmap_kernel(const int64_t* indptr,
   for (int i = tid; i < Gw; i += kThreads) bits[w * Gw + i] = row[i];
 }
 
-// 64 x 64 block of the distance matrix of one slice per workgroup; a thread owns a 4 x 4 patch (rows ty*4 + a, columns
-// tx + 16*b).  The matrix is symmetric: only blocks on and above the diagonal are computed, the others are written from
-// them.  Words are read from LDS four at a time; rows of 36 words put the 16 columns a wave reads at once into
-// different banks.  Bound: latency and the counting adds.  12 slices of 2048 tiles x 2048 key blocks: 265 us with all blocks
-// computed, 270 with half of them but every word fetched by a load of its own that was waited for; 244 us with the
-// words of a step fetched together and one step ahead.
+// 64 x 64 block of the distance matrix of one slice per workgroup, 32 x 32 per wave: |a ^ b| = |a| + |b| - 2 |a & b|, and |a & b|
+// for all pairs is a matrix product over the bits.  A bit becomes a 4-bit float, 1.0 = 0b0010, by a shift and a mask: a word of
+// 32 bits is a lane's whole operand of v_mfma_f32_32x32x64_f8f6f4, its bits in the order 4n, 4n + 1, 4n + 2, 4n + 3, which is the
+// same in both factors and so changes nothing.  The sums are whole numbers far below 2^24: exact.  The matrix is symmetric: only
+// blocks on and above the diagonal are computed, the others are written from them.  Rows of 36 words in LDS put the 16 rows that a
+// quarter of a wave reads at once into different banks.  Bound: latency of the steps, then the writes (100 MB of these figures').
+// 12 slices of 2048 tiles x 2048 key blocks: with population counts, 4 x 4 pairs per thread, 260 us; now 83, and no less
+// with blocks of 128, which leave small slices with too few workgroups (8 of 293 tiles, the whole call 276 -> 283 us).
+constexpr int kDist = 64;           // tiles per side of a block
+constexpr int kDistWords = 32;      // words of a row per step
+constexpr int kDistFlush = 1024;    // words after which sums of longer rows go to whole numbers
+
 template <typename T>
 __global__ void __launch_bounds__(kThreads) distance_kernel(const uint32_t* bits, int QB, int Gw, int ld, T* dist) {
-  __shared__ alignas(16) uint32_t words[2][64][36];
-  uint32_t (&A)[64][36] = words[0], (&B)[64][36] = words[1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int slice = blockIdx.z;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  if (j0 < i0) return;
-  const uint32_t* base = bits + (int64_t)slice * QB * Gw;
-  uint32_t acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; a++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) acc[a][b] = 0;
-  // 32 words of the 64 + 64 rows at a time, eight of each per thread, fetched one step ahead of their use; rows past the
-  // end repeat the last one (their distances are not written)
+  typedef int i32x8 __attribute__((ext_vector_type(8)));
+  typedef float f32x16 __attribute__((ext_vector_type(16)));
   typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  const int lr = tid >> 2, lc = (tid & 3) * 8;
-  const uint32_t* const rows[2] = {base + (int64_t)min(i0 + lr, QB - 1) * Gw + lc, base + (int64_t)min(j0 + lr, QB - 1) * Gw + lc};
-  u32x4 next[2][2];
+  constexpr int PITCH = sizeof(T) == 2 ? kDist + 2 : kDist + 1;
+  __shared__ alignas(16) uint32_t words[2 * kDist][36];
+  __shared__ uint32_t ones[2 * kDist];   // set bits per row
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = blockIdx.y * kDist, j0 = blockIdx.x * kDist;
+  if (j0 < i0) return;
+  const uint32_t* base = bits + (int64_t)blockIdx.z * QB * Gw;
+  // rows i0 .. and then j0 .., 16 bytes of a row per thread, fetched one step ahead of their use; rows past the end repeat
+  // the last one (their distances are not written)
+  const int lc = (tid & 7) * 4, lr = tid >> 3;
+  constexpr int PASS = kThreads / 8, PER = 2 * kDist / PASS;
+  u32x4 next[PER];
+  uint32_t set[PER];
+#pragma unroll
+  for (int m = 0; m < PER; m++) set[m] = 0;
   auto fetch = [&](int w0) {
-    if (w0 + 32 <= Gw) {
 #pragma unroll
-      for (int m = 0; m < 2; m++)
+    for (int m = 0; m < PER; m++) {
+      const int r = m * PASS + lr;
+      const uint32_t* const row = base + (int64_t)min(r < kDist ? i0 + r : j0 + r - kDist, QB - 1) * Gw;
+      if (w0 + kDistWords <= Gw) next[m] = *reinterpret_cast<const u32x4_any*>(row + w0 + lc);
+      else
 #pragma unroll
-        for (int h = 0; h < 2; h++) next[m][h] = *reinterpret_cast<const u32x4_any*>(rows[m] + w0 + 4 * h);
-    } else {
-#pragma unroll
-      for (int m = 0; m < 2; m++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) next[m][e >> 2][e & 3] = w0 + lc + e < Gw ? rows[m][w0 + e] : 0u;
+        for (int e = 0; e < 4; e++) next[m][e] = w0 + lc + e < Gw ? row[w0 + lc + e] : 0u;
     }
   };
-  fetch(0);
-  for (int w0 = 0; w0 < Gw; w0 += 32) {
+  f32x16 acc;
+  uint32_t whole[sizeof(T) == 4 ? 16 : 1];
 #pragma unroll
-    for (int h = 0; h < 2; h++) {
-      *reinterpret_cast<u32x4*>(&A[lr][lc + 4 * h]) = next[0][h];
-      *reinterpret_cast<u32x4*>(&B[lr][lc + 4 * h]) = next[1][h];
+  for (int r = 0; r < 16; r++) acc[r] = 0.f;
+  if constexpr (sizeof(T) == 4)
+#pragma unroll
+    for (int r = 0; r < 16; r++) whole[r] = 0u;
+  const int i_wave = (wave >> 1) * 32, j_wave = (wave & 1) * 32;
+  const int ra = i_wave + (lane & 31), rb = kDist + j_wave + (lane & 31);
+  auto operand = [](uint32_t w) {
+    constexpr uint32_t ONE = 0x22222222u;
+    const i32x8 v = {(int)((w << 1) & ONE), (int)(w & ONE), (int)((w >> 1) & ONE), (int)((w >> 2) & ONE), 0, 0, 0, 0};
+    return v;   // (the last four registers are no part of a 4-bit operand)
+  };
+  fetch(0);
+  for (int w0 = 0; w0 < Gw; w0 += kDistWords) {
+#pragma unroll
+    for (int m = 0; m < PER; m++) {
+      *reinterpret_cast<u32x4*>(&words[m * PASS + lr][lc]) = next[m];
+#pragma unroll
+      for (int e = 0; e < 4; e++) set[m] += (uint32_t)__popc(next[m][e]);
     }
     __syncthreads();
-    if (w0 + 32 < Gw) fetch(w0 + 32);
-#pragma unroll 2
-    for (int c = 0; c < 32; c += 4) {
-      u32x4 av[4], bv[4];
+    if (w0 + kDistWords < Gw) fetch(w0 + kDistWords);
+    for (int c = 0; c < kDistWords && w0 + c < Gw; c += 8) {   // eight words: four for either half of the wave
+      const int cc = c + (lane >> 5) * 4;
+      const u32x4 av = *reinterpret_cast<const u32x4*>(&words[ra][cc]), bv = *reinterpret_cast<const u32x4*>(&words[rb][cc]);
 #pragma unroll
-      for (int a = 0; a < 4; a++) av[a] = *reinterpret_cast<const u32x4*>(&A[ty * 4 + a][c]);
-#pragma unroll
-      for (int b = 0; b < 4; b++) bv[b] = *reinterpret_cast<const u32x4*>(&B[tx + 16 * b][c]);
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++)
-#pragma unroll
-          for (int e = 0; e < 4; e++) acc[a][b] += (uint32_t)__popc(av[a][e] ^ bv[b][e]);
+      for (int e = 0; e < 4; e++)   // (4: both factors in 4-bit floats; no scales)
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(operand(av[e]), operand(bv[e]), acc, 4, 4, 0, 0, 0, 0);
     }
+    if constexpr (sizeof(T) == 4)
+      if ((w0 & (kDistFlush - 1)) == kDistFlush - kDistWords)
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          whole[r] += (uint32_t)acc[r];
+          acc[r] = 0.f;
+        }
     __syncthreads();
   }
+#pragma unroll
+  for (int m = 0; m < PER; m++) {
+    uint32_t n = set[m];
+    for (int off = 1; off < 8; off <<= 1) n += __shfl_xor(n, off);
+    if ((tid & 7) == 0) ones[m * PASS + lr] = n;
+  }
+  __syncthreads();
   // through LDS, so that the block and its mirror image are both written in whole rows
-  T* out = dist + (int64_t)slice * QB * ld;
-  uint32_t (&block)[64][65] = *reinterpret_cast<uint32_t (*)[64][65]>(words);
+  T (&block)[kDist][PITCH] = *reinterpret_cast<T (*)[kDist][PITCH]>(words);
   static_assert(sizeof(block) <= sizeof(words), "the block takes the place of the words");
 #pragma unroll
-  for (int a = 0; a < 4; a++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) block[ty * 4 + a][tx + 16 * b] = acc[a][b];
-  __syncthreads();
-  const int c = tid & 63;
-  for (int r = tid >> 6; r < 64; r += kThreads / 64) {
-    if (i0 + r < QB && j0 + c < QB) out[(int64_t)(i0 + r) * ld + j0 + c] = (T)block[r][c];
-    if (j0 > i0 && j0 + r < QB && i0 + c < QB) out[(int64_t)(j0 + r) * ld + i0 + c] = (T)block[c][r];
+  for (int r = 0; r < 16; r++) {
+    const int i = i_wave + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), j = j_wave + (lane & 31);
+    uint32_t both = (uint32_t)acc[r];
+    if constexpr (sizeof(T) == 4) both += whole[r];
+    block[i][j] = (T)(ones[i] + ones[kDist + j] - 2 * both);
   }
+  __syncthreads();
+  T* out = dist + (int64_t)blockIdx.z * QB * ld;
+  if constexpr (sizeof(T) == 2) {   // two to a lane: rows start 16-byte aligned and end in padding
+    const int c = 2 * (lane & 31);
+    for (int r = tid >> 5; r < kDist; r += kThreads / 32) {
+      if (i0 + r < QB && j0 + c < QB)
+        *reinterpret_cast<uint32_t*>(out + (int64_t)(i0 + r) * ld + j0 + c) = block[r][c] | (uint32_t)block[r][c + 1] << 16;
+      if (j0 > i0 && j0 + r < QB && i0 + c < QB)
+        *reinterpret_cast<uint32_t*>(out + (int64_t)(j0 + r) * ld + i0 + c) = block[c][r] | (uint32_t)block[c + 1][r] << 16;
+    }
+  } else {
+    for (int r = wave; r < kDist; r += kThreads / 64) {
+      if (i0 + r < QB && j0 + lane < QB) out[(int64_t)(i0 + r) * ld + j0 + lane] = block[r][lane];
+      if (j0 > i0 && j0 + r < QB && i0 + lane < QB) out[(int64_t)(j0 + r) * ld + i0 + lane] = block[lane][r];
+    }
+  }
+}
+
+// distances of all pairs of tiles of every slice, rows `ld` apart
+template <typename T>
+static void launch_distances(const uint32_t* bits, T* dist, int slices, int QB, int Gw, int ld, hipStream_t stream) {
+  const unsigned side = (unsigned)((QB + kDist - 1) / kDist);
+  hipLaunchKernelGGL(distance_kernel<T>, dim3(side, side, (unsigned)slices), dim3(kThreads), 0, stream, bits, QB, Gw, ld, dist);
 }
 
 __global__ void __launch_bounds__(kThreads) consecutive_kernel(int QB, int R, int NG, int32_t* group_tiles) {
@@ -418,8 +463,7 @@ static int distance_stride(int QB) { return ((QB + 7) & ~7) + 72; }   // 2 (QB +
 template <typename T>
 static bool greedy_small(const uint32_t* bits, T* dist, int slices, int QB, int Gw, int ld, int R, int NG, int jbits,
                          int32_t* group_tiles, hipStream_t stream) {
-  hipLaunchKernelGGL(distance_kernel<T>, dim3((unsigned)((QB + 63) / 64), (unsigned)((QB + 63) / 64), (unsigned)slices),
-                     dim3(kThreads), 0, stream, bits, QB, Gw, ld, dist);
+  launch_distances(bits, dist, slices, QB, Gw, ld, stream);
   if (!launched()) return false;
   if (R == 2) launch_greedy_small<T, 2>(dist, slices, QB, ld, NG, jbits, group_tiles, stream);
   else if (R == 4) launch_greedy_small<T, 4>(dist, slices, QB, ld, NG, jbits, group_tiles, stream);
@@ -602,8 +646,7 @@ int fgattn_group_select(const int64_t* mask_indptr, const int32_t* mask_indices,
     } else if (small) {
       if (!greedy_small(bits, dist, (int)lo.slices, QB, Gw, QB, R, NG, jbits, group_tiles, stream)) return FGATTN_E_DEVICE;
     } else {
-      hipLaunchKernelGGL(distance_kernel<uint32_t>, dim3((unsigned)((QB + 63) / 64), (unsigned)((QB + 63) / 64), (unsigned)lo.slices),
-                         dim3(kThreads), 0, stream, bits, QB, Gw, QB, dist);
+      launch_distances(bits, dist, (int)lo.slices, QB, Gw, QB, stream);
       if (!launched()) return FGATTN_E_DEVICE;
       hipLaunchKernelGGL(greedy_kernel, dim3((unsigned)lo.slices), dim3(kThreads), (size_t)QB, stream, dist, QB, R, NG,
                          group_tiles);

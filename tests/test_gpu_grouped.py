@@ -221,6 +221,22 @@ def test_greedy_grouping_at_the_edges_of_its_variants(M, QB, G):
         assert np.array_equal(a, b), name
 
 
+# the distance matrix in blocks of 64 tiles, in 32 bits and in 16: a block and a tile past it, odd numbers of tiles, which leave
+# half of the last pair of 16-bit distances; rows of one word, of a step of 32 words and a word, of several steps, and lists so
+# dense that the sums are large
+@pytest.mark.parametrize("M,QB,G,H,density", [(64, 65, 2079, 2, 0.4), (64, 128, 20, 2, 0.4), (64, 193, 6111, 2, 0.97), (32, 129, 33, 9, 0.4),
+                                              (16, 383, 1021, 3, 0.4), (16, 256, 1025, 9, 0.97)])
+def test_distance_blocks_at_their_edges(M, QB, G, H, density):
+    L = QB * M - 3
+    w = W.Workload("grouping-blocks", H=H, L=L, d=64, M=M, N=max(1, L // G), kind=W.MASK_RANDOM, density=density, seed=6850 + QB)
+    prob = Problem(w)
+    say("device grouping %d-row tiles: %d slices of %d tiles, %d key blocks" % (M, H, w.QB, w.G))
+    got = gpu_grouping(prob, "xor")
+    ref = GR.grouped_mask(prob.indptr, prob.indices, w.H, w.QB, w.G, 128 // M, "xor")
+    for a, b, name in zip(got, ref, ("group_tiles", "union_indptr", "union_indices", "union_members")):
+        assert np.array_equal(a, b), name
+
+
 def test_greedy_grouping_with_distances_past_16_bits():
     # 66048 key blocks: distances stay in 32 bits, with eight tiles per thread
     w = W.Workload("grouping-wide", H=1, L=66048, d=64, M=64, N=1, kind=W.MASK_RANDOM, density=0.01, seed=6900)
