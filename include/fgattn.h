@@ -55,12 +55,12 @@ enum {
                                      earlier fgattn_plan or forward call for the same mask and params (any forward call
                                      without this flag leaves one; where all items start at once, the natural order) */
   /* Read by the fgattn_mask_* calls only (the others ignore it): use the general selection kernel, which reads a
-   * row of scores from device memory in every pass, also for rows of at most 131072 key blocks (which otherwise
-   * take the kernel that reads the row once).  Same results; pass the same flags to all three mask calls. */
+   * row of scores from device memory in every pass, for all rows (which otherwise take a kernel that reads the row
+   * once, or kernels that keep no scores).  Same results; pass the same flags to all three mask calls. */
   FGATTN_FLAG_MASK_ROWS_IN_HBM = 8,
   /* Read by the fgattn_mask_* calls only: a score buffer of the smallest size (one tile of 128 query blocks)
-   * instead of up to 1 GiB, so that small inputs also take several chunks.  Same results; it changes the
-   * workspace size, so pass the same flags to all three mask calls. */
+   * instead of up to 1 GiB, so that small inputs also take several chunks of kept scores.  Same results; it changes
+   * the workspace size, so pass the same flags to all three mask calls. */
   FGATTN_FLAG_MASK_ONE_TILE_CHUNKS = 16
 };
 
@@ -174,8 +174,9 @@ int fgattn_validate_mask(const int64_t* mask_indptr, const int32_t* mask_indices
  *   (FGATTN_E_SCALE otherwise).
  *   Workspace size: the block means (2*d bytes per query block, and per key block unless B == 1 and N == 1),
  *   20 bytes per query block, one bit per (query block, key block), and a buffer for fp32 scores that is
- *   bounded: the scores are produced and consumed in chunks of whole tiles of 128 query blocks, and the buffer
- *   holds min(all tiles, max(1, floor(1 GiB / tile))) tiles, a tile being 128 * 4 * ceil32(ceil(L/N)) bytes.
+ *   bounded: the scores are produced and consumed in chunks of whole tiles of 128 query blocks (or not kept at
+ *   all, and the buffer takes what the selection needs instead), and it holds min(all tiles, max(1, floor(1 GiB /
+ *   tile))) tiles, a tile being 128 * 4 * ceil32(ceil(L/N)) bytes.
  *   So it never exceeds max(1 GiB, one tile); a tile is below 1 GiB up to 2 097 152 key blocks.
  * fgattn_mask_emit: after the caller has read nnz = mask_indptr[last] and provided mask_indices (device, int32,
  *   capacity >= nnz entries): writes the kept key-block ids of every query block in ascending order.  Entries
