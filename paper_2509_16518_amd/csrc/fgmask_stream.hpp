@@ -67,14 +67,17 @@ struct StreamArgs {
 // first value of a histogram bin's float form: 2^23 + bin has the bin in its low bits
 constexpr float kBinBias = 8388608.0f;
 
-// bins per unit of score, negated; 0 for a row of equal scores
+// Finite and above zero.  By bits: the library is built without regard for NaN, so a comparison with one may turn out either way.
+__device__ __forceinline__ bool positive_finite(float x) { return __float_as_uint(x) - 1u < 0x7F7FFFFFu; }
+// bins per unit of score, negated; 0 for a row without a range to divide: equal scores, infinite ones, a range so narrow that the
+// quotient is infinite.  All of such a row lies in bin 0.
 __device__ __forceinline__ float neg_bins_per_score(float rmax, float rmin) {
 #pragma clang fp contract(off)
-  const float width = rmax - rmin;
-  return width > 0.0f ? -(float)(kMassBins - 1) / width : 0.0f;
+  const float width = rmax - rmin, bins = (float)(kMassBins - 1) / width;
+  return positive_finite(width) && positive_finite(bins) ? -bins : 0.0f;
 }
 // below = score - rmax (not positive).  The low 16 bits of the result are the bin, falling scores in rising bins (0 to
-// kMassBins - 1; 0 also for what infinite scores make of it).
+// kMassBins - 1; 0 also for the NaN that an infinite `below` makes of it).
 __device__ __forceinline__ float biased_bin(float below, float neg_bins) { return __builtin_fmaf(below, neg_bins, kBinBias); }
 // Rounds results of 64-bit floating point toward zero from here on (MODE register, bits 3:2), as mass_update needs.  (No other
 // 64-bit float instruction may be in the kernel: the compiler would set the mode back ahead of it.)
@@ -491,10 +494,13 @@ __global__ void __launch_bounds__(kLocateParts * 32) locate_kernel(const StreamA
   const int64_t row = (int64_t)(a.slice0 + local_slice) * a.QB + min(q, a.QB - 1);
   const float rmax = from_ordered(a.range[2 * row]);
   const float mag = fabsf(a.scale);
-  if (part < 2) {
-    // the smallest x whose bin is below `limit` (part 0: above the crossing bin; part 1: in it or above)
+  const float neg_bins = neg_bins_per_score(rmax, from_ordered(a.range[2 * row + 1]));
+  if (part < 2 && neg_bins == 0.0f) {
+    edge[part][ln] = part == 0 ? INFINITY : -INFINITY;   // all of the row lies in the bin
+  } else if (part < 2) {
+    // the smallest x whose bin is below `limit` (part 0: above the crossing bin; part 1: in it or above).  (Scores of the
+    // largest floats may be infinite, but neg_bins is not zero: nothing here is NaN.)
     const float limit = kBinBias + (float)(crossing[ln] + part);
-    const float neg_bins = neg_bins_per_score(rmax, from_ordered(a.range[2 * row + 1]));
     auto higher = [&](unsigned o) {
       return biased_bin(below_max(score_of(from_ordered(o), mag), rmax), neg_bins) < limit;
     };
@@ -523,8 +529,9 @@ __global__ void __launch_bounds__(kLocateParts * 32) locate_kernel(const StreamA
     // ordered bits of the bin's scores: below that of the first one above it, not below that of its own first one
     c.hi = xa == INFINITY ? ordered_bits(rmax) : ordered_bits(score_of(xa, mag)) - 1u;
     c.lo = xi == -INFINITY ? 0u : ordered_bits(score_of(xi, mag));
-    c.mass_above = above[ln];
-    c.target = goal[ln];
+    // (a row without a range has one bin; one with an infinite maximum has no weights either)
+    c.mass_above = neg_bins == 0.0f ? 0ull : above[ln];
+    c.target = fabsf(rmax) == INFINITY ? 0ull : goal[ln];
     a.cuts[(int64_t)local_slice * a.QB + q] = c;
   }
 }

@@ -226,3 +226,44 @@ def test_short_rows_equal_selection_from_memory(B, H, L, d, M, N):
                 res.append((indptr.clone(), emitted(p, ws, indptr)))
             assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
             assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
+
+
+# Rows whose scores leave no usable range: equal scores (zero query blocks among ordinary ones, heads of identical keys), at scales
+# above 1 that take the largest floats to infinity, scale zero, a range below the smallest one that can be divided by, and scores that
+# are infinite.  No row stays empty, and a row of equal scores keeps its first ceil(p G) key blocks.
+@pytest.mark.parametrize("H,L,d,M,N", [(1, 33000, 64, 16, 1), (3, 30001, 128, 32, 1), (5, 80000, 64, 64, 8)])
+def test_rows_without_a_range(H, L, d, M, N):
+    QB, G = (L + M - 1) // M, (L + N - 1) // N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q0, k0 = (torch.nn.functional.normalize(torch.randn((1, H, L, d), generator=gen, device="cuda"), dim=-1).bfloat16() for _ in range(2))
+    indptr = torch.empty(H * QB + 1, dtype=torch.int64, device="cuda")
+    for kind, scale in (("zero blocks", 10.0), ("zero blocks", -4.0), ("identical keys", 1.5), ("identical keys", 4.0), ("identical keys", -64.0),
+                        ("ordinary", 0.0), ("ordinary", 1e-38), ("infinite", 1.0), ("some infinite", 1.0)):
+        q, k, equal = q0.clone(), k0.clone(), torch.zeros((H, QB), dtype=torch.bool, device="cuda")
+        if kind == "zero blocks":
+            equal[:, ::3] = True
+            q[equal.repeat_interleave(M, 1)[None, :, :L]] = 0.0
+        elif kind == "identical keys":
+            equal[::2] = True
+            k[:, ::2] = k[:, ::2, :1]
+        elif "infinite" in kind:
+            q, k = q.abs() * 2.0 ** 70, k.abs()
+            k[:, :, ::97 if kind == "some infinite" else 1] *= 2.0 ** 70
+        for top_p in (0.3, 0.9):
+            res = []
+            for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+                p = F.make_params(q, k, k, q, M, N, scale, flags)
+                ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+                F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
+                res.append((indptr.clone(), emitted(p, ws, indptr)))
+            say("    %s, scale %g: %d and %d kept" % (kind, scale, int(res[0][0][-1]), int(res[1][0][-1])))
+            counts = (res[0][0][1:] - res[0][0][:-1]).view(H, QB)
+            assert int(counts.min()) >= 1, (kind, scale)
+            want = int(np.ceil(float(np.float32(top_p)) * G))
+            assert (counts[equal] == want).all(), (kind, scale)
+            first = torch.zeros((H * QB, G), dtype=torch.bool, device="cuda")
+            first[torch.repeat_interleave(torch.arange(H * QB, device="cuda"), counts.view(-1)), res[0][1].long()] = True
+            assert first.view(H, QB, G)[equal][:, :want].all(), (kind, scale)
+            assert torch.equal(res[0][0], res[1][0]), (kind, scale)
+            assert torch.equal(res[0][1], res[1][1]), (kind, scale)
