@@ -62,7 +62,9 @@ __global__ void __launch_bounds__(kShortRows * 64) short_rows_kernel(const uint1
     hi = max(hi, is[k] ? ordered_bits(x[k]) : 0u);
     lo = max(lo, is[k] ? ~ordered_bits(x[k]) : 0u);
   }
-  const float rmax = from_ordered(lane_max(hi)), rmin = from_ordered(~lane_max(lo));
+  hi = lane_max(hi);
+  lo = ~lane_max(lo);
+  const float rmax = from_ordered(hi), rmin = from_ordered(lo);
   const float inv = bins_per_score<kShortBins>(rmax, rmin);
   unsigned bins[K];
 #pragma unroll
@@ -98,7 +100,8 @@ __global__ void __launch_bounds__(kShortRows * 64) short_rows_kernel(const uint1
 #pragma unroll
           for (int k = 0; k < K; k++) fn(rank_key(x[k], k * 64 + lane), is[k] && bins[k] == bin);
         },
-        [](unsigned long long, bool) {}, 0ull, ~0ull, cand, mass, before, target, rmax);
+        [](unsigned long long, bool) {}, (unsigned long long)lo << 32, ((unsigned long long)hi << 32) | 0xFFFFFFFFull, cand, mass, before,
+        target, rmax);   // (the row's own range: with infinite scores nothing weighs anything, and the first range that holds a key is it)
   }
   unsigned kept = 0;
   uint32_t* const bits_row = keep_bits + row * Gw;

@@ -231,7 +231,7 @@ def test_short_rows_equal_selection_from_memory(B, H, L, d, M, N):
 # Rows whose scores leave no usable range: equal scores (zero query blocks among ordinary ones, heads of identical keys), at scales
 # above 1 that take the largest floats to infinity, scale zero, a range below the smallest one that can be divided by, and scores that
 # are infinite.  No row stays empty, and a row of equal scores keeps its first ceil(p G) key blocks.
-@pytest.mark.parametrize("H,L,d,M,N", [(1, 33000, 64, 16, 1), (3, 30001, 128, 32, 1), (5, 80000, 64, 64, 8)])
+@pytest.mark.parametrize("H,L,d,M,N", [(1, 33000, 64, 16, 1), (3, 30001, 128, 32, 1), (5, 80000, 64, 64, 8), (3, 2047, 64, 32, 2), (2, 300, 128, 16, 1)])
 def test_rows_without_a_range(H, L, d, M, N):
     QB, G = (L + M - 1) // M, (L + N - 1) // N
     gen = torch.Generator(device="cuda")
