@@ -15,6 +15,9 @@ constexpr int kShortMax = 1024;
 // mass over it, the crossing bin's members ranked.  Bound: latency, which a scores kernel and a selection by workgroups paid for twice
 // and with a barrier for every step.  Both mask calls: 12 heads x 147 rows of 147 scores 44.6 -> 23.6 us, 32 x 83 of 165 43.7 ->
 // 20.7, 40 x 512 of 512 276 -> 204, 12 x 1024 of 1024 142 -> 122, 40 x 7425 of 929 2.33 -> 1.30 ms.
+// Rows with more than 64 members of the crossing bin go on in cut_of_many (the select call alone, 12 x 1024 rows of 1024: equal scores
+// 390 us when a round did not begin with the range of its keys and one bin took every addition, now 87; two values 137, now 90; by
+// workgroups 239 and 127).
 template <int D, int K>
 __global__ void __launch_bounds__(kShortRows * 64) short_rows_kernel(const uint16_t* qp, const uint16_t* kp, int64_t k_slice_stride,
                                                                      int64_t k_row_stride, int QB, int G, int Gw, float scale,
@@ -68,9 +71,17 @@ __global__ void __launch_bounds__(kShortRows * 64) short_rows_kernel(const uint1
   const float inv = bins_per_score<kShortBins>(rmax, rmin);
   unsigned bins[K];
 #pragma unroll
-  for (int k = 0; k < K; k++) {
-    bins[k] = value_bin_of<kShortBins>(x[k], rmax, inv);
-    if (is[k]) atomicAdd(&mass[bins[k]], weight_of(x[k], rmax));
+  for (int k = 0; k < K; k++) bins[k] = value_bin_of<kShortBins>(x[k], rmax, inv);
+  if (inv != 0.0f) {
+#pragma unroll
+    for (int k = 0; k < K; k++)
+      if (is[k]) atomicAdd(&mass[bins[k]], weight_of(x[k], rmax));
+  } else {   // one bin for all: added up over the lanes (additions to the same word are served one by one)
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int k = 0; k < K; k++) sum += is[k] ? weight_of(x[k], rmax) : 0ull;
+    sum = lane_prefix(sum);
+    if (lane == 63) mass[0] = sum;
   }
   wave_order();
   unsigned long long before = 0, target = 0;
@@ -95,10 +106,13 @@ __global__ void __launch_bounds__(kShortRows * 64) short_rows_kernel(const uint1
   if (found - 1u < 64u) {   // 1 to 64
     c = cut_of_few(cand, (int)found, mass, before, target, rmax);
   } else if (found != 0u) {
-    c = cut_of_many<kShortBins>(
-        [&](auto&& fn) {
-#pragma unroll
-          for (int k = 0; k < K; k++) fn(rank_key(x[k], k * 64 + lane), is[k] && bins[k] == bin);
+    c = cut_of_many<kShortBins, true>(
+        [&](auto&& fn) {   // (from LDS again, not unrolled: the usual rows pay for this path with registers and code)
+#pragma unroll 1
+          for (int j = lane; j < K * 64; j += 64) {
+            const float v = scores[wv][j];
+            fn(rank_key(v, j), j < G && value_bin_of<kShortBins>(v, rmax, inv) == bin);
+          }
         },
         [](unsigned long long, bool) {}, (unsigned long long)lo << 32, ((unsigned long long)hi << 32) | 0xFFFFFFFFull, cand, mass, before,
         target, rmax);   // (the row's own range: with infinite scores nothing weighs anything, and the first range that holds a key is it)

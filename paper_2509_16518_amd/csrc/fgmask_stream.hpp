@@ -593,7 +593,7 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
       }
     };
     uint32_t* const bits_row = a.keep_bits + row * a.Gw;
-    const unsigned long long cut_key = cut_of_many<kSettleBins>(
+    const unsigned long long cut_key = cut_of_many<kSettleBins, false>(
         for_each,
         [&](unsigned long long key, bool is) {
           const unsigned id = 0xFFFFFFFFu - (unsigned)key;

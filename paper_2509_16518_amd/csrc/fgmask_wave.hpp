@@ -46,6 +46,10 @@ __device__ __forceinline__ unsigned lane_max(unsigned x) {
   x = max(x, from_lane<kRowBcast31, 0xc>(x, 0u));
   return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
 }
+__device__ __forceinline__ unsigned long long lane_max(unsigned long long x) {
+  const unsigned hi = lane_max((unsigned)(x >> 32));
+  return ((unsigned long long)hi << 32) | lane_max((unsigned)(x >> 32) == hi ? (unsigned)x : 0u);
+}
 __device__ __forceinline__ unsigned long long of_lane(unsigned long long x, int lane) {   // (the lane's number is the same in all)
   return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32) |
          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, lane);
@@ -105,13 +109,29 @@ __device__ __forceinline__ unsigned long long cut_of_few(unsigned long long* can
 // The cut among the rank keys in [klo, khi], before which there is the mass `before`.  for_each(fn) calls fn(key, there is one) for
 // all keys, by all lanes together.  Rounds of BINS bins over the range that holds the cut until 64 keys or fewer are left
 // (one, by then, in a run of equal scores).  keep(key, do) is called, by all lanes together, for what turns out to lie above that range.
-template <int BINS, typename ForEach, typename Keep>
+// TIGHT: a round begins with the range of the keys that there are, where going over them once more costs little: a run of equal scores
+// then differs in the few bits of its ids, one round instead of six with every sum in the same bin.
+template <int BINS, bool TIGHT, typename ForEach, typename Keep>
 __device__ __forceinline__ unsigned long long cut_of_many(ForEach&& for_each, Keep&& keep, unsigned long long klo, unsigned long long khi,
                                                           unsigned long long* cand, unsigned long long* mass,
                                                           unsigned long long before, unsigned long long target, float rmax) {
   const int lane = threadIdx.x & 63;
   unsigned found = 0;
   for (int round = 0; round < 10; round++) {
+    if constexpr (TIGHT) {
+      unsigned long long most = 0ull, least = ~0ull;
+      for_each([&](unsigned long long key, bool is) {
+        const bool in = is && key >= klo && key <= khi;
+        most = max(most, in ? key : 0ull);
+        least = min(least, in ? key : ~0ull);
+      });
+      most = lane_max(most);
+      least = ~lane_max(~least);
+      if (most >= least) {
+        klo = least;
+        khi = most;
+      }
+    }
     const unsigned long long span = khi - klo;
     const int bits = span == 0 ? 0 : 64 - __clzll((long long)span);
     constexpr int DIGIT = BINS == 512 ? 9 : 8;
