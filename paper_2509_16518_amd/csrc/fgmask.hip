@@ -1149,20 +1149,20 @@ __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bit
       // whole groups to memory (LDS operations of a wave complete in order)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const unsigned whole = fill & ~31u;
-      if (to + (int64_t)whole <= capacity) {
-        if ((unsigned)lane >= skip && (unsigned)lane < min(whole, begins)) indices[to + lane] = stage[lane];   // (none past the first flush)
-        if (begins != 0u && w1 - w0 > kEmitBatch) {
-          for (unsigned i = begins + 4 * lane; i < whole; i += 256)
-            *reinterpret_cast<i32x4*>(indices + to + i) = *reinterpret_cast<const i32x4*>(stage + i);
-        } else {
-          for (unsigned i = begins + 4 * lane; i < whole; i += 256)
-            __builtin_nontemporal_store(*reinterpret_cast<const i32x4*>(stage + i), reinterpret_cast<i32x4*>(indices + to + i));
+      if (whole != 0u) {
+        if (to + (int64_t)whole <= capacity) {
+          if ((unsigned)lane >= skip && (unsigned)lane < begins) indices[to + lane] = stage[lane];   // (none past the first flush)
+          if (begins != 0u && w1 - w0 > kEmitBatch) {
+            for (unsigned i = begins + 4 * lane; i < whole; i += 256)
+              *reinterpret_cast<i32x4*>(indices + to + i) = *reinterpret_cast<const i32x4*>(stage + i);
+          } else {
+            for (unsigned i = begins + 4 * lane; i < whole; i += 256)
+              __builtin_nontemporal_store(*reinterpret_cast<const i32x4*>(stage + i), reinterpret_cast<i32x4*>(indices + to + i));
+          }
+        } else {   // the end of the buffer
+          for (unsigned i = lane; i < whole; i += 64)
+            if (i >= skip && to + i < capacity) indices[to + i] = stage[i];
         }
-      } else {   // the end of the buffer
-        for (unsigned i = lane; i < whole; i += 64)
-          if (i >= skip && to + i < capacity) indices[to + i] = stage[i];
-      }
-      if (whole > 0) {
         const int rest = stage[whole + (lane & 31)];   // (up to 31 ids; the array has the slots to spare)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if (lane < 32) stage[lane] = rest;
