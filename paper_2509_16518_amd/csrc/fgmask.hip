@@ -271,9 +271,10 @@ __global__ void __launch_bounds__(256, 4) scores_kernel(const uint16_t* qp, cons
 // Step 2b + 3: selection.
 // ---------------------------------------------------------------------------------------------
 // rank key of key block j with score s: higher score first, then lower id first
-__device__ __forceinline__ unsigned long long rank_key(float s, int j) {
-  return ((unsigned long long)ordered_bits(s) << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)j);
+__device__ __forceinline__ unsigned long long rank_key_of_bits(unsigned ordered, int j) {
+  return ((unsigned long long)ordered << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)j);
 }
+__device__ __forceinline__ unsigned long long rank_key(float s, int j) { return rank_key_of_bits(ordered_bits(s), j); }
 // Weight of a score relative to the row maximum: trunc(2^40 * 2^((s - rmax) * log2 e)), 2^-40 fixed point.
 // The bare exponential instruction differs from exp2f only below 2^-126, where the weight is zero either way.
 // The products with powers of two are exact, and so is the split into a whole and a fractional part (the hardware
@@ -1299,15 +1300,13 @@ static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus
     size_t off = 256;
     const size_t cuts = off;
     off = align256(off + (size_t)rows * sizeof(RowCut));
-    const size_t hist = off, scratch = off;   // (rows of scores for overfull_kernel, when all but the cuts is done with)
-    const int over_rows = slices * ((lo.QB + 7) / 8) >= 2 * cus ? 8 : 4;   // (two workgroups to a compute unit)
-    const size_t scratch_group = (size_t)over_rows * lo.Gs * sizeof(float);
+    const size_t hist = off;
     off = align256(off + (size_t)(groups + slices * tiles) * kMassWords * 8);
     const size_t counts = off;
     off = align256(off + (size_t)(rows * segs) * sizeof(uint2));
     const size_t lists = off;
     off = align256(off + (size_t)(rows * segs * cap) * sizeof(Member));
-    if (off > bytes || scratch + scratch_group > bytes) continue;
+    if (off > bytes) continue;
     a->slices = (int)slices;
     a->units = (int)units;
     a->segs = (int)segs;
@@ -1322,9 +1321,6 @@ static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus
     a->cuts = reinterpret_cast<RowCut*>(at + cuts);
     a->counts = reinterpret_cast<uint2*>(at + counts);
     a->lists = reinterpret_cast<Member*>(at + lists);
-    a->scratch = reinterpret_cast<float*>(at + scratch);
-    a->scratch_fits = (int)((bytes - scratch) / scratch_group < 65535 ? (bytes - scratch) / scratch_group : 65535);
-    a->over_rows = over_rows;
     return true;
   }
   return false;
@@ -1333,7 +1329,6 @@ static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus
 template <int D>
 static bool launch_stream(StreamArgs a, const Layout& lo, int cus, hipStream_t stream) {
   const int64_t per_slice = (lo.QB + kSweepRows - 1) / kSweepRows, tiles = (lo.QB + kMassRows - 1) / kMassRows;
-  const int64_t over_per_slice = (lo.QB + a.over_rows - 1) / a.over_rows;
   const int step = a.slices;
   for (int64_t slice0 = 0; slice0 < lo.slices; slice0 += step) {
     a.slice0 = (int)slice0;
@@ -1352,11 +1347,16 @@ static bool launch_stream(StreamArgs a, const Layout& lo, int cus, hipStream_t s
     const int64_t rows = (int64_t)a.slices * lo.QB, waves = (rows + 3) / 4;
     hipLaunchKernelGGL(settle_kernel, dim3((unsigned)(waves < 8 * cus ? waves : 8 * cus)), dim3(256), 0, stream, a);
     if (!launched()) return false;
-    int64_t over = a.slices * over_per_slice;
-    if (over > 2 * cus) over = 2 * cus;
-    over = (over + 7) & ~(int64_t)7;
-    if (over > a.scratch_fits) over = a.scratch_fits >= 8 ? a.scratch_fits & ~7 : a.scratch_fits;
-    hipLaunchKernelGGL(overfull_kernel<D>, dim3((unsigned)over), dim3(kOverfullThreads), 0, stream, a);
+    // One workgroup to a compute unit, 32 rows each where that is enough of them: at d = 128, 90 workgroups of 32 take 0.41 ms for rows of
+    // two values and 1.03 for crowded ones, of 8 0.51 and 0.99 (8 x 512 rows of 32760, 128 of them, 0.54 and 1.26, 0.65 and 1.24; 929 rows of
+    // 118800, 30 of them, 1.01 and 3.30, 0.85 and 1.76).
+    auto overfull = [&](auto rows) {
+      int64_t over = a.slices * ((lo.QB + rows - 1) / rows);
+      if (over > cus) over = cus;
+      hipLaunchKernelGGL((overfull_kernel<D, decltype(rows)::value>), dim3((unsigned)((over + 7) & ~(int64_t)7)), dim3(kOverfullThreads), 0, stream, a);
+    };
+    if (a.slices * ((lo.QB + 31) / 32) >= cus * 3 / 8) overfull(std::integral_constant<int, 32>());
+    else overfull(std::integral_constant<int, 8>());
     if (!launched()) return false;
   }
   return true;
@@ -1449,7 +1449,6 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
     sa.QB = (int)lo.QB;
     sa.G = (int)lo.G;
     sa.Gw = (int)lo.Gw;
-    sa.Gs = (int)lo.Gs;
     sa.range = range;
     sa.cut = cut;
     sa.count = count;

@@ -8,7 +8,7 @@
 //   locate_kernel           the bin where the descending mass crosses the target, as two thresholds on a score's product
 //   sweep_kernel<D, true>   the bits of all key blocks above that bin; a list of its members and their scores
 //   settle_kernel           ranks the members, adds the bits of those at or above the cut
-//   overfull_kernel         rows whose lists were too short: scores formed into a row of memory, then select_row
+//   overfull_kernel         rows whose lists were too short: the range around the cut narrowed by further passes
 // The matrix product has the keys in its rows and the queries in its columns, so a lane owns one query: its range, its
 // thresholds and its place in the lists are plain registers, and the 32 lanes of a histogram update name 32 different
 // banks.  Against scores in memory, both mask calls, with the same emit kernel: 12 heads x 512 rows of 32760 532 -> 365 us,
@@ -43,7 +43,7 @@ struct StreamArgs {
   const uint16_t* kp;                // of K (or K itself)
   int64_t k_slice_stride, k_row_stride;   // elements
   float scale, top_p;
-  int QB, G, Gw, Gs;
+  int QB, G, Gw;
   int slice0, slices;                // of this chunk
   int units, segs, seg_tiles;        // sweep: workgroup rows of kSweepRows, stretches of key tiles, tiles of a stretch
   int tiles, steps;                  // mass: row tiles of kMassRows, steps (of kMassWaves key tiles) per row tile
@@ -58,9 +58,6 @@ struct StreamArgs {
   unsigned* count;                   // [row]; 0 marks a row left to overfull_kernel
   uint32_t* keep_bits;               // [row][Gw]
   unsigned* overfull;                // number of such rows
-  int over_rows;                     // overfull_kernel: rows formed at a time, 8 or 4
-  float* scratch;                    // over_rows x Gs floats per workgroup,
-  int scratch_fits;                  // for this many workgroups at most
 };
 
 // ---- arithmetic that several kernels have to agree on to the last bit (no contraction into fused operations) ----
@@ -115,6 +112,8 @@ __device__ __forceinline__ float score_of(float product, float scale) {
 #pragma clang fp contract(off)
   return product * scale;
 }
+// Of n infinite scores, which weigh nothing, rank_row keeps the first where it sorts them and all where it counts them off.
+__device__ __forceinline__ unsigned kept_of_infinite(unsigned n) { return n <= (unsigned)kCap ? 1u : n; }
 __device__ __forceinline__ float below_max(float score, float rmax) {
 #pragma clang fp contract(off)
   return score - rmax;
@@ -495,8 +494,10 @@ __global__ void __launch_bounds__(kLocateParts * 32) locate_kernel(const StreamA
   const float rmax = from_ordered(a.range[2 * row]);
   const float mag = fabsf(a.scale);
   const float neg_bins = neg_bins_per_score(rmax, from_ordered(a.range[2 * row + 1]));
+  const bool equal = a.range[2 * row] == a.range[2 * row + 1];
   if (part < 2 && neg_bins == 0.0f) {
-    edge[part][ln] = part == 0 ? INFINITY : -INFINITY;   // all of the row lies in the bin
+    // all of the row lies in the bin; equal scores are no members, settle_kernel counts them off by id
+    edge[part][ln] = part == 0 || equal ? INFINITY : -INFINITY;
   } else if (part < 2) {
     // the smallest x whose bin is below `limit` (part 0: above the crossing bin; part 1: in it or above).  (Scores of the
     // largest floats may be infinite, but neg_bins is not zero: nothing here is NaN.)
@@ -549,7 +550,21 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
   for (int local = blockIdx.x * 4 + wv; local < rows; local += gridDim.x * 4) {
     const int64_t row = (int64_t)a.slice0 * a.QB + local;
     const RowCut c = a.cuts[local];
-    const float rmax = from_ordered(a.range[2 * row]);
+    const unsigned highest = a.range[2 * row];
+    const float rmax = from_ordered(highest);
+    uint32_t* const bits_row = a.keep_bits + row * a.Gw;
+    if (highest == a.range[2 * row + 1]) {   // equal scores, of weight 2^40: the first so many key blocks
+      const unsigned keep = c.target != 0ull ? (unsigned)((c.target + (1ull << 40) - 1ull) >> 40) : kept_of_infinite((unsigned)a.G);
+      for (int w = lane; w < a.Gw; w += 64) {
+        const unsigned left = keep > 32u * (unsigned)w ? keep - 32u * (unsigned)w : 0u;
+        bits_row[w] = left >= 32u ? ~0u : (1u << left) - 1u;
+      }
+      if (lane == 0) {
+        a.cut[row] = rank_key(rmax, (int)keep - 1);
+        a.count[row] = keep;
+      }
+      continue;
+    }
     uint2 n = make_uint2(0u, 0u);   // of stretch `lane`
     if (lane < a.segs) n = a.counts[(int64_t)local * a.segs + lane];
     if (__builtin_amdgcn_ballot_w64(n.y > (unsigned)a.cap) != 0) {
@@ -592,7 +607,6 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
         }
       }
     };
-    uint32_t* const bits_row = a.keep_bits + row * a.Gw;
     const unsigned long long cut_key = cut_of_many<kSettleBins, false>(
         for_each,
         [&](unsigned long long key, bool is) {
@@ -609,85 +623,348 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows with more members in some stretch than its list takes (scores crowded beside a few that stand out, many equal
-// ones): eight or four rows at a time are formed into memory, and the selection goes on from the crossing bin as it does for
-// rows of kept scores.  Bound: reading K once per such group, then the latency of a row's passes.  6144 rows of 32760 equal
-// scores, eight at a time 2.07 ms for the select call (four 2.65, sixteen 3.09; from kept scores 1.56); 1858 of 118800, which
-// make too few groups of eight, four at a time 2.06 ms (eight 2.20; from kept scores 2.17); 6144 rows of 32760 scores crowded
-// beside one large one 0.27 ms (from kept scores 0.96).
+// Rows with more members in some stretch than its list takes (scores crowded beside a few that stand out, many equal ones; rows of
+// nothing but equal scores don't come here): 32 or 8 rows per workgroup, their scores formed anew in every pass over the keys, a
+// stretch of the key tiles per wave.
+//   FIRST   how many members there are, their smallest and largest score.  Taking it that they are equal, their number ahead of a wave
+//           follows from what the sweep counted, and their weight from one that it listed: the bits are written in the same pass.
+//   NARROW  a histogram of the members' mass, until the bin that holds the cut has few enough
+//   COUNT   of members of a single score that was left after that, per wave
+//   LAST    the bits above the cut's range; its members into a list in LDS, ranked by a wave each, or counted off if they are equal
+// Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1.3 us.  (Fetching further ahead changes nothing; with the operands read from LDS one after the other a pass takes a
+// tenth more, straight from memory twice as long.)  Select call, against the kernels with kept scores / a kernel that formed eight or four
+// rows into memory for rank_row / this one: 6144 rows of 32760 in two values 1.34 / 1.91 / 0.69 ms, crowded beside one large
+// negative score 1.72 / 2.24 / 1.43; 20480 of 4095 0.77 / 2.10 / 0.70 and 1.24 / 2.11 / 1.02; 929 of 118800 0.97 / 1.74 / 0.85 and
+// 1.19 / 1.92 / 1.72.  Equal scores (settle_kernel), 6144 of 32760: 1.57 / 2.04 / 0.26.
+// The matrix product has 32 columns.  With 8 ROWS a lane holds what the three lanes 8, 16 and 24 from it hold, and takes a quarter of
+// it: workgroups enough where rows are few.
 // ---------------------------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kOverfullThreads, 4) overfull_kernel(const StreamArgs a) {
-  constexpr int STEPS = D / 16, WAVES = kOverfullThreads / 64;
+template <int D, int ROWS>
+__global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const StreamArgs a) {
+  constexpr int STEPS = D / 16, WAVES = kOverfullThreads / 64, ROWB = D * 2, CHUNKS = ROWB / 16, TILEB = 32 * ROWB, LPT = TILEB / 16 / 64;
+  constexpr int DIGIT = ROWS == 32 ? 8 : 10, BINS = 1 << DIGIT, LIST = BINS;   // (64 KB of LDS)
+  constexpr int PER = ROWS / 2;                                               // scores of a tile per lane
+  enum { FIRST, NARROW, COUNT, LAST };                                        // steps
+  static_assert(ROWS == 32 || ROWS == 8, "written out for these");
   if (*a.overfull == 0) return;
-  __shared__ SelShared<kOverfullThreads, kBins, kCap> sh;
+  __shared__ __attribute__((aligned(16))) unsigned char staged[WAVES][TILEB];   // a wave's own
+  __shared__ unsigned long long hist[BINS][ROWS];   // then the lists of rank keys
+  __shared__ unsigned long long mass[WAVES][kShortBins], cand[WAVES][64];
+  __shared__ unsigned long long mass_above[ROWS], target[ROWS], cut_key[ROWS];
+  __shared__ unsigned lo[ROWS], hi[ROWS], least[ROWS], most[ROWS], listed[ROWS], kept[ROWS];
+  __shared__ unsigned members[WAVES][ROWS], guess[ROWS];
+  __shared__ unsigned todo, wide, single, done;   // a bit per row: to be selected; range still too wide; one score, not counted; bits written
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int ln = lane & 31, g = lane >> 5;
-  const int per_slice = (a.QB + a.over_rows - 1) / a.over_rows;
-  float* const scratch = a.scratch + (int64_t)blockIdx.x * a.over_rows * a.Gs;
+  const int ln = lane & 31, g = lane >> 5, rl = lane % ROWS, part = ln / ROWS;
+  const int per_slice = (a.QB + ROWS - 1) / ROWS, ktiles = (a.G + 31) / 32;
+  // A wave's key tiles, in the order of ids: whole stretches of the sweep where these divide well, since the numbers of members that the
+  // sweep counted in them then say how many are ahead of a wave's own.
+  const bool counted = a.segs >= 2 * WAVES || a.segs == WAVES;
+  const int s0 = a.segs * wv / WAVES, s1 = a.segs * (wv + 1) / WAVES;
+  const int t0 = counted ? min(s0 * a.seg_tiles, ktiles) : (int)((int64_t)ktiles * wv / WAVES);
+  const int t1 = counted ? min(s1 * a.seg_tiles, ktiles) : (int)((int64_t)ktiles * (wv + 1) / WAVES);
   // (an eighth of the rows per XCD, where there are workgroups enough: those of a slice read its keys at about the same time)
   const int64_t all = (int64_t)a.slices * per_slice;
   const int xcds = (gridDim.x & 7) == 0 ? 8 : 1, xcd = (int)blockIdx.x & (xcds - 1);
   const int e_end = (int)(all * (xcd + 1) / xcds), e_step = (int)gridDim.x / xcds;
   for (int e = (int)(all * xcd / xcds) + (int)blockIdx.x / xcds; e < e_end; e += e_step) {
-    const int local_slice = e / per_slice, slice = a.slice0 + local_slice, q0 = (e - local_slice * per_slice) * a.over_rows;
+    const int local_slice = e / per_slice, slice = a.slice0 + local_slice, q0 = (e - local_slice * per_slice) * ROWS;
     const int64_t row0 = (int64_t)slice * a.QB + q0;
-    const int n = min(a.over_rows, a.QB - q0);
-    unsigned todo = 0;
-    for (int i = 0; i < n; i++) todo |= a.count[row0 + i] == 0u ? 1u << i : 0u;   // (the same in all threads)
-    __syncthreads();   // (all have read them; the rows before these are done with the scratch)
-    if (todo == 0u) continue;
+    __syncthreads();   // the rows before these are done with the shared state
+    if (tid == 0) todo = wide = single = done = 0;
+    __syncthreads();
+    if (tid < ROWS && q0 + tid < a.QB && a.count[row0 + tid] == 0u) {
+      const RowCut c = a.cuts[(int64_t)local_slice * a.QB + q0 + tid];
+      lo[tid] = max(c.lo, 1u);   // (0 stands for key blocks past the end; no score has those bits)
+      hi[tid] = c.hi;
+      mass_above[tid] = c.mass_above;
+      target[tid] = c.target;
+      guess[tid] = 0;
+      atomicOr(&todo, 1u << tid);
+    }
+    __syncthreads();
+    const unsigned rows = todo;
+    if (rows == 0u) continue;   // (the same in all threads)
+    const int64_t row = row0 + min(rl, a.QB - 1 - q0);
+    if (counted) {   // a score that the sweep has listed: if the members are equal, it is theirs
+      const int64_t first_list = ((int64_t)local_slice * a.QB + min(q0 + rl, a.QB - 1)) * a.segs;
+      unsigned own = 0;
+      int seg_of_one = -1;
+      for (int seg = s0; seg < s1; seg++) {
+        const unsigned n = a.counts[first_list + seg].y;
+        own += n;
+        if (n != 0u) seg_of_one = seg;
+      }
+      if (lane < ROWS) {
+        members[wv][rl] = own;
+        if (seg_of_one >= 0) atomicMax(&guess[rl], ordered_bits(a.lists[(first_list + seg_of_one) * a.cap].score));
+      }
+    }
+    const float rmax = from_ordered(a.range[2 * row]);
+    bf16x8 qf[STEPS];
     {
-      const char* src = reinterpret_cast<const char*>(a.qp + (row0 + min(ln & (a.over_rows - 1), n - 1)) * D);
-      bf16x8 qf[STEPS];
+      const char* src = reinterpret_cast<const char*>(a.qp + row * D);
 #pragma unroll
       for (int s = 0; s < STEPS; s++) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const i32x4*>(src + (2 * s + g) * 16));
-      const char* kbase = reinterpret_cast<const char*>(a.kp + slice * a.k_slice_stride) + g * 16;
-      auto fetch = [&](i32x4 (&kf)[STEPS], int tile) {   // key blocks past the end repeat the last one
-        const char* key = kbase + (int64_t)min(tile * 32 + ln, a.G - 1) * a.k_row_stride * 2;
+    }
+    const char* const kbase = reinterpret_cast<const char*>(a.kp + slice * a.k_slice_stride);
+    const unsigned odd = (unsigned)-(part & 1), upper = (unsigned)-(part >> 1);
+    unsigned char* const kt = staged[wv];
+    // fn(tile, scores, ordered bits) of the lane's scores of every tile of the wave, the next tile's keys on their way: score i is
+    // key 8 (r / 4) + 4 g + r % 4 of the tile with r = part * PER + i; the bits of those past the end are 0.  (The keys come in whole
+    // rows and go through LDS: as operands straight from memory, 32 rows for every instruction, a pass takes three times as long.)
+    auto pass = [&](auto&& fn) {
+      auto swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+      i32x4 stage[LPT];
+      const int64_t lane_at = (lane / CHUNKS) * a.k_row_stride * 2 + lane % CHUNKS * 16;
+      auto fetch = [&](int tile) {
+        if (tile * 32 + 32 <= a.G) {   // (64-bit products by the scalar unit)
+          const char* const at = kbase + (int64_t)tile * 32 * a.k_row_stride * 2;
 #pragma unroll
-        for (int s = 0; s < STEPS; s++) kf[s] = *reinterpret_cast<const i32x4*>(key + s * 32);
+          for (int i = 0; i < LPT; i++) stage[i] = *reinterpret_cast<const i32x4*>(at + (int64_t)i * (64 / CHUNKS) * a.k_row_stride * 2 + lane_at);
+        } else {   // key blocks past the end repeat the last one
+#pragma unroll
+          for (int i = 0; i < LPT; i++) {
+            const int ci = i * 64 + lane, row = ci / CHUNKS, c = ci % CHUNKS;
+            stage[i] = *reinterpret_cast<const i32x4*>(kbase + (int64_t)min(tile * 32 + row, a.G - 1) * a.k_row_stride * 2 + c * 16);
+          }
+        }
       };
-      auto form = [&](const i32x4 (&kf)[STEPS], int tile) {
+      if (t0 < t1) fetch(t0);
+#pragma unroll 1
+      for (int tile = t0; tile < t1; tile++) {
+        wave_order();
+#pragma unroll
+        for (int i = 0; i < LPT; i++) {
+          const int ci = i * 64 + lane, row = ci / CHUNKS, c = ci % CHUNKS;
+          *reinterpret_cast<i32x4*>(kt + row * ROWB + ((c ^ swz(row)) * 16)) = stage[i];
+        }
+        wave_order();
+        fetch(min(tile + 1, t1 - 1));
+        i32x4 kf[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; s++) kf[s] = *reinterpret_cast<const i32x4*>(kt + ln * ROWB + (((2 * s + g) ^ swz(ln)) * 16));
+        __builtin_amdgcn_sched_barrier(0);   // (all on their way; left to itself the compiler waits for each by itself)
         f32x16 acc;
 #pragma unroll
         for (int r = 0; r < 16; r++) acc[r] = 0.0f;
 #pragma unroll
         for (int s = 0; s < STEPS; s++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[s], acc, 0, 0, 0);
-        if (ln < a.over_rows && tile * 32 < a.G) {   // (the rows hold Gs floats, whole tiles)
+        float x[PER];
+        unsigned o[PER];
 #pragma unroll
-          for (int r = 0; r < 16; r += 4)
-            *reinterpret_cast<f32x4*>(scratch + (int64_t)ln * a.Gs + tile * 32 + 2 * r + 4 * g) =
-                f32x4{score_of(acc[r], a.scale), score_of(acc[r + 1], a.scale), score_of(acc[r + 2], a.scale), score_of(acc[r + 3], a.scale)};
+        for (int i = 0; i < PER; i++) {
+          float product = acc[i];
+          if constexpr (ROWS == 8) {
+            auto either = [](float lower_half, float upper_half, unsigned mask) {
+              return __uint_as_float((__float_as_uint(upper_half) & mask) | (__float_as_uint(lower_half) & ~mask));
+            };
+            product = either(either(acc[i], acc[4 + i], odd), either(acc[8 + i], acc[12 + i], odd), upper);
+          }
+          x[i] = score_of(product, a.scale);
+          const unsigned u = __float_as_uint(x[i]);
+          o[i] = u ^ ((unsigned)((int)u >> 31) | 0x80000000u);   // (ordered_bits)
         }
-      };
-      i32x4 even[STEPS], odd[STEPS];
-      fetch(even, wv);
-      for (int tile = wv; tile * 32 < a.G; tile += 2 * WAVES) {
-        fetch(odd, tile + WAVES);
-        form(even, tile);
-        fetch(even, tile + 2 * WAVES);
-        form(odd, tile + WAVES);
+        const int left = a.G - tile * 32;
+        if (left < 32) {
+#pragma unroll
+          for (int i = 0; i < PER; i++) {
+            const int r = part * PER + i;
+            o[i] = 8 * (r / 4) + 4 * g + r % 4 < left ? o[i] : 0u;
+          }
+        }
+        fn(tile, x, o);
       }
+    };
+    // a value of a row, combined over its lanes
+    auto over_lanes = [&](unsigned v, auto&& combine) {
+      if constexpr (ROWS == 8) {
+        v = combine(v, (unsigned)__shfl_xor(v, 8));
+        v = combine(v, (unsigned)__shfl_xor(v, 16));
+      }
+      return combine(v, (unsigned)__shfl_xor(v, 32));
+    };
+    uint32_t* const bits_row = a.keep_bits + row * a.Gw;
+    int step = FIRST;
+    unsigned act = rows;   // rows that the step is about
+    for (int round = 0; round < 16; round++) {   // (FIRST, up to four times NARROW, COUNT, LAST)
+      if (step == NARROW) {
+        for (int i = tid; i < ROWS * BINS / 2; i += kOverfullThreads) reinterpret_cast<ulonglong2*>(hist)[i] = ulonglong2{0ull, 0ull};
+        if (tid == 0) wide = 0;
+      } else if (tid < ROWS && ((act >> tid) & 1u)) {
+        least[tid] = ~0u;
+        most[tid] = 0u;
+        listed[tid] = 0;
+        kept[tid] = 0;
+        cut_key[tid] = ~0ull;
+      }
+      __syncthreads();
+      const bool active = (act >> rl) & 1u;
+      const unsigned from = active ? lo[rl] : ~0u, to = active ? hi[rl] : ~0u, span = to - from;   // (no score has the bits ~0)
+      if (step == NARROW) {
+        const int shift = max(0, 32 - __clz((int)span) - DIGIT);
+        pass([&](int, const float (&x)[PER], const unsigned (&o)[PER]) {
+#pragma unroll
+          for (int i = 0; i < PER; i++)
+            if (o[i] - from <= span) atomicAdd(&hist[(to - o[i]) >> shift][rl], weight_of(x[i], rmax));
+        });
+        __syncthreads();
+        for (int r = wv; r < ROWS; r += WAVES) {
+          if (!((act >> r) & 1u)) continue;
+          const unsigned low = lo[r], high = hi[r];
+          const int bin_shift = max(0, 32 - __clz((int)(high - low)) - DIGIT);
+          unsigned long long before = mass_above[r];
+          const int bin = crossing_bin<BINS, ROWS>(&hist[0][r], before, [&](unsigned long long) { return target[r]; });
+          if (lane == 0) {
+            const unsigned top = high - ((unsigned)bin << bin_shift), deep = (1u << bin_shift) - 1u;
+            const unsigned bottom = top - low > deep ? top - deep : low;
+            mass_above[r] = before;
+            hi[r] = top;
+            lo[r] = bottom;
+            // how many members it has at most, by the weight of the least of them
+            const unsigned long long weight = weight_of(from_ordered(bottom), from_ordered(a.range[2 * (row0 + r)]));
+            const unsigned long long many = weight != 0ull ? hist[bin][r] / weight : ~0ull;
+            if (top == bottom) atomicOr(&single, 1u << r);
+            else if (many >= (unsigned long long)(LIST - LIST / 16)) atomicOr(&wide, 1u << r);
+          }
+        }
+        __syncthreads();
+      } else {
+        // equal scores: so many of this wave's are kept, and the last one of all is the cut.  The first step takes it that they are equal.
+        const bool ties = active && (step == FIRST ? counted : step == LAST && from == to), collect = active && step == LAST && !ties;
+        int allowed = 0;
+        bool last = false;
+        unsigned equal_bits = 0;
+        if (ties) {
+          unsigned n = 0, ahead = 0;
+          for (int w = 0; w < WAVES; w++) {
+            if (w < wv) ahead += members[w][rl];
+            n += members[w][rl];
+          }
+          // (if they are not, what the first step writes is overwritten)
+          equal_bits = step == FIRST ? guess[rl] : to;
+          const unsigned long long weight = weight_of(from_ordered(equal_bits), rmax);
+          unsigned long long need = target[rl] > mass_above[rl] ? target[rl] - mass_above[rl] : 1ull;
+          need = weight != 0ull ? (need + weight - 1ull) / weight : kept_of_infinite(n);
+          const unsigned keep = (unsigned)min(need, (unsigned long long)n), own = members[wv][rl];
+          allowed = (int)min((int64_t)own, max((int64_t)keep - (int64_t)ahead, (int64_t)0));
+          last = keep > ahead && keep <= ahead + own;
+        }
+        unsigned count = 0, n = 0, small = ~0u, large = 0u;
+        pass([&](int tile, const float (&)[PER], const unsigned (&o)[PER]) {
+          unsigned above = 0, in = 0;   // bit i: score i
+#pragma unroll
+          for (int i = PER - 1; i >= 0; i--) {   // (shifted in: an addition with carry each)
+            above = above + above + (o[i] > to ? 1u : 0u);
+            in = in + in + (o[i] - from <= span ? 1u : 0u);
+          }
+          n += (unsigned)__popc(in);
+          if (step == FIRST) {
+#pragma unroll
+            for (int i = 0; i < PER; i++)
+              if (o[i] - from <= span) {
+                small = min(small, o[i]);
+                large = max(large, o[i]);
+              }
+          }
+          auto word_of = [&](unsigned v) {   // of all lanes of the row, by key
+            if constexpr (ROWS == 32) {
+              v = (v | (v << 8)) & 0x00FF00FFu;
+              v = ((v | (v << 4)) & 0x0F0F0F0Fu) << (4 * g);
+            } else {
+              v <<= 8 * part + 4 * g;
+            }
+            return over_lanes(v, [](unsigned p, unsigned q) { return p | q; });
+          };
+          unsigned word = word_of(above);
+          if (__builtin_amdgcn_ballot_w64(allowed != 0 && in != 0u) != 0) {
+            unsigned equal = word_of(in);
+            if (allowed != 0 && equal != 0u) {
+              while (__popc(equal) > allowed) equal &= ~(0x80000000u >> __clz((int)equal));
+              allowed -= __popc(equal);
+              word |= equal;
+              if (allowed == 0 && last) cut_key[rl] = rank_key_of_bits(equal_bits, tile * 32 + 31 - __clz((int)equal));
+            }
+          }
+          if (active && lane < ROWS) {
+            count += (unsigned)__popc(word);
+            bits_row[tile] = word;
+          }
+          if (collect && in != 0u) {
+            unsigned pos = atomicAdd(&listed[rl], (unsigned)__popc(in));
+#pragma unroll
+            for (int i = 0; i < PER; i++)
+              if ((in >> i) & 1u) {
+                const int r = part * PER + i;
+                if (pos < (unsigned)LIST) hist[pos][rl] = rank_key_of_bits(o[i], tile * 32 + 8 * (r / 4) + 4 * g + r % 4);
+                pos++;
+              }
+          }
+        });
+        n = over_lanes(n, [](unsigned p, unsigned q) { return p + q; });
+        small = over_lanes(small, [](unsigned p, unsigned q) { return min(p, q); });
+        large = over_lanes(large, [](unsigned p, unsigned q) { return max(p, q); });
+        __syncthreads();   // (all have read the numbers of members)
+        if (active && lane < ROWS) {
+          atomicAdd(&kept[rl], count);
+          members[wv][rl] = n;
+          atomicMin(&least[rl], small);
+          atomicMax(&most[rl], large);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the bits are in this L2 before those of listed members are added there
+        __syncthreads();
+        if (step == FIRST && tid < ROWS && active) {
+          unsigned all_members = 0;
+          for (int w = 0; w < WAVES; w++) all_members += members[w][tid];
+          const bool equal = least[tid] == most[tid];
+          if (all_members != 0u) {
+            lo[tid] = least[tid];
+            hi[tid] = most[tid];
+          }
+          if (equal && counted && least[tid] == guess[tid]) atomicOr(&done, 1u << tid);
+          if (!equal && all_members > (unsigned)LIST) atomicOr(&wide, 1u << tid);
+        }
+        if (step == COUNT && tid == 0) single = 0;
+        __syncthreads();
+      }
+      if (step == LAST) break;
+      act = wide;
+      step = NARROW;
+      if (act == 0u) {
+        act = single;
+        step = COUNT;
+      }
+      if (act == 0u) {
+        act = rows & ~done;
+        step = LAST;
+        if (act == 0u) break;
+      }
+      __syncthreads();
     }
-    for (int i = 0; i < n; i++) {
-      __syncthreads();   // the scores are written; the row before this one is done with the shared state
-      if (!((todo >> i) & 1u)) continue;
-      const int64_t row = row0 + i;
-      const RowCut c = a.cuts[(int64_t)local_slice * a.QB + q0 + i];
-      if (tid == 0) {
-        sh.mass_above = c.mass_above;
-        sh.target = c.target;
-        sh.n_above = 0;
+    for (int r = wv; r < ROWS; r += WAVES) {
+      if (!((rows >> r) & 1u)) continue;
+      const int64_t this_row = row0 + r;
+      uint32_t* const bits_row = a.keep_bits + this_row * a.Gw;
+      unsigned count = kept[r];
+      unsigned long long cut = cut_key[r];
+      const unsigned n = min(listed[r], (unsigned)LIST);
+      if (n != 0u)
+        cut = cut_of_many<kShortBins, true>(
+            [&](auto&& fn) {
+#pragma unroll 1
+              for (unsigned i = lane; i < (n + 63u) / 64u * 64u; i += 64) fn(hist[min(i, n - 1u)][r], i < n);
+            },
+            [&](unsigned long long key, bool is) {
+              const unsigned id = 0xFFFFFFFFu - (unsigned)key;
+              if (is) atomicOr(&bits_row[id >> 5], 1u << (id & 31));
+              count += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(is));
+            },
+            (unsigned long long)lo[r] << 32, ((unsigned long long)hi[r] << 32) | 0xFFFFFFFFull, cand[wv], mass[wv], mass_above[r], target[r],
+            from_ordered(a.range[2 * this_row]));
+      if (lane == 0) {
+        a.cut[this_row] = cut;
+        a.count[this_row] = count;
       }
-      const unsigned lo = c.lo, hi = c.hi;
-      rank_row<kOverfullThreads, kBins, kCap, 4>(
-          sh, scratch + (int64_t)i * a.Gs, row, from_ordered(a.range[2 * row]),
-          [=](float v) -> int {
-            const unsigned o = ordered_bits(v);
-            return o > hi ? -1 : (o >= lo ? 0 : 1);
-          },
-          a.G, a.top_p, a.cut, a.count, a.keep_bits, a.Gw);
     }
   }
 }

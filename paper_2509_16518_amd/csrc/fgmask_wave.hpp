@@ -60,15 +60,15 @@ __device__ __forceinline__ unsigned lanes_below(uint64_t lanes) {
 }
 
 // Mass of all BINS bins and, with `target_of(mass)` and the mass `before` them, the bin in which the running mass reaches that
-// target; `before` becomes the mass before that bin.  Every lane reads BINS / 64 consecutive bins.  The last bin if the
-// masses fall short.
-template <int BINS, typename TargetOf>
+// target; `before` becomes the mass before that bin.  Every lane reads BINS / 64 consecutive bins, which lie STRIDE words
+// apart.  The last bin if the masses fall short.
+template <int BINS, int STRIDE = 1, typename TargetOf>
 __device__ __forceinline__ int crossing_bin(const unsigned long long* mass, unsigned long long& before, TargetOf&& target_of) {
   constexpr int PER = BINS / 64;
   const int lane = threadIdx.x & 63;
   unsigned long long own[PER], sum = 0;
 #pragma unroll
-  for (int i = 0; i < PER; i++) sum += own[i] = mass[lane * PER + i];
+  for (int i = 0; i < PER; i++) sum += own[i] = mass[(lane * PER + i) * STRIDE];
   const unsigned long long incl = lane_prefix(sum);
   const unsigned long long target = target_of(of_lane(incl, 63));
   unsigned long long run = before + incl - sum;

@@ -267,3 +267,40 @@ def test_rows_without_a_range(H, L, d, M, N):
             assert first.view(H, QB, G)[equal][:, :want].all(), (kind, scale)
             assert torch.equal(res[0][0], res[1][0]), (kind, scale)
             assert torch.equal(res[0][1], res[1][1]), (kind, scale)
+
+
+# Long rows whose crossing bin holds more key blocks than the lists take: a few values (equal members), scores crowded beside a large
+# negative one (several narrowings), half of them equal in the crowd (a single score left after narrowing, to be counted), two
+# scores one bit apart (scale zero).  Eight rows per workgroup and 32; stretches of the sweep that divide over the waves and that do not;
+# some heads ordinary; row ends off a tile and a group of rows.
+@pytest.mark.parametrize("H,L,d,M,N", [(1, 33000, 64, 16, 1), (3, 30001, 128, 32, 1), (6, 22000, 128, 32, 1), (64, 40000, 64, 128, 16)])
+def test_long_rows_with_many_members(H, L, d, M, N):
+    QB, G = (L + M - 1) // M, (L + N - 1) // N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q0, k0 = (torch.randn((1, H, L, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    indptr = torch.empty(H * QB + 1, dtype=torch.int64, device="cuda")
+    for kind, gain in (("two values", 1.0), ("few values", -1.0), ("crowded", 1.0), ("equal and crowded", 1.0), ("zero scale", 0.0)):
+        q, k = q0, k0.clone()
+        if kind == "two values":
+            k[:] = (k0[..., :1] > 0.5).to(k0.dtype)
+        elif kind == "few values":
+            k[:] = (k0[..., :1].float().clamp(-1.2, 1.2) * 1.5).round().to(k0.dtype)
+        elif "crowded" in kind:
+            q = q0.abs()
+            k = 1.0 + (k0 > 1.0).to(k0.dtype) * 2.0 ** -7
+            if kind == "equal and crowded":
+                k[:, :, (torch.arange(L, device="cuda") // N) % 2 == 0] = 1.0
+            k[:, :, L // 2:L // 2 + N] = -40.0
+        if H > 2:
+            k[:, 1] = k0[:, 1]
+        for top_p in (0.2, 0.9, 1.0) if H * QB * G < 1 << 27 else (0.9,):
+            res = []
+            for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+                p = F.make_params(q, k, k, q, M, N, gain * d ** -0.5, flags)
+                ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+                F.fgattn_mask_select(q, k, p, top_p, indptr, ws)
+                res.append((indptr.clone(), emitted(p, ws, indptr)))
+            say("    %s, p %g: %d and %d kept" % (kind, top_p, int(res[0][0][-1]), int(res[1][0][-1])))
+            assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
+            assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
