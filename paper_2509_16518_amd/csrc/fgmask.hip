@@ -1283,7 +1283,9 @@ static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus
     int64_t seg_tiles = ((ktiles + segs - 1) / segs + 3) & ~(int64_t)3;
     if (seg_tiles < 16) seg_tiles = 16;
     segs = (ktiles + seg_tiles - 1) / seg_tiles;
-    if (segs > 64 || seg_tiles > 2047) return false;   // (a wave settles 64 lists; a list's places have 16 bits)
+    // (A wave settles 64 lists; a list's places have 16 bits.  Many query blocks make few stretches, of more tiles than that: fewer slices
+    // in a chunk then make more.)
+    if (segs > 64 || seg_tiles > 2047) continue;
     const int64_t cap = seg_tiles * 32 / 8;
     // mass: one workgroup fits a compute unit; setting up a row tile and leaving its histogram cost it about six steps
     const int64_t most = cus & ~7;

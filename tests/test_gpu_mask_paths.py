@@ -304,3 +304,20 @@ def test_long_rows_with_many_members(H, L, d, M, N):
             say("    %s, p %g: %d and %d kept" % (kind, top_p, int(res[0][0][-1]), int(res[1][0][-1])))
             assert torch.equal(res[0][0], res[1][0]), (kind, top_p)
             assert torch.equal(res[0][1], res[1][1]), (kind, top_p)
+
+
+# So many query blocks that the sweep of all slices at once would make stretches longer than a list can count: chunks of fewer slices
+def test_selection_without_scores_of_many_query_blocks():
+    H, L, d, M = 96, 131072, 64, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    q, k = (torch.randn((1, H, L, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    indptr = torch.empty(H * L // M + 1, dtype=torch.int64, device="cuda")
+    res = []
+    for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+        p = F.make_params(q, k, k, q, M, 1, d ** -0.5, flags)
+        ws = torch.empty(F.fgattn_mask_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        F.fgattn_mask_select(q, k, p, 0.02, indptr, ws)
+        res.append((indptr.clone(), emitted(p, ws, indptr)))
+    say("    %d and %d kept" % (int(res[0][0][-1]), int(res[1][0][-1])))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
