@@ -1262,16 +1262,22 @@ static bool launched() { return hipGetLastError() == hipSuccess; }
 
 // Lays out the score buffer (`bytes` at `at`) for the selection without scores (fgmask_stream.hpp), in chunks of whole
 // slices.  False where it does not fit, or where the selection from scores is the better one: with few scores the six kernels
-// of a chunk are mostly set-up, the more so at head dim 128, where a score takes twice the matrix work (at 128, 2 heads x 512
-// rows of 32760 scores, 34 million, 118 us from scores and 161 without; 40 x 256 x 4096, 42 million, 147 and 158; 4 x 512 x
-// 32760, 67 million, 184 and 187; 929 x 118800, 110 million, 411 and 378; 40 x 585 x 9360, 219 million, 725 and 456; at 64,
-// 12 x 256 x 16384, 50 million, 157 and 132; 24 x 929 x 3713, 83 million, 458 and 366), and a histogram has to be worth its
-// setting up for 64 rows.
-static int64_t stream_min_scores(int d) { return (int64_t)(d == 128 ? 72 : 48) << 20; }
+// of a chunk are mostly set-up, the more so at head dim 128, where a score takes twice the matrix work, and with few rows, whose
+// histograms are the same keys' work for less.  A histogram has to be worth its setting up for 64 rows, too.  The line, in units of
+// 2^20 scores, between measured pairs (select call, us, from scores / without, masks of video-like and of random scores):
+//   d = 64, from 2048 rows on   48: 2816 x 16384 (44) 95 / 96 and 98 / 105; 3328 x 16384 (52) 125 / 99 and 129 / 111
+//           from 1024 rows on   54: 1875 x 30000 (53.6) 102 / 101 and 107 / 118; 1641 x 35000 (54.8) 132 / 110 and 146 / 129
+//           below               72: 750 x 96000 (68.7) 163 / 168 and 176 / 196; 782 x 100000 (74.6) 209 / 173 and 222 / 204
+//   d = 128, from 1024 rows on  72: 1470 x 47000 (65.9) 151 / 156 and 160 / 177; 1548 x 49500 (73.1) 184 / 166 and 192 / 187
+//            below              96: 860 x 110000 (90.2) 242 / 241 and 259 / 272; 891 x 114000 (96.9) 261 / 245 and 280 / 277
+static int64_t stream_min_scores(int d, int64_t rows) {
+  const int64_t mi = d == 128 ? (rows < 1024 ? 96 : 72) : rows < 1024 ? 72 : rows < 2048 ? 54 : 48;
+  return mi << 20;
+}
 constexpr int64_t kStreamMinRow = 2048;
 
 static bool plan_stream(const Layout& lo, int d, char* at, size_t bytes, int cus, StreamArgs* a) {
-  if (lo.G < kStreamMinRow || lo.rows * lo.G < stream_min_scores(d)) return false;
+  if (lo.G < kStreamMinRow || lo.rows * lo.G < stream_min_scores(d, lo.rows)) return false;
   const int64_t ktiles = (lo.G + 31) / 32, per_slice = (lo.QB + kSweepRows - 1) / kSweepRows, tiles = (lo.QB + kMassRows - 1) / kMassRows;
   a->steps = (int)((ktiles + kMassWaves - 1) / kMassWaves);
   for (int64_t chunks = 1; chunks <= lo.slices; chunks++) {
