@@ -202,6 +202,37 @@ def check_spills(asm_path):
                 raise RuntimeError("%s: %s spills %s vector registers" % (asm_path, name, m.group(2)))
 
 
+def check_rounding_mode(asm_path):
+    """The histogram of the mask selection forms its weights by 64-bit float instructions written as inline assembly, under a
+    rounding mode that the kernel sets once at its start and that the compiler does not know of.  A 64-bit float
+    instruction of the compiler's own in such a kernel would be rounded wrongly, or the compiler would set the mode back ahead of it;
+    and the statement in a kernel that does not set the mode would round to nearest.  Per function: one write of the mode at
+    most, ahead of every 64-bit float instruction; with it, all of these are inline assembly, without it, none is.  Returns how many
+    functions set the mode."""
+    import re
+    double = re.compile(r"v_\w*f64")
+    found, mode, inline, first = 0, None, False, None
+    with open(asm_path) as f:
+        for n, line in enumerate(f, 1):
+            if "#ASMSTART" in line or "#ASMEND" in line:
+                inline = "#ASMSTART" in line
+                continue
+            text = line.split(";", 1)[0].strip()
+            op = text.split()[0] if text else ""
+            if text.startswith(".Lfunc_end"):
+                found += mode is not None
+                mode, first = None, None
+            elif op.startswith(("s_setreg", "s_round_mode", "s_denorm_mode")):
+                if mode is not None or first is not None or "HW_REG_MODE, 2, 2), 3" not in text:
+                    raise RuntimeError("%s:%d: the mode of float operations is written again, late or otherwise: %s" % (asm_path, n, text))
+                mode = n
+            elif double.match(op):
+                first = n if first is None else first
+                if inline != (mode is not None):
+                    raise RuntimeError("%s:%d: a 64-bit float instruction under the wrong rounding mode: %s" % (asm_path, n, text))
+    return found
+
+
 def build_hip(force=True, extra_flags=()):
     """Compile every .hip translation unit for gfx950 (in parallel) and link libfgattn.so in-tree."""
     from concurrent.futures import ThreadPoolExecutor
@@ -221,6 +252,7 @@ def build_hip(force=True, extra_flags=()):
             check_inline_asm_hazards(os.path.join(objdir, f))
             check_untracked_loads(os.path.join(objdir, f))
             check_spills(os.path.join(objdir, f))
+            check_rounding_mode(os.path.join(objdir, f))
         elif not f.endswith(".o"):
             os.remove(os.path.join(objdir, f))   # other intermediates of -save-temps
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIBFGATTN])

@@ -399,7 +399,7 @@ __global__ void __launch_bounds__(kMassWaves * 64, 2) mass_kernel(const StreamAr
 #pragma unroll
       for (int i = 0; i < 4; i++)
         if (i < n)
-          __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long*)place[i], weight[i], __ATOMIC_RELAXED,
+          __hip_atomic_fetch_add((__attribute__((address_space(3))) unsigned long long*)(uintptr_t)place[i], weight[i], __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     // the tile of `step` (products in cur) into the histogram, and the products of the next one's into nxt

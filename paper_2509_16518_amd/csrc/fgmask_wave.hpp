@@ -122,8 +122,8 @@ __device__ __forceinline__ unsigned long long cut_of_many(ForEach&& for_each, Ke
       unsigned long long most = 0ull, least = ~0ull;
       for_each([&](unsigned long long key, bool is) {
         const bool in = is && key >= klo && key <= khi;
-        most = max(most, in ? key : 0ull);
-        least = min(least, in ? key : ~0ull);
+        if (in && key > most) most = key;
+        if (in && key < least) least = key;
       });
       most = lane_max(most);
       least = ~lane_max(~least);

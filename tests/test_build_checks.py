@@ -71,3 +71,22 @@ def test_spills_of_forward_kernels(tmp_path):
     scan(tmp_path, listing("_ZN3fgm13select_kernel", 9), build.check_spills)
     with pytest.raises(RuntimeError):
         scan(tmp_path, listing("_ZN2fg17fgattn_fwd_kernelILi64E", 2), build.check_spills)
+
+
+MODE = "s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 3"
+WEIGHT = [";#ASMSTART", "v_cvt_f64_f32 v[4:5], v1", "v_mul_f64 v[4:5], v[4:5], s[2:3]", ";#ASMEND"]
+PLAIN = "v_mul_f64 v[4:5], v[4:5], s[2:3]"
+
+
+def test_rounding_mode_that_holds(tmp_path):
+    assert scan(tmp_path, [MODE] + WEIGHT + ["v_add_u32_e32 v1, v2, v3"] + WEIGHT + [END], build.check_rounding_mode) == 1
+    assert scan(tmp_path, [PLAIN, "v_cvt_f64_f32_e32 v[4:5], v1", END], build.check_rounding_mode) == 0
+    assert scan(tmp_path, [MODE] + WEIGHT + [END, ".Lfunc_end7:", PLAIN, END], build.check_rounding_mode) == 1
+
+
+@pytest.mark.parametrize("lines", [[MODE, PLAIN, END], [MODE] + WEIGHT + ["v_cvt_f64_u32_e32 v[4:5], v1", END], [MODE] + WEIGHT + [MODE, END],
+                                   [MODE] + WEIGHT + ["s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0", END], WEIGHT + [END],
+                                   ["s_setreg_imm32_b32 hwreg(HW_REG_MODE, 0, 2), 3"] + WEIGHT + [END], [PLAIN, MODE] + WEIGHT + [END]])
+def test_rounding_mode_that_does_not(tmp_path, lines):
+    with pytest.raises(RuntimeError):
+        scan(tmp_path, lines, build.check_rounding_mode)
