@@ -119,17 +119,27 @@ def test_scores_of_every_tile_and_stretch(H, L, d, M, N, one_tile):
     assert (most_out <= least * (1 + (1e-4 if tol < 1e-4 else 0.3)) + 1e-9).all(), float((most_out / least).max())
 
 
-# The selection that reads a row once, in each of its sizes, against the one that reads it in every pass.  Rows of scores that
-# are spread out, that leave most weights zero, that take a few values only, that sit close together beside one
-# dominant score, and that are all equal: from few members of the crossing bin to more than any kernel keeps.  Rows end
-# at, before and after a group of sixteen, a word, and the largest row of a kernel.
+# The selection that a row of this length takes (by a wave, from bytes, or without kept scores), against the one that reads it in
+# every pass.  Rows of scores that are spread out, that leave most weights zero, that take a few values only, that sit close
+# together beside one dominant score, and that are all equal: from few members of the crossing bin to more than any kernel
+# keeps.  Rows end at, before and after a group of sixteen, a word, and the largest row of a kernel.
 @pytest.mark.parametrize("G", [1, 15, 147, 257, 1000, 4096, 4097, 8195, 32768, 32769, 65536, 65537, 118800, 131072, 131073])
 def test_selection_from_bytes_equals_selection_from_memory(G):
+    compare_with_selection_from_memory(G, 0)
+
+
+# Score tiles one by one leave every length to the kernels that read a row once, up to their longest, and to the general one above
+@pytest.mark.parametrize("G", [1, 15, 147, 257, 1000, 1025, 4096, 4097, 32768, 32769, 65536, 65537, 118800, 131071, 131072, 131073])
+def test_selection_from_bytes_of_single_tiles_equals_selection_from_memory(G):
+    compare_with_selection_from_memory(G, F.FLAG_MASK_ONE_TILE_CHUNKS)
+
+
+def compare_with_selection_from_memory(G, flags_of_first):
     d, M = 64, 128
     for kind in ("spread", "peaked", "few values", "close", "equal"):
         for top_p in (0.3, 0.9, 1.0):
             res = []
-            for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
+            for flags in (flags_of_first, F.FLAG_MASK_ROWS_IN_HBM):
                 q, k, _, ws, indptr = problem(1, G, d, M, 1, seed=G, flags=flags)
                 if kind == "few values":
                     k = (k[..., :1] > 0.5).to(k.dtype).expand_as(k).contiguous()
@@ -150,10 +160,19 @@ def test_selection_from_bytes_equals_selection_from_memory(G):
 # which none, some or all are such rows (heads of equal keys between heads of ordinary ones)
 @pytest.mark.parametrize("H,L,M", [(20, 2000, 16), (3, 8195, 16), (2, 40000, 64), (2, 70000, 128)])
 def test_overfull_rows_among_others(H, L, M):
+    overfull_rows_among_others(H, L, 64, M)
+
+
+# rows beyond 65536 that are few enough for kept scores, several to a workgroup
+def test_overfull_rows_among_others_in_the_longest_rows():
+    overfull_rows_among_others(2, 66000, 128, 128)
+
+
+def overfull_rows_among_others(H, L, d, M):
     for full in ([], list(range(0, H, 2)), list(range(H))):
         res = []
         for flags in (0, F.FLAG_MASK_ROWS_IN_HBM):
-            q, k, p, ws, indptr = problem(H, L, 64, M, 1, seed=L + len(full), flags=flags)
+            q, k, p, ws, indptr = problem(H, L, d, M, 1, seed=L + len(full), flags=flags)
             k[:, full] = 1.0
             F.fgattn_mask_select(q, k, p, 0.9, indptr, ws)
             res.append((indptr, emitted(p, ws, indptr)))
