@@ -127,8 +127,8 @@ __global__ void __launch_bounds__(64) pool_kernel(PoolTensor q, PoolTensor k, in
 // bank conflicts.  In the accumulator a register holds one query block and 32 consecutive key
 // blocks across lanes, so every store covers whole 128-byte lines.  Bound: the writes of the scores (a kernel that
 // only stores this pattern takes 173-188 us per GiB).  With a lane test and its branches around every store, and 160 lane
-// exchanges per workgroup and wave for the ranges, it took 239 us for 805 MB (rows of 32760), now 206; 301 us per GiB (rows of
-// 118800, K shared as below), now 242.
+// exchanges per workgroup and wave for the ranges, it took 239 us for 805 MB (6144 rows of 32760), then 206; 301 us per GiB (rows of
+// 118800, K shared as below), then 242.  (Calls of that size keep no scores now; 1024 rows of 32760, 134 MB, take 28 us.)
 // ---------------------------------------------------------------------------------------------
 // Tiles of a workgroup: with sixteen, the calls that come this way leave compute units idle or a second round nearly empty (both
 // mask calls, 12 heads x 147 rows of 9360 scores 110 us, 98 with eight, 101 with four; 40 x 64 x 4096 85, 74, 75; 2 x 512 x 32760
@@ -137,7 +137,7 @@ constexpr int kTilesPerGroup = 8;
 // Workgroups go to the eight XCDs in turn.  With at least eight stretches of key blocks, every XCD keeps to its own eighth of
 // them and takes a stretch for up to kShareUnits consecutive score tiles (of one slice, mostly) before the next one, so
 // that the tiles read K through one L2 at about the same time.  (In the order of their indices they read it from device
-// memory again, half as many bytes as they write: rows of 118800 scores 337 us per GiB of scores, shared 301.)
+// memory again, half as many bytes as they write: many rows of 118800 scores 337 us per GiB of scores, shared 301.)
 constexpr int kShareUnits = 8;
 
 template <int D>
@@ -797,11 +797,12 @@ __global__ void __launch_bounds__(THREADS) select_kernel(const float* scores, co
 // Bound: the first pass's vector instructions and LDS atomics (one 64-bit addition per score) and the latencies of the short
 // phases between barriers, so what matters is how many waves a compute unit holds; bytes (16-bit bins before) let three
 // workgroups of 512 threads share one for rows of up to 32768 scores instead of two, and let rows of up to 131072 in at all
-// (before, they were read from memory in every pass).  6144 rows of 32760: 359 -> 256 us; 22296 rows of 118800:
-// 5.6 -> 4.5 ms.  (The histogram's atomics are not what binds: without seven eighths of them it is no faster.)  Too many members
-// for LDS are rare (many equal scores): such a row goes on from its histogram as in select_kernel, after the other rows.  (A
-// launch of its own, which started those rows over, cost every call 2 us, 33.8 -> 31.6 us for 16 rows of 1000; 1858 rows of
-// 118800 equal scores 3.02 -> 2.42 ms, 3072 rows of 32760 1.29 -> 0.91.)
+// (before, they were read from memory in every pass).  Against select_kernel, which does that: 1024 rows of 32760 51 -> 36 us, 469 of
+// 60000 61 -> 35, 782 of 100000 172 -> 132, 10240 of 2048 77 -> 52; fewer short rows, whose scores stay in the caches, are
+// slower: 1764 of 9360 35 -> 47, 2560 of 4096 25 -> 31.  (The histogram's atomics are not what binds: without seven eighths of them it
+// is no faster.)  Too many members for LDS are rare (many equal scores): such a row goes on from its histogram as in select_kernel,
+// after the other rows (1024 rows of 32760 equal scores 217 us, there 202; 10240 of 2048 211 and 1814).  A launch of its own, which
+// started those rows over, cost every call 2 us.
 template <int THREADS, int MAXROW, int IDCAP, typename ID>
 struct alignas(16) CodesShared {
   static constexpr int CAND = IDCAP * sizeof(ID) / 8;
@@ -840,7 +841,7 @@ select_codes_kernel(const float* scores, const unsigned* range, int64_t chunk_ro
 
     // pass 1: four consecutive scores per thread and step, DEPTH steps in flight while DEPTH are processed.  The loads are
     // unconditional, 16 bytes of the row's padding or of its last scores again past the end (with a test around them the
-    // compiler makes four 4-byte loads and four branches of each: 311 us for 6144 rows of 32760).
+    // compiler makes four 4-byte loads and four branches of each, and it takes a fifth more time).
     {
       constexpr int STEP = THREADS * 4, DEPTH = WAVES_PER_SIMD > 4 ? 2 : 4;
       auto one = [&](float v) -> unsigned {
@@ -1120,7 +1121,7 @@ __global__ void __launch_bounds__(256) emit_bits_kernel(const uint32_t* keep_bit
   int64_t to = out - skip;
   unsigned fill = skip, begins = 32;   // slots of the stretch's first line, until it has been written
   for (int w = w0; w < w1; w += 64) {
-    asm volatile("" : "+v"(words));   // (waits for these words here: after the next load is under way, it would wait for that too)
+    asm volatile("" : "+v"(words));   // (waits for these words here, and for the stores before them: after the next load is under way, for that too)
     const uint32_t next = w + 64 + lane < w1 ? bits[w + 64 + lane] : 0u;
     for (int half = 0; half < 64 && w + half < w1; half += kEmitBatch) {
 #pragma unroll
@@ -1479,8 +1480,8 @@ int fgattn_mask_select(const void* q, const void* k, const fgattn_params* p, flo
     if (!launched()) return FGATTN_E_DEVICE;
     if (lo.row_in_lds) {
       // As many persistent workgroups as LDS or registers let in: three per compute unit with the codes of 32768 scores, two
-      // with 65536, one, of 1024 threads, with 131072.  Short rows are all latency: workgroups of 256, seven of them (1764
-      // rows of 147 scores 38 us with two workgroups of 512 per unit -> 16).
+      // with 65536, one, of 1024 threads, with 131072.  Short rows are all latency: workgroups of 256, seven of them (10240
+      // rows of 2048 scores 102 us with three workgroups of 512 per unit -> 52, 2560 of 4096 54 -> 31).
       auto launch = [&](auto kernel, int threads, int per_cu) {
         const int64_t fit = (int64_t)per_cu * cus;
         hipLaunchKernelGGL(kernel, dim3((unsigned)(chunk_rows < fit ? chunk_rows : fit)), dim3(threads), 0, stream, scores, range,

@@ -271,8 +271,8 @@ __global__ void __launch_bounds__(256, 3) sweep_kernel(const StreamArgs a) {
             if ((t & 3) > 1) to[2] = words[2];
           }
         }
-        // The next tiles go to LDS before the members' stores: after them, the wait for their loads (they complete in order) would
-        // be one for the stores too.
+        // The next tiles go to LDS before the members' stores of a step's last tile: after them, the wait for their loads (they complete
+        // in order) would be one for these stores too, as it is for those of the step's first tile.
         if (!stashed && (sub == kSweepStep - 1 || t + 1 == ntiles)) {
           if (t0 + kSweepStep < ntiles) stash_tile((t0 / kSweepStep + 1) & 1);
           stashed = true;
@@ -631,11 +631,12 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
 //   NARROW  a histogram of the members' mass, until the bin that holds the cut has few enough
 //   COUNT   of members of a single score that was left after that, per wave
 //   LAST    the bits above the cut's range; its members into a list in LDS, ranked by a wave each, or counted off if they are equal
-// Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1.3 us.  (Fetching further ahead changes nothing; with the operands read from LDS one after the other a pass takes a
-// tenth more, straight from memory twice as long.)  Select call, against the kernels with kept scores / a kernel that formed eight or four
-// rows into memory for rank_row / this one: 6144 rows of 32760 in two values 1.34 / 1.91 / 0.69 ms, crowded beside one large
-// negative score 1.72 / 2.24 / 1.43; 20480 of 4095 0.77 / 2.10 / 0.70 and 1.24 / 2.11 / 1.02; 929 of 118800 0.97 / 1.74 / 0.85 and
-// 1.19 / 1.92 / 1.72.  Equal scores (settle_kernel), 6144 of 32760: 1.57 / 2.04 / 0.26.
+// Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1.3 us.  (Fetching further ahead
+// changes nothing; with the operands read from LDS one after the other a pass takes a tenth more, straight from memory twice as
+// long.)  Select call, from kept scores / with eight or four rows formed into memory for rank_row / now: 6144 rows of 32760 in two
+// values 1.34 / 1.91 / 0.69 ms, crowded beside one large negative score 1.72 / 2.24 / 1.43; 20480 of 4095 0.77 / 2.10 / 0.70 and
+// 1.24 / 2.11 / 1.02; 929 of 118800 0.97 / 1.74 / 0.85 and 1.19 / 1.92 / 1.72.  Equal scores (settle_kernel), 6144 of 32760:
+// 1.57 / 2.04 / 0.26.
 // The matrix product has 32 columns.  With 8 ROWS a lane holds what the three lanes 8, 16 and 24 from it hold, and takes a quarter of
 // it: workgroups enough where rows are few.
 // ---------------------------------------------------------------------------------------------
