@@ -57,7 +57,7 @@ struct StreamArgs {
   unsigned long long* cut;           // [row]
   unsigned* count;                   // [row]; 0 marks a row left to overfull_kernel
   uint32_t* keep_bits;               // [row][Gw]
-  unsigned* overfull;                // number of such rows
+  unsigned* overfull;                // not zero if there are such rows
 };
 
 // ---- arithmetic that several kernels have to agree on to the last bit (no contraction into fused operations) ----
@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
     if (__builtin_amdgcn_ballot_w64(n.y > (unsigned)a.cap) != 0) {
       if (lane == 0) {
         a.count[row] = 0u;
-        atomicAdd(a.overfull, 1u);
+        *a.overfull = 1u;   // (not counted: additions to one word take 12 ns each, 72 us for 6144 rows)
       }
       continue;
     }
@@ -634,8 +634,8 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
 // Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1.3 us.  (Fetching further ahead
 // changes nothing; with the operands read from LDS one after the other a pass takes a tenth more, straight from memory twice as
 // long.)  Select call, from kept scores / with eight or four rows formed into memory for rank_row / now: 6144 rows of 32760 in two
-// values 1.34 / 1.91 / 0.69 ms, crowded beside one large negative score 1.72 / 2.24 / 1.43; 20480 of 4095 0.77 / 2.10 / 0.70 and
-// 1.24 / 2.11 / 1.02; 929 of 118800 0.97 / 1.74 / 0.85 and 1.19 / 1.92 / 1.72.  Equal scores (settle_kernel), 6144 of 32760:
+// values 1.34 / 1.91 / 0.62 ms, crowded beside one large negative score 1.72 / 2.24 / 1.36; 20480 of 4095 0.77 / 2.10 / 0.47 and
+// 1.24 / 2.11 / 0.79; 929 of 118800 0.97 / 1.74 / 0.84 and 1.19 / 1.92 / 1.70.  Equal scores (settle_kernel), 6144 of 32760:
 // 1.57 / 2.04 / 0.26.
 // The matrix product has 32 columns.  With 8 ROWS a lane holds what the three lanes 8, 16 and 24 from it hold, and takes a quarter of
 // it: workgroups enough where rows are few.
