@@ -626,17 +626,17 @@ __global__ void __launch_bounds__(256) settle_kernel(const StreamArgs a) {
 // Rows with more members in some stretch than its list takes (scores crowded beside a few that stand out, many equal ones; rows of
 // nothing but equal scores don't come here): 32 or 8 rows per workgroup, their scores formed anew in every pass over the keys, a
 // stretch of the key tiles per wave.
-//   FIRST   how many members there are, their smallest and largest score.  Taking it that they are equal, their number ahead of a wave
-//           follows from what the sweep counted, and their weight from one that it listed: the bits are written in the same pass.
-//   NARROW  a histogram of the members' mass, until the bin that holds the cut has few enough
+//   FIRST   (not where the listed scores differ) how many members there are, their smallest and largest score.  Taking it that they are
+//           equal, their number ahead of a wave follows from what the sweep counted: the bits are written in the same pass.
+//   NARROW  a histogram of the members' mass, its bins over the range of the listed ones, until the bin that holds the cut has few enough
 //   COUNT   of members of a single score that was left after that, per wave
 //   LAST    the bits above the cut's range; its members into a list in LDS, ranked by a wave each, or counted off if they are equal
-// Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1.3 us.  (Fetching further ahead
+// Bound: the chain of a tile (LDS, matrix instructions, scores) with two waves to a SIMD, about 1 us.  (Fetching further ahead
 // changes nothing; with the operands read from LDS one after the other a pass takes a tenth more, straight from memory twice as
 // long.)  Select call, from kept scores / with eight or four rows formed into memory for rank_row / now: 6144 rows of 32760 in two
-// values 1.34 / 1.91 / 0.62 ms, crowded beside one large negative score 1.72 / 2.24 / 1.36; 20480 of 4095 0.77 / 2.10 / 0.47 and
-// 1.24 / 2.11 / 0.79; 929 of 118800 0.97 / 1.74 / 0.84 and 1.19 / 1.92 / 1.70.  Equal scores (settle_kernel), 6144 of 32760:
-// 1.57 / 2.04 / 0.26.
+// values 1.34 / 1.91 / 0.63 ms, crowded beside one large negative score 1.72 / 2.24 / 1.18; 20480 of 4095 0.76 / 2.10 / 0.47 and
+// 1.24 / 2.11 / 0.72; 929 of 118800 0.97 / 1.74 / 0.85 and 1.18 / 1.92 / 1.22 (with FIRST for all and bins over the whole range
+// 1.70).  Equal scores (settle_kernel), 6144 of 32760: 1.57 / 2.04 / 0.26.
 // The matrix product has 32 columns.  With 8 ROWS a lane holds what the three lanes 8, 16 and 24 from it hold, and takes a quarter of
 // it: workgroups enough where rows are few.
 // ---------------------------------------------------------------------------------------------
@@ -653,8 +653,10 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
   __shared__ unsigned long long mass[WAVES][kShortBins], cand[WAVES][64];
   __shared__ unsigned long long mass_above[ROWS], target[ROWS], cut_key[ROWS];
   __shared__ unsigned lo[ROWS], hi[ROWS], least[ROWS], most[ROWS], listed[ROWS], kept[ROWS];
-  __shared__ unsigned members[WAVES][ROWS], guess[ROWS];
-  __shared__ unsigned todo, wide, single, done;   // a bit per row: to be selected; range still too wide; one score, not counted; bits written
+  __shared__ unsigned members[WAVES][ROWS];
+  __shared__ unsigned dense_lo[ROWS], dense_hi[ROWS];   // most members lie in here, as far as is known
+  // a bit per row: to be selected; known to have members of different scores; range still too wide; one score, not counted; bits written
+  __shared__ unsigned todo, differ, wide, single, done;
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, g = lane >> 5, rl = lane % ROWS, part = ln / ROWS;
   const int per_slice = (a.QB + ROWS - 1) / ROWS, ktiles = (a.G + 31) / 32;
@@ -672,7 +674,7 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
     const int local_slice = e / per_slice, slice = a.slice0 + local_slice, q0 = (e - local_slice * per_slice) * ROWS;
     const int64_t row0 = (int64_t)slice * a.QB + q0;
     __syncthreads();   // the rows before these are done with the shared state
-    if (tid == 0) todo = wide = single = done = 0;
+    if (tid == 0) todo = differ = wide = single = done = 0;
     __syncthreads();
     if (tid < ROWS && q0 + tid < a.QB && a.count[row0 + tid] == 0u) {
       const RowCut c = a.cuts[(int64_t)local_slice * a.QB + q0 + tid];
@@ -680,26 +682,40 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
       hi[tid] = c.hi;
       mass_above[tid] = c.mass_above;
       target[tid] = c.target;
-      guess[tid] = 0;
+      dense_lo[tid] = ~0u;
+      dense_hi[tid] = 0u;
       atomicOr(&todo, 1u << tid);
     }
     __syncthreads();
     const unsigned rows = todo;
     if (rows == 0u) continue;   // (the same in all threads)
     const int64_t row = row0 + min(rl, a.QB - 1 - q0);
-    if (counted) {   // a score that the sweep has listed: if the members are equal, it is theirs
+    if (counted) {   // some of the scores that the sweep has listed, a few of each stretch
       const int64_t first_list = ((int64_t)local_slice * a.QB + min(q0 + rl, a.QB - 1)) * a.segs;
-      unsigned own = 0;
-      int seg_of_one = -1;
+      unsigned own = 0, small = ~0u, large = 0u;
       for (int seg = s0; seg < s1; seg++) {
         const unsigned n = a.counts[first_list + seg].y;
         own += n;
-        if (n != 0u) seg_of_one = seg;
+        if (n != 0u) {
+          const unsigned at = (min(n, (unsigned)a.cap) - 1u) * (unsigned)(lane / ROWS) / (64u / ROWS - 1u);
+          const unsigned o = ordered_bits(a.lists[(first_list + seg) * a.cap + at].score);
+          small = min(small, o);
+          large = max(large, o);
+        }
       }
-      if (lane < ROWS) {
-        members[wv][rl] = own;
-        if (seg_of_one >= 0) atomicMax(&guess[rl], ordered_bits(a.lists[(first_list + seg_of_one) * a.cap].score));
+      if (lane < ROWS) members[wv][rl] = own;
+      if (own != 0u) {
+        atomicMin(&dense_lo[rl], small);
+        atomicMax(&dense_hi[rl], large);
       }
+      __syncthreads();
+      if (tid < ROWS && ((rows >> tid) & 1u) && dense_lo[tid] < dense_hi[tid]) {   // not equal: no need to see whether they are
+        unsigned n = 0;
+        for (int w = 0; w < WAVES; w++) n += members[w][tid];
+        atomicOr(&differ, 1u << tid);
+        if (n > (unsigned)LIST) atomicOr(&wide, 1u << tid);
+      }
+      __syncthreads();
     }
     const float rmax = from_ordered(a.range[2 * row]);
     bf16x8 qf[STEPS];
@@ -777,6 +793,11 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
         fn(tile, x, o);
       }
     };
+    // so that a range gives at most BINS - 2 bins
+    auto shift_for = [](unsigned range) {
+      const int shift = max(0, 32 - __clz((int)range) - DIGIT);
+      return (range >> shift) > (unsigned)(BINS - 3) ? shift + 1 : shift;
+    };
     // a value of a row, combined over its lanes
     auto over_lanes = [&](unsigned v, auto&& combine) {
       if constexpr (ROWS == 8) {
@@ -786,9 +807,18 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
       return combine(v, (unsigned)__shfl_xor(v, 32));
     };
     uint32_t* const bits_row = a.keep_bits + row * a.Gw;
+    unsigned act = rows & ~differ;   // rows that the step is about
     int step = FIRST;
-    unsigned act = rows;   // rows that the step is about
-    for (int round = 0; round < 16; round++) {   // (FIRST, up to four times NARROW, COUNT, LAST)
+    if (act == 0u) {
+      act = wide;
+      step = NARROW;
+    }
+    if (act == 0u) {
+      act = rows;
+      step = LAST;
+    }
+    __syncthreads();
+    for (int round = 0; round < 16; round++) {   // (FIRST, a few times NARROW, COUNT, LAST)
       if (step == NARROW) {
         for (int i = tid; i < ROWS * BINS / 2; i += kOverfullThreads) reinterpret_cast<ulonglong2*>(hist)[i] = ulonglong2{0ull, 0ull};
         if (tid == 0) wide = 0;
@@ -803,25 +833,34 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
       const bool active = (act >> rl) & 1u;
       const unsigned from = active ? lo[rl] : ~0u, to = active ? hi[rl] : ~0u, span = to - from;   // (no score has the bits ~0)
       if (step == NARROW) {
-        const int shift = max(0, 32 - __clz((int)span) - DIGIT);
+        // bins over the dense part, and one each for what lies above and below it
+        const unsigned high = active ? dense_hi[rl] : 0u;
+        const int shift = active ? shift_for(high - dense_lo[rl]) : 0;
         pass([&](int, const float (&x)[PER], const unsigned (&o)[PER]) {
 #pragma unroll
           for (int i = 0; i < PER; i++)
-            if (o[i] - from <= span) atomicAdd(&hist[(to - o[i]) >> shift][rl], weight_of(x[i], rmax));
+            if (o[i] - from <= span) {
+              const unsigned bin = o[i] > high ? 0u : min((high - o[i]) >> shift, (unsigned)(BINS - 2)) + 1u;
+              atomicAdd(&hist[bin][rl], weight_of(x[i], rmax));
+            }
         });
         __syncthreads();
         for (int r = wv; r < ROWS; r += WAVES) {
           if (!((act >> r) & 1u)) continue;
-          const unsigned low = lo[r], high = hi[r];
-          const int bin_shift = max(0, 32 - __clz((int)(high - low)) - DIGIT);
+          const unsigned high = dense_hi[r];
+          const int bin_shift = shift_for(high - dense_lo[r]);
           unsigned long long before = mass_above[r];
-          const int bin = crossing_bin<BINS, ROWS>(&hist[0][r], before, [&](unsigned long long) { return target[r]; });
+          int bin = crossing_bin<BINS, ROWS>(&hist[0][r], before, [&](unsigned long long) { return target[r]; });
           if (lane == 0) {
-            const unsigned top = high - ((unsigned)bin << bin_shift), deep = (1u << bin_shift) - 1u;
-            const unsigned bottom = top - low > deep ? top - deep : low;
+            const unsigned whole_lo = lo[r], whole_hi = hi[r];
+            if (bin == 0 && high == whole_hi) bin = 1;   // (nothing lies above: members without mass, of a target of zero)
+            const unsigned below = (unsigned)max(bin - 1, 0) << bin_shift;
+            const unsigned top = bin == 0 ? whole_hi : high - whole_lo > below ? high - below : whole_lo;
+            const unsigned deep = (1u << bin_shift) - 1u;
+            const unsigned bottom = bin == 0 ? high + 1u : bin == BINS - 1 || top - whole_lo <= deep ? whole_lo : top - deep;
             mass_above[r] = before;
-            hi[r] = top;
-            lo[r] = bottom;
+            dense_hi[r] = hi[r] = top;
+            dense_lo[r] = lo[r] = bottom;
             // how many members it has at most, by the weight of the least of them
             const unsigned long long weight = weight_of(from_ordered(bottom), from_ordered(a.range[2 * (row0 + r)]));
             const unsigned long long many = weight != 0ull ? hist[bin][r] / weight : ~0ull;
@@ -843,7 +882,7 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
             n += members[w][rl];
           }
           // (if they are not, what the first step writes is overwritten)
-          equal_bits = step == FIRST ? guess[rl] : to;
+          equal_bits = step == FIRST ? dense_hi[rl] : to;
           const unsigned long long weight = weight_of(from_ordered(equal_bits), rmax);
           unsigned long long need = target[rl] > mass_above[rl] ? target[rl] - mass_above[rl] : 1ull;
           need = weight != 0ull ? (need + weight - 1ull) / weight : kept_of_infinite(n);
@@ -918,12 +957,12 @@ __global__ void __launch_bounds__(kOverfullThreads, 2) overfull_kernel(const Str
           unsigned all_members = 0;
           for (int w = 0; w < WAVES; w++) all_members += members[w][tid];
           const bool equal = least[tid] == most[tid];
-          if (all_members != 0u) {
-            lo[tid] = least[tid];
-            hi[tid] = most[tid];
-          }
-          if (equal && counted && least[tid] == guess[tid]) atomicOr(&done, 1u << tid);
+          if (equal && counted && least[tid] == dense_hi[tid]) atomicOr(&done, 1u << tid);
           if (!equal && all_members > (unsigned)LIST) atomicOr(&wide, 1u << tid);
+          if (all_members != 0u) {
+            dense_lo[tid] = lo[tid] = least[tid];
+            dense_hi[tid] = hi[tid] = most[tid];
+          }
         }
         if (step == COUNT && tid == 0) single = 0;
         __syncthreads();

@@ -289,8 +289,8 @@ def test_rows_without_a_range(H, L, d, M, N):
 
 
 # Long rows whose crossing bin holds more key blocks than the lists take: a few values (equal members), scores crowded beside a large
-# negative one (several narrowings), half of them equal in the crowd (a single score left after narrowing, to be counted), two
-# scores one bit apart (scale zero).  Eight rows per workgroup and 32; stretches of the sweep that divide over the waves and that do not;
+# negative one (several narrowings), half of them equal in the crowd (a single score left after narrowing, to be counted), most of
+# them above or below those that come first and are listed, two scores one bit apart (scale zero).  Eight rows per workgroup and 32; stretches of the sweep that divide over the waves and that do not;
 # some heads ordinary; row ends off a tile and a group of rows.
 @pytest.mark.parametrize("H,L,d,M,N", [(1, 33000, 64, 16, 1), (3, 30001, 128, 32, 1), (6, 22000, 128, 32, 1), (66, 40000, 64, 128, 16)])
 def test_long_rows_with_many_members(H, L, d, M, N):
@@ -300,7 +300,8 @@ def test_long_rows_with_many_members(H, L, d, M, N):
     gen.manual_seed(L)
     q0, k0 = (torch.randn((1, H, L, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
     indptr = torch.empty(H * QB + 1, dtype=torch.int64, device="cuda")
-    for kind, gain in (("two values", 1.0), ("few values", -1.0), ("crowded", 1.0), ("equal and crowded", 1.0), ("zero scale", 0.0)):
+    for kind, gain in (("two values", 1.0), ("few values", -1.0), ("crowded", 1.0), ("equal and crowded", 1.0), ("drifting and crowded", 1.0),
+                       ("zero scale", 0.0)):
         q, k = q0, k0.clone()
         if kind == "two values":
             k[:] = (k0[..., :1] > 0.5).to(k0.dtype)
@@ -311,6 +312,10 @@ def test_long_rows_with_many_members(H, L, d, M, N):
             k = 1.0 + (k0 > 1.0).to(k0.dtype) * 2.0 ** -7
             if kind == "equal and crowded":
                 k[:, :, (torch.arange(L, device="cuda") // N) % 2 == 0] = 1.0
+            if kind == "drifting and crowded":   # the first fifth of every 512 key blocks in the middle of the others
+                step = torch.randint(0, 18, (H, L), generator=gen, device="cuda")
+                early = (torch.arange(L, device="cuda") // N) % 512 < 102
+                k[0] = (1.0 + 2.0 ** -7 * torch.where(early, 8 + step % 2, step)).to(k0.dtype)[:, :, None]
             k[:, :, L // 2:L // 2 + N] = -40.0
         if H > 2:
             k[:, 1] = k0[:, 1]
