@@ -1356,15 +1356,16 @@ static bool launch_stream(StreamArgs a, const Layout& lo, int cus, hipStream_t s
     const int64_t rows = (int64_t)a.slices * lo.QB, waves = (rows + 3) / 4;
     hipLaunchKernelGGL(settle_kernel, dim3((unsigned)(waves < 8 * cus ? waves : 8 * cus)), dim3(256), 0, stream, a);
     if (!launched()) return false;
-    // One workgroup to a compute unit, 32 rows each where that is enough of them: at d = 128, 90 workgroups of 32 take 0.41 ms for rows of
-    // two values and 1.03 for crowded ones, of 8 0.51 and 0.99 (8 x 512 rows of 32760, 128 of them, 0.54 and 1.26, 0.65 and 1.24; 929 rows of
-    // 118800, 30 of them, 1.01 and 3.30, 0.85 and 1.76).
+    // One workgroup to a compute unit, 32 rows each where that is enough of them: rows of two values and crowded rows take, of 32 / of 8,
+    // 0.32 / 0.40 and 0.53 / 0.55 ms with 65 workgroups of 32 (2063 rows of 33000, d = 64), 0.39 / 0.49 and 0.60 / 0.69 with 90 (3 x 938 of
+    // 30000), 0.50 / 0.61 and 1.07 / 0.90 with 128 (8 x 512 of 32760), 0.63 / 0.89 and 1.17 / 1.28 with 192, but 1.01 / 0.85 and
+    // 2.69 / 1.25 with 30 (929 of 118800).
     auto overfull = [&](auto rows) {
       int64_t over = a.slices * ((lo.QB + rows - 1) / rows);
       if (over > cus) over = cus;
       hipLaunchKernelGGL((overfull_kernel<D, decltype(rows)::value>), dim3((unsigned)((over + 7) & ~(int64_t)7)), dim3(kOverfullThreads), 0, stream, a);
     };
-    if (a.slices * ((lo.QB + 31) / 32) >= cus * 3 / 8) overfull(std::integral_constant<int, 32>());
+    if (a.slices * ((lo.QB + 31) / 32) >= cus / 4) overfull(std::integral_constant<int, 32>());
     else overfull(std::integral_constant<int, 8>());
     if (!launched()) return false;
   }
